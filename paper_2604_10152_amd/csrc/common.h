@@ -43,7 +43,7 @@ __device__ __forceinline__ float silu_f32(float z) { return z / (1.0f + __expf(-
 hipError_t launch_route_topk(const void* x, const void* wr, const float* bias, int T, int d,
                              int E, int k, int renorm, int dtype, int32_t* idx, float* w,
                              hipStream_t s, const int32_t* remap = nullptr);
-// speculation phase (draft_route.hip)
+// speculation phase (affinity.hip, draft_route.hip)
 size_t affinity_workspace_bytes(int E);
 hipError_t launch_affinity_table(const void* wg, const void* wu, const void* wd, int E, int d,
                                  int f, int dtype, float* table, void* workspace, hipStream_t s);

@@ -297,3 +297,53 @@ def test_active_expert_bytes_and_greedy_accept_chain():
     torch.cuda.synchronize()
     ea, eo = orc.accept(draft.numpy(), tgt_want)
     assert np.array_equal(alen.cpu().numpy(), ea) and np.array_equal(out.cpu().numpy(), eo)
+
+
+# ------------------------------------------------------------------ affinity table: edges
+@pytest.mark.parametrize("E,d,f,dtype", [
+    (1, 64, 64, torch.bfloat16), (2, 64, 64, torch.bfloat16), (4, 72, 40, torch.bfloat16),
+    (8, 264, 24, torch.bfloat16), (9, 256, 64, torch.bfloat16), (16, 128, 72, torch.bfloat16),
+    (33, 64, 192, torch.bfloat16), (49, 64, 128, torch.float32), (65, 64, 64, torch.bfloat16),
+    (140, 24, 32, torch.float32), (3, 4, 1, torch.float32)])
+def test_affinity_table_operand_edges(E, d, f, dtype):
+    """One to four 16-expert row blocks per wave, column slices for 4 and 8 experts, a second and
+    third group of 64 experts, and column counts that end inside a unit of 16 or 32 columns."""
+    _say(f"affinity edges E={E} d={d} f={f} {dtype}")
+    wg, wu, wd = _weights(E, d, f, dtype, seed=200 + E, planted=E >= 9)
+    got = _gpu_affinity(wg, wu, wd)
+    want = orc.affinity_table(f64(wg), f64(wu), f64(wd))
+    assert np.all(np.diag(got) == 0) and np.array_equal(got, got.T)
+    np.testing.assert_allclose(got, want, rtol=AFFINITY_RTOL, atol=0)
+
+
+def test_affinity_table_close_pairs_and_non_finite_weights():
+    """Pairs far below their norms (a copy, one element off by one bf16 step, a 1e-4 relative
+    offset; with and without a common part in all experts) keep the accuracy of a direct sum, and
+    an infinite or NaN weight reaches exactly the pairs of its expert."""
+    _say("affinity close pairs, non-finite weights")
+    E, d, f = 12, 128, 192
+    for common in (0.0, 1.0):
+        wg, wu, wd = (w.float() for w in _weights(E, d, f, torch.float32, seed=7, planted=False))
+        for w in (wg, wu, wd):
+            w += common * w[0].clone() * 50
+            w[5] = w[4]
+            w[7] = w[6]
+            w[9] = w[8] * (1 + 1e-4)
+        wg[7, 3, 5] *= 1 + 2.0 ** -7
+        got = _gpu_affinity(wg, wu, wd)
+        want = orc.affinity_table(f64(wg), f64(wu), f64(wd))
+        assert got[4, 5] == 0 and got[6, 7] > 0
+        np.testing.assert_allclose(got, want, rtol=AFFINITY_RTOL, atol=0)
+    for bad in (float("inf"), float("nan")):
+        for e in (0, 6):
+            w2 = wu.clone()
+            w2[e, 1, 2] = bad
+            got = _gpu_affinity(wg, w2, wd)
+            hit = np.zeros((E, E), dtype=bool)
+            hit[e, :] = hit[:, e] = True
+            hit[e, e] = False
+            assert np.array_equal(~np.isfinite(got), hit) and (not np.isinf(bad) or np.all(got[hit] == np.inf))
+            np.testing.assert_allclose(got[~hit], want[~hit], rtol=AFFINITY_RTOL, atol=0)
+    w2 = wu.clone()
+    w2[2, 1, 2] = w2[3, 1, 3] = float("inf")       # both infinite, at different places
+    assert _gpu_affinity(wg, w2, wd)[2, 3] == np.inf
