@@ -261,6 +261,24 @@ def test_grouped_fp32(d, f, rows):
     _grouped_case(torch.float32, d, f, rows, seed=d + f)
 
 
+@pytest.mark.parametrize("mean", [10, 28, 60])          # 16-, 32- and 64-row tiles
+@pytest.mark.parametrize("d,f,E", [
+    (68, 72, 5),                                     # waves split the contraction; 16-byte loads
+    (66, 35, 5),                                     # 4-byte loads, ragged last columns
+    # many tiles: waves side by side (up / down).  72 hidden columns, not fewer: the worst row's
+    # rms error is about 3 * eps * sqrt(d) * max_j |h_j| / rms(h) = 2.2e-6 with 9 columns (a
+    # sequential fp32 chain over d gives the same), above the 2e-6 bar, and 1.1e-6 with 72
+    (12, 600, 44), (602, 72, 44),
+])
+def test_grouped_fp32_tile_forms(mean, d, f, E):
+    """Every tile height with the contraction split over the waves or not, row lengths that allow
+    16-byte loads and that do not, and row counts around the edges of the tiles."""
+    edge = [0, 1, 15, 16, 17, 31, 33, 63, 65, 2 * mean]
+    rows = (edge + [mean] * E)[:E] if E > 10 else [2 * mean, 0, 17, 1, 5 * mean - 2 * mean - 18]
+    _say(f"grouped f32 tiles d={d} f={f} rows={rows}")
+    _grouped_case(torch.float32, d, f, rows, seed=d + f + mean)
+
+
 @pytest.mark.parametrize("d,f,rows", [
     (256, 384, [300, 0, 37, 1, 513, 256, 330]),      # large-batch tiles: full, ragged, empty
     (512, 1408, [700, 650]),
