@@ -37,6 +37,28 @@ __device__ __forceinline__ T wave_sum(T v) {
     return v;
 }
 
+// Transposing butterfly over the 64 lanes of a wave: v[0..CNT) in every lane -> v[0] = total of
+// value (lane * CNT0 / 64) where CNT0 is the count at the first step.
+template <int CNT, int BIT>
+struct TransposeReduce {
+    __device__ __forceinline__ static void run(double* v, int lane) {
+        if constexpr (CNT > 1) {
+            constexpr int H = CNT / 2;
+            const bool up = (lane & BIT) != 0;
+#pragma unroll
+            for (int i = 0; i < H; ++i) {
+                const double send = up ? v[i] : v[i + H];
+                const double keep = up ? v[i + H] : v[i];
+                v[i] = keep + __shfl_xor(send, BIT, kWave);
+            }
+            if constexpr (BIT > 1) TransposeReduce<H, BIT / 2>::run(v, lane);
+        } else {
+            v[0] += __shfl_xor(v[0], BIT, kWave);
+            if constexpr (BIT > 1) TransposeReduce<1, BIT / 2>::run(v, lane);
+        }
+    }
+};
+
 __device__ __forceinline__ float silu_f32(float z) { return z / (1.0f + __expf(-z)); }
 
 // ---- launchers (host side, defined in the .hip files) -------------------------------

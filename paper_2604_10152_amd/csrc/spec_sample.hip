@@ -21,6 +21,7 @@ namespace {
 constexpr int kSampleThreads = 1024;  // 16 waves: enough loads in flight for one CU per sequence
 constexpr int kSampleWaves = kSampleThreads / kWave;
 constexpr int kTileIds = kWave * 4;          // ids one wave covers per step: 4 per lane (16 bytes)
+constexpr int kBurst = 8;                    // tiles a wave requests at once
 constexpr int kMaxLdsTiles = 2048;           // tile sums kept in LDS (V <= 524288); beyond that
                                              // the tiles are re-summed from memory
 
@@ -35,10 +36,14 @@ __device__ __forceinline__ double wave_scan_incl(double v, int lane) {
 }
 
 // One workgroup per sequence.  The draw needs the smallest id whose running weight exceeds
-// u * total: wave w of the 16 sums the 256-id tiles w, w+16, ... (coalesced 16-byte loads, butterfly sum,
-// fp64) into LDS, every thread walks the tile sums to find the tile where the threshold is
-// crossed, and one wave scans that tile.  Only the order of the fp64 additions differs from a
-// sequential running sum.
+// u * total.  Wave w of the 16 owns the 256-id tiles w, w+16, ...: it requests kBurst of them
+// (16-byte loads) before it adds anything up - 128 KB in flight per CU, at V = 32000 the whole
+// row - and reduces the kBurst fp64 sums over its lanes with one transposing butterfly.  The tile
+// sums meet in LDS; a wave scan over them, 64 tiles at a time, gives the total and then the tile
+// where the threshold is crossed, and one wave scans that tile.  Only the order of the fp64
+// additions differs from a sequential running sum.  B = 256, gamma = 7, V = 32000: 32 us with one
+// tile at a time and a serial walk over the tile sums -> 16.2 us; HBM is the bound (2 V 4 bytes per
+// sequence, after two dependent round trips for the first rejection).
 __global__ __launch_bounds__(kSampleThreads) void spec_accept_sample_kernel(
     const int32_t* __restrict__ draft, const float* __restrict__ p_draft,
     const float* __restrict__ p_target, const float* __restrict__ u_accept,
@@ -68,23 +73,24 @@ __global__ __launch_bounds__(kSampleThreads) void spec_accept_sample_kernel(
         const unsigned long long m = __ballot(reject);
         if (lane == 0) n_sh = m ? __ffsll((long long)m) - 1 : gamma;
     }
+    const double u_draw = (double)u_sample[b];
     __syncthreads();
-    const int n = n_sh;
+    const int n = __builtin_amdgcn_readfirstlane(n_sh);
     const float* ptn = pt + (size_t)n * V;
     const float* pdn = n < gamma ? pd + (size_t)n * V : nullptr;
     const bool vec = (V % 4 == 0) && ((((uintptr_t)p_draft | (uintptr_t)p_target) & 15u) == 0);
     const int n_tiles = (V + kTileIds - 1) / kTileIds;
 
-    // this lane's 4 weights of tile `tile` (0 beyond V)
-    auto tile_weights = [&](int tile, bool resid, double (&w)[4]) {
+    // this lane's 4 probabilities of tile `tile` (0 beyond V) under both models; q = 0 when
+    // drawing from pt
+    auto load_tile = [&](int tile, bool resid, floatx4& t, floatx4& q) __attribute__((always_inline)) {
         const int v0 = tile * kTileIds + lane * 4;
-        float t[4] = {0.f, 0.f, 0.f, 0.f}, q[4] = {0.f, 0.f, 0.f, 0.f};
-        if (vec && v0 + 3 < V) {
-            const float4 a = *reinterpret_cast<const float4*>(ptn + v0);
-            t[0] = a.x; t[1] = a.y; t[2] = a.z; t[3] = a.w;
-            if (resid) {
-                const float4 c = *reinterpret_cast<const float4*>(pdn + v0);
-                q[0] = c.x; q[1] = c.y; q[2] = c.z; q[3] = c.w;
+        t = floatx4{0.f, 0.f, 0.f, 0.f};
+        q = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (vec) {                                  // V % 4 == 0: all four ids or none
+            if (v0 < V) {
+                t = *reinterpret_cast<const floatx4*>(ptn + v0);
+                if (resid) q = *reinterpret_cast<const floatx4*>(pdn + v0);
             }
         } else {
 #pragma unroll
@@ -94,104 +100,136 @@ __global__ __launch_bounds__(kSampleThreads) void spec_accept_sample_kernel(
                     if (resid) q[i] = pdn[v0 + i];
                 }
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const double r = (double)t[i] - (double)q[i];      // q = 0 when drawing from pt
-            w[i] = (v0 + i < V && r > 0.0) ? r : 0.0;
+    };
+    auto weight = [](float t, float q) -> double {
+        const double r = (double)t - (double)q;
+        return r > 0.0 ? r : 0.0;
+    };
+    auto tile_total = [&](int tile, bool resid) -> double {      // whole wave, same in every lane
+        floatx4 t, q;
+        load_tile(tile, resid, t, q);
+        return wave_sum((weight(t[0], q[0]) + weight(t[1], q[1])) +
+                        (weight(t[2], q[2]) + weight(t[3], q[3])));
+    };
+    auto sum_tiles = [&](bool resid) {
+        if (n_tiles <= kSampleWaves) {              // at most one tile per wave
+            if (wave < n_tiles) {
+                const double s = tile_total(wave, resid);
+                if (lane == 0) tile_sum[wave] = s;
+            }
+            __syncthreads();
+            return;
         }
-    };
-    auto tile_total = [&](int tile, bool resid) -> double {
-        double w[4];
-        tile_weights(tile, resid, w);
-        return wave_sum((w[0] + w[1]) + (w[2] + w[3]));
-    };
-    // walk the tiles in id order; returns the total and the tile where `thr` is crossed
-    auto sum_tiles = [&](bool resid) -> double {
-        for (int tile = wave; tile < n_tiles; tile += kSampleWaves) {
-            const double s = tile_total(tile, resid);
-            if (lane == 0 && tile < kMaxLdsTiles) tile_sum[tile] = s;
+        for (int t0 = wave; t0 < n_tiles; t0 += kSampleWaves * kBurst) {
+            floatx4 t[kBurst], q[kBurst];
+#pragma unroll
+            for (int i = 0; i < kBurst; ++i) load_tile(t0 + i * kSampleWaves, resid, t[i], q[i]);
+            __builtin_amdgcn_sched_barrier(0);
+            double s[kBurst];
+#pragma unroll
+            for (int i = 0; i < kBurst; ++i)
+                s[i] = (weight(t[i][0], q[i][0]) + weight(t[i][1], q[i][1])) +
+                       (weight(t[i][2], q[i][2]) + weight(t[i][3], q[i][3]));
+            TransposeReduce<kBurst, kWave / 2>::run(s, lane);
+            const int tile = t0 + lane / (kWave / kBurst) * kSampleWaves;
+            if (lane % (kWave / kBurst) == 0 && tile < n_tiles && tile < kMaxLdsTiles)
+                tile_sum[tile] = s[0];
         }
         __syncthreads();
+    };
+    // inclusive running sums of tiles c0 .. c0 + 63, tile c0 + lane in each lane
+    auto scan_chunk = [&](int c0, bool resid) -> double {
+        double s = 0.0;
+        if (c0 < kMaxLdsTiles) {                    // kMaxLdsTiles is a multiple of 64
+            if (c0 + lane < n_tiles) s = tile_sum[c0 + lane];
+        } else {
+            for (int i = 0; i < kWave && c0 + i < n_tiles; ++i) {
+                const double v = tile_total(c0 + i, resid);
+                if (lane == i) s = v;
+            }
+        }
+        return wave_scan_incl(s, lane);
+    };
+    auto total_of = [&](bool resid) -> double {     // every wave for itself, same result
         double tot = 0.0;
-        for (int tile = 0; tile < n_tiles; ++tile)
-            tot += tile < kMaxLdsTiles ? tile_sum[tile] : tile_total(tile, resid);
+        for (int c0 = 0; c0 < n_tiles; c0 += kWave) tot += __shfl(scan_chunk(c0, resid), kWave - 1, kWave);
         return tot;
     };
     bool resid = pdn != nullptr;
-    double total = sum_tiles(resid);
+    sum_tiles(resid);
+    double total = total_of(resid);
     if (resid && !(total > 0.0)) {                   // pt == pd everywhere: draw from pt
         __syncthreads();
         resid = false;
-        total = sum_tiles(false);
+        sum_tiles(false);
+        total = total_of(false);
     }
     if (wave != 0) return;
-    const double thr = (double)u_sample[b] * total;
+    const double thr = u_draw * total;
     int tok = V - 1;
-    double before = 0.0;
-    for (int tile = 0; tile < n_tiles; ++tile) {
-        const double s = tile < kMaxLdsTiles ? tile_sum[tile] : tile_total(tile, resid);
-        if (before + s > thr) {
-            double w[4];
-            tile_weights(tile, resid, w);
-            const double c1 = w[0], c2 = c1 + w[1], c3 = c2 + w[2], c4 = c3 + w[3];
-            const double excl = before + (wave_scan_incl(c4, lane) - c4);
-            int first = 4;
-            if (excl + c4 > thr) first = 3;
-            if (excl + c3 > thr) first = 2;
-            if (excl + c2 > thr) first = 1;
-            if (excl + c1 > thr) first = 0;
-            const unsigned long long hit = __ballot(first < 4);
-            const unsigned long long pos = __ballot(c4 > 0.0);
-            if (hit) {
-                const int src = __ffsll((long long)hit) - 1;
-                tok = tile * kTileIds + src * 4 + __shfl(first, src, kWave);
-            } else if (pos) {
-                // rounding: the tile's running sums stop a hair below the threshold;
-                // take its last id with a positive weight
-                const int src = 63 - __clzll((long long)pos);
-                const int last = w[3] > 0.0 ? 3 : (w[2] > 0.0 ? 2 : (w[1] > 0.0 ? 1 : 0));
-                tok = tile * kTileIds + src * 4 + __shfl(last, src, kWave);
-            }
-            break;
+    double base = 0.0;                               // sum of the chunks in front
+    for (int c0 = 0; c0 < n_tiles; c0 += kWave) {
+        const double incl = scan_chunk(c0, resid);
+        const unsigned long long over = __ballot(base + incl > thr);
+        if (!over) {
+            base += __shfl(incl, kWave - 1, kWave);
+            continue;
         }
-        before += s;
+        const int at = __ffsll((long long)over) - 1;
+        const int tile = c0 + at;
+        const double before = at > 0 ? base + __shfl(incl, at - 1, kWave) : base;
+        floatx4 t, q;
+        load_tile(tile, resid, t, q);
+        const double w0 = weight(t[0], q[0]), w1 = weight(t[1], q[1]), w2 = weight(t[2], q[2]),
+                     w3 = weight(t[3], q[3]);
+        const double c1 = w0, c2 = c1 + w1, c3 = c2 + w2, c4 = c3 + w3;
+        const double excl = before + (wave_scan_incl(c4, lane) - c4);
+        int first = 4;
+        if (excl + c4 > thr) first = 3;
+        if (excl + c3 > thr) first = 2;
+        if (excl + c2 > thr) first = 1;
+        if (excl + c1 > thr) first = 0;
+        const unsigned long long hit = __ballot(first < 4);
+        const unsigned long long pos = __ballot(c4 > 0.0);
+        if (hit) {
+            const int src = __ffsll((long long)hit) - 1;
+            tok = tile * kTileIds + src * 4 + __shfl(first, src, kWave);
+        } else if (pos) {
+            // rounding: the tile's running sums stop a hair below the threshold;
+            // take its last id with a positive weight
+            const int src = 63 - __clzll((long long)pos);
+            const int last = w3 > 0.0 ? 3 : (w2 > 0.0 ? 2 : (w1 > 0.0 ? 1 : 0));
+            tok = tile * kTileIds + src * 4 + __shfl(last, src, kWave);
+        }
+        break;
     }
-    if (lane == 0) {
-        int32_t* ot = out_tokens + (size_t)b * (gamma + 1);
-        for (int i = 0; i <= gamma; ++i) ot[i] = i < n ? dr[i] : (i == n ? tok : -1);
-        accept_len[b] = n + 1;
-    }
+    int32_t* ot = out_tokens + (size_t)b * (gamma + 1);
+    for (int i = lane; i <= gamma; i += kWave) ot[i] = i < n ? dr[i] : (i == n ? tok : -1);
+    if (lane == 0) accept_len[b] = n + 1;
 }
 
 template <typename T> struct Row;
 template <> struct Row<float> {
     static constexpr int N = 4;
     __device__ static float one(const float* p) { return *p; }
-    __device__ static void vec(const float* p, float (&v)[4]) {
-        const float4 q = *reinterpret_cast<const float4*>(p);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    }
+    __device__ static float at(const U128& v, int i) { return __uint_as_float(v[i]); }
 };
 template <> struct Row<bf16_t> {
     static constexpr int N = 8;
     __device__ static float one(const bf16_t* p) {
         return __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t*>(p) << 16);
     }
-    __device__ static void vec(const bf16_t* p, float (&v)[8]) {
-        const uint4 q = *reinterpret_cast<const uint4*>(p);
-        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[2 * i] = __uint_as_float(w[i] << 16);
-            v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-        }
+    __device__ static float at(const U128& v, int i) {
+        return __uint_as_float(i & 1 ? v[i >> 1] & 0xffff0000u : v[i >> 1] << 16);
     }
 };
+
+constexpr int kRowBurst = 4;          // chunks requested together where few rows leave CUs short of loads
 
 // One workgroup per row.  Thread t visits its ids in ascending order (16-byte chunks t, t+256,
 // ... when the row allows it) and keeps the first maximum it sees; the reduction prefers the
 // larger value, then the lower id.  Logits must not contain NaN.
-template <typename T, bool VEC>
+template <typename T, bool VEC, int BURST>
 __global__ __launch_bounds__(256) void greedy_tokens_kernel(const T* __restrict__ logits, int V,
                                                             int32_t* __restrict__ tokens) {
     const T* row = logits + (size_t)blockIdx.x * V;
@@ -199,13 +237,26 @@ __global__ __launch_bounds__(256) void greedy_tokens_kernel(const T* __restrict_
     float bv = 0.f;
     int bi = -1;
     if (VEC) {
+        // BURST chunks are requested before the first is looked at; the ones beyond the row
+        // repeat its last chunk, whose ids cannot win again (only a larger value replaces bv)
         constexpr int N = Row<T>::N;
-        for (int c = tid; c < V / N; c += 256) {
-            float x[N];
-            Row<T>::vec(row + (size_t)c * N, x);
+        const int chunks = V / N;
+        auto at = [&](int i, int c0) -> int { return i == 0 ? c0 : min(c0 + i * 256, chunks - 1); };
+        for (int c0 = tid; c0 < chunks; c0 += 256 * BURST) {
+            U128 raw[BURST];
 #pragma unroll
-            for (int q = 0; q < N; ++q)
-                if (bi < 0 || x[q] > bv) { bv = x[q]; bi = c * N + q; }
+            for (int i = 0; i < BURST; ++i)
+                raw[i] = *reinterpret_cast<const U128*>(row + (size_t)at(i, c0) * N);
+            if (BURST > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < BURST; ++i) {
+                const int c = at(i, c0);
+#pragma unroll
+                for (int q = 0; q < N; ++q) {
+                    const float x = Row<T>::at(raw[i], q);
+                    if (bi < 0 || x > bv) { bv = x; bi = c * N + q; }
+                }
+            }
         }
     } else {
         for (int v = tid; v < V; v += 256) {
@@ -254,11 +305,19 @@ template <typename T>
 static void launch_greedy_typed(const void* logits, int R, int V, int32_t* tokens, hipStream_t s) {
     const bool vec = V % Row<T>::N == 0 && ((uintptr_t)logits & 15u) == 0 &&
                      ((size_t)V * sizeof(T)) % 16 == 0;
-    if (vec)
-        hipLaunchKernelGGL((greedy_tokens_kernel<T, true>), dim3(R), dim3(256), 0, s,
+    // Up to 1024 rows (four workgroups per CU) of at least four chunks per thread, one thread's
+    // chunks are requested together: 512 x 32000 bf16 10.9 -> 7.7 us.  More rows keep enough loads in
+    // flight by themselves (2048 x 32000 bf16: 22.3 us = 5.9 TB/s, 23.0 with the burst), and
+    // shorter rows have nothing to request ahead (2048 x 1000: 4.2 us, 5.3 with it).
+    const bool burst = vec && R <= 1024 && V / Row<T>::N >= 256 * kRowBurst;
+    if (burst)
+        hipLaunchKernelGGL((greedy_tokens_kernel<T, true, kRowBurst>), dim3(R), dim3(256), 0, s,
+                           (const T*)logits, V, tokens);
+    else if (vec)
+        hipLaunchKernelGGL((greedy_tokens_kernel<T, true, 1>), dim3(R), dim3(256), 0, s,
                            (const T*)logits, V, tokens);
     else
-        hipLaunchKernelGGL((greedy_tokens_kernel<T, false>), dim3(R), dim3(256), 0, s,
+        hipLaunchKernelGGL((greedy_tokens_kernel<T, false, 1>), dim3(R), dim3(256), 0, s,
                            (const T*)logits, V, tokens);
 }
 

@@ -347,3 +347,39 @@ def test_affinity_table_close_pairs_and_non_finite_weights():
     w2 = wu.clone()
     w2[2, 1, 2] = w2[3, 1, 3] = float("inf")       # both infinite, at different places
     assert _gpu_affinity(wg, w2, wd)[2, 3] == np.inf
+
+
+@pytest.mark.parametrize("B,gamma,V", [(9, 3, 4096), (9, 3, 4097), (3, 2, 32769), (5, 1, 40003), (2, 1, 524288),
+                                       (2, 1, 540672)])
+def test_accept_sample_vocabulary_edges(B, gamma, V):
+    """One tile per wave and one more, a second burst of tiles, rows without 16-byte alignment, and
+    the last vocabulary whose tile sums fit in LDS and a larger one; u_sample at both ends."""
+    _say(f"spec_accept_sample edges B={B} gamma={gamma} V={V}")
+    draft, pd, pt, ua, us = _sample_case(B, gamma, V, seed=V, sharp=3.0)
+    us[0] = 0.0
+    us[1] = 1.0 - 2.0 ** -24
+    a, o = _gpu_accept_sample(draft, pd, pt, ua, us)
+    ea, eo = orc.accept_sample(draft.numpy(), pd.numpy(), pt.numpy(), ua.numpy(), us.numpy())
+    assert np.array_equal(a, ea)
+    for b in range(B):
+        n = ea[b] - 1
+        assert np.array_equal(o[b, :n], eo[b, :n]) and np.all(o[b, n + 1:] == -1)
+        if o[b, n] != eo[b, n]:                        # only legitimate on a rounding boundary
+            wts = np.maximum(pt[b, n].double().numpy() - pd[b, n].double().numpy(), 0) \
+                if n < gamma else pt[b, n].double().numpy()
+            assert _draw_is_valid(wts, us[b].item(), int(o[b, n])), (b, o[b, n], eo[b, n])
+
+
+@pytest.mark.parametrize("R,V,dtype", [(1024, 8192, torch.bfloat16), (1025, 8192, torch.bfloat16),
+                                       (3, 8200, torch.bfloat16), (2, 4100, torch.float32)])
+def test_greedy_tokens_burst_edges(R, V, dtype):
+    """Rows at the edge of the burst rule, and a burst whose last chunks lie beyond the row."""
+    _say(f"spec_greedy_tokens edges R={R} V={V}")
+    g = torch.Generator().manual_seed(R + V)
+    logits = torch.round(torch.randn(R, V, generator=g) * 2).to(dtype)     # many exact ties
+    logits[0] = 0
+    logits[-1, -1] = 50
+    tok = torch.full((R,), -5, dtype=I32, device="cuda")
+    sm.spec_greedy_tokens(dev(logits), tok)
+    torch.cuda.synchronize()
+    assert np.array_equal(tok.cpu().numpy(), orc.greedy_tokens(logits.float().numpy()))
