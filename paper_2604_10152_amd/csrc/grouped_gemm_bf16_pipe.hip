@@ -20,6 +20,7 @@
 // Hand-placed s_waitcnt vmcnt(n) is safe next to compiler-generated waits: extra outstanding
 // loads can only make a compiler-chosen wait stricter, never weaker.
 #include "pipe_common.h"
+#include "stream_tiles.h"
 
 #include <type_traits>
 
@@ -28,16 +29,16 @@ namespace {
 
 using namespace pipe;
 
+// one tile: the work of workgroup blockIdx.x (lds_raw: C::LDS_BYTES)
 template <typename C>
-__global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe_kernel(
+__device__ __forceinline__ void pipe_tile(
+    unsigned char* lds_raw,
     const bf16_t* __restrict__ A,        // [n_rows, K]
     const int32_t* __restrict__ offsets, // [E+1]
     const bf16_t* __restrict__ W0,       // [E, N, K]   (gate, or down)
     const bf16_t* __restrict__ W1,       // [E, N, K]   (up; SWIGLU only)
     int E, int N, int K, bf16_t* __restrict__ Cout /* [n_rows, N] */,
     const int32_t* __restrict__ row_src /* nullable: A row r is A[row_src[r] / topk] */, int topk) {
-    extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
-
     const int NT = (N + C::BN_OUT - 1) / C::BN_OUT;
     TileLoc t;
     if (!locate_tile_even<C::BM>(offsets, E, NT, blockIdx.x, t)) return;
@@ -303,6 +304,33 @@ __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe_kernel(
 }
 
 template <typename C>
+__global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe_kernel(
+    const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets,
+    const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int E, int N, int K,
+    bf16_t* __restrict__ Cout, const int32_t* __restrict__ row_src, int topk) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+    pipe_tile<C>(lds_raw, A, offsets, W0, W1, E, N, K, Cout, row_src, topk);
+}
+
+// Down projection with few rows per expert: by the number of tiles this batch has (known on the
+// device only) the ring above or the independent streams of stream_tiles.h.
+typedef PipeCfg<64, 128, 64, 6, 1, 4, false> DownSmall;
+constexpr size_t kDownSmallLds =
+    DownSmall::LDS_BYTES > stream::kStreamLds ? DownSmall::LDS_BYTES : stream::kStreamLds;
+
+__global__ __launch_bounds__(DownSmall::THREADS) void grouped_down_bf16_small_kernel(
+    const bf16_t* __restrict__ h, const int32_t* __restrict__ offsets,
+    const bf16_t* __restrict__ wd, int E, int N, int K, bf16_t* __restrict__ y) {
+    static_assert(DownSmall::THREADS == stream::kStreamThreads, "one launch serves both");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+    const int mt = count_mtiles<stream::Split>(offsets, E);
+    if (stream::stream_few(mt, N))
+        stream::stream_tiles(lds_raw, h, offsets, wd, E, N, K, y, mt);
+    else
+        pipe_tile<DownSmall>(lds_raw, h, offsets, wd, nullptr, E, N, K, y, nullptr, 1);
+}
+
+template <typename C>
 hipError_t launch_pipe(const bf16_t* A, const int32_t* offsets, const bf16_t* W0,
                        const bf16_t* W1, int n_rows, int E, int N, int K, bf16_t* Cout,
                        hipStream_t s, const int32_t* row_src = nullptr, int topk = 1) {
@@ -334,8 +362,17 @@ hipError_t launch_expert_up_bf16_small(const bf16_t* x_perm, const int32_t* offs
 hipError_t launch_expert_down_bf16_small(const bf16_t* h, const int32_t* offsets,
                                          const bf16_t* wd, int n_rows, int d, int f, int E,
                                          bf16_t* y, hipStream_t s) {
-    return launch_pipe<PipeCfg<64, 128, 64, 6, 1, 4, false>>(h, offsets, wd, nullptr, n_rows, E,
-                                                              d, f, y, s);
+    // one-time, thread-safe (C++11 static initialisation): raise the dynamic LDS limit
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&grouped_down_bf16_small_kernel),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDownSmallLds);
+    if (attr != hipSuccess) return attr;
+    const long long NT = (d + DownSmall::BN_OUT - 1) / DownSmall::BN_OUT;
+    const long long tiles = grid_upper_bound(n_rows, E, DownSmall::BM, NT);
+    const long long grid = tiles > stream::kCus ? tiles : stream::kCus;
+    hipLaunchKernelGGL(grouped_down_bf16_small_kernel, dim3((unsigned)grid),
+                       dim3(DownSmall::THREADS), kDownSmallLds, s, h, offsets, wd, E, d, f, y);
+    return hipGetLastError();
 }
 
 // In between (tens to a few hundred rows per expert, e.g. 16 experts with top-1 routing), down

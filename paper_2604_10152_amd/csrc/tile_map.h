@@ -59,9 +59,9 @@ struct FixedPolicy {
     }
 };
 
+// m-tiles of all experts together
 template <typename Split>
-__device__ __forceinline__ bool locate_tile_impl(const int32_t* __restrict__ offsets, int E,
-                                                 int NT, unsigned block_id, TileLoc& t) {
+__device__ __forceinline__ int count_mtiles(const int32_t* __restrict__ offsets, int E) {
     const int lane = threadIdx.x % kWave;
     int total_mt = 0;
     for (int e0 = 0; e0 < E; e0 += kWave) {
@@ -69,11 +69,14 @@ __device__ __forceinline__ bool locate_tile_impl(const int32_t* __restrict__ off
         const int M = e < E ? offsets[e + 1] - offsets[e] : 0;
         total_mt += wave_sum(Split::of(M).mt);
     }
-    const long long G = (long long)total_mt * NT;
-    const long long per_xcd = (G + kXcds - 1) / kXcds;
-    const long long slot = block_id / kXcds;
-    const long long L = (long long)(block_id % kXcds) * per_xcd + slot;
-    if (slot >= per_xcd || L >= G) return false;
+    return __builtin_amdgcn_readfirstlane(total_mt);
+}
+
+// the tile at place L of the logical order (expert, n-tile, m-tile)
+template <typename Split>
+__device__ __forceinline__ bool locate_logical(const int32_t* __restrict__ offsets, int E, int NT,
+                                               long long L, TileLoc& t) {
+    const int lane = threadIdx.x % kWave;
     int base_mt = 0;                              // m-tiles of the experts before this sweep
     int base_blk = 0;                             // 16-row blocks of the experts before this sweep
     int expert = -1, row0 = 0, rows = 0, nt = 0, blk0 = 0, mts = 0;
@@ -117,6 +120,17 @@ __device__ __forceinline__ bool locate_tile_impl(const int32_t* __restrict__ off
     t.blk0 = __builtin_amdgcn_readfirstlane(blk0);
     t.mt = __builtin_amdgcn_readfirstlane(mts);
     return t.expert >= 0;
+}
+
+template <typename Split>
+__device__ __forceinline__ bool locate_tile_impl(const int32_t* __restrict__ offsets, int E,
+                                                 int NT, unsigned block_id, TileLoc& t) {
+    const long long G = (long long)count_mtiles<Split>(offsets, E) * NT;
+    const long long per_xcd = (G + kXcds - 1) / kXcds;
+    const long long slot = block_id / kXcds;
+    const long long L = (long long)(block_id % kXcds) * per_xcd + slot;
+    if (slot >= per_xcd || L >= G) return false;
+    return locate_logical<Split>(offsets, E, NT, L, t);
 }
 
 template <int BM_MAX, int GRAN = 32>

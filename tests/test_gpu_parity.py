@@ -293,6 +293,30 @@ def test_grouped_bf16(d, f, rows):
     _grouped_case(torch.bfloat16, d, f, rows, seed=d + f)
 
 
+@pytest.mark.parametrize("d,f,rows", [
+    (256, 4096, [5, 0, 17, 32, 0, 1]),               # four waves per slab, 1..4 wave-loads of rows
+    (192, 4160, [8, 9, 0, 16, 24, 25]),              # ragged weight tiles, an odd number of k-steps
+    (64, 8192, [0, 0, 33, 0, 0, 0, 64, 0]),          # experts of several m-tiles share weights
+    (4096, 4096, [3, 0, 31, 2, 0, 0, 20, 0]),        # two waves per slab (a workgroup per CU)
+    (4096, 4096, [3, 0, 31, 2, 1, 0, 20, 0]),        # one m-tile more: the shared ring
+    (128, 4096, [0] * 66 + [7, 0, 17]),              # more experts than lanes
+])
+def test_down_projection_of_few_active_experts(d, f, rows):
+    """The device-side choice between private weight streams and the shared ring, and the tile
+    forms of the streams."""
+    _say(f"down, few active experts d={d} f={f} rows={rows}")
+    E, n = len(rows), sum(rows)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator().manual_seed(d + f + n)
+    h = torch.randn(n, f, generator=g).to(torch.bfloat16)
+    wd = (torch.randn(E, d, f, generator=g) * (0.5 / f ** 0.5)).to(torch.bfloat16)
+    y = torch.full((n, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sm.moe_expert_down(dev(h), dev(torch.from_numpy(off)), dev(wd), y)
+    torch.cuda.synchronize()
+    want = np.concatenate([f64(h[off[e]:off[e + 1]]) @ f64(wd[e]).T for e in range(E)])
+    check_float(f64(y), want, torch.bfloat16, f"rows={rows}")
+
+
 def test_expert_up_alone_matches_swiglu_definition():
     """h = silu(x Wg^T) * (x Wu^T) checked on its own (the gate/up GEMM with its epilogue)."""
     _say("expert up only")
