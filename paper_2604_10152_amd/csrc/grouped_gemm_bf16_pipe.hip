@@ -39,6 +39,8 @@ __device__ __forceinline__ void pipe_tile(
     const bf16_t* __restrict__ W1,       // [E, N, K]   (up; SWIGLU only)
     int E, int N, int K, bf16_t* __restrict__ Cout /* [n_rows, N] */,
     const int32_t* __restrict__ row_src /* nullable: A row r is A[row_src[r] / topk] */, int topk) {
+    static_assert(!C::SWIGLU || ((C::BN / 2 / C::ROWS_PER_DMA) % C::NWAVES == 0 && C::TN % 2 == 0),
+                  "gate/up halves must split on a wave-load round and pair up inside a wave");
     const int NT = (N + C::BN_OUT - 1) / C::BN_OUT;
     TileLoc t;
     if (!locate_tile_even<C::BM>(offsets, E, NT, blockIdx.x, t)) return;

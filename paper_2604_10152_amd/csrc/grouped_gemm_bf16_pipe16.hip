@@ -127,7 +127,12 @@ __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe16_kernel(
                 dma16(a_base, a_off[jj] + ka, sbase + jj * C::NWAVES * 1024u);
 #pragma unroll
         for (int jj = 0; jj < C::B_PW; ++jj) {
-            const bool up = C::SWIGLU && (jj * C::NWAVES * C::ROWS_PER_DMA >= C::BN / 2);
+            // the gate / up halves split on a round of wave-loads, or inside a round between waves
+            const bool up =
+                C::SWIGLU &&
+                ((C::BN / 2 / C::ROWS_PER_DMA) % C::NWAVES == 0
+                     ? jj * C::NWAVES * C::ROWS_PER_DMA >= C::BN / 2
+                     : (wave + jj * C::NWAVES) * C::ROWS_PER_DMA >= C::BN / 2);
             if (which == C::A_PW + jj) {
                 if (decltype(nt_tag)::value)
                     dma16_nt(up ? w1 : w0, b_off[jj] + kb,
@@ -182,14 +187,12 @@ __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe16_kernel(
                 }
                 const uint2 pk = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
                 if (C::SWIGLU && PO) {
-                    // tile-packed h straight from the registers: the wave's sub-tile j is the
-                    // column half j of the 32-column block wn of row block (wm + WM*i); this
-                    // lane holds half a 16-byte chunk.  Rows beyond the tile's last row (padding
-                    // of the expert's last block) are written as zeros.
-                    static_assert(!PO || (TN16 == 4 && C::BN_OUT == 128), "packed output tiling");
-                    const int col0 = n0 + 32 * wn;
+                    // tile-packed h straight from the registers: 16 of the 32 columns of a block of
+                    // row block (wm + WM*i); this lane holds half a 16-byte chunk.  Rows beyond the
+                    // tile's last row (padding of the expert's last block) are written as zeros.
+                    const int col0 = n0 + 16 * (wn * JN + j);
                     if (col0 < N) {
-                        const int chunk = 2 * j + (cq >> 3);
+                        const int chunk = ((col0 & 31) >> 3) + (cq >> 3);
                         const int piece = 4 * mrow + (chunk ^ ((mrow >> 1) & 3));
                         unsigned char* blk = reinterpret_cast<unsigned char*>(
                             Cout + ((size_t)(t.blk0 + wm + C::WM * i) * 16 * N +
@@ -302,8 +305,8 @@ __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe16_kernel(
 
     if (C::SWIGLU && !PO) {
         // cooperative write-out of the staged tile: 16 bytes per lane, whole rows
-        static_assert(!C::SWIGLU || (size_t)C::BM * kStageRowBytes <= C::LDS_BYTES, "stage tile");
-        static_assert(!C::SWIGLU || C::BN_OUT == 128, "stage row pitch assumes 128 columns");
+        static_assert(!C::SWIGLU || PO || (size_t)C::BM * kStageRowBytes <= C::LDS_BYTES, "stage tile");
+        static_assert(!C::SWIGLU || PO || C::BN_OUT == 128, "stage row pitch assumes 128 columns");
         __builtin_amdgcn_s_barrier();
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         constexpr int CPR = C::BN_OUT / 8;                  // 16-byte chunks per tile row
@@ -368,8 +371,29 @@ hipError_t launch_expert_up_bf16_packed(const bf16_t* x, const int32_t* offsets,
         x, offsets, wg_packed, wu_packed, n_rows, E, f, d, h_packed, s, row_src, topk);
 }
 
-// Tile height by the average rows per expert, as for the row-major operands: 320-row tiles from
-// 192 rows per expert, 192-row tiles below.  h_row_major: h is written [n_rows, f] row-major
+// Tiles of 128 weight rows instead of 256 where a batch has few tiles: a 256-wide tile takes a
+// whole CU (112 or 144 KB of LDS), so up to 128 of them leave half the chip idle - the down
+// projection of 8 experts x 4096 outputs, or both projections of small experts.  128 x 128 tiles (64
+// KB: two workgroups per CU) while an expert's rows fit in one of them or even those would not
+// fill the chip, 320 x 128 in between (fewer m-tiles; down only).  The number of m-tiles is
+// estimated from the average rows per expert plus 15 % for the spread; with two or more of them
+// the narrow tiles' second pass over the activations costs more than it gains unless at most 64 wide
+// tiles are there.  Measured, packed operands, us, 256-wide -> narrow: down 4096 x 14336, 8 experts: 50
+// rows each 199 -> 151, 83 214 -> 162, 120 229 -> 188, 175 257 -> 220, 275 319 -> 279 (312: 340 -> 479,
+// hence the 15 %); down 1024 x 2048, 16 experts: 64 rows 32 -> 23, 256 55 -> 32; gate/up 1024 x
+// 3072, 8 experts: 25 rows 38 -> 30, 250 63 -> 40 (500: 63 -> 78).  At 256 wide tiles and more the
+// 256-wide ones are ahead or level (gate/up 2048 x 1024, 16 experts, 256 rows 39 -> 62).
+enum class Narrow { none, rows128, rows320 };
+static Narrow narrow_tiles(int n_rows, int E, int N, int wide) {
+    const long long spread = 115ll * n_rows, per = 100ll * E;      // 1.15 x rows per expert
+    const long long m = spread <= 320 * per ? 1 : (spread + 320 * per - 1) / (320 * per);
+    const long long tiles = E * m * ((N + wide - 1) / wide);
+    if (tiles > (m == 1 ? 128 : 64)) return Narrow::none;
+    return spread <= 128 * per || tiles <= 64 ? Narrow::rows128 : Narrow::rows320;
+}
+
+// Otherwise tile height by the average rows per expert, as for the row-major operands: 320-row
+// tiles from 192 rows per expert, 192-row tiles below.  h_row_major: h is written [n_rows, f] row-major
 // (for a down projection on row-major operands) instead of tile-packed.
 hipError_t launch_expert_up_bf16_packed_x(const bf16_t* x_packed, const int32_t* offsets,
                                           const bf16_t* wg_packed, const bf16_t* wu_packed,
@@ -377,12 +401,16 @@ hipError_t launch_expert_up_bf16_packed_x(const bf16_t* x_packed, const int32_t*
                                           bool h_row_major, hipStream_t s) {
     typedef PipeCfg<320, 256, 32, 4, 2, 4, true> Large;
     typedef PipeCfg<192, 256, 32, 4, 2, 4, true> Mid;
+    typedef PipeCfg<128, 128, 32, 4, 2, 4, true> Small;
     const bool large = (long long)n_rows >= 192ll * E;
     if (h_row_major)
         return large ? launch_pipe16<Large, true, true, false>(x_packed, offsets, wg_packed,
                                                                wu_packed, n_rows, E, f, d, h, s)
                      : launch_pipe16<Mid, true, true, false>(x_packed, offsets, wg_packed,
                                                              wu_packed, n_rows, E, f, d, h, s);
+    if (narrow_tiles(n_rows, E, f, Large::BN_OUT) == Narrow::rows128)
+        return launch_pipe16<Small, true, true, true>(x_packed, offsets, wg_packed, wu_packed, n_rows,
+                                                      E, f, d, h, s);
     return large ? launch_pipe16<Large, true, true, true>(x_packed, offsets, wg_packed, wu_packed,
                                                           n_rows, E, f, d, h, s)
                  : launch_pipe16<Mid, true, true, true>(x_packed, offsets, wg_packed, wu_packed,
@@ -392,6 +420,13 @@ hipError_t launch_expert_up_bf16_packed_x(const bf16_t* x_packed, const int32_t*
 hipError_t launch_expert_down_bf16_packed(const bf16_t* h_packed, const int32_t* offsets,
                                           const bf16_t* wd_packed, int n_rows, int d, int f,
                                           int E, bf16_t* y, hipStream_t s) {
+    const Narrow narrow = narrow_tiles(n_rows, E, d, 256);
+    if (narrow == Narrow::rows128)
+        return launch_pipe16<PipeCfg<128, 128, 32, 4, 2, 4, false>, true, true, false>(
+            h_packed, offsets, wd_packed, nullptr, n_rows, E, d, f, y, s);
+    if (narrow == Narrow::rows320)
+        return launch_pipe16<PipeCfg<320, 128, 32, 4, 2, 4, false>, true, true, false>(
+            h_packed, offsets, wd_packed, nullptr, n_rows, E, d, f, y, s);
     if ((long long)n_rows >= 192ll * E)
         return launch_pipe16<PipeCfg<320, 256, 32, 4, 2, 4, false>, true, true, false>(
             h_packed, offsets, wd_packed, nullptr, n_rows, E, d, f, y, s);

@@ -30,8 +30,7 @@ struct PipeCfg {
     static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "tile / wave grid mismatch");
     static_assert(BM % ROWS_PER_DMA == 0 && BN % (ROWS_PER_DMA * NWAVES) == 0,
                   "wave-loads must divide evenly");
-    static_assert(!SWIGLU || ((BN / 2 / ROWS_PER_DMA) % NWAVES == 0 && TN % 2 == 0),
-                  "gate/up halves must split on a wave-load round and pair up inside a wave");
+    static_assert(!SWIGLU || (BN / 2) % ROWS_PER_DMA == 0, "a wave-load is all gate or all up");
     static_assert(STAGES >= 3 && (STAGES - 3) * G_MAX <= 63, "ring depth (vmcnt is 6 bits)");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };

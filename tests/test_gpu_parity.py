@@ -688,6 +688,12 @@ def test_pack_weights_layout(E, R, K):
     (256, 512, [3, 0, 70, 1, 129, 64, 0, 0]),
     (128, 256, [5, 17, 64, 1, 0, 33, 65, 16]),
     (512, 1024, [40, 1]),
+    # few tiles: 128-row tiles of 128 weight rows with one and two m-tiles, 320-row ones (down), and
+    # the 256-wide tiles from 129 wide tiles (65 experts x 2) and from two m-tiles on
+    (256, 128, [128, 129, 16, 0, 255, 97]),
+    (2304, 128, [300, 320, 321, 1, 150, 0, 120, 100]),
+    (384, 256, [3, 0, 17, 1, 20] * 13),
+    (320, 192, [400, 380, 333, 321]),
 ])
 def test_packed_expert_gemms(d, f, rows):
     """moe_expert_up_swiglu_gather_packed + moe_expert_down_packed against the oracle, and - where
