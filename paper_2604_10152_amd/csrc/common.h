@@ -61,6 +61,21 @@ struct TransposeReduce {
 
 __device__ __forceinline__ float silu_f32(float z) { return z / (1.0f + __expf(-z)); }
 
+// Whether the 256-wide tiles (wide outputs each) of a batch leave much of the chip idle: a tile
+// takes a whole CU, and with m-tiles of up to 320 rows (estimated from the average rows per
+// expert plus 15 % for the spread) there are at most 128 of them, or 64 if an expert needs
+// several.  The measurements are at the rules that use it.
+struct WideTiles {
+    long long m, tiles;         // m-tiles per expert, tiles in all
+    WideTiles(int n_rows, int E, int N, int wide)
+        : m((115ll * n_rows + 32000ll * E - 1) / (32000ll * E)),
+          tiles(E * m * ((N + wide - 1) / wide)) {}
+    bool few() const { return tiles <= (m <= 1 ? 128 : 64); }
+};
+inline bool few_wide_tiles(int n_rows, int E, int N, int wide) {
+    return WideTiles(n_rows, E, N, wide).few();
+}
+
 // ---- launchers (host side, defined in the .hip files) -------------------------------
 hipError_t launch_route_topk(const void* x, const void* wr, const float* bias, int T, int d,
                              int E, int k, int renorm, int dtype, int32_t* idx, float* w,
@@ -115,10 +130,10 @@ hipError_t launch_gather_pack_rows(const bf16_t* x, const int32_t* row_src, int 
                                    const int32_t* offsets, int n_rows, int E, int K,
                                    bf16_t* dst, hipStream_t s);
 hipError_t launch_pack_tiles(const bf16_t* src, long long rows, int K, bf16_t* dst, hipStream_t s);
-hipError_t launch_expert_up_bf16_small(const bf16_t* x_perm, const int32_t* offsets,
-                                       const bf16_t* wg, const bf16_t* wu, int n_rows, int d,
-                                       int f, int E, bf16_t* h, hipStream_t s,
-    const int32_t* row_src, int topk);
+hipError_t launch_expert_up_bf16_ring(const bf16_t* x_perm, const int32_t* offsets,
+                                      const bf16_t* wg, const bf16_t* wu, int n_rows, int d, int f,
+                                      int E, bf16_t* h, hipStream_t s, const int32_t* row_src,
+                                      int topk);
 hipError_t launch_expert_down_bf16_small(const bf16_t* h, const int32_t* offsets,
                                          const bf16_t* wd, int n_rows, int d, int f, int E,
                                          bf16_t* y, hipStream_t s);
@@ -128,6 +143,8 @@ hipError_t launch_expert_up_bf16_mid(const bf16_t* x_perm, const int32_t* offset
                                      int topk);
 hipError_t launch_expert_down_bf16_mid(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
                                        int n_rows, int d, int f, int E, bf16_t* y, hipStream_t s);
+hipError_t launch_expert_down_bf16_tall(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
+                                        int n_rows, int d, int f, int E, bf16_t* y, hipStream_t s);
 hipError_t launch_combine(const void* y_perm, const int32_t* row_of, const float* w,
                           const void* residual, int T, int d, int k, int dtype, void* out,
                           hipStream_t s);

@@ -350,17 +350,21 @@ hipError_t launch_pipe(const bf16_t* A, const int32_t* offsets, const bf16_t* W0
 
 }  // namespace
 
-// Few rows per expert: the weights stream from HBM once and nothing else matters.  64-row
-// tiles, narrow N so that every CU owns a stream, 128-byte rows per step (BK = 64; 64-byte rows
-// lose ~10 % of HBM throughput) and a 4 / 6 stage ring (~70-120 KB of requests in flight per CU).
-hipError_t launch_expert_up_bf16_small(const bf16_t* x_perm, const int32_t* offsets,
-                                       const bf16_t* wg, const bf16_t* wu, int n_rows, int d,
-                                       int f, int E, bf16_t* h, hipStream_t s,
-                                       const int32_t* row_src, int topk) {
-    return launch_pipe<PipeCfg<64, 128, 64, 4, 1, 2, true>>(x_perm, offsets, wg, wu, n_rows, E, f,
-                                                            d, h, s, row_src, topk);
+// Gate/up with up to about 90 rows per expert: 128 x 128 tiles (64 gate and 64 up rows), 128-byte
+// rows per step (BK = 64; 64-byte rows lose ~10 % of HBM throughput), 4-stage ring of 128 KB, 8
+// wavefronts.  Against the 64 x 128 ring of two wavefronts before, rows beyond 64 no longer cost a
+// second pass over the weights, and below that the eight waves issue the wave-loads faster.
+hipError_t launch_expert_up_bf16_ring(const bf16_t* x_perm, const int32_t* offsets,
+                                      const bf16_t* wg, const bf16_t* wu, int n_rows, int d, int f,
+                                      int E, bf16_t* h, hipStream_t s, const int32_t* row_src,
+                                      int topk) {
+    return launch_pipe<PipeCfg<128, 128, 64, 4, 4, 2, true>>(x_perm, offsets, wg, wu, n_rows, E, f,
+                                                             d, h, s, row_src, topk);
 }
 
+// Down projection with few rows per expert and a long contraction: the weights stream from HBM
+// once and nothing else matters.  64-row tiles, 6-stage ring (~120 KB in flight per CU), or the
+// private streams where few experts are active.
 hipError_t launch_expert_down_bf16_small(const bf16_t* h, const int32_t* offsets,
                                          const bf16_t* wd, int n_rows, int d, int f, int E,
                                          bf16_t* y, hipStream_t s) {
@@ -384,6 +388,14 @@ hipError_t launch_expert_down_bf16_mid(const bf16_t* h, const int32_t* offsets, 
                                        int n_rows, int d, int f, int E, bf16_t* y,
                                        hipStream_t s) {
     return launch_pipe<PipeCfg<128, 128, 64, 4, 2, 4, false>>(h, offsets, wd, nullptr, n_rows, E,
+                                                              d, f, y, s);
+}
+
+// The same with 192-row tiles (160 KB): one m-tile per expert between 128 and 192 rows.
+hipError_t launch_expert_down_bf16_tall(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
+                                        int n_rows, int d, int f, int E, bf16_t* y,
+                                        hipStream_t s) {
+    return launch_pipe<PipeCfg<192, 128, 64, 4, 2, 4, false>>(h, offsets, wd, nullptr, n_rows, E,
                                                               d, f, y, s);
 }
 

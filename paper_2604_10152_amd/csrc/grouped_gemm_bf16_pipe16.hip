@@ -385,11 +385,10 @@ hipError_t launch_expert_up_bf16_packed(const bf16_t* x, const int32_t* offsets,
 // 256-wide ones are ahead or level (gate/up 2048 x 1024, 16 experts, 256 rows 39 -> 62).
 enum class Narrow { none, rows128, rows320 };
 static Narrow narrow_tiles(int n_rows, int E, int N, int wide) {
-    const long long spread = 115ll * n_rows, per = 100ll * E;      // 1.15 x rows per expert
-    const long long m = spread <= 320 * per ? 1 : (spread + 320 * per - 1) / (320 * per);
-    const long long tiles = E * m * ((N + wide - 1) / wide);
-    if (tiles > (m == 1 ? 128 : 64)) return Narrow::none;
-    return spread <= 128 * per || tiles <= 64 ? Narrow::rows128 : Narrow::rows320;
+    const WideTiles w(n_rows, E, N, wide);
+    if (!w.few()) return Narrow::none;
+    const bool one = 115ll * n_rows <= 12800ll * E;     // 1.15 x the average rows fit in 128
+    return one || w.tiles <= 64 ? Narrow::rows128 : Narrow::rows320;
 }
 
 // Otherwise tile height by the average rows per expert, as for the row-major operands: 320-row

@@ -272,49 +272,87 @@ hipError_t launch_one(const bf16_t* A, const int32_t* offsets, const bf16_t* W0,
 
 }  // namespace
 
-// Rows per expert (average) from which a kernel family applies: >= 192 large (MFMA-bound,
-// up to 320-row tiles), >= 48 with a long contraction mid (gate/up: up to 192-row tiles of the
-// same kernel; down: 128-row tiles of the 32x32x16 pipeline), below that small (64-row tiles).
+// Which kernel a batch takes, by r = rows per expert on average, the contraction length K and the
+// number of 256-wide tiles (gate/up: 128 outputs).  The host knows no more; the map from tiles to
+// experts is made on the device.  Every line was measured on both sides (us; shapes d_model x
+// d_ff, E experts, top-k uniform or under a Zipf bias; rows given per expert).
 constexpr int g_large_rows = 192, g_mid_rows = 48;
 static inline bool large_batch(int n_rows, int E) {
     return (long long)n_rows >= (long long)g_large_rows * E;
 }
-static inline bool mid_batch(int n_rows, int E, int K) {
-    return K >= 4096 && (long long)n_rows >= (long long)g_mid_rows * E;
+static inline bool rows_at_least(int n_rows, int E, int r) {
+    return (long long)n_rows >= (long long)r * E;
 }
-// Few rows per expert, two kernels: with a long contraction axis the deep global->LDS ring wins
-// (5.8 vs 5.3 TB/s at the Mixtral shape); with a short one (fine-grained experts) a tile lives
-// for a few dozen steps only and three co-resident register-staged workgroups per CU hide the
-// prologue / epilogue of each other better (360 vs 490 us at the 64-expert shape).
 constexpr int kLongK = 4096;
 
-// Large batches: up to 320-row tiles, 8 wavefronts, MFMA-bound.  Fewer rows per expert: the
-// weights stream once from HBM and narrow tiles give every CU its own stream (measured at 16
-// experts x 128 rows on average: mid 1116 us, large 1231 us, small 1437 us per layer).
+// Gate/up (K = d_model, 128 outputs per 256-wide tile).
+//  - r >= 192, large: up to 320-row tiles, MFMA-bound.  Unless they are few: 8 x 1024 outputs are
+//    64 tiles on 256 CUs (3072 x 1024, 200 rows: 59 -> 32 with the ring).
+//  - ring (128 x 128 tiles, BK = 64: whole 128-byte lines of row-major operands) for K >= 2048 up to
+//    88 rows: against the 64 x 128 ring that was here 309 -> 305 (4096 x 14336, 8 experts, 20 rows),
+//    118 -> 92 (4096 x 2048, 16, 31 rows); against register-staged tiles 141 -> 108 (2048 x 1408, 64,
+//    15 rows), 46 -> 30 (3072 x 1024, 8, 50 rows); against mid 357 -> 320 (4096 x 14336, 50 rows),
+//    378 -> 352 (83 rows), and behind it from there (120 rows: 404 / 410, 150: 428 / 557).
+//  - mid (192-row tiles, half lines): above that, and at K < 4096 from 48 rows if there are tiles for
+//    two rounds of the chip (2048 x 1408, 64 experts: register-staged 220 -> 199 at 120 rows, 178 -> 157
+//    at 48), or from 96 rows (1024 x 2048, 16 experts, 128 rows: 49 -> 30 uniform, 49 -> 45 skewed; but
+//    31 -> 43 at 64 rows, skewed).
+//  - register-staged otherwise: contractions of a few dozen steps, where several co-resident
+//    workgroups hide each other's prologue (1024 x 2048, 25 rows: 29 against 31 with the ring).
 hipError_t launch_expert_up_bf16(const bf16_t* x_perm, const int32_t* offsets, const bf16_t* wg,
                                  const bf16_t* wu, int n_rows, int d, int f, int E, bf16_t* h,
                                  hipStream_t s, const int32_t* row_src, int topk) {
     if (n_rows == 0) return hipSuccess;
-    if (large_batch(n_rows, E))
+    const long long tiles = (long long)E * ((f + 127) / 128);
+    const bool few = few_wide_tiles(n_rows, E, f, 128);
+    if (large_batch(n_rows, E) && !(few && d >= 2048))
         return launch_expert_up_bf16_large16(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s,
                                              row_src, topk);
-    if (mid_batch(n_rows, E, d))
+    bool mid;
+    if (d >= kLongK) mid = rows_at_least(n_rows, E, 88);
+    else if (rows_at_least(n_rows, E, 96)) mid = tiles > (d >= 2048 ? 128 : 191);
+    else mid = rows_at_least(n_rows, E, g_mid_rows) && tiles >= 512;
+    if (mid && !large_batch(n_rows, E))
         return launch_expert_up_bf16_mid(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s, row_src,
                                          topk);
-    if (d >= kLongK)
-        return launch_expert_up_bf16_small(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s, row_src,
-                                           topk);
+    if (d >= 2048)
+        return launch_expert_up_bf16_ring(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s, row_src,
+                                          topk);
     return launch_one<TileCfg<64, 256, 1, 4, true>>(x_perm, offsets, wg, wu, n_rows, E, f, d, h, s, row_src, topk);
 }
 
+// Down (K = d_ff).
+//  - r >= 192, large, unless its tiles are few: mid then has 128 x 128 ones (4096 x 14336, 8 experts,
+//    225 rows: 363 -> 308; 1024 x 4096, 8, 250 rows: 88 -> 34).
+//  - mid (128 x 128 tiles) from 48 rows, at 1280 <= K < 4096 from 12 rows (2048 x 1408, 64 experts:
+//    register-staged 70 -> 61 at 15 rows, 99 -> 89 at 60; 8 rows 41 -> 46; K = 768 15 -> 21).
+//  - tall (192 x 128) where mid would need a second m-tile per expert: at K >= 4096 from 100 rows if
+//    the tiles make one round of the chip (4096 x 14336, 8 experts, 120 rows 301 -> 198, 175 rows 283
+//    -> 210; with more tiles the skewed 5120 x 8192, 16 experts, 128 rows loses, 330 -> 382, with fewer
+//    1024 x 4096, 8 experts, 30 -> 47); at 1280 <= K < 4096 from 112 rows with several rounds of
+//    tiles (2048 x 1408, 64 experts, 120 rows: 127 -> 112).
+//  - small: K >= 4096 with few rows, choosing on the device (grouped_gemm_bf16_pipe.hip).
 hipError_t launch_expert_down_bf16(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
                                    int n_rows, int d, int f, int E, bf16_t* y, hipStream_t s) {
     if (n_rows == 0) return hipSuccess;
-    if (large_batch(n_rows, E))
+    const long long tiles = (long long)E * ((d + 127) / 128);
+    if (large_batch(n_rows, E)) {
+        if (few_wide_tiles(n_rows, E, d, 256))
+            return launch_expert_down_bf16_mid(h, offsets, wd, n_rows, d, f, E, y, s);
         return launch_expert_down_bf16_large16(h, offsets, wd, n_rows, d, f, E, y, s);
-    if (mid_batch(n_rows, E, f))
+    }
+    if (f >= kLongK) {
+        if (!rows_at_least(n_rows, E, g_mid_rows))
+            return launch_expert_down_bf16_small(h, offsets, wd, n_rows, d, f, E, y, s);
+        if (rows_at_least(n_rows, E, 100) && tiles >= 128 && tiles <= 256)
+            return launch_expert_down_bf16_tall(h, offsets, wd, n_rows, d, f, E, y, s);
         return launch_expert_down_bf16_mid(h, offsets, wd, n_rows, d, f, E, y, s);
-    if (f >= kLongK) return launch_expert_down_bf16_small(h, offsets, wd, n_rows, d, f, E, y, s);
+    }
+    if (f >= 1280 && rows_at_least(n_rows, E, 12)) {
+        if (rows_at_least(n_rows, E, 112) && tiles >= 512)
+            return launch_expert_down_bf16_tall(h, offsets, wd, n_rows, d, f, E, y, s);
+        return launch_expert_down_bf16_mid(h, offsets, wd, n_rows, d, f, E, y, s);
+    }
     return launch_one<TileCfg<64, 128, 1, 4, false>>(h, offsets, wd, nullptr, n_rows, E, d, f, y, s);
 }
 
