@@ -77,16 +77,38 @@ __global__ __launch_bounds__(kRowThreads) void combine_kernel(
     }
 }
 
-template <typename T>
+// One workgroup per row.  NV > 0: 16-byte accesses, the row stays in registers between the sum of
+// squares and the scaling (NV pieces per thread: one read of x instead of two passes of 2-byte
+// loads; 80 x 4096 bf16 5.6 -> 3.4 us, 2048 x 4096 10.5 -> 7.1).  NV = 0: any length and alignment.
+template <typename T, int NV>
 __global__ __launch_bounds__(kRowThreads) void rmsnorm_kernel(
     const T* __restrict__ x, const T* __restrict__ gain, int d, float eps, T* __restrict__ out) {
     __shared__ float part[kRowThreads / kWave];
+    constexpr int V = RowVec<T>::N, N = NV > 0 ? NV : 1;
     const int t = blockIdx.x;
     const T* xt = x + (size_t)t * d;
+    float v[N][V];
     float ss = 0.f;
-    for (int j = threadIdx.x; j < d; j += kRowThreads) {
-        float v = load_as_float(xt + j);
-        ss = fmaf(v, v, ss);
+    if (NV > 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int j = (i * kRowThreads + threadIdx.x) * V;
+            if (j < d) {
+                RowVec<T>::load(xt + j, v[i]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < V; ++q) v[i][q] = 0.f;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int q = 0; q < V; ++q) ss = fmaf(v[i][q], v[i][q], ss);
+    } else {
+        for (int j = threadIdx.x; j < d; j += kRowThreads) {
+            float e = load_as_float(xt + j);
+            ss = fmaf(e, e, ss);
+        }
     }
     ss = wave_sum(ss);
     if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave] = ss;
@@ -95,9 +117,39 @@ __global__ __launch_bounds__(kRowThreads) void rmsnorm_kernel(
 #pragma unroll
     for (int i = 0; i < kRowThreads / kWave; ++i) tot += part[i];
     const float scale = 1.0f / sqrtf(tot / (float)d + eps);
-    for (int j = threadIdx.x; j < d; j += kRowThreads)
-        store_from_float(out + (size_t)t * d + j,
-                         load_as_float(xt + j) * scale * load_as_float(gain + j));
+    if (NV > 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int j = (i * kRowThreads + threadIdx.x) * V;
+            if (j < d) {
+                float g[V], o[V];
+                RowVec<T>::load(gain + j, g);
+#pragma unroll
+                for (int q = 0; q < V; ++q) o[q] = v[i][q] * scale * g[q];
+                RowVec<T>::store(out + (size_t)t * d + j, o);
+            }
+        }
+    } else {
+        for (int j = threadIdx.x; j < d; j += kRowThreads)
+            store_from_float(out + (size_t)t * d + j,
+                             load_as_float(xt + j) * scale * load_as_float(gain + j));
+    }
+}
+
+template <typename T>
+void launch_rmsnorm_typed(const T* x, const T* gain, int T_, int d, float eps, T* out,
+                          hipStream_t s) {
+    constexpr int V = RowVec<T>::N;
+    const bool vec = d % V == 0 && (((uintptr_t)x | (uintptr_t)gain | (uintptr_t)out) & 15u) == 0;
+    const int pieces = (d + kRowThreads * V - 1) / (kRowThreads * V);      // per thread
+    if (vec && pieces <= 1)
+        hipLaunchKernelGGL((rmsnorm_kernel<T, 1>), dim3(T_), dim3(kRowThreads), 0, s, x, gain, d, eps, out);
+    else if (vec && pieces <= 2)
+        hipLaunchKernelGGL((rmsnorm_kernel<T, 2>), dim3(T_), dim3(kRowThreads), 0, s, x, gain, d, eps, out);
+    else if (vec && pieces <= 4)
+        hipLaunchKernelGGL((rmsnorm_kernel<T, 4>), dim3(T_), dim3(kRowThreads), 0, s, x, gain, d, eps, out);
+    else
+        hipLaunchKernelGGL((rmsnorm_kernel<T, 0>), dim3(T_), dim3(kRowThreads), 0, s, x, gain, d, eps, out);
 }
 
 }  // namespace
@@ -122,11 +174,9 @@ hipError_t launch_rmsnorm(const void* x, const void* gain, int T, int d, float e
                           void* out, hipStream_t s) {
     if (T == 0 || d == 0) return hipSuccess;
     if (dtype == 0)
-        hipLaunchKernelGGL(rmsnorm_kernel<float>, dim3(T), dim3(kRowThreads), 0, s,
-                           (const float*)x, (const float*)gain, d, eps, (float*)out);
+        launch_rmsnorm_typed((const float*)x, (const float*)gain, T, d, eps, (float*)out, s);
     else
-        hipLaunchKernelGGL(rmsnorm_kernel<bf16_t>, dim3(T), dim3(kRowThreads), 0, s,
-                           (const bf16_t*)x, (const bf16_t*)gain, d, eps, (bf16_t*)out);
+        launch_rmsnorm_typed((const bf16_t*)x, (const bf16_t*)gain, T, d, eps, (bf16_t*)out, s);
     return hipGetLastError();
 }
 
