@@ -2,31 +2,125 @@
 // (SpecMoE Fig. 2: tokens that activate the same expert are served together; Sec. 3.2: the
 // per-expert activation counts of the verification pass are the differences of expert_offsets.)
 //
-// Index phase: ONE workgroup of 16 wavefronts (8 beyond 64 experts).  Wave w owns the w-th contiguous slice of the
-// flat pair array.  (A) per-wave, per-expert counts in LDS (integer atomics: order-free);
-// (B) totals -> exclusive prefix sum over experts -> each wave's first destination row per
-// expert; (C) every wave walks its slice in order, 64 pairs at a time, ranks equal experts
-// inside the 64 with ballots, and bumps its private LDS cursors.  Contiguous slices walked in
-// order make the sort stable with no ordered atomics.  Gather phase: a coalesced 16-byte copy
-// of whole rows over the full grid.
+// Index phase: ONE workgroup; wave w owns the w-th contiguous slice of the flat pair array and
+// walks it in order, 64 pairs at a time.
+//  - E <= 64: up to 16384 pairs (16 waves x 16 rows of 64) the slice sits in registers.  Every lane finds the lanes of its row with the same expert (one ballot per bit of the
+//    id), its rank among them, and its place in the wave's share of the expert through a running
+//    count in LDS; wave 0 turns the 16 x E counts into the offsets and every wave's first row; a
+//    pair's row is then first + place.  (Longer slices are walked a second time.)
+//  - otherwise: per-wave, per-expert counts (LDS integer atomics: order-free), totals -> exclusive
+//    prefix sum -> first rows, then a second walk that ranks equal experts by a loop over the
+//    distinct ones.
+// Contiguous slices walked in order make the sort stable with no ordered atomics.  The loop over
+// distinct experts took 23.8 us for 1285 tokens x 6 of 64 skewed experts, the ballots take 9.6;
+// 320 x 6 of 64: 8.7 -> 4.6, 2048 x 2 of 8: 8.4 -> 5.9, 80 x 2 of 8: 4.4 -> 3.2 (a launch is 2.5).
+// Gather phase: a coalesced 16-byte copy of whole rows over the full grid.
 #include "common.h"
 
 namespace specmoe {
 namespace {
 
-constexpr int kPermWavesSmallE = 16;   // E <= 64: shorter slices per wave (the walk is serial)
-constexpr int kPermWavesLargeE = 8;    // (waves + 1) * E counters have to fit the LDS default
+constexpr int kSmallWaves = 16;    // E <= 64: short slices per wave
+constexpr int kSmallRows = 16;     // rows of 64 pairs a wave keeps in registers
+constexpr int kPermWaves = 8;      // otherwise: (waves + 1) * E counters have to fit the LDS default
 constexpr int kBatch = 8;          // index rows fetched ahead per wavefront
 
-// SMALL_E (E <= 64): in phase (C) lane e keeps expert e's cursor in a register and the loop
-// over the distinct experts of a 64-pair row uses readlane instead of an LDS read-modify-write
-// chain (the chain dominated the kernel: 19 -> ~9 us at 4096 pairs).
-template <bool SMALL_E>
-__global__ __launch_bounds__((SMALL_E ? kPermWavesSmallE : kPermWavesLargeE) * kWave)
-void permute_index_kernel(
+__device__ __forceinline__ unsigned long long lanes_below(int lane) {
+    return lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+}
+
+// E <= 64.  BITS: bits of an expert id.  Beyond kSmallRows rows per wave the slice is walked twice,
+// first for the counts alone, then from the wave's first rows.
+template <int BITS>
+__global__ __launch_bounds__(kSmallWaves * kWave) void permute_index_small_kernel(
     const int32_t* __restrict__ idx, int P, int E, int32_t* __restrict__ offsets,
     int32_t* __restrict__ row_src, int32_t* __restrict__ row_of) {
-    constexpr int kPermWaves = SMALL_E ? kPermWavesSmallE : kPermWavesLargeE;
+    __shared__ int cnt[kSmallWaves][kWave];
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    volatile int* mine = cnt[wave];
+    const int per_wave = ((P + kSmallWaves - 1) / kSmallWaves + kWave - 1) / kWave * kWave;
+    const int lo = min(P, wave * per_wave), hi = min(P, lo + per_wave);
+    const bool once = per_wave <= kSmallRows * kWave;
+    int ev[kSmallRows], place[kSmallRows];
+    // kSmallRows rows from `base`: the expert of every pair and its place behind mine[expert]
+    auto walk = [&](int base) __attribute__((always_inline)) {
+        const int rows = (hi - base + kWave - 1) / kWave;         // wave-uniform
+#pragma unroll
+        for (int b = 0; b < kSmallRows; ++b) {
+            const int p = base + b * kWave + lane;
+            ev[b] = p < hi ? idx[p] : 0;
+        }
+#pragma unroll
+        for (int b = 0; b < kSmallRows; ++b) {
+            if (b >= rows) break;
+            const bool valid = base + b * kWave + lane < hi;
+            const int e = min(max(ev[b], 0), E - 1);
+            unsigned long long same = __ballot(valid);
+#pragma unroll
+            for (int t = 0; t < BITS; ++t) {
+                const unsigned long long m = __ballot((e >> t) & 1);
+                same &= ((e >> t) & 1) ? m : ~m;
+            }
+            const int before = mine[e];
+            __builtin_amdgcn_wave_barrier();
+            const int rank = __popcll(same & lanes_below(lane));
+            ev[b] = e;
+            place[b] = before + rank;
+            // the last lane of a group moves the count on (LDS accesses of a wave stay in order)
+            if (valid && (same >> lane) == 1ull) mine[e] = before + rank + 1;
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
+    auto store = [&](int base, bool add_first) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < kSmallRows; ++b) {
+            const int p = base + b * kWave + lane;
+            if (p < hi) {
+                const int dest = (add_first ? mine[ev[b]] : 0) + place[b];
+                row_src[dest] = p;
+                row_of[p] = dest;
+            }
+        }
+    };
+    mine[lane] = 0;                                                // private to the wave
+    for (int base = lo; base < hi; base += kSmallRows * kWave) walk(base);
+    __syncthreads();
+    if (wave == 0) {                                               // lane e: expert e
+        int c[kSmallWaves], total = 0;
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) c[w] = cnt[w][lane];
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) total += c[w];
+        int incl = total;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int v = __shfl_up(incl, off, kWave);
+            if (lane >= off) incl += v;
+        }
+        int run = incl - total;
+        if (lane < E) offsets[lane] = run;
+        if (lane == E - 1) offsets[E] = incl;
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; ++w) {
+            cnt[w][lane] = run;
+            run += c[w];
+        }
+    }
+    __syncthreads();
+    if (once) {
+        store(lo, true);
+    } else {
+        for (int base = lo; base < hi; base += kSmallRows * kWave) {
+            walk(base);
+            store(base, false);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kPermWaves * kWave) void permute_index_kernel(
+    const int32_t* __restrict__ idx, int P, int E, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ row_src, int32_t* __restrict__ row_of) {
     constexpr int kPermThreads = kPermWaves * kWave;
     extern __shared__ int lds[];             // wave_cnt[kPermWaves][E], excl[E]
     int* wave_cnt = lds;
@@ -93,8 +187,7 @@ void permute_index_kernel(
     }
     __syncthreads();
 
-    const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-    int cursor = (SMALL_E && lane < E) ? mine[lane] : 0;                // lane e: cursor of expert e
+    const unsigned long long lt_mask = lanes_below(lane);
     for (int base0 = lo; base0 < hi; base0 += kWave * kBatch) {         // (C)
 #pragma unroll
         for (int b = 0; b < kBatch; ++b) {
@@ -113,16 +206,10 @@ void permute_index_kernel(
                 const int leader = __ffsll((long long)todo) - 1;
                 const int cur = __builtin_amdgcn_readlane(e, leader);
                 const unsigned long long grp = __ballot(e == cur);
-                if (SMALL_E) {
-                    const int first = __builtin_amdgcn_readlane(cursor, cur);
-                    if (e == cur) dest = first + __popcll(grp & lt_mask);
-                    if (lane == cur) cursor += __popcll(grp);
-                } else {
-                    if (e == cur) dest = mine[cur] + __popcll(grp & lt_mask);
-                    __builtin_amdgcn_wave_barrier();
-                    if (lane == leader) mine[cur] += __popcll(grp);
-                    __builtin_amdgcn_wave_barrier();
-                }
+                if (e == cur) dest = mine[cur] + __popcll(grp & lt_mask);
+                __builtin_amdgcn_wave_barrier();
+                if (lane == leader) mine[cur] += __popcll(grp);
+                __builtin_amdgcn_wave_barrier();
                 todo &= ~grp;
             }
             if (valid) { row_src[dest] = p; row_of[p] = dest; }
@@ -153,14 +240,22 @@ hipError_t launch_permute(const void* x, const int32_t* idx, int T, int d, int E
                           int dtype, void* x_perm, int32_t* offsets, int32_t* row_src,
                           int32_t* row_of, hipStream_t s) {
     const int P = T * k;
-    if (E <= kWave)
-        hipLaunchKernelGGL(permute_index_kernel<true>, dim3(1), dim3(kPermWavesSmallE * kWave),
-                           (size_t)(kPermWavesSmallE + 1) * E * sizeof(int), s, idx, P, E, offsets,
-                           row_src, row_of);
-    else
-        hipLaunchKernelGGL(permute_index_kernel<false>, dim3(1), dim3(kPermWavesLargeE * kWave),
-                           (size_t)(kPermWavesLargeE + 1) * E * sizeof(int), s, idx, P, E, offsets,
-                           row_src, row_of);
+    if (E <= kWave) {
+        const dim3 block(kSmallWaves * kWave);
+        if (E <= 8)
+            hipLaunchKernelGGL(permute_index_small_kernel<3>, dim3(1), block, 0, s, idx, P, E, offsets,
+                               row_src, row_of);
+        else if (E <= 16)
+            hipLaunchKernelGGL(permute_index_small_kernel<4>, dim3(1), block, 0, s, idx, P, E, offsets,
+                               row_src, row_of);
+        else
+            hipLaunchKernelGGL(permute_index_small_kernel<6>, dim3(1), block, 0, s, idx, P, E, offsets,
+                               row_src, row_of);
+    } else {
+        hipLaunchKernelGGL(permute_index_kernel, dim3(1), dim3(kPermWaves * kWave),
+                           (size_t)(kPermWaves + 1) * E * sizeof(int), s, idx, P, E, offsets, row_src,
+                           row_of);
+    }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || x_perm == nullptr || P == 0) return err;
     const size_t row_bytes = (size_t)d * (dtype == 0 ? 4 : 2);

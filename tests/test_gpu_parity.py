@@ -194,6 +194,26 @@ def test_permute_cases(dtype, T, d, E, k):
     assert (np.bincount(rs // k, minlength=T) == k).all()
 
 
+@pytest.mark.parametrize("T,E,k", [(4096, 16, 4), (4097, 16, 4), (3000, 64, 6), (40, 3, 3), (65, 33, 1),
+                                   (64, 8, 8), (1, 64, 64)])
+def test_permute_slice_forms(T, E, k):
+    """Slices that fill a wave's registers exactly, one row more (second walk), ids of 1 to 6 bits, and
+    ids outside [0, E), which are clamped."""
+    _say(f"permute slices T={T} E={E} k={k}")
+    rng = np.random.default_rng(T + E)
+    idx = rng.integers(0, E, size=(T, k)).astype(np.int32)
+    idx[rng.random((T, k)) < 0.3] = min(2, E - 1)               # a hot expert
+    clamped = idx.copy()
+    if T > 4:
+        idx[1, 0], idx[T // 2, 0] = -5, E + 9
+        clamped[1, 0], clamped[T // 2, 0] = 0, E - 1
+    off, rs, ro, _ = _gpu_permute(torch.zeros((T, 8), dtype=torch.bfloat16), torch.from_numpy(idx), E,
+                                  want_rows=False)
+    order = np.argsort(clamped.ravel(), kind="stable")
+    assert (off == np.concatenate([[0], np.cumsum(np.bincount(clamped.ravel(), minlength=E))])).all()
+    assert (rs == order).all() and (ro[order] == np.arange(T * k)).all()
+
+
 def test_permute_degenerate():
     _say("permute T=0 and indices-only")
     x = torch.zeros((0, 64), dtype=torch.bfloat16)
@@ -359,7 +379,12 @@ def test_combine(dtype, T, d, k, res):
     check_float(f64(out), want, dtype, "combine")
 
 
-@pytest.mark.parametrize("dtype,T,d", [(torch.float32, 5, 100), (torch.bfloat16, 160, 4096)])
+@pytest.mark.parametrize("dtype,T,d", [(torch.float32, 5, 100), (torch.bfloat16, 160, 4096),
+                                       # one, two and four pieces per thread, and what goes the general way
+                                       (torch.bfloat16, 3, 2048), (torch.bfloat16, 3, 2056),
+                                       (torch.bfloat16, 2, 8192), (torch.bfloat16, 2, 8200),
+                                       (torch.bfloat16, 2, 77), (torch.float32, 2, 4096),
+                                       (torch.float32, 2, 1028), (torch.float32, 2, 4100)])
 def test_rmsnorm(dtype, T, d):
     _say(f"rmsnorm {dtype} T={T} d={d}")
     g = torch.Generator().manual_seed(d)
