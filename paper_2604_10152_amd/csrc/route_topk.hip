@@ -1,9 +1,11 @@
 // Gate of one MoE block: router logits in fp64, top-k on logits, softmax gate weights.
 // (SpecMoE Sec. 2.1: the gate selects the top-K experts per token.)
 //
-// A workgroup owns TOK tokens and consists of 4 groups of 4 wavefronts; group g takes the
+// Two forms: vector (few tokens, fp32, more than 64 experts) and matrix (route_topk_mfma_kernel).
+//
+// Vector form: a workgroup owns TOK tokens and consists of 4 groups of 4 wavefronts; group g takes the
 // expert chunks g, g+4, ... of EC experts each, so the widening of the router weights to fp64
-// (the bulk of the work: every weight is converted once per workgroup) is spread over 1024
+// (every weight is converted once per workgroup) is spread over 1024
 // lanes.  Inside a group the d_model axis is dealt to its 256 lanes in 16-byte chunks (chunk q
 // -> wave (q/64)%4, lane q%64), every lane keeps fp64 partial sums for TOK tokens x EC experts
 // (TOK*EC <= 16), so one router-weight load feeds TOK tokens.
@@ -47,6 +49,10 @@ template <> struct Chunk<bf16_t, true> {
             o[2 * i + 1] = (double)bf16_bits_to_float(v[i] >> 16);
         }
     }
+    __device__ static double get(const Raw& v, int i) {
+        const uint32_t w = v[i >> 1];
+        return (double)__uint_as_float(i & 1 ? w & 0xffff0000u : w << 16);
+    }
 };
 template <typename T> struct Chunk<T, false> {          // any d_model, any alignment
     static constexpr int N = 1;
@@ -57,6 +63,50 @@ template <typename T> struct Chunk<T, false> {          // any d_model, any alig
 
 __device__ __forceinline__ bool better(double av, int aid, double bv, int bid) {
     return (av > bv) || (av == bv && aid < bid);
+}
+
+// Ranks token t by one wave, E <= 64: one expert per lane.  Every lane counts the experts that beat
+// its own on the key (logit descending, id ascending) - its rank, i.e. the slot it would fill.  The
+// other lanes' logits arrive through v_readlane broadcasts (a few cycles each) instead of the
+// k x 6 dependent cross-lane exchanges of arg-max rounds.
+__device__ __forceinline__ void rank_token(const double* logit, int lane, int E, int k, int renorm,
+                                           int t, int32_t* __restrict__ idx_out,
+                                           float* __restrict__ w_out,
+                                           const int32_t* __restrict__ remap) {
+    const bool valid = lane < E;
+    const double v = valid ? logit[lane] : 0.0;
+    const int vlo = (int)(uint32_t)__double_as_longlong(v);
+    const int vhi = (int)(uint32_t)((uint64_t)__double_as_longlong(v) >> 32);
+    auto lane_value = [&](double val, int src) __attribute__((always_inline)) -> double {
+        const long long bits = __double_as_longlong(val);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, src);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)bits >> 32), src);
+        return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    };
+    int rank = 0;
+#pragma unroll 8
+    for (int j = 0; j < E; ++j) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(vlo, j);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(vhi, j);
+        const double vj = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+        rank += better(vj, j, v, lane) ? 1 : 0;
+    }
+    const int first = __builtin_amdgcn_readfirstlane(
+        __ffsll((long long)__ballot(valid && rank == 0)) - 1);
+    const double vmax = lane_value(v, first);
+    // softmax over all E experts, relative to the largest logit
+    const double pe = valid ? exp(v - vmax) : 0.0;
+    const double p = pe / wave_sum(pe);
+    double wsum_sel = 0.0;                            // slot order, identical on every lane
+    for (int sl = 0; sl < k; ++sl) {
+        const int src = __builtin_amdgcn_readfirstlane(
+            __ffsll((long long)__ballot(valid && rank == sl)) - 1);
+        wsum_sel += lane_value(p, src);
+    }
+    if (valid && rank < k) {
+        idx_out[(size_t)t * k + rank] = remap ? remap[lane] : lane;
+        w_out[(size_t)t * k + rank] = (float)(renorm ? p / wsum_sel : p);
+    }
 }
 
 template <typename T, bool VEC, int TOK, int EC>
@@ -136,43 +186,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     const int t = t0 + wave_all;
     const double* logit = logits + (size_t)wave_all * E;
     if (E <= kWave) {
-        // One expert per lane: every lane counts the experts that beat its own on the key
-        // (logit descending, id ascending) - its rank, i.e. the slot it would fill.  The other
-        // lanes' logits arrive through v_readlane broadcasts (a few cycles each) instead of the
-        // k x 6 dependent cross-lane exchanges of the arg-max rounds below.
-        const bool valid = lane < E;
-        const double v = valid ? logit[lane] : 0.0;
-        const int vlo = (int)(uint32_t)__double_as_longlong(v);
-        const int vhi = (int)(uint32_t)((uint64_t)__double_as_longlong(v) >> 32);
-        auto lane_value = [&](double val, int src) __attribute__((always_inline)) -> double {
-            const long long bits = __double_as_longlong(val);
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, src);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)bits >> 32), src);
-            return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-        };
-        int rank = 0;
-        for (int j = 0; j < E; ++j) {
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(vlo, j);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(vhi, j);
-            const double vj = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-            rank += better(vj, j, v, lane) ? 1 : 0;
-        }
-        const int first = __builtin_amdgcn_readfirstlane(
-            __ffsll((long long)__ballot(valid && rank == 0)) - 1);
-        const double vmax = lane_value(v, first);
-        // softmax over all E experts, relative to the largest logit
-        const double pe = valid ? exp(v - vmax) : 0.0;
-        const double p = pe / wave_sum(pe);
-        double wsum_sel = 0.0;                        // slot order, identical on every lane
-        for (int sl = 0; sl < k; ++sl) {
-            const int src = __builtin_amdgcn_readfirstlane(
-                __ffsll((long long)__ballot(valid && rank == sl)) - 1);
-            wsum_sel += lane_value(p, src);
-        }
-        if (valid && rank < k) {
-            idx_out[(size_t)t * k + rank] = remap ? remap[lane] : lane;
-            w_out[(size_t)t * k + rank] = (float)(renorm ? p / wsum_sel : p);
-        }
+        rank_token(logit, lane, E, k, renorm, t, idx_out, w_out, remap);
         return;
     }
     // More than 64 experts: lane owns experts lane, lane+64, ...; `taken` marks the ones already
@@ -215,6 +229,126 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     }
 }
 
+// Many tokens, at most 64 experts, bf16: logits on the fp64 matrix cores.  v_mfma_f64_4x4x4 takes
+// 16 cycles for four independent 4 x 4 x 4 blocks - as many multiply-adds per cycle as the vector
+// unit - and sums over the contraction by itself, so neither partial sums per lane nor the
+// butterfly over 64 lanes are needed, and a workgroup of 8 waves needs few enough registers
+// that several share a CU and hide each other's memory and ranking phases.  What bounds it is
+// issue on the fp64 pipe, about half of it the widening conversions (as fast as a multiply-add,
+// but one per weight and 4 RT tokens).
+// A workgroup owns 4 RT tokens (a widened router weight serves RT instructions).  Lane l = i + 4 (b + 4 q) of an operand is row i, contraction element
+// q of block b: the blocks hold the same 4 tokens and 4 experts each (16 experts per instruction,
+// NG instructions for all), or with KS = 2 or 4 (at most 8 or 4 experts) the same experts at KS
+// different column ranges, which are added at the end.  A lane loads 16 bytes, so a unit of 32 KS
+// columns is 8 steps; the waves take units in turn.  Every expert's logit goes through the same
+// order of additions, so duplicated router rows tie exactly.  Products and sums in fp64 as in the
+// vector form.
+constexpr int kMfmaWaves = 8;
+
+template <int NG, int KS, int RT>
+__global__ __launch_bounds__(kMfmaWaves * kWave) void route_topk_mfma_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ wr, const float* __restrict__ bias,
+    int Tn, int d, int E, int k, int renorm, int32_t* __restrict__ idx_out,
+    float* __restrict__ w_out, const int32_t* __restrict__ remap) {
+    typedef Chunk<bf16_t, true> CH;
+    constexpr int BE = 4 / KS;                        // blocks with experts of their own
+    constexpr int PF = 2;                             // units in flight
+    __shared__ double part[kMfmaWaves][RT * NG][kWave];
+    __shared__ double logits[4 * RT][kWave];
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int t0 = blockIdx.x * (4 * RT);
+    const int i = lane & 3, b = (lane >> 2) & 3, q = lane >> 4;
+    const int col0 = (b / BE) * 32 + q * 8;           // column of this lane inside a unit
+    const bf16_t* xrow[RT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) xrow[r] = x + (size_t)min(t0 + 4 * r + i, Tn - 1) * d;
+    const bf16_t* wrow[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) wrow[g] = wr + (size_t)min(16 * g + 4 * (b % BE) + i, E - 1) * d;
+    const int units = (d + 32 * KS - 1) / (32 * KS);
+
+    U128 xr[PF][RT], wv[PF][NG];
+    bool live[PF];
+    auto load = [&](int p, int u) __attribute__((always_inline)) {
+        const int col = u * (32 * KS) + col0;
+        live[p] = col < d;                            // d % 8 == 0: a whole piece or nothing
+        const int at = live[p] ? col : 0;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) xr[p][r] = CH::load(xrow[r] + at);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) wv[p][g] = CH::load(wrow[g] + at);
+        __builtin_amdgcn_sched_barrier(0);            // the requests stay ahead of their use
+    };
+    double acc[RT * NG];
+#pragma unroll
+    for (int g = 0; g < RT * NG; ++g) acc[g] = 0.0;
+#pragma unroll
+    for (int p = 0; p < PF; ++p) load(p, wave + p * kMfmaWaves);
+    for (int u0 = wave; u0 < units; u0 += PF * kMfmaWaves) {
+#pragma unroll
+        for (int p = 0; p < PF; ++p) {
+            const U128 zero = {0, 0, 0, 0};
+            U128 xc[RT], wc[NG];
+#pragma unroll
+            for (int r = 0; r < RT; ++r) xc[r] = live[p] ? xr[p][r] : zero;
+#pragma unroll
+            for (int g = 0; g < NG; ++g) wc[g] = live[p] ? wv[p][g] : zero;
+            load(p, u0 + (p + PF) * kMfmaWaves);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                double xd[RT];
+#pragma unroll
+                for (int r = 0; r < RT; ++r) xd[r] = CH::get(xc[r], e);
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    const double wd = CH::get(wc[g], e);
+#pragma unroll
+                    for (int r = 0; r < RT; ++r)
+                        acc[r * NG + g] =
+                            __builtin_amdgcn_mfma_f64_4x4x4f64(xd[r], wd, acc[r * NG + g], 0, 0, 0);
+                }
+            }
+        }
+    }
+    // lane l holds token l / 16, expert column l % 4 of block (l / 4) % 4
+#pragma unroll
+    for (int g = 0; g < RT * NG; ++g) {
+        if (KS >= 2) acc[g] += __shfl_xor(acc[g], 8, kWave);
+        if (KS >= 4) acc[g] += __shfl_xor(acc[g], 4, kWave);
+        part[wave][g][lane] = acc[g];
+    }
+    __syncthreads();
+    for (int rg = wave; rg < RT * NG; rg += kMfmaWaves) {
+        const int e = 16 * (rg % NG) + 4 * (b % BE) + i;
+        if (b < BE && e < E) {
+            double s = part[0][rg][lane];             // waves in order
+#pragma unroll
+            for (int w = 1; w < kMfmaWaves; ++w) s += part[w][rg][lane];
+            logits[4 * (rg / NG) + q][e] = s + (bias ? (double)bias[e] : 0.0);
+        }
+    }
+    __syncthreads();
+    static_assert(4 * RT <= kMfmaWaves, "a wave ranks one token");
+    if (wave < 4 * RT && t0 + wave < Tn)
+        rank_token(logits[wave], lane, E, k, renorm, t0 + wave, idx_out, w_out, remap);
+}
+
+template <int RT>
+void launch_mfma(const bf16_t* x, const bf16_t* wr, const float* bias, int Tn, int d, int E, int k,
+                 int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
+    const dim3 grid((Tn + 4 * RT - 1) / (4 * RT)), block(kMfmaWaves * kWave);
+#define SPECMOE_ROUTE(NG, KS)                                                                    \
+    hipLaunchKernelGGL((route_topk_mfma_kernel<NG, KS, RT>), grid, block, 0, s, x, wr, bias, Tn, \
+                       d, E, k, renorm, idx, w, remap)
+    if (E <= 4) SPECMOE_ROUTE(1, 4);
+    else if (E <= 8) SPECMOE_ROUTE(1, 2);
+    else if (E <= 16) SPECMOE_ROUTE(1, 1);
+    else if (E <= 32) SPECMOE_ROUTE(2, 1);
+    else SPECMOE_ROUTE(4, 1);
+#undef SPECMOE_ROUTE
+}
+
 template <typename T, bool VEC, int TOK, int EC>
 void launch_variant(const T* x, const T* wr, const float* bias, int Tn, int d, int E, int k,
                     int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
@@ -252,13 +386,28 @@ void launch_typed(const void* x, const void* wr, const float* bias, int Tn, int 
         launch_by_experts<T, false, 1>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);
         return;
     }
-    // Tokens per workgroup.  The kernel is bound by the widening conversions to fp64 (about 8x
-    // the cost of an fp64 FMA per instruction; its time does not depend on d_model below one
-    // chunk per lane and does not depend on k).  Per SIMD of the busiest CU they number
-    //   workgroups per CU x 4 waves x passes x 8 x (TOK + EC)
-    // (every group of 4 waves widens its TOK token chunks and its EC router chunks per pass;
-    // passes x EC covers a quarter of the experts).  More tokens per workgroup share the
-    // widened router weights but leave CUs idle while the batch is small: take the minimum.
+    // Matrix form: from 1025 tokens on with 8 tokens per workgroup (the vector form then needs a
+    // second round of workgroups; 2048 tokens, vector -> matrix: 8 x 4096 13.2 -> 10.6 us, 64 x 2048
+    // 39.9 -> 22.8, 16 x 5120 23.1 -> 19.2, 4 x 1024 7.9 -> 6.3), and with more than 16 experts also
+    // below, 4 tokens per workgroup: from 513 tokens (64 x 2048, 640 tokens 22.8 -> 18.2), or 257 if
+    // rows are short (32 x 1024, 320 tokens 9.5 -> 8.7; 64 x 2048 16.2 against 17.9).  Its workgroups
+    // take longer than the vector form's, so fewer tokens stay there (64 tokens 12.6 against 17.5).
+    if constexpr (sizeof(T) == 2) {
+        if (E <= kWave && Tn > 1024) {
+            launch_mfma<2>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+            return;
+        }
+        if (E <= kWave && E > 16 && (Tn > 512 || (Tn > 256 && d <= 1024))) {
+            launch_mfma<1>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+            return;
+        }
+    }
+    // Vector form, tokens per workgroup: every group of 4 waves widens its TOK token chunks and its
+    // EC router chunks per pass (passes x EC covers a quarter of the experts), so the busiest CU
+    // issues work in proportion to
+    //   workgroups per CU x passes x (TOK + EC).
+    // More tokens per workgroup share the widened router weights but leave CUs idle while the
+    // batch is small: take the minimum, which agreed with the measured order over T, d, E, k.
     int best_tok = 1;
     long long best = -1;
     for (int tok = 1; tok <= 4; tok *= 2) {

@@ -112,6 +112,30 @@ def test_route_cases(dtype, T, d, E, k, renorm, bias):
     _check_route(x, wr, b, k, renorm)
 
 
+@pytest.mark.parametrize("T,d,E,k,bias", [
+    (1025, 72, 3, 2, True), (1030, 40, 8, 8, False), (1029, 136, 16, 1, True), (1027, 264, 17, 3, False),
+    (1032, 2048, 64, 6, True), (4099, 96, 33, 4, True),            # 8 tokens per workgroup
+    (513, 520, 17, 2, True), (1024, 8, 64, 64, False), (257, 1024, 40, 5, True),   # 4 tokens
+])
+def test_route_matrix_forms(T, d, E, k, bias):
+    """The matrix form of the logits: every number of expert groups and column slices, row lengths that
+    end inside a unit, token counts that end inside a workgroup, and exact ties of duplicated
+    router rows across groups and blocks."""
+    _say(f"route matrix form T={T} d={d} E={E} k={k}")
+    g = torch.Generator().manual_seed(T + d + E)
+    x = (torch.randn(T, d, generator=g) / d ** 0.5).to(torch.bfloat16)
+    wr = torch.randn(E, d, generator=g).to(torch.bfloat16)
+    wr[E - 1] = wr[0]
+    if E > 16:
+        wr[16] = wr[5]
+    b = torch.randn(E, generator=g) if bias else None
+    if bias:
+        b[E - 1] = b[0]
+        if E > 16:
+            b[16] = b[5]
+    _check_route(x, wr, b, k, True)
+
+
 def test_route_ties_go_to_lower_expert_id():
     _say("route ties")
     g = torch.Generator().manual_seed(5)
