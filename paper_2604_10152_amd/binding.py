@@ -120,13 +120,16 @@ def _ptr(t, dtype=None, name="tensor"):
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must have dtype {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()                       # argtypes make it a void*
 
 
 def _stream(stream):
+    """Raw handle of `stream`, or of the current device's current stream.  A layer is five calls of
+    a few microseconds of device work each, so the handle is taken without building the stream
+    object and its device first (about 2 us per call)."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _check(status, where):
