@@ -322,10 +322,17 @@ def kernel_name(cfg, T, packed=True):
         return (f"grouped_gemm_bf16_pipe16_kernel<PipeCfg<{tile},256,32,4,2,4,true>,PA,PB> (gate/up + "
                 "SwiGLU on tile-packed operands: the permute step writes the dispatched rows "
                 "tile-packed)")
-    if rows >= 192 * cfg.E or (cfg.d_model >= 4096 and rows >= 48 * cfg.E):
-        return f"grouped_gemm_bf16_pipe16_kernel<PipeCfg<{tile},256,32,4,2,4,true>> (gate/up + SwiGLU)"
+    tiles = cfg.E * -(-cfg.d_ff // 128)      # gate/up tiles of 256 weight rows, for the lines below
     if cfg.d_model >= 4096:
-        return "grouped_gemm_bf16_pipe_kernel<PipeCfg<64,128,64,4,1,2,true>> (gate/up + SwiGLU)"
+        mid = rows >= 88 * cfg.E
+    elif rows >= 96 * cfg.E:
+        mid = tiles > (128 if cfg.d_model >= 2048 else 191)
+    else:
+        mid = rows >= 48 * cfg.E and tiles >= 512
+    if rows >= 192 * cfg.E or mid:
+        return f"grouped_gemm_bf16_pipe16_kernel<PipeCfg<{tile},256,32,4,2,4,true>> (gate/up + SwiGLU)"
+    if cfg.d_model >= 2048:
+        return "grouped_gemm_bf16_pipe_kernel<PipeCfg<128,128,64,4,4,2,true>> (gate/up + SwiGLU)"
     return "grouped_gemm_bf16_kernel<TileCfg<64,256,1,4,true>> (gate/up + SwiGLU)"
 
 

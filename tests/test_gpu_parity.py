@@ -337,6 +337,53 @@ def test_grouped_bf16(d, f, rows):
     _grouped_case(torch.bfloat16, d, f, rows, seed=d + f)
 
 
+def _rows_around(mean, E, seed):
+    """E row counts with the given mean, among them 0, 1 and both sides of 128 and 192."""
+    rng = np.random.default_rng(seed)
+    rows = rng.integers(0, 2 * mean + 1, size=E)
+    edge = [0, 1, 127, 128, 129, 191, 192, 193][:max(0, E - 4)]
+    rows[:len(edge)] = edge
+    rows[-1] = max(0, mean * E - int(rows[:-1].sum()))
+    return rows.tolist()
+
+
+@pytest.mark.parametrize("d,f,rows", [
+    (2048, 64, [128, 129, 1, 0, 61]),                # gate/up ring: one and two m-tiles
+    (2048, 192, [300, 129, 128, 250]),               # ... many rows but few tiles
+    (4096, 64, [90, 88, 87, 86]),                    # ... on both sides of its last row count:
+    (4096, 64, [90, 88, 87, 88]),                    # mid from 88 rows per expert
+    (64, 1024, _rows_around(50, 64, 1)),             # mid, short contraction, many tiles
+    (128, 1024, _rows_around(100, 24, 2)),           # mid from 96 rows
+    (64, 1280, _rows_around(13, 9, 3)),              # down: 128-row tiles from 12 rows
+    (256, 4096, _rows_around(101, 64, 4)),           # down: 192-row tiles, one round of tiles
+    (1024, 1280, _rows_around(113, 64, 5)),          # down: 192-row tiles, several rounds
+    (128, 64, [200, 190, 193]),                      # down: few wide tiles, one k-step
+])
+def test_row_major_dispatch_forms(d, f, rows):
+    """Both projections of every batch shape at which the row-major entry points change kernels."""
+    _say(f"row-major dispatch d={d} f={f} n={sum(rows)} E={len(rows)}")
+    E, n = len(rows), sum(rows)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator().manual_seed(d + f + n)
+    x = (torch.randn(n, d, generator=g) / d ** 0.5).to(torch.bfloat16)
+    wg, wu = ((torch.randn(E, f, d, generator=g) * 0.5).to(torch.bfloat16) for _ in range(2))
+    wd = (torch.randn(E, d, f, generator=g) * (0.5 / f ** 0.5)).to(torch.bfloat16)
+    h = torch.full((n, f), float("nan"), dtype=torch.bfloat16, device="cuda")
+    y = torch.full((n, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    doff = dev(torch.from_numpy(off))
+    sm.moe_expert_up_swiglu(dev(x), doff, dev(wg), dev(wu), h)
+    sm.moe_expert_down(h, doff, dev(wd), y)
+    torch.cuda.synchronize()
+    hc = h.cpu()
+    for e in range(E):
+        lo, hi = off[e], off[e + 1]
+        if lo == hi:
+            continue
+        xe = f64(x[lo:hi])
+        check_float(f64(hc[lo:hi]), orc.silu(xe @ f64(wg[e]).T) * (xe @ f64(wu[e]).T), torch.bfloat16, "h")
+        check_float(f64(y[lo:hi]), f64(hc[lo:hi]) @ f64(wd[e]).T, torch.bfloat16, "y")
+
+
 @pytest.mark.parametrize("d,f,rows", [
     (256, 4096, [5, 0, 17, 32, 0, 1]),               # four waves per slab, 1..4 wave-loads of rows
     (192, 4160, [8, 9, 0, 16, 24, 25]),              # ragged weight tiles, an odd number of k-steps
