@@ -3,19 +3,19 @@
 //
 // Two forms: vector (few tokens, fp32, more than 64 experts) and matrix (route_topk_mfma_kernel).
 //
-// Vector form: a workgroup owns TOK tokens and consists of 4 groups of 4 wavefronts; group g takes the
-// expert chunks g, g+4, ... of EC experts each, so the widening of the router weights to fp64
-// (every weight is converted once per workgroup) is spread over 1024
-// lanes.  Inside a group the d_model axis is dealt to its 256 lanes in 16-byte chunks (chunk q
-// -> wave (q/64)%4, lane q%64), every lane keeps fp64 partial sums for TOK tokens x EC experts
-// (TOK*EC <= 16), so one router-weight load feeds TOK tokens.
+// Vector form: a workgroup owns TOK tokens and consists of 16/W groups of W wavefronts; group g takes
+// the expert chunks g, g + 16/W, ... of EC experts each, so the widening of the router weights to fp64
+// (every weight is converted once per workgroup) is spread over 1024 lanes.  Inside a group the
+// d_model axis is dealt to its 64 W lanes in 16-byte chunks (chunk q -> wave (q/64) % W, lane
+// q % 64), every lane keeps fp64 partial sums for TOK tokens x EC experts (TOK*EC <= 16), so one
+// router-weight load feeds TOK tokens.
 // The TOK*EC partial sums of a wave are reduced over its 64 lanes by a transposing butterfly:
 // at the step with lane distance h a lane hands the half of its values that its partner keeps
 // to the partner and adds what it receives, so 63 exchange-and-add steps reduce all values at
 // once (a plain butterfly needs 6 per value) and lane l ends up with the total of value l.
 // Every value is summed over the same pairs of lanes in the same order, and fp addition is
 // commutative, so two experts with identical router rows get bit-identical logits and the tie
-// goes to the lower id.  The 4 wave totals are added in fixed order.  Wave t then ranks token
+// goes to the lower id.  The W wave totals are added in fixed order.  Wave t then ranks token
 // t: the E logits sit in LDS, top-k is k rounds of a wave-wide arg-max on the key (logit
 // descending, expert id ascending).
 #include "common.h"
@@ -23,10 +23,7 @@
 namespace specmoe {
 namespace {
 
-constexpr int kRouteWaves = 4;                        // wavefronts per group
-constexpr int kGroupThreads = kRouteWaves * kWave;
-constexpr int kRouteGroups = 4;                       // groups per workgroup (split the experts)
-constexpr int kRouteThreads = kRouteGroups * kGroupThreads;
+constexpr int kRouteThreads = 1024;                   // 16 wavefronts: groups of W, which split the experts
 
 template <typename T, bool VEC> struct Chunk;
 template <> struct Chunk<float, true> {
@@ -109,23 +106,24 @@ __device__ __forceinline__ void rank_token(const double* logit, int lane, int E,
     }
 }
 
-template <typename T, bool VEC, int TOK, int EC>
+template <typename T, bool VEC, int TOK, int EC, int W>
 __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     const T* __restrict__ x, const T* __restrict__ wr, const float* __restrict__ bias, int Tn,
     int d, int E, int k, int renorm, int32_t* __restrict__ idx_out, float* __restrict__ w_out,
     const int32_t* __restrict__ remap /* nullable: draft-mode expert substitution, [E] */) {
     static_assert(TOK * EC <= 16 && (TOK * EC & (TOK * EC - 1)) == 0, "values per wave");
     constexpr int NV = TOK * EC;                      // partial sums per lane and pass
-    extern __shared__ double lds_d[];                 // logits[TOK][E], then part[groups][4][NV]
+    constexpr int kGroupThreads = W * kWave, kRouteGroups = kRouteThreads / kGroupThreads;
+    extern __shared__ double lds_d[];                 // logits[TOK][E], then part[groups][W][NV]
     double* logits = lds_d;
     typedef Chunk<T, VEC> CH;
     constexpr int V = CH::N;
     constexpr int G = EC < 8 ? EC : 8;                // router rows loaded together
     const int lane = threadIdx.x % kWave;
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int group = wave_all / kRouteWaves, wave = wave_all % kRouteWaves;
+    const int group = wave_all / W, wave = wave_all % W;
     const int gtid = threadIdx.x % kGroupThreads;     // thread index inside the group
-    double* part = lds_d + (size_t)TOK * E + (size_t)group * kRouteWaves * NV;
+    double* part = lds_d + (size_t)TOK * E + (size_t)group * W * NV;
     const int t0 = blockIdx.x * TOK;
     const int nq = d / V;                             // chunks per row (VEC: d % V == 0)
 
@@ -164,7 +162,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
                 }
             }
         }
-        // lanes -> wave totals (transposing butterfly), waves -> workgroup total (order 0,1,2,3)
+        // lanes -> wave totals (transposing butterfly), waves -> workgroup total (in order)
         TransposeReduce<NV, kWave / 2>::run(acc, lane);
         constexpr int REP = kWave / NV;               // lanes holding the same value
         if (lane % REP == 0) part[wave * NV + lane / REP] = acc[0];
@@ -174,7 +172,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
             if (e0 + c < E) {
                 double s = part[gtid];
 #pragma unroll
-                for (int w = 1; w < kRouteWaves; ++w) s += part[w * NV + gtid];
+                for (int w = 1; w < W; ++w) s += part[w * NV + gtid];
                 logits[(size_t)t * E + e0 + c] = s + (bias ? (double)bias[e0 + c] : 0.0);
             }
         }
@@ -349,31 +347,42 @@ void launch_mfma(const bf16_t* x, const bf16_t* wr, const float* bias, int Tn, i
 #undef SPECMOE_ROUTE
 }
 
-template <typename T, bool VEC, int TOK, int EC>
+template <typename T, bool VEC, int TOK, int EC, int W>
 void launch_variant(const T* x, const T* wr, const float* bias, int Tn, int d, int E, int k,
                     int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
     dim3 grid((Tn + TOK - 1) / TOK), block(kRouteThreads);
-    size_t lds = ((size_t)TOK * E + (size_t)kRouteGroups * kRouteWaves * TOK * EC) * sizeof(double);
-    hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC>), grid, block, lds, s, x, wr, bias, Tn,
+    size_t lds = ((size_t)TOK * E + (size_t)(kRouteThreads / kWave) * TOK * EC) * sizeof(double);
+    hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC, W>), grid, block, lds, s, x, wr, bias, Tn,
                        d, E, k, renorm, idx, w, remap);
 }
 
-// experts per group and pass: a quarter of E rounded up to a power of two, at most 16 / TOK
+// Experts per group and pass: the group's share of E rounded up to a power of two, at most 16 / TOK.
+// Up to 16 experts 4 groups of 4 waves, beyond that 8 groups of 2: twice the columns per lane, but
+// half the sums to exchange over the lanes: 64 x 2048, 64 tokens 12.5 -> 11.3 us, 320 tokens 16.0 ->
+// 13.6; 64 x 512 12.1 -> 9.2; 256 x 1024 38.1 -> 27.9.
+template <typename T, bool VEC, int TOK, int W>
+void launch_by_share(const T* x, const T* wr, const float* bias, int Tn, int d, int E, int k,
+                     int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
+    constexpr int EC_MAX = 16 / TOK, G = 16 / W;
+    const int share = (E + G - 1) / G;
+    if (share <= 1)
+        launch_variant<T, VEC, TOK, 1, W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+    else if (share <= 2 || EC_MAX == 2)
+        launch_variant<T, VEC, TOK, (EC_MAX < 2 ? EC_MAX : 2), W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+    else if (share <= 4 || EC_MAX == 4)
+        launch_variant<T, VEC, TOK, (EC_MAX < 4 ? EC_MAX : 4), W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+    else if (share <= 8 || EC_MAX == 8)
+        launch_variant<T, VEC, TOK, (EC_MAX < 8 ? EC_MAX : 8), W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+    else
+        launch_variant<T, VEC, TOK, EC_MAX, W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+}
 template <typename T, bool VEC, int TOK>
 void launch_by_experts(const T* x, const T* wr, const float* bias, int Tn, int d, int E, int k,
                        int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
-    constexpr int EC_MAX = 16 / TOK;
-    const int quarter = (E + kRouteGroups - 1) / kRouteGroups;
-    if (quarter <= 1)
-        launch_variant<T, VEC, TOK, 1>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
-    else if (quarter <= 2 || EC_MAX == 2)
-        launch_variant<T, VEC, TOK, (EC_MAX < 2 ? EC_MAX : 2)>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
-    else if (quarter <= 4 || EC_MAX == 4)
-        launch_variant<T, VEC, TOK, (EC_MAX < 4 ? EC_MAX : 4)>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
-    else if (quarter <= 8 || EC_MAX == 8)
-        launch_variant<T, VEC, TOK, (EC_MAX < 8 ? EC_MAX : 8)>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+    if (E <= 16)
+        launch_by_share<T, VEC, TOK, 4>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
     else
-        launch_variant<T, VEC, TOK, EC_MAX>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+        launch_by_share<T, VEC, TOK, 2>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
 }
 
 template <typename T, int V>
@@ -389,21 +398,23 @@ void launch_typed(const void* x, const void* wr, const float* bias, int Tn, int 
     // Matrix form: from 1025 tokens on with 8 tokens per workgroup (the vector form then needs a
     // second round of workgroups; 2048 tokens, vector -> matrix: 8 x 4096 13.2 -> 10.6 us, 64 x 2048
     // 39.9 -> 22.8, 16 x 5120 23.1 -> 19.2, 4 x 1024 7.9 -> 6.3), and with more than 16 experts also
-    // below, 4 tokens per workgroup: from 513 tokens (64 x 2048, 640 tokens 22.8 -> 18.2), or 257 if
-    // rows are short (32 x 1024, 320 tokens 9.5 -> 8.7; 64 x 2048 16.2 against 17.9).  Its workgroups
-    // take longer than the vector form's, so fewer tokens stay there (64 tokens 12.6 against 17.5).
+    // below, 4 tokens per workgroup: from 513 tokens (64 x 2048, 640 tokens 22.8 -> 18.2; up to 32
+    // experts only with rows up to 2048: 20 x 5120, 1000 tokens 16.6 against 17.2), or 257 if rows are
+    // short (64 x 512, 320 tokens 15.2 -> 10.4).  Its workgroups take longer than the vector form's, so
+    // fewer tokens stay there (64 tokens 11.3 against 17.5).
     if constexpr (sizeof(T) == 2) {
         if (E <= kWave && Tn > 1024) {
             launch_mfma<2>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);
             return;
         }
-        if (E <= kWave && E > 16 && (Tn > 512 || (Tn > 256 && d <= 1024))) {
+        if (E <= kWave && E > 16 && (E > 32 || d <= 2048) &&
+            (Tn > 512 || (Tn > 256 && d <= 1024))) {
             launch_mfma<1>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);
             return;
         }
     }
-    // Vector form, tokens per workgroup: every group of 4 waves widens its TOK token chunks and its
-    // EC router chunks per pass (passes x EC covers a quarter of the experts), so the busiest CU
+    // Vector form, tokens per workgroup: every group of waves widens its TOK token chunks and its
+    // EC router chunks per pass (passes x EC covers the group's share of the experts), so the busiest CU
     // issues work in proportion to
     //   workgroups per CU x passes x (TOK + EC).
     // More tokens per workgroup share the widened router weights but leave CUs idle while the
@@ -412,9 +423,10 @@ void launch_typed(const void* x, const void* wr, const float* bias, int Tn, int 
     long long best = -1;
     for (int tok = 1; tok <= 4; tok *= 2) {
         const int ec_max = 16 / tok;
+        const int groups = E <= 16 ? 4 : 8;
         int ec = 1;
-        while (ec < ec_max && ec * kRouteGroups < E) ec *= 2;
-        const long long passes = (E + kRouteGroups * ec - 1) / (kRouteGroups * ec);
+        while (ec < ec_max && ec * groups < E) ec *= 2;
+        const long long passes = (E + groups * ec - 1) / (groups * ec);
         const long long wgs = (Tn + tok - 1) / tok;
         const long long per_cu = (wgs + 255) / 256;
         const long long load = per_cu * passes * (tok + ec);
