@@ -467,6 +467,26 @@ def test_rmsnorm(dtype, T, d):
     assert row_rel_err(f64(out), orc.rmsnorm(f64(x), f64(gain), 1e-5)) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 24), (torch.bfloat16, 2048), (torch.bfloat16, 4096),
+                                     (torch.bfloat16, 5120), (torch.bfloat16, 8192), (torch.float32, 1024),
+                                     (torch.float32, 1028), (torch.float32, 4096)])
+def test_rmsnorm_does_not_depend_on_alignment(dtype, d):
+    """A row adds up in one order whether its buffers allow 16-byte accesses or not: identical bits
+    (a different order of the fp32 sum moves single roundings of the output)."""
+    _say(f"rmsnorm alignment {dtype} d={d}")
+    g = torch.Generator().manual_seed(d)
+    T = 40
+    x = dev(torch.randn(T, d, generator=g).to(dtype))
+    gain = dev((1 + 0.1 * torch.randn(d, generator=g)).to(dtype))
+    out, out_odd = (torch.empty(T, d, dtype=dtype, device="cuda") for _ in range(2))
+    x_odd = torch.empty(T * d + 1, dtype=dtype, device="cuda")[1:].view(T, d)
+    x_odd.copy_(x)
+    sm.moe_rmsnorm(x, gain, 1e-5, out)
+    sm.moe_rmsnorm(x_odd, gain, 1e-5, out_odd)
+    torch.cuda.synchronize()
+    assert torch.equal(out, out_odd)
+
+
 # ------------------------------------------------------------------ whole layer
 def _run_layer(cfg, L, packed=False):
     """packed: hand the layer tile-packed copies of the expert weights as well (what the
