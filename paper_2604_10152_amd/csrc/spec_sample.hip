@@ -137,9 +137,9 @@ __global__ __launch_bounds__(kSampleThreads) void spec_accept_sample_kernel(
         }
         __syncthreads();
     };
-    // inclusive running sums of tiles c0 .. c0 + 63, tile c0 + lane in each lane
-    auto scan_chunk = [&](int c0, bool resid) -> double {
-        double s = 0.0;
+    // inclusive running sums of tiles c0 .. c0 + 63, tile c0 + lane in each lane (s: its own sum)
+    auto scan_chunk = [&](int c0, bool resid, double& s) -> double {
+        s = 0.0;
         if (c0 < kMaxLdsTiles) {                    // kMaxLdsTiles is a multiple of 64
             if (c0 + lane < n_tiles) s = tile_sum[c0 + lane];
         } else {
@@ -151,8 +151,9 @@ __global__ __launch_bounds__(kSampleThreads) void spec_accept_sample_kernel(
         return wave_scan_incl(s, lane);
     };
     auto total_of = [&](bool resid) -> double {     // every wave for itself, same result
-        double tot = 0.0;
-        for (int c0 = 0; c0 < n_tiles; c0 += kWave) tot += __shfl(scan_chunk(c0, resid), kWave - 1, kWave);
+        double tot = 0.0, s;
+        for (int c0 = 0; c0 < n_tiles; c0 += kWave)
+            tot += __shfl(scan_chunk(c0, resid, s), kWave - 1, kWave);
         return tot;
     };
     bool resid = pdn != nullptr;
@@ -169,8 +170,13 @@ __global__ __launch_bounds__(kSampleThreads) void spec_accept_sample_kernel(
     int tok = V - 1;
     double base = 0.0;                               // sum of the chunks in front
     for (int c0 = 0; c0 < n_tiles; c0 += kWave) {
-        const double incl = scan_chunk(c0, resid);
-        const unsigned long long over = __ballot(base + incl > thr);
+        // Every lane of a scan adds up in an order of its own, so over tiles that hold nothing the
+        // running sums still move by a rounding and may pass the threshold there: only a tile
+        // (and below, an id) with weight of its own can be the one that crosses it.  With u < 1
+        // one always does: the sums agree to 1e-14, u * total lies at least 2^-24 below the total.
+        double own;
+        const double incl = scan_chunk(c0, resid, own);
+        const unsigned long long over = __ballot(own > 0.0 && base + incl > thr);
         if (!over) {
             base += __shfl(incl, kWave - 1, kWave);
             continue;
@@ -185,10 +191,10 @@ __global__ __launch_bounds__(kSampleThreads) void spec_accept_sample_kernel(
         const double c1 = w0, c2 = c1 + w1, c3 = c2 + w2, c4 = c3 + w3;
         const double excl = before + (wave_scan_incl(c4, lane) - c4);
         int first = 4;
-        if (excl + c4 > thr) first = 3;
-        if (excl + c3 > thr) first = 2;
-        if (excl + c2 > thr) first = 1;
-        if (excl + c1 > thr) first = 0;
+        if (w3 > 0.0 && excl + c4 > thr) first = 3;
+        if (w2 > 0.0 && excl + c3 > thr) first = 2;
+        if (w1 > 0.0 && excl + c2 > thr) first = 1;
+        if (w0 > 0.0 && excl + c1 > thr) first = 0;
         const unsigned long long hit = __ballot(first < 4);
         const unsigned long long pos = __ballot(c4 > 0.0);
         if (hit) {

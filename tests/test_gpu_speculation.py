@@ -383,3 +383,54 @@ def test_greedy_tokens_burst_edges(R, V, dtype):
     sm.spec_greedy_tokens(dev(logits), tok)
     torch.cuda.synchronize()
     assert np.array_equal(tok.cpu().numpy(), orc.greedy_tokens(logits.float().numpy()))
+
+
+def _wave_scan_witnesses(m, n=30000):
+    """Tile sums for which a log-step scan over 64 lanes passes half of its total on a tile that
+    holds nothing: the first m tiles, zeros, and a permutation of the first m."""
+    rng = np.random.default_rng(5)
+    w = np.zeros((n, 64))
+    w[:, :m] = (rng.random((n, m)) * 10.0 ** rng.uniform(-9, 0, (n, m))).astype(np.float32)
+    w[:, 64 - m:] = rng.permuted(w[:, :m], axis=1)
+    s = w.copy()
+    for off in (1, 2, 4, 8, 16, 32):
+        s[:, off:] = s[:, off:] + s[:, :-off].copy()
+    first = (s > 0.5 * s[:, -1:]).argmax(axis=1)
+    return w[w[np.arange(n), first] == 0]
+
+
+def test_accept_sample_never_draws_from_empty_tiles():
+    """Distributions with most ids at exactly zero (a truncated target, a residual): the running
+    sums of the tiles move by a rounding over empty tiles, the draw must not land there."""
+    _say("spec_accept_sample, empty tiles")
+    w = np.concatenate([_wave_scan_witnesses(m)[:16] for m in (4, 8, 12, 20)])
+    assert len(w) >= 16
+    pt = torch.zeros(len(w), 1, 64 * 256)
+    pt[:, 0, ::256] = torch.from_numpy(w.astype(np.float32))
+    empty = torch.zeros(len(w), 0)
+    a, o = _gpu_accept_sample(empty.to(I32), torch.zeros(len(w), 0, 64 * 256), pt, empty,
+                              torch.full((len(w),), 0.5))
+    assert np.all(a == 1)
+    for b in range(len(w)):
+        assert _draw_is_valid(pt[b, 0].double().numpy(), 0.5, int(o[b, 0])), (b, o[b, 0])
+
+
+@pytest.mark.parametrize("V,keep", [(16384, 40), (40003, 300), (32000, 5), (4096, 17)])
+def test_accept_sample_truncated_distributions(V, keep):
+    """A few ids with weight among empty tiles and empty lanes, the uniform at their running sums."""
+    _say(f"spec_accept_sample truncated V={V} keep={keep}")
+    B = 64
+    rng = np.random.default_rng(V + keep)
+    pt = torch.zeros(B, 1, V)
+    us = torch.zeros(B)
+    for b in range(B):
+        ids = np.sort(rng.choice(V, size=keep, replace=False))
+        p = (rng.random(keep) * 10.0 ** rng.uniform(-9, 0, keep)).astype(np.float32)
+        pt[b, 0, ids] = torch.from_numpy(p)
+        c = np.cumsum(p.astype(np.float64))
+        us[b] = min(float(np.float32(c[rng.integers(keep)] / c[-1])), 1.0 - 2.0 ** -24)
+    empty = torch.zeros(B, 0)
+    a, o = _gpu_accept_sample(empty.to(I32), torch.zeros(B, 0, V), pt, empty, us)
+    assert np.all(a == 1)
+    for b in range(B):
+        assert _draw_is_valid(pt[b, 0].double().numpy(), us[b].item(), int(o[b, 0])), (b, o[b, 0])
