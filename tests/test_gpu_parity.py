@@ -268,6 +268,35 @@ def test_hot_experts_match_oracle():
             assert (cnt.cpu().numpy() == counts[want]).all()
 
 
+def test_hot_experts_cost_with_many_experts():
+    """1024 experts are placed by as many CUs as hold them, 64 each, not by one (measured 2.7 times the time
+    of 64 experts; 11 times when one workgroup made all comparisons)."""
+    _say("hot experts, cost")
+    ms = {}
+    for E in (64, 1024):
+        off = torch.arange(E + 1, dtype=I32, device="cuda")
+        ids = torch.empty((1,), dtype=I32, device="cuda")
+        stream = torch.cuda.Stream()
+        sm.moe_hot_experts(off, ids)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            for _ in range(20):
+                sm.moe_hot_experts(off, ids, stream=stream)
+        t = []
+        for _ in range(7):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b) / 20)
+        ms[E] = sorted(t)[3]
+        assert ids.item() == 0
+    print(f"   64 experts {ms[64] * 1e3:.1f} us, 1024 experts {ms[1024] * 1e3:.1f} us")
+    assert ms[1024] <= 5 * ms[64]
+
+
 # ------------------------------------------------------------------ a3 experts
 def _gpu_grouped(xp, off, wg, wu, wd):
     n, d = xp.shape
