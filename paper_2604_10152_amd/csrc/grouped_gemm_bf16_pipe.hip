@@ -325,7 +325,7 @@ __global__ __launch_bounds__(DownSmall::THREADS) void grouped_down_bf16_small_ke
     const bf16_t* __restrict__ wd, int E, int N, int K, bf16_t* __restrict__ y) {
     static_assert(DownSmall::THREADS == stream::kStreamThreads, "one launch serves both");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
-    const int mt = count_mtiles<stream::Split>(offsets, E);
+    const int mt = __builtin_amdgcn_readfirstlane(count_mtiles<stream::Split>(offsets, E));
     if (stream::stream_few(mt, N))
         stream::stream_tiles(lds_raw, h, offsets, wd, E, N, K, y, mt);
     else

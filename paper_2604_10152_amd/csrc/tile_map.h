@@ -59,7 +59,9 @@ struct FixedPolicy {
     }
 };
 
-// m-tiles of all experts together
+// m-tiles of all experts together (the same in every lane; not made scalar here: that would put
+// the next step of every workgroup behind this one's round trip to memory, measured at 1 us per
+// launch)
 template <typename Split>
 __device__ __forceinline__ int count_mtiles(const int32_t* __restrict__ offsets, int E) {
     const int lane = threadIdx.x % kWave;
@@ -69,7 +71,7 @@ __device__ __forceinline__ int count_mtiles(const int32_t* __restrict__ offsets,
         const int M = e < E ? offsets[e + 1] - offsets[e] : 0;
         total_mt += wave_sum(Split::of(M).mt);
     }
-    return __builtin_amdgcn_readfirstlane(total_mt);
+    return total_mt;
 }
 
 // the tile at place L of the logical order (expert, n-tile, m-tile)
