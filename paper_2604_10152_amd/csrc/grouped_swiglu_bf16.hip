@@ -20,6 +20,9 @@
 // read-back), consecutive logical tiles go to the same XCD and its L2 (tile_map.h).
 // 32-row MFMA sub-tiles beyond the expert's last row are skipped (wave-uniform), and waves
 // take sub-tiles interleaved so that a partial tile stays balanced across the SIMDs.
+// It also serves every operand that is not 16-byte aligned (a view that starts at an odd element):
+// its global accesses are ordinary loads of any alignment, where the other kernels' direct
+// global->LDS loads and 16-byte stores need aligned rows.
 #include "common.h"
 #include "tile_map.h"
 
@@ -27,6 +30,8 @@
 
 namespace specmoe {
 namespace {
+
+typedef U128 U128Any __attribute__((aligned(2)));   // 16 bytes at any bf16 element
 
 constexpr int kBK = 64;                       // contraction elements per LDS stage
 constexpr int kChunksPerRow = kBK / 8;        // 16-byte chunks per tile row (8)
@@ -139,11 +144,11 @@ __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_kernel(
         const bf16_t* w1k = C::SWIGLU ? w1 + (size_t)kt * kBK : nullptr;
 #pragma unroll
         for (int l = 0; l < C::A_LD; ++l)
-            a_reg[l] = *reinterpret_cast<const U128*>(ak + a_off[l]);
+            a_reg[l] = *reinterpret_cast<const U128Any*>(ak + a_off[l]);
 #pragma unroll
         for (int l = 0; l < C::B_LD; ++l) {
             const bool up = C::SWIGLU && (l * kRowsPerPass >= C::BN / 2);   // compile-time per l
-            b_reg[l] = *reinterpret_cast<const U128*>((up ? w1k : w0k) + b_off[l]);
+            b_reg[l] = *reinterpret_cast<const U128Any*>((up ? w1k : w0k) + b_off[l]);
         }
     };
     auto store_lds = [&](int buf) __attribute__((always_inline)) {
@@ -284,6 +289,11 @@ static inline bool rows_at_least(int n_rows, int E, int r) {
     return (long long)n_rows >= (long long)r * E;
 }
 constexpr int kLongK = 4096;
+// The pipelined kernels load rows straight into LDS and store 8 or 16 bytes at a time: every base
+// pointer has to be 16-byte aligned (rows are, K and N being multiples of 64).
+static inline bool rows_aligned(const void* a, const void* b, const void* c, const void* d = nullptr) {
+    return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d) & 15u) == 0;
+}
 
 // Gate/up (K = d_model, 128 outputs per 256-wide tile).
 //  - r >= 192, large: up to 320-row tiles, MFMA-bound.  Unless they are few: 8 x 1024 outputs are
@@ -303,6 +313,9 @@ hipError_t launch_expert_up_bf16(const bf16_t* x_perm, const int32_t* offsets, c
                                  const bf16_t* wu, int n_rows, int d, int f, int E, bf16_t* h,
                                  hipStream_t s, const int32_t* row_src, int topk) {
     if (n_rows == 0) return hipSuccess;
+    typedef TileCfg<64, 256, 1, 4, true> Staged;
+    if (!rows_aligned(x_perm, wg, wu, h))
+        return launch_one<Staged>(x_perm, offsets, wg, wu, n_rows, E, f, d, h, s, row_src, topk);
     const long long tiles = (long long)E * ((f + 127) / 128);
     const bool few = few_wide_tiles(n_rows, E, f, 128);
     if (large_batch(n_rows, E) && !(few && d >= 2048))
@@ -318,7 +331,7 @@ hipError_t launch_expert_up_bf16(const bf16_t* x_perm, const int32_t* offsets, c
     if (d >= 2048)
         return launch_expert_up_bf16_ring(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s, row_src,
                                           topk);
-    return launch_one<TileCfg<64, 256, 1, 4, true>>(x_perm, offsets, wg, wu, n_rows, E, f, d, h, s, row_src, topk);
+    return launch_one<Staged>(x_perm, offsets, wg, wu, n_rows, E, f, d, h, s, row_src, topk);
 }
 
 // Down (K = d_ff).
@@ -335,6 +348,9 @@ hipError_t launch_expert_up_bf16(const bf16_t* x_perm, const int32_t* offsets, c
 hipError_t launch_expert_down_bf16(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
                                    int n_rows, int d, int f, int E, bf16_t* y, hipStream_t s) {
     if (n_rows == 0) return hipSuccess;
+    typedef TileCfg<64, 128, 1, 4, false> Staged;
+    if (!rows_aligned(h, wd, y))
+        return launch_one<Staged>(h, offsets, wd, nullptr, n_rows, E, d, f, y, s);
     const long long tiles = (long long)E * ((d + 127) / 128);
     if (large_batch(n_rows, E)) {
         if (few_wide_tiles(n_rows, E, d, 256))
@@ -353,7 +369,7 @@ hipError_t launch_expert_down_bf16(const bf16_t* h, const int32_t* offsets, cons
             return launch_expert_down_bf16_tall(h, offsets, wd, n_rows, d, f, E, y, s);
         return launch_expert_down_bf16_mid(h, offsets, wd, n_rows, d, f, E, y, s);
     }
-    return launch_one<TileCfg<64, 128, 1, 4, false>>(h, offsets, wd, nullptr, n_rows, E, d, f, y, s);
+    return launch_one<Staged>(h, offsets, wd, nullptr, n_rows, E, d, f, y, s);
 }
 
 }  // namespace specmoe

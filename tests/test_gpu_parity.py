@@ -413,6 +413,50 @@ def test_row_major_dispatch_forms(d, f, rows):
         check_float(f64(y[lo:hi]), f64(hc[lo:hi]) @ f64(wd[e]).T, torch.bfloat16, "y")
 
 
+def _odd_view(t):
+    """The same values on the GPU in a contiguous view that starts one element past a 16-byte line."""
+    v = torch.empty(t.numel() + 8, dtype=t.dtype, device="cuda")[1:1 + t.numel()].view(t.shape)
+    return v.copy_(t)
+
+
+@pytest.mark.parametrize("which", ["rows", "weights", "out"])
+@pytest.mark.parametrize("d,f,rows", [
+    (2048, 1408, [20, 0, 33, 1]),                    # few rows, contractions of both projections
+    (2048, 1408, [130, 0, 129, 101]),                # ... and many
+    (256, 4096, [5, 70, 0, 1]),                      # down: long contraction
+    (320, 128, [200, 193, 330, 0]),                  # large batch
+])
+def test_expert_gemms_take_operands_of_any_alignment(d, f, rows, which):
+    """Contiguous views at an odd element are accepted by the row-major entry points and give the same
+    numbers; with and without the gather of the token rows."""
+    _say(f"alignment d={d} f={f} rows={rows} {which}")
+    E, n = len(rows), sum(rows)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator().manual_seed(d + f + n)
+    x = (torch.randn(n, d, generator=g) / d ** 0.5).to(torch.bfloat16)
+    wg, wu = ((torch.randn(E, f, d, generator=g) * 0.5).to(torch.bfloat16) for _ in range(2))
+    wd = (torch.randn(E, d, f, generator=g) * (0.5 / f ** 0.5)).to(torch.bfloat16)
+    put = {name: (_odd_view if which == name else dev) for name in ("rows", "weights", "out")}
+    nan = lambda *s: put["out"](torch.full(s, float("nan"), dtype=torch.bfloat16))
+    doff, src = dev(torch.from_numpy(off)), torch.arange(n, dtype=I32, device="cuda")
+    h, h2, y = nan(n, f), nan(n, f), nan(n, d)
+    assert (y.data_ptr() % 16 != 0) == (which == "out")
+    dx, dwg, dwu, dwd = put["rows"](x), put["weights"](wg), put["weights"](wu), put["weights"](wd)
+    sm.moe_expert_up_swiglu(dx, doff, dwg, dwu, h)
+    sm.moe_expert_up_swiglu_gather(dx, src, 1, doff, dwg, dwu, h2)
+    sm.moe_expert_down(put["rows"](h.cpu()), doff, dwd, y)
+    torch.cuda.synchronize()
+    assert torch.equal(h, h2)
+    hc = h.cpu()
+    for e in range(E):
+        lo, hi = off[e], off[e + 1]
+        if lo == hi:
+            continue
+        xe = f64(x[lo:hi])
+        check_float(f64(hc[lo:hi]), orc.silu(xe @ f64(wg[e]).T) * (xe @ f64(wu[e]).T), torch.bfloat16, "h")
+        check_float(f64(y[lo:hi]), f64(hc[lo:hi]) @ f64(wd[e]).T, torch.bfloat16, "y")
+
+
 @pytest.mark.parametrize("d,f,rows", [
     (256, 4096, [5, 0, 17, 32, 0, 1]),               # four waves per slab, 1..4 wave-loads of rows
     (192, 4160, [8, 9, 0, 16, 24, 25]),              # ragged weight tiles, an odd number of k-steps
