@@ -14,9 +14,15 @@
 // bf16, before -> now: 12 experts x 2048 x 2048 249 -> 160 us, 16 x 5120 x 8192 2.29 -> 1.45 ms,
 // 24 x 2048 x 1408 500 -> 253 us, 64 x 2048 x 1408 3.36 -> 0.70 ms, 130 x 1024 x 704 7.39 -> 1.43.
 // Cancellation: subtracting W_0 removes what all experts have in common (experts grown from one
-// dense model).  A pair that still lies closer together than 2^-10 of its norms - copies
-// included - is listed by the finish kernel and summed from its differences by a second pass, so
-// no distance is less exact than a direct sum.
+// dense model).  A pair that still lies closer together than 2^-10 of its norms - a copy, or any pair
+// where expert 0 lies far from all others - takes its distance from its differences: the finish
+// kernel lists the 8 x 8 blocks of the table that hold such a pair, and a second pass sums the
+// differences of all pairs of a listed block, so no distance is less exact than a direct sum.  A
+// block costs as much however many of its pairs are close.  Measured, us: no pair close / two copies /
+// expert 0 far from all others (every other pair close) / direct sums of the whole table: 64 experts x
+// 2048 x 1408 708 / 738 / 2340 / 3360, 16 x 4096 x 4096 608 / 735 / 1210 / 966, 12 x 2048 x 2048 168 / 204 /
+// 329 / 260 - so up to 16 experts a table full of close pairs is the one case where direct sums alone
+// would be faster.
 //
 // Up to 8 experts (28 pairs): the direct sums are the faster form (the matrix kernel spends the
 // same 64 cycles on 16 rows however few experts there are: 1.03 ms at 8 x 4096 x 14336 with two
@@ -29,10 +35,12 @@
 //   affinity_pairs_kernel     partial sums of squared differences, one set per workgroup
 //   affinity_pairs_finish_kernel
 //   affinity_gram_kernel      partial Gram matrices, one per workgroup
-//   affinity_finish_kernel    adds the partials, writes the table, lists the close pairs
-//   affinity_close_kernel     differences of the listed pairs (exits at once when there are none)
+//   affinity_finish_kernel    adds the partials, writes the table, lists the blocks with close pairs
+//   affinity_close_kernel     differences of the listed blocks (exits at once when there are none)
 //   affinity_close_finish_kernel
 #include "common.h"
+
+#include <type_traits>
 
 namespace specmoe {
 namespace {
@@ -42,7 +50,9 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int kRows = 16;           // experts of one matrix-instruction operand
 constexpr int kSuper = 4;           // row blocks a wave keeps: 64 experts
 constexpr int kMaxGroups = 256;     // workgroups (partials): one per CU
-constexpr int kCloseThreads = 256;
+constexpr int kCloseThreads = 256, kCloseGroups = 1024;
+constexpr int kCloseSide = 8;       // a block of the second pass: 8 x 8 pairs
+constexpr int kCloseSlabs = 512;    // partials per block
 constexpr int kPairThreads = 256, kPairGroups = 1024;   // up to 8 experts
 constexpr double kClose = 1.0 / (1 << 20);   // D^2 below this share of the norms: sum differences
 
@@ -52,10 +62,17 @@ __host__ __device__ inline int tile_index(int I, int J, int nb) {
     return I * nb - I * (I - 1) / 2 + (J - I);
 }
 constexpr int kTile = kRows * kRows;
-inline size_t gram_doubles(int E, int groups) {
-    const int nb = row_blocks(E);
-    return (size_t)(nb * (nb + 1) / 2) * groups * kTile;
-}
+// What the finish kernel hands to the second pass.  It follows the partial sums in the workspace.
+__host__ __device__ inline int side_blocks(int E) { return (E + kCloseSide - 1) / kCloseSide; }
+__host__ __device__ inline int side_pairs(int E) { return side_blocks(E) * (side_blocks(E) + 1) / 2; }
+struct CloseList {
+    int* n;             // listed blocks
+    int* blocks;        // [n] I * side_blocks + J, I <= J, in any order
+    int* flags;         // [side_blocks^2] listed already
+    __host__ __device__ CloseList(double* partial, int E)
+        : n(reinterpret_cast<int*>(partial + (size_t)side_pairs(E) * kCloseSlabs * 64)),
+          blocks(n + 2), flags(blocks + side_pairs(E)) {}
+};
 
 template <typename T> struct Piece;                 // one 16-byte piece of a weight row
 template <> struct Piece<float> {
@@ -65,6 +82,18 @@ template <> struct Piece<float> {
 template <> struct Piece<bf16_t> {
     static constexpr int N = 8;
     __device__ static float get(const U128& v, int i) {
+        const uint32_t w = v[i >> 1];
+        return __uint_as_float(i & 1 ? w & 0xffff0000u : w << 16);
+    }
+};
+
+typedef uint32_t U64 __attribute__((ext_vector_type(2)));
+template <typename T> struct Half;                  // one 8-byte piece
+template <> struct Half<float> {
+    __device__ static float get(const U64& v, int i) { return __uint_as_float(v[i]); }
+};
+template <> struct Half<bf16_t> {
+    __device__ static float get(const U64& v, int i) {
         const uint32_t w = v[i >> 1];
         return __uint_as_float(i & 1 ? w & 0xffff0000u : w << 16);
     }
@@ -168,7 +197,7 @@ template <typename T, int NBI, bool OFF, int WAVES, int PF>
 __global__ __launch_bounds__(WAVES * kWave) void affinity_gram_kernel(
     const T* __restrict__ wg, const T* __restrict__ wu, const T* __restrict__ wd, int E,
     size_t n1 /* elements of one matrix of one expert, a multiple of N */,
-    double* __restrict__ partial /* [tiles][groups][kTile] */, int* __restrict__ n_close) {
+    double* __restrict__ partial /* [tiles][groups][kTile] */, CloseList close) {
     constexpr int N = Piece<T>::N;
     constexpr int NR = OFF ? 2 * NBI : NBI;                     // row blocks loaded
     constexpr int TILES = OFF ? NBI * NBI : NBI * (NBI + 1) / 2;
@@ -184,7 +213,11 @@ __global__ __launch_bounds__(WAVES * kWave) void affinity_gram_kernel(
         while (rem >= ns - 1 - SI) { rem -= ns - 1 - SI; ++SI; }
         SJ = SI + 1 + rem;
     }
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && !OFF) *n_close = 0;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && !OFF) {          // nothing listed yet
+        const int ns = side_blocks(E);
+        if (threadIdx.x == 0) *close.n = 0;
+        for (int i = threadIdx.x; i < ns * ns; i += WAVES * kWave) close.flags[i] = 0;
+    }
 
     size_t row_off[NR];
 #pragma unroll
@@ -280,7 +313,7 @@ __global__ __launch_bounds__(WAVES * kWave) void affinity_gram_kernel(
 // the partials s, s + 16, ... of G[i,j], G[j,j] and G[i,i]; the 16 slices are added in order.
 __global__ __launch_bounds__(256) void affinity_finish_kernel(
     const double* __restrict__ partial, int E, int groups, float* __restrict__ table,
-    int* __restrict__ n_close, int* __restrict__ close) {
+    CloseList close) {
     __shared__ double red[3][16][kRows];
     const int nb = row_blocks(E);
     const int i = blockIdx.x, J = blockIdx.y, I = i / kRows;
@@ -315,63 +348,111 @@ __global__ __launch_bounds__(256) void affinity_finish_kernel(
     table[(size_t)i * E + j] = dist;
     table[(size_t)j * E + i] = dist;
     // (order of the list does not matter; two experts with infinite weights go there as well)
-    if (sq < kClose * norms || (__builtin_isinf(gii) && __builtin_isinf(gjj)))
-        close[atomicAdd(n_close, 1)] = i * E + j;
+    if (sq < kClose * norms || (__builtin_isinf(gii) && __builtin_isinf(gjj))) {
+        const int at = i / kCloseSide * side_blocks(E) + j / kCloseSide;
+        if (atomicExch(close.flags + at, 1) == 0) close.blocks[atomicAdd(close.n, 1)] = at;
+    }
 }
 
-// The listed pairs, one after the other: every workgroup sums its share of the squared
-// differences in fp64.
+// The listed blocks: squared differences of all 64 pairs in fp64, bound by the vector units (a
+// subtraction and a multiply-add per pair and element).  The concatenated columns of the three
+// matrices are dealt in `slabs` contiguous slabs; a workgroup takes a slab of a block at a time.
+// The blocks of a slab run next to each other on one die and share its weights in the L2.  8-byte
+// pieces: 16 of them, the next 16 and 64 fp64 sums fit in 256 registers.
 template <typename T>
-__global__ __launch_bounds__(kCloseThreads) void affinity_close_kernel(
+__global__ __launch_bounds__(kCloseThreads, 2) void affinity_close_kernel(
     const T* __restrict__ wg, const T* __restrict__ wu, const T* __restrict__ wd, int E, size_t n1,
-    const int* __restrict__ n_close, const int* __restrict__ close, double* __restrict__ partial) {
-    constexpr int N = Piece<T>::N;
-    __shared__ double red[kCloseThreads / kWave];
-    const int n = *n_close;
-    const size_t pieces = n1 / N;
-    for (int p = 0; p < n; ++p) {
-        const int i = close[p] / E, j = close[p] % E;
-        double s = 0.0;
-        for (int m = 0; m < 3; ++m) {
-            const T* W = m == 0 ? wg : (m == 1 ? wu : wd);
-            const U128* a = reinterpret_cast<const U128*>(W + (size_t)i * n1);
-            const U128* b = reinterpret_cast<const U128*>(W + (size_t)j * n1);
-            for (size_t q = (size_t)blockIdx.x * kCloseThreads + threadIdx.x; q < pieces;
-                 q += (size_t)gridDim.x * kCloseThreads) {
-                const U128 x = a[q], y = b[q];
+    int slabs, CloseList close, double* __restrict__ partial /* [n][slabs][64] */) {
+    constexpr int N = 8 / sizeof(T), S = kCloseSide;            // elements of a piece
+    typedef const U64 __attribute__((address_space(1)))* Global;
+    __shared__ double red[kCloseThreads / kWave][S * S];
+    const int n = __builtin_amdgcn_readfirstlane(*close.n);
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const size_t row_bytes = n1 * sizeof(T);
+    const int per_matrix = (int)((row_bytes + 8 * kCloseThreads - 1) / (8 * kCloseThreads));
+    const uint64_t base = (uint64_t)wg, to_up = (uint64_t)wu - base, to_down = (uint64_t)wd - (uint64_t)wu;
+    const int die = blockIdx.x % kXcds, mine = (slabs - die + kXcds - 1) / kXcds;   // slabs of this die
+    for (long long item = blockIdx.x / kXcds; item < (long long)mine * n; item += gridDim.x / kXcds) {
+        const int slab = die + kXcds * (int)(item / n), at = (int)(item % n);
+        const int code = __builtin_amdgcn_readfirstlane(close.blocks[at]);
+        const int I = code / side_blocks(E), J = code % side_blocks(E);
+        const int u0 = (int)(3ll * per_matrix * slab / slabs), u1 = (int)(3ll * per_matrix * (slab + 1) / slabs);
+        double acc[S * S];                                      // diagonal blocks: the pairs a < b
+#pragma unroll
+        for (int p = 0; p < S * S; ++p) acc[p] = 0.0;
+        auto sum = [&](auto diagonal) __attribute__((always_inline)) {
+            constexpr bool DIAG = decltype(diagonal)::value;
+            constexpr int ROWS = DIAG ? S : 2 * S;              // rows of I, then rows of J
+            U64 next[ROWS];
+            auto load = [&](int u) __attribute__((always_inline)) {
+                const int uc = min(u, u1 - 1), m = uc / per_matrix;
+                const size_t col = ((size_t)(uc - m * per_matrix) * kCloseThreads + threadIdx.x) * 8;
+                const uint64_t p =
+                    base + (m >= 1 ? to_up : 0) + (m == 2 ? to_down : 0) + (col < row_bytes ? col : 0);
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r)
+                    next[r] = *(Global)(p + (size_t)min((r < S ? I : J) * S + r % S, E - 1) * row_bytes);
+                if (col >= row_bytes) {
+#pragma unroll
+                    for (int r = 0; r < ROWS; ++r) next[r] = U64{0, 0};
+                }
+                __builtin_amdgcn_sched_barrier(0);              // the requests stay ahead of their use
+            };
+            load(u0);
+            for (int u = u0; u < u1; ++u) {
+                U64 cur[ROWS];
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) cur[r] = next[r];
+                load(u + 1);
 #pragma unroll
                 for (int k = 0; k < N; ++k) {
-                    const double d = (double)Piece<T>::get(x, k) - (double)Piece<T>::get(y, k);
-                    s = fma(d, d, s);
+                    double v[ROWS];
+#pragma unroll
+                    for (int r = 0; r < ROWS; ++r) v[r] = (double)Half<T>::get(cur[r], k);
+#pragma unroll
+                    for (int a = 0; a < S; ++a)
+#pragma unroll
+                        for (int b = DIAG ? a + 1 : 0; b < S; ++b) {
+                            const double df = v[a] - v[DIAG ? b : S + b];
+                            acc[a * S + b] = fma(df, df, acc[a * S + b]);
+                        }
                 }
             }
-        }
-        s = wave_sum(s);
-        if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = s;
+        };
+        if (I == J) sum(std::true_type{});
+        else sum(std::false_type{});
+        TransposeReduce<S * S, kWave / 2>::run(acc, lane);      // lane p: pair p of the wave
+        red[wave][lane] = acc[0];
         __syncthreads();
-        if (threadIdx.x == 0) {
-            double v = red[0];
-            for (int w = 1; w < kCloseThreads / kWave; ++w) v += red[w];
-            partial[(size_t)p * gridDim.x + blockIdx.x] = v;
+        if (wave == 0) {
+            double v = red[0][lane];
+            for (int w = 1; w < kCloseThreads / kWave; ++w) v += red[w][lane];
+            partial[((size_t)at * slabs + slab) * (S * S) + lane] = v;
         }
         __syncthreads();
     }
 }
 
-__global__ __launch_bounds__(kWave) void affinity_close_finish_kernel(
-    const int* __restrict__ n_close, const int* __restrict__ close,
-    const double* __restrict__ partial, int groups, int E, float* __restrict__ table) {
-    const int n = *n_close;
-    for (int p = blockIdx.x; p < n; p += gridDim.x) {
+// One workgroup per listed block: thread (g, p) adds the slabs g, g + 4, ... of pair p.
+__global__ __launch_bounds__(256) void affinity_close_finish_kernel(
+    CloseList close, const double* __restrict__ partial, int slabs, int E, float* __restrict__ table) {
+    constexpr int S = kCloseSide;
+    __shared__ double red[4][S * S];
+    const int n = *close.n, p = threadIdx.x % (S * S), g = threadIdx.x / (S * S);
+    for (int at = blockIdx.x; at < n; at += gridDim.x) {
         double s = 0.0;
-        for (int g = threadIdx.x; g < groups; g += kWave) s += partial[(size_t)p * groups + g];
-        s = wave_sum(s);
-        if (threadIdx.x == 0) {
-            const int i = close[p] / E, j = close[p] % E;
-            const float dist = (float)sqrt(s);
+#pragma unroll 8
+        for (int slab = g; slab < slabs; slab += 4) s += partial[((size_t)at * slabs + slab) * (S * S) + p];
+        red[g][p] = s;
+        __syncthreads();
+        const int code = close.blocks[at];
+        const int i = code / side_blocks(E) * S + p / S, j = code % side_blocks(E) * S + p % S;
+        if (g == 0 && i < j && j < E) {
+            const float dist = (float)sqrt(((red[0][p] + red[1][p]) + red[2][p]) + red[3][p]);
             table[(size_t)i * E + j] = dist;
             table[(size_t)j * E + i] = dist;
         }
+        __syncthreads();
     }
 }
 
@@ -394,11 +475,12 @@ hipError_t launch_affinity_typed(const T* wg, const T* wu, const T* wd, int E, s
     const int nb = row_blocks(E), ns = (nb + kSuper - 1) / kSuper;
     const size_t units = 3 * ((n1 + 4 * Piece<T>::N - 1) / (4 * Piece<T>::N));
     const int groups = (int)(units < (size_t)kMaxGroups * 8 ? (units + 7) / 8 : kMaxGroups);
-    int* n_close = reinterpret_cast<int*>(partial + gram_doubles(E, groups));
-    int* close = n_close + 2;
+    const CloseList close(partial, E);
+    const size_t pieces = 3 * ((n1 * sizeof(T) + 8 * kCloseThreads - 1) / (8 * kCloseThreads));
+    const int slabs = (int)(pieces < (size_t)kCloseSlabs ? pieces : kCloseSlabs);
 #define SPECMOE_GRAM(NBI, OFF, WAVES, PF, GY)                                                     \
     hipLaunchKernelGGL((affinity_gram_kernel<T, NBI, OFF, WAVES, PF>), dim3(groups, GY),          \
-                       dim3(WAVES * kWave), 0, s, wg, wu, wd, E, n1, partial, n_close)
+                       dim3(WAVES * kWave), 0, s, wg, wu, wd, E, n1, partial, close)
     if (nb == 1) SPECMOE_GRAM(1, false, 16, 4, 1);
     else if (nb == 2) SPECMOE_GRAM(2, false, 8, 4, 1);
     else if (nb == 3) SPECMOE_GRAM(3, false, 8, 2, 1);
@@ -406,20 +488,22 @@ hipError_t launch_affinity_typed(const T* wg, const T* wu, const T* wd, int E, s
     if (ns > 1) SPECMOE_GRAM(4, true, 8, 1, ns * (ns - 1) / 2);
 #undef SPECMOE_GRAM
     hipLaunchKernelGGL(affinity_finish_kernel, dim3(E, nb), dim3(256), 0, s, partial, E, groups,
-                       table, n_close, close);
-    hipLaunchKernelGGL((affinity_close_kernel<T>), dim3(groups), dim3(kCloseThreads), 0, s, wg, wu,
-                       wd, E, n1, n_close, close, partial);
-    hipLaunchKernelGGL(affinity_close_finish_kernel, dim3(256), dim3(kWave), 0, s, n_close, close,
-                       partial, groups, E, table);
+                       table, close);
+    hipLaunchKernelGGL((affinity_close_kernel<T>), dim3(kCloseGroups), dim3(kCloseThreads), 0, s, wg,
+                       wu, wd, E, n1, slabs, close, partial);
+    hipLaunchKernelGGL(affinity_close_finish_kernel, dim3(256), dim3(256), 0, s, close, partial, slabs,
+                       E, table);
     return hipGetLastError();
 }
 
 }  // namespace
 
 // Room for 1024 partials of 64 doubles per pair of 8-expert blocks: what the direct sums of up to
-// 8 experts take.  The Gram matrix needs less for every E: at most kMaxGroups x 256 doubles per
-// pair of 16-expert blocks, then 2 + E (E - 1) / 2 ints; the differences of the listed pairs (one
-// double per pair and workgroup) go where the Gram partials were.
+// 8 experts take.  Beyond that half of it holds the partial sums - of the Gram matrix (at most
+// kMaxGroups x 256 doubles per pair of 16-expert blocks: with n = row_blocks(E), n (n + 1) / 2 x 128
+// partials of 512 doubles, and 8-expert blocks come in at least n (2 n - 1) >= n (n + 1) pairs from
+// n = 2 on, in 3 for n = 1, of 64 partials of 512 doubles), then of the listed blocks - and CloseList
+// follows them.
 size_t affinity_workspace_bytes(int E) {
     const size_t nb8 = (size_t)(E + 7) / 8;
     return nb8 * (nb8 + 1) / 2 * 1024 * 64 * sizeof(double);

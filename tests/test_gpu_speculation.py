@@ -349,6 +349,65 @@ def test_affinity_table_close_pairs_and_non_finite_weights():
     assert _gpu_affinity(wg, w2, wd)[2, 3] == np.inf
 
 
+def _many_close(kind, wg, wu, wd):
+    E = wg.shape[0]
+    for w in (wg, wu, wd):
+        if kind == "outlier":                      # expert 0 lies far from all others
+            w[0] *= 5000.0
+        elif kind == "clusters":                   # copies of the first eight
+            w[:] = w[torch.arange(E, device=w.device) % 8]
+        elif kind == "half":                       # copies of one expert, each off by a little
+            w[E // 2:] = w[E // 2] * (1 + 1e-4 * torch.arange(E - E // 2, device=w.device)
+                                      .view(-1, 1, 1)).to(w.dtype)
+        elif kind == "last pair":
+            w[E - 1] = w[E - 2]
+
+
+@pytest.mark.parametrize("kind", ["outlier", "clusters", "half", "last pair"])
+@pytest.mark.parametrize("E,d,f,dtype", [(9, 64, 64, torch.bfloat16), (17, 24, 20, torch.float32),
+                                         (40, 64, 68, torch.float32), (64, 128, 96, torch.bfloat16),
+                                         (70, 256, 512, torch.bfloat16)])
+def test_affinity_table_many_close_pairs(E, d, f, dtype, kind):
+    """Blocks of close pairs: whole, at the ragged end of the table, with fewer columns than
+    partial sums and with slabs that cross from one matrix to the next."""
+    _say(f"affinity {kind} E={E} d={d} f={f} {dtype}")
+    W = _weights(E, d, f, dtype, seed=300 + E, planted=False)
+    _many_close(kind, *W)
+    got = _gpu_affinity(*W)
+    want = orc.affinity_table(*(f64(w) for w in W))
+    assert np.all(np.diag(got) == 0) and np.array_equal(got, got.T)
+    np.testing.assert_allclose(got, want, rtol=AFFINITY_RTOL, atol=0)
+
+
+def test_affinity_table_cost_of_close_pairs():
+    """A table full of close pairs costs a few times one without (measured 3.6), not the tens
+    of times that it takes to sum the pairs one after the other."""
+    _say("affinity, cost of close pairs")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    E, d, f = 64, 2048, 704
+    W = [(torch.randn(s, generator=g, device="cuda") * 0.02).to(torch.bfloat16)
+         for s in ((E, f, d), (E, f, d), (E, d, f))]
+    table = torch.empty((E, E), dtype=torch.float32, device="cuda")
+    ws = torch.empty((sm.moe_affinity_table_workspace_bytes(E),), dtype=torch.uint8, device="cuda")
+
+    def median_ms():
+        t = []
+        for _ in range(7):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            sm.moe_affinity_table(*W, table, ws)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return sorted(t)[3]
+
+    plain = median_ms()
+    _many_close("outlier", *W)
+    close = median_ms()
+    print(f"   {plain:.3f} ms -> {close:.3f} ms")
+    assert close <= 8 * plain
+
+
 @pytest.mark.parametrize("B,gamma,V", [(9, 3, 4096), (9, 3, 4097), (3, 2, 32769), (5, 1, 40003), (2, 1, 524288),
                                        (2, 1, 540672)])
 def test_accept_sample_vocabulary_edges(B, gamma, V):
