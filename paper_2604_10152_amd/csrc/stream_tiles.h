@@ -64,7 +64,7 @@ __device__ __forceinline__ void stream_tiles(
          slot += gridDim.x / kXcds) {
         const long long L = (long long)(blockIdx.x % kXcds) * per_xcd + slot;
         TileLoc t;
-        if (L >= G || !locate_logical<Split>(offsets, E, NT, L, t)) break;
+        if (L >= G || !locate<Split, From::place>(offsets, E, NT, L, 0, t)) break;
         const int n0 = (t.nt * NW + wn) * OUT;              // may lie beyond N (last tile)
         const int n_left = N - n0;
 
