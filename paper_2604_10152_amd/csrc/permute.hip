@@ -4,16 +4,18 @@
 //
 // Index phase: ONE workgroup; wave w owns the w-th contiguous slice of the flat pair array and
 // walks it in order, 64 pairs at a time.
-//  - E <= 64: up to 16384 pairs (16 waves x 16 rows of 64) the slice sits in registers.  Every lane finds the lanes of its row with the same expert (one ballot per bit of the
-//    id), its rank among them, and its place in the wave's share of the expert through a running
-//    count in LDS; wave 0 turns the 16 x E counts into the offsets and every wave's first row; a
-//    pair's row is then first + place.  (Longer slices are walked a second time.)
+//  - E <= 64: up to 16384 pairs (16 waves x 16 rows of 64) the slice sits in registers.  Every lane
+//    finds the lanes of its row with the same expert (one ballot per bit of the id), its rank among
+//    them, and its place in the wave's share of the expert through a running count in LDS; wave 0 turns the 16 x E counts into the offsets and every wave's first row; a
+//    pair's row is then first + place.  (Of longer slices the places wait in row_of, which the same
+//    lane reads back.)
 //  - otherwise: per-wave, per-expert counts (LDS integer atomics: order-free), totals -> exclusive
 //    prefix sum -> first rows, then a second walk that ranks equal experts by a loop over the
 //    distinct ones.
 // Contiguous slices walked in order make the sort stable with no ordered atomics.  The loop over
 // distinct experts took 23.8 us for 1285 tokens x 6 of 64 skewed experts, the ballots take 9.6;
-// 320 x 6 of 64: 8.7 -> 4.6, 2048 x 2 of 8: 8.4 -> 5.9, 80 x 2 of 8: 4.4 -> 3.2 (a launch is 2.5).
+// 320 x 6 of 64: 8.7 -> 4.6, 2048 x 2 of 8: 8.4 -> 5.9, 80 x 2 of 8: 4.4 -> 3.2 (a launch is 2.5).  Of
+// 30000 pairs 36 us (152; 38 where the slice was ranked twice; all tokens on the same experts 33, 33, 38).
 // Gather phase: a coalesced 16-byte copy of whole rows over the full grid.
 #include "common.h"
 
@@ -29,8 +31,7 @@ __device__ __forceinline__ unsigned long long lanes_below(int lane) {
     return lane == 0 ? 0ull : (~0ull >> (kWave - lane));
 }
 
-// E <= 64.  BITS: bits of an expert id.  Beyond kSmallRows rows per wave the slice is walked twice,
-// first for the counts alone, then from the wave's first rows.
+// E <= 64.  BITS: bits of an expert id.
 template <int BITS>
 __global__ __launch_bounds__(kSmallWaves * kWave) void permute_index_small_kernel(
     const int32_t* __restrict__ idx, int P, int E, int32_t* __restrict__ offsets,
@@ -72,19 +73,16 @@ __global__ __launch_bounds__(kSmallWaves * kWave) void permute_index_small_kerne
             __builtin_amdgcn_wave_barrier();
         }
     };
-    auto store = [&](int base, bool add_first) __attribute__((always_inline)) {
+    mine[lane] = 0;                                                // private to the wave
+    for (int base = lo; base < hi; base += kSmallRows * kWave) {
+        walk(base);
+        if (once) break;
 #pragma unroll
         for (int b = 0; b < kSmallRows; ++b) {
             const int p = base + b * kWave + lane;
-            if (p < hi) {
-                const int dest = (add_first ? mine[ev[b]] : 0) + place[b];
-                row_src[dest] = p;
-                row_of[p] = dest;
-            }
+            if (p < hi) row_of[p] = place[b];
         }
-    };
-    mine[lane] = 0;                                                // private to the wave
-    for (int base = lo; base < hi; base += kSmallRows * kWave) walk(base);
+    }
     __syncthreads();
     if (wave == 0) {                                               // lane e: expert e
         int c[kSmallWaves], total = 0;
@@ -108,12 +106,23 @@ __global__ __launch_bounds__(kSmallWaves * kWave) void permute_index_small_kerne
         }
     }
     __syncthreads();
-    if (once) {
-        store(lo, true);
-    } else {
-        for (int base = lo; base < hi; base += kSmallRows * kWave) {
-            walk(base);
-            store(base, false);
+    for (int base = lo; base < hi; base += kSmallRows * kWave) {
+        if (!once) {
+#pragma unroll
+            for (int b = 0; b < kSmallRows; ++b) {
+                const int p = base + b * kWave + lane;
+                ev[b] = p < hi ? min(max(idx[p], 0), E - 1) : 0;
+                place[b] = p < hi ? row_of[p] : 0;
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < kSmallRows; ++b) {
+            const int p = base + b * kWave + lane;
+            if (p < hi) {
+                const int dest = mine[ev[b]] + place[b];
+                row_src[dest] = p;
+                row_of[p] = dest;
+            }
         }
     }
 }
@@ -247,6 +256,9 @@ hipError_t launch_permute(const void* x, const int32_t* idx, int T, int d, int E
                                row_src, row_of);
         else if (E <= 16)
             hipLaunchKernelGGL(permute_index_small_kernel<4>, dim3(1), block, 0, s, idx, P, E, offsets,
+                               row_src, row_of);
+        else if (E <= 32)
+            hipLaunchKernelGGL(permute_index_small_kernel<5>, dim3(1), block, 0, s, idx, P, E, offsets,
                                row_src, row_of);
         else
             hipLaunchKernelGGL(permute_index_small_kernel<6>, dim3(1), block, 0, s, idx, P, E, offsets,

@@ -219,9 +219,9 @@ def test_permute_cases(dtype, T, d, E, k):
 
 
 @pytest.mark.parametrize("T,E,k", [(4096, 16, 4), (4097, 16, 4), (3000, 64, 6), (40, 3, 3), (65, 33, 1),
-                                   (64, 8, 8), (1, 64, 64)])
+                                   (64, 8, 8), (1, 64, 64), (9000, 32, 3), (300, 17, 2), (20000, 4, 3)])
 def test_permute_slice_forms(T, E, k):
-    """Slices that fill a wave's registers exactly, one row more (second walk), ids of 1 to 6 bits, and
+    """Slices that fill a wave's registers exactly, one row more (places read back), ids of 1 to 6 bits, and
     ids outside [0, E), which are clamped."""
     _say(f"permute slices T={T} E={E} k={k}")
     rng = np.random.default_rng(T + E)
