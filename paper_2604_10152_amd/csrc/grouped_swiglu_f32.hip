@@ -53,14 +53,16 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_f32_kernel(
         w_row[0][c] = W0 + at;
         if (SWIGLU) w_row[NM - 1][c] = W1 + at;
     }
-    auto load = [&](const float* p, int k) __attribute__((always_inline)) -> floatx4 {
+    // unsigned: the steps in flight run past the largest K
+    const uint32_t k_end = K;
+    auto load = [&](const float* p, uint32_t k) __attribute__((always_inline)) -> floatx4 {
         floatx4 v = {0.f, 0.f, 0.f, 0.f};
         if (VEC) {                            // K % 4 == 0, rows 16-byte aligned
-            if (k < K) v = *reinterpret_cast<const floatx4*>(p + k);
+            if (k < k_end) v = *reinterpret_cast<const floatx4*>(p + k);
         } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (k + q < K) v[q] = p[k + q];
+                if (k + q < k_end) v[q] = p[k + q];
         }
         return v;
     };
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_f32_kernel(
     // cover the way to L2
     constexpr int PF = RB >= 4 ? 2 : 4;
     floatx4 av[PF][RB], wv[PF][NM][CB];
-    auto fetch = [&](int p, int k) __attribute__((always_inline)) {
+    auto fetch = [&](int p, uint32_t k) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < RB; ++i) av[p][i] = load(a_row[i], k + kq);
 #pragma unroll
@@ -87,10 +89,10 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_f32_kernel(
         __builtin_amdgcn_sched_barrier(0);    // keeps the requests PF steps ahead of their use
     };
     constexpr int STRIDE = kStep * WK;
-    const int k_first = wk * kStep;
+    const uint32_t k_first = wk * kStep;
 #pragma unroll
     for (int p = 0; p < PF; ++p) fetch(p, k_first + p * STRIDE);
-    for (int k0 = k_first; k0 < K; k0 += PF * STRIDE) {
+    for (uint32_t k0 = k_first; k0 < k_end; k0 += PF * STRIDE) {
 #pragma unroll
         for (int p = 0; p < PF; ++p) {        // steps beyond K hold zeros
             floatx4 a[RB], w[NM][CB];

@@ -25,6 +25,12 @@ constexpr int kBurst = 8;                    // tiles a wave requests at once
 constexpr int kMaxLdsTiles = 2048;           // tile sums kept in LDS (V <= 524288); beyond that
                                              // the tiles are re-summed from memory
 
+// First id of a tile.  The last burst of a wave asks for tiles beyond the row (load_tile answers with
+// zeros), whose ids may exceed the int range at the largest vocabularies.
+constexpr __host__ __device__ uint32_t tile_id(int tile) { return (uint32_t)tile * kTileIds; }
+static_assert(tile_id((INT32_MAX - 1) / kTileIds + (kBurst - 1) * kSampleWaves) >= INT32_MAX,
+              "the tiles of the last burst beyond the row must not wrap around to its start");
+
 // inclusive wave scan (fp64)
 __device__ __forceinline__ double wave_scan_incl(double v, int lane) {
 #pragma unroll
@@ -79,23 +85,23 @@ __global__ __launch_bounds__(kSampleThreads) void spec_accept_sample_kernel(
     const float* ptn = pt + (size_t)n * V;
     const float* pdn = n < gamma ? pd + (size_t)n * V : nullptr;
     const bool vec = (V % 4 == 0) && ((((uintptr_t)p_draft | (uintptr_t)p_target) & 15u) == 0);
-    const int n_tiles = (V + kTileIds - 1) / kTileIds;
+    const int n_tiles = (V - 1) / kTileIds + 1;
 
     // this lane's 4 probabilities of tile `tile` (0 beyond V) under both models; q = 0 when
     // drawing from pt
     auto load_tile = [&](int tile, bool resid, floatx4& t, floatx4& q) __attribute__((always_inline)) {
-        const int v0 = tile * kTileIds + lane * 4;
+        const uint32_t v0 = tile_id(tile) + lane * 4, end = V;
         t = floatx4{0.f, 0.f, 0.f, 0.f};
         q = floatx4{0.f, 0.f, 0.f, 0.f};
         if (vec) {                                  // V % 4 == 0: all four ids or none
-            if (v0 < V) {
+            if (v0 < end) {
                 t = *reinterpret_cast<const floatx4*>(ptn + v0);
                 if (resid) q = *reinterpret_cast<const floatx4*>(pdn + v0);
             }
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (v0 + i < V) {
+                if (v0 + i < end) {
                     t[i] = ptn[v0 + i];
                     if (resid) q[i] = pdn[v0 + i];
                 }
