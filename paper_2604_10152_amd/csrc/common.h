@@ -7,6 +7,7 @@ namespace specmoe {
 
 constexpr int kWave = 64;           // CDNA wavefront width
 constexpr int kXcds = 8;            // MI355X: 8 accelerator dies, workgroups dealt round-robin
+constexpr int kCus = 256;           // compute units of all dies
 
 typedef __bf16 bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -143,8 +144,6 @@ hipError_t launch_expert_up_bf16_mid(const bf16_t* x_perm, const int32_t* offset
                                      int topk);
 hipError_t launch_expert_down_bf16_mid(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
                                        int n_rows, int d, int f, int E, bf16_t* y, hipStream_t s);
-hipError_t launch_expert_down_bf16_tall(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
-                                        int n_rows, int d, int f, int E, bf16_t* y, hipStream_t s);
 hipError_t launch_combine(const void* y_perm, const int32_t* row_of, const float* w,
                           const void* residual, int T, int d, int k, int dtype, void* out,
                           hipStream_t s);

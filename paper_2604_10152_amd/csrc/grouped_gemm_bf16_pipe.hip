@@ -29,21 +29,17 @@ namespace {
 
 using namespace pipe;
 
-// one tile: the work of workgroup blockIdx.x (lds_raw: C::LDS_BYTES)
+// the work of one workgroup: tile t (lds_raw: C::LDS_BYTES)
 template <typename C>
 __device__ __forceinline__ void pipe_tile(
-    unsigned char* lds_raw,
+    unsigned char* lds_raw, const TileLoc& t,
     const bf16_t* __restrict__ A,        // [n_rows, K]
-    const int32_t* __restrict__ offsets, // [E+1]
     const bf16_t* __restrict__ W0,       // [E, N, K]   (gate, or down)
     const bf16_t* __restrict__ W1,       // [E, N, K]   (up; SWIGLU only)
-    int E, int N, int K, bf16_t* __restrict__ Cout /* [n_rows, N] */,
+    int N, int K, bf16_t* __restrict__ Cout /* [n_rows, N] */,
     const int32_t* __restrict__ row_src /* nullable: A row r is A[row_src[r] / topk] */, int topk) {
     static_assert(!C::SWIGLU || ((C::BN / 2 / C::ROWS_PER_DMA) % C::NWAVES == 0 && C::TN % 2 == 0),
                   "gate/up halves must split on a wave-load round and pair up inside a wave");
-    const int NT = (N + C::BN_OUT - 1) / C::BN_OUT;
-    TileLoc t;
-    if (!locate_tile_even<C::BM>(offsets, E, NT, blockIdx.x, t)) return;
     const int row0 = t.row0, tile_rows = t.tile_rows;
     const int n0 = t.nt * C::BN_OUT;
     const int nsub = (tile_rows + 31) / 32;
@@ -311,7 +307,9 @@ __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe_kernel(
     const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int E, int N, int K,
     bf16_t* __restrict__ Cout, const int32_t* __restrict__ row_src, int topk) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
-    pipe_tile<C>(lds_raw, A, offsets, W0, W1, E, N, K, Cout, row_src, topk);
+    TileLoc t;
+    if (locate_tile_even<C::BM>(offsets, E, (N + C::BN_OUT - 1) / C::BN_OUT, blockIdx.x, t))
+        pipe_tile<C>(lds_raw, t, A, W0, W1, N, K, Cout, row_src, topk);
 }
 
 // Down projection with few rows per expert: by the number of tiles this batch has (known on the
@@ -325,11 +323,41 @@ __global__ __launch_bounds__(DownSmall::THREADS) void grouped_down_bf16_small_ke
     const bf16_t* __restrict__ wd, int E, int N, int K, bf16_t* __restrict__ y) {
     static_assert(DownSmall::THREADS == stream::kStreamThreads, "one launch serves both");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
-    const int mt = __builtin_amdgcn_readfirstlane(count_mtiles<stream::Split>(offsets, E));
-    if (stream::stream_few(mt, N))
-        stream::stream_tiles(lds_raw, h, offsets, wd, E, N, K, y, mt);
-    else
-        pipe_tile<DownSmall>(lds_raw, h, offsets, wd, nullptr, E, N, K, y, nullptr, 1);
+    typedef EvenPolicy<DownSmall::BM, 32> Ring;
+    int mt[2];
+    count_mtiles<stream::Split, Ring>(offsets, E, mt);
+    const int streams = __builtin_amdgcn_readfirstlane(mt[0]);
+    const int NT = (N + DownSmall::BN_OUT - 1) / DownSmall::BN_OUT;
+    TileLoc t;
+    if (stream::stream_few(streams, N))
+        stream::stream_tiles(lds_raw, h, offsets, wd, E, N, K, y, streams);
+    else if (locate<Ring, From::counted>(offsets, E, NT, blockIdx.x, mt[1], t))
+        pipe_tile<DownSmall>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
+}
+
+// Down projection from tens of rows per expert on: 128-row tiles, or 192-row ones if the chip then
+// needs fewer rounds (launch_expert_down_bf16_mid).
+typedef PipeCfg<128, 128, 64, 4, 2, 4, false> DownMid;
+typedef PipeCfg<192, 128, 64, 4, 2, 4, false> DownTall;
+
+__global__ __launch_bounds__(DownTall::THREADS) void grouped_down_bf16_mid_kernel(
+    const bf16_t* __restrict__ h, const int32_t* __restrict__ offsets,
+    const bf16_t* __restrict__ wd, int E, int N, int K, bf16_t* __restrict__ y) {
+    static_assert(DownTall::THREADS == DownMid::THREADS && DownTall::BN_OUT == DownMid::BN_OUT,
+                  "one launch serves both");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+    typedef EvenPolicy<DownMid::BM, 32> Mid;
+    typedef EvenPolicy<DownTall::BM, 32> Tall;
+    const int NT = (N + DownMid::BN_OUT - 1) / DownMid::BN_OUT;
+    int mt[2];
+    count_mtiles<Mid, Tall>(offsets, E, mt);
+    TileLoc t;
+    if (tile_rounds(mt[1], NT) < tile_rounds(mt[0], NT)) {
+        if (locate<Tall, From::counted>(offsets, E, NT, blockIdx.x, mt[1], t))
+            pipe_tile<DownTall>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
+    } else if (locate<Mid, From::counted>(offsets, E, NT, blockIdx.x, mt[0], t)) {
+        pipe_tile<DownMid>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
+    }
 }
 
 template <typename C>
@@ -375,28 +403,32 @@ hipError_t launch_expert_down_bf16_small(const bf16_t* h, const int32_t* offsets
     if (attr != hipSuccess) return attr;
     const long long NT = (d + DownSmall::BN_OUT - 1) / DownSmall::BN_OUT;
     const long long tiles = grid_upper_bound(n_rows, E, DownSmall::BM, NT);
-    const long long grid = tiles > stream::kCus ? tiles : stream::kCus;
+    const long long grid = tiles > kCus ? tiles : kCus;
     hipLaunchKernelGGL(grouped_down_bf16_small_kernel, dim3((unsigned)grid),
                        dim3(DownSmall::THREADS), kDownSmallLds, s, h, offsets, wd, E, d, f, y);
     return hipGetLastError();
 }
 
-// In between (tens to a few hundred rows per expert, e.g. 16 experts with top-1 routing), down
-// projection: still bound by streaming the weights, but 64-row tiles would re-read them several
-// times through L2.  128-row tiles, 128-byte rows per step, 4-stage ring (128 KB).
+// In between (tens to a few hundred rows per expert), down projection: still bound by streaming the
+// weights, but 64-row tiles would re-read them several times through L2.  128-byte rows per step, 4-stage
+// ring, tiles of up to 128 or 192 rows, one workgroup per CU.  A workgroup's time hardly depends on its
+// rows, so the form with fewer rounds of the chip is ahead, and how many a batch takes depends on how
+// its rows are spread, which only the device knows.  Measured, us, 128 / 192 rows (rounds): 12 experts x
+// 2048 x 3072, 130 rows each 59 (2) / 44 (1); 4096 x 14336, 8 experts, 120 rows 301 (2) / 198 (1), two
+// active with 440 rows each 112 (1) / 128 (1), under a Zipf exponent of 1.1 253 (2) / 296 (2).
 hipError_t launch_expert_down_bf16_mid(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
                                        int n_rows, int d, int f, int E, bf16_t* y,
                                        hipStream_t s) {
-    return launch_pipe<PipeCfg<128, 128, 64, 4, 2, 4, false>>(h, offsets, wd, nullptr, n_rows, E,
-                                                              d, f, y, s);
-}
-
-// The same with 192-row tiles (160 KB): one m-tile per expert between 128 and 192 rows.
-hipError_t launch_expert_down_bf16_tall(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
-                                        int n_rows, int d, int f, int E, bf16_t* y,
-                                        hipStream_t s) {
-    return launch_pipe<PipeCfg<192, 128, 64, 4, 2, 4, false>>(h, offsets, wd, nullptr, n_rows, E,
-                                                              d, f, y, s);
+    // one-time, thread-safe (C++11 static initialisation): raise the dynamic LDS limit
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&grouped_down_bf16_mid_kernel),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)DownTall::LDS_BYTES);
+    if (attr != hipSuccess) return attr;
+    const long long NT = (d + DownMid::BN_OUT - 1) / DownMid::BN_OUT;
+    const long long grid = grid_upper_bound(n_rows, E, DownMid::BM, NT);
+    hipLaunchKernelGGL(grouped_down_bf16_mid_kernel, dim3((unsigned)grid), dim3(DownTall::THREADS),
+                       DownTall::LDS_BYTES, s, h, offsets, wd, E, d, f, y);
+    return hipGetLastError();
 }
 
 }  // namespace specmoe

@@ -335,15 +335,14 @@ hipError_t launch_expert_up_bf16(const bf16_t* x_perm, const int32_t* offsets, c
 }
 
 // Down (K = d_ff).
-//  - r >= 192, large, unless its tiles are few: mid then has 128 x 128 ones (4096 x 14336, 8 experts,
+//  - r >= 192, large, unless its tiles are few: mid then has twice as many (4096 x 14336, 8 experts,
 //    225 rows: 363 -> 308; 1024 x 4096, 8, 250 rows: 88 -> 34).
-//  - mid (128 x 128 tiles) from 48 rows, at 1280 <= K < 4096 from 12 rows (2048 x 1408, 64 experts:
-//    register-staged 70 -> 61 at 15 rows, 99 -> 89 at 60; 8 rows 41 -> 46; K = 768 15 -> 21).
-//  - tall (192 x 128) where mid would need a second m-tile per expert: at K >= 4096 from 100 rows if
-//    the tiles make one round of the chip (4096 x 14336, 8 experts, 120 rows 301 -> 198, 175 rows 283
-//    -> 210; with more tiles the skewed 5120 x 8192, 16 experts, 128 rows loses, 330 -> 382, with fewer
-//    1024 x 4096, 8 experts, 30 -> 47); at 1280 <= K < 4096 from 112 rows with several rounds of
-//    tiles (2048 x 1408, 64 experts, 120 rows: 127 -> 112).
+//  - mid (128 outputs per tile, 128 or 192 rows, chosen on the device): K >= 4096 from 48 rows.  At
+//    1280 <= K < 4096 from 12 rows while the experts' weight tiles make one round of the chip (12 experts x
+//    2048 outputs, K = 3072: register-staged 51 -> 33 at 14 rows, 56 -> 42 at 110), and from 88 rows with more
+//    (64 x 2048, K = 1408: 113 -> 103 at 110 rows, 128 -> 108 at 130); below that a second round costs more than
+//    the ring gains (16 x 4096, K = 2048, 14 to 52 rows: 45 -> 63; 64 x 2048, K = 1408, 40 rows: 87 -> 80 when
+//    uniform, but 83 -> 94 under a Zipf exponent of 0.5).
 //  - small: K >= 4096 with few rows, choosing on the device (grouped_gemm_bf16_pipe.hip).
 hipError_t launch_expert_down_bf16(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
                                    int n_rows, int d, int f, int E, bf16_t* y, hipStream_t s) {
@@ -351,24 +350,17 @@ hipError_t launch_expert_down_bf16(const bf16_t* h, const int32_t* offsets, cons
     typedef TileCfg<64, 128, 1, 4, false> Staged;
     if (!rows_aligned(h, wd, y))
         return launch_one<Staged>(h, offsets, wd, nullptr, n_rows, E, d, f, y, s);
-    const long long tiles = (long long)E * ((d + 127) / 128);
-    if (large_batch(n_rows, E)) {
-        if (few_wide_tiles(n_rows, E, d, 256))
-            return launch_expert_down_bf16_mid(h, offsets, wd, n_rows, d, f, E, y, s);
+    if (large_batch(n_rows, E) && !few_wide_tiles(n_rows, E, d, 256))
         return launch_expert_down_bf16_large16(h, offsets, wd, n_rows, d, f, E, y, s);
-    }
+    const long long tiles = (long long)E * ((d + 127) / 128);
+    bool mid = large_batch(n_rows, E);
     if (f >= kLongK) {
-        if (!rows_at_least(n_rows, E, g_mid_rows))
-            return launch_expert_down_bf16_small(h, offsets, wd, n_rows, d, f, E, y, s);
-        if (rows_at_least(n_rows, E, 100) && tiles >= 128 && tiles <= 256)
-            return launch_expert_down_bf16_tall(h, offsets, wd, n_rows, d, f, E, y, s);
-        return launch_expert_down_bf16_mid(h, offsets, wd, n_rows, d, f, E, y, s);
+        mid = mid || rows_at_least(n_rows, E, g_mid_rows);
+        if (!mid) return launch_expert_down_bf16_small(h, offsets, wd, n_rows, d, f, E, y, s);
+    } else if (f >= 1280) {
+        mid = mid || rows_at_least(n_rows, E, tiles <= kCus ? 12 : 88);
     }
-    if (f >= 1280 && rows_at_least(n_rows, E, 12)) {
-        if (rows_at_least(n_rows, E, 112) && tiles >= 512)
-            return launch_expert_down_bf16_tall(h, offsets, wd, n_rows, d, f, E, y, s);
-        return launch_expert_down_bf16_mid(h, offsets, wd, n_rows, d, f, E, y, s);
-    }
+    if (mid) return launch_expert_down_bf16_mid(h, offsets, wd, n_rows, d, f, E, y, s);
     return launch_one<Staged>(h, offsets, wd, nullptr, n_rows, E, d, f, y, s);
 }
 

@@ -26,7 +26,6 @@ constexpr int kBM = 32, kBK = 64, kRowBytes = kBK * 2;
 constexpr int kWBytes = 32 * kRowBytes;                     // weight part of a stage (4 KB)
 constexpr int kRingBytes = 40 * 1024;                       // LDS of one wave
 constexpr size_t kStreamLds = (size_t)kStreamWaves * kRingBytes;
-constexpr int kCus = 256;
 typedef EvenPolicy<kBM, 16> Split;
 
 // chunk c of row r of a 128-byte-row image sits at chunk c ^ ((r / 2) % 8): conflict-free for

@@ -59,19 +59,25 @@ struct FixedPolicy {
     }
 };
 
-// m-tiles of all experts together (the same in every lane; not made scalar here: that would put
-// the next step of every workgroup behind this one's round trip to memory, measured at 1 us per
-// launch)
-template <typename Split>
-__device__ __forceinline__ int count_mtiles(const int32_t* __restrict__ offsets, int E) {
+// m-tiles of all experts together, one total per split, from one sweep over the offsets (the same in
+// every lane; not made scalar here: that would put the next step of every workgroup behind this
+// one's round trip to memory, measured at 1 us per launch)
+template <typename... Split>
+__device__ __forceinline__ void count_mtiles(const int32_t* __restrict__ offsets, int E,
+                                             int (&total)[sizeof...(Split)]) {
     const int lane = threadIdx.x % kWave;
-    int total_mt = 0;
+    for (int& n : total) n = 0;
     for (int e0 = 0; e0 < E; e0 += kWave) {
         const int e = e0 + lane;
         const int M = e < E ? offsets[e + 1] - offsets[e] : 0;
-        total_mt += wave_sum(Split::of(M).mt);
+        int i = 0;
+        ((total[i++] += wave_sum(Split::of(M).mt)), ...);
     }
-    return total_mt;
+}
+
+// Rounds of the chip that a batch's workgroups take, one per CU at a time.
+__device__ __forceinline__ int tile_rounds(int total_mt, int NT) {
+    return __builtin_amdgcn_readfirstlane((int)(((long long)total_mt * NT + kCus - 1) / kCus));
 }
 
 enum class From { workgroup, counted, place };

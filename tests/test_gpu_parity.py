@@ -384,8 +384,11 @@ def _rows_around(mean, E, seed):
     (64, 1024, _rows_around(50, 64, 1)),             # mid, short contraction, many tiles
     (128, 1024, _rows_around(100, 24, 2)),           # mid from 96 rows
     (64, 1280, _rows_around(13, 9, 3)),              # down: 128-row tiles from 12 rows
-    (256, 4096, _rows_around(101, 64, 4)),           # down: 192-row tiles, one round of tiles
-    (1024, 1280, _rows_around(113, 64, 5)),          # down: 192-row tiles, several rounds
+    (256, 4096, _rows_around(101, 64, 4)),           # down: 128-row tiles, one round of tiles
+    (2048, 1280, [0, 1, 127, 128, 129, 191, 192, 193, 140, 150, 160, 170, 180, 100, 190, 185]),
+                                                     # down: 192-row tiles, one round instead of two
+    (1024, 1280, _rows_around(113, 64, 5)),          # down: several rounds
+    (1152, 1280, _rows_around(60, 29, 6)),           # down: 261 weight tiles, not before 88 rows
     (128, 64, [200, 190, 193]),                      # down: few wide tiles, one k-step
 ])
 def test_row_major_dispatch_forms(d, f, rows):
