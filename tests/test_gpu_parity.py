@@ -880,12 +880,16 @@ def test_pack_weights_layout(E, R, K):
     (256, 512, [3, 0, 70, 1, 129, 64, 0, 0]),
     (128, 256, [5, 17, 64, 1, 0, 33, 65, 16]),
     (512, 1024, [40, 1]),
-    # few tiles: 128-row tiles of 128 weight rows with one and two m-tiles, 320-row ones (down), and
-    # the 256-wide tiles from 129 wide tiles (65 experts x 2) and from two m-tiles on
+    # few tiles: 128-row tiles of 128 weight rows with one and more m-tiles
     (256, 128, [128, 129, 16, 0, 255, 97]),
-    (2304, 128, [300, 320, 321, 1, 150, 0, 120, 100]),
-    (384, 256, [3, 0, 17, 1, 20] * 13),
+    (384, 256, [3, 0, 17, 1, 20] * 13),              # down: up to 12 rows per expert on average
     (320, 192, [400, 380, 333, 321]),
+    # down, 65 to 128 wide tiles, by what makes one round of the chip: 128 x 128 tiles (14 m-tiles x 18),
+    # 320 x 128 (18 x 18 of 128 rows, 9 x 18 of 320), or neither and 192 x 256 (10 x 32) or 320 x 256 (66 x 4)
+    (2304, 128, [300, 320, 321, 1, 150, 0, 120, 100]),
+    (2304, 128, [300, 320, 321, 1, 150, 130, 140, 129]),
+    (4096, 128, [500, 400, 330, 1, 0, 17, 100, 64]),
+    (512, 128, [641] * 13 + [64] * 27),
 ])
 def test_packed_expert_gemms(d, f, rows):
     """moe_expert_up_swiglu_gather_packed + moe_expert_down_packed against the oracle, and - where
