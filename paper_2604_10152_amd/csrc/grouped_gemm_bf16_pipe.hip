@@ -19,6 +19,7 @@
 // front of every LDS read that follows an LDS-DMA load, which collapses the ring to depth 1.
 // Hand-placed s_waitcnt vmcnt(n) is safe next to compiler-generated waits: extra outstanding
 // loads can only make a compiler-chosen wait stricter, never weaker.
+#include "pipe16_tile.h"
 #include "pipe_common.h"
 #include "stream_tiles.h"
 
@@ -301,17 +302,6 @@ __device__ __forceinline__ void pipe_tile(
     }
 }
 
-template <typename C>
-__global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe_kernel(
-    const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets,
-    const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int E, int N, int K,
-    bf16_t* __restrict__ Cout, const int32_t* __restrict__ row_src, int topk) {
-    extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
-    TileLoc t;
-    if (locate_tile_even<C::BM>(offsets, E, (N + C::BN_OUT - 1) / C::BN_OUT, blockIdx.x, t))
-        pipe_tile<C>(lds_raw, t, A, W0, W1, N, K, Cout, row_src, topk);
-}
-
 // Down projection with few rows per expert: by the number of tiles this batch has (known on the
 // device only) the ring above or the independent streams of stream_tiles.h.
 typedef PipeCfg<64, 128, 64, 6, 1, 4, false> DownSmall;
@@ -360,34 +350,72 @@ __global__ __launch_bounds__(DownTall::THREADS) void grouped_down_bf16_mid_kerne
     }
 }
 
-template <typename C>
-hipError_t launch_pipe(const bf16_t* A, const int32_t* offsets, const bf16_t* W0,
-                       const bf16_t* W1, int n_rows, int E, int N, int K, bf16_t* Cout,
-                       hipStream_t s, const int32_t* row_src = nullptr, int topk = 1) {
-    // one-time, thread-safe (C++11 static initialisation): raise the dynamic LDS limit
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&grouped_gemm_bf16_pipe_kernel<C>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES);
-    if (attr != hipSuccess) return attr;
-    const long long NT = (N + C::BN_OUT - 1) / C::BN_OUT;
-    const long long grid = grid_upper_bound(n_rows, E, C::BM, NT);
-    hipLaunchKernelGGL(grouped_gemm_bf16_pipe_kernel<C>, dim3((unsigned)grid), dim3(C::THREADS),
-                       C::LDS_BYTES, s, A, offsets, W0, W1, E, N, K, Cout, row_src, topk);
-    return hipGetLastError();
+// Gate/up on row-major operands: the ring above with 128-row tiles or the 192-row tiles of
+// pipe16_tile.h (launch_expert_up_bf16_ring_or_mid).
+typedef PipeCfg<128, 128, 64, 4, 4, 2, true> UpRing;
+typedef PipeCfg<192, 256, 32, 4, 2, 4, true> UpMid;
+
+__global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
+    const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets,
+    const bf16_t* __restrict__ wg, const bf16_t* __restrict__ wu, int E, int N, int K,
+    bf16_t* __restrict__ h, const int32_t* __restrict__ row_src, int topk, int mid_if_less,
+    int mid_if_equal) {
+    static_assert(UpRing::THREADS == UpMid::THREADS && UpRing::LDS_BYTES >= UpMid::LDS_BYTES,
+                  "one launch serves both");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+    typedef EvenPolicy<UpRing::BM, 32> Ring;
+    typedef EvenPolicy<UpMid::BM, 16> Mid;
+    const int NR = (N + UpRing::BN_OUT - 1) / UpRing::BN_OUT;
+    const int NM = (N + UpMid::BN_OUT - 1) / UpMid::BN_OUT;
+    int mt[2];
+    count_mtiles<Ring, Mid>(offsets, E, mt);
+    const int ring = tile_rounds(mt[0], NR), mid = 2 * tile_rounds(mt[1], NM);
+    // contractions below 4096: a second round of ring tiles that is at most half full
+    const bool small = K < 4096 && 2ll * __builtin_amdgcn_readfirstlane(mt[0]) * NR <= 3ll * kCus &&
+                       2ll * __builtin_amdgcn_readfirstlane(mt[1]) * NM >= kCus;
+    TileLoc t;
+    if (mid < ring ? mid_if_less : (mid == ring && (mid_if_equal || small))) {
+        if (locate<Mid, From::counted>(offsets, E, NM, blockIdx.x, mt[1], t))
+            pipe16_tile<UpMid>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk);
+    } else if (locate<Ring, From::counted>(offsets, E, NR, blockIdx.x, mt[0], t)) {
+        pipe_tile<UpRing>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk);
+    }
 }
 
 }  // namespace
 
-// Gate/up with up to about 90 rows per expert: 128 x 128 tiles (64 gate and 64 up rows), 128-byte
-// rows per step (BK = 64; 64-byte rows lose ~10 % of HBM throughput), 4-stage ring of 128 KB, 8
-// wavefronts.  Against the 64 x 128 ring of two wavefronts before, rows beyond 64 no longer cost a
-// second pass over the weights, and below that the eight waves issue the wave-loads faster.
-hipError_t launch_expert_up_bf16_ring(const bf16_t* x_perm, const int32_t* offsets,
-                                      const bf16_t* wg, const bf16_t* wu, int n_rows, int d, int f,
-                                      int E, bf16_t* h, hipStream_t s, const int32_t* row_src,
-                                      int topk) {
-    return launch_pipe<PipeCfg<128, 128, 64, 4, 4, 2, true>>(x_perm, offsets, wg, wu, n_rows, E, f,
-                                                             d, h, s, row_src, topk);
+// Gate/up on row-major operands, up to 192 rows per expert.
+//  - ring: 128 x 128 tiles (64 gate and 64 up rows), 128-byte rows per step (BK = 64; 64-byte rows lose
+//    ~10 % of HBM throughput), 4-stage ring of 128 KB, 8 wavefronts, one workgroup per CU.
+//  - mid: 192-row tiles of 128 gate and 128 up rows, twice the weights per workgroup, so about twice the
+//    time, in half lines.
+// The ring is ahead unless its smaller tiles take more rounds of the chip than twice the mid tiles.
+// How many a batch takes depends on how its rows are spread: the draft model routes everything to a
+// few experts.  Measured, us, ring / mid (rounds): 4096 x 14336, 8 experts, 70 rows each 335 (7) / 381 (4),
+// the same rows on two experts 219 (6) / 174 (2); 5120 x 8192, 16 experts, 70 rows under a Zipf exponent of 0.5
+// 590 (9) / 555 (4); 2048 x 1408, 64 experts, 70 rows, exponent 1.1 169 (8) / 196 (4).
+// At equal rounds mid is ahead only for long contractions from about 88 rows on (5120 x 8192, 16
+// experts: 92 rows 550 / 530, 110 rows 575 / 546; 52 rows 490 / 502), and where a short one leaves the
+// ring's second round at most half full (2048 x 1408, 16 of 64 experts active, 40 rows each: 43 / 33).
+// Below 60 rows per expert a mid tile of a hot expert outlasts the round it saves (4096 x 8192, 8 experts,
+// 52 rows, exponent 1.1: 201 / 254).
+hipError_t launch_expert_up_bf16_ring_or_mid(const bf16_t* x_perm, const int32_t* offsets,
+                                             const bf16_t* wg, const bf16_t* wu, int n_rows, int d,
+                                             int f, int E, bf16_t* h, hipStream_t s,
+                                             const int32_t* row_src, int topk) {
+    // one-time, thread-safe (C++11 static initialisation): raise the dynamic LDS limit
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&grouped_up_bf16_kernel),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)UpRing::LDS_BYTES);
+    if (attr != hipSuccess) return attr;
+    const int mid_if_less = (long long)n_rows >= 60ll * E;
+    const int mid_if_equal = d >= 4096 && (long long)n_rows >= 88ll * E;
+    const long long NR = (f + UpRing::BN_OUT - 1) / UpRing::BN_OUT;
+    const long long grid = grid_upper_bound(n_rows, E, UpRing::BM, NR);
+    hipLaunchKernelGGL(grouped_up_bf16_kernel, dim3((unsigned)grid), dim3(UpRing::THREADS),
+                       UpRing::LDS_BYTES, s, x_perm, offsets, wg, wu, E, f, d, h, row_src, topk,
+                       mid_if_less, mid_if_equal);
+    return hipGetLastError();
 }
 
 // Down projection with few rows per expert and a long contraction: the weights stream from HBM

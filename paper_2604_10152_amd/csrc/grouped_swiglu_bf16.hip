@@ -297,16 +297,13 @@ static inline bool rows_aligned(const void* a, const void* b, const void* c, con
 
 // Gate/up (K = d_model, 128 outputs per 256-wide tile).
 //  - r >= 192, large: up to 320-row tiles, MFMA-bound.  Unless they are few: 8 x 1024 outputs are
-//    64 tiles on 256 CUs (3072 x 1024, 200 rows: 59 -> 32 with the ring).
-//  - ring (128 x 128 tiles, BK = 64: whole 128-byte lines of row-major operands) for K >= 2048 up to
-//    88 rows: against the 64 x 128 ring that was here 309 -> 305 (4096 x 14336, 8 experts, 20 rows),
-//    118 -> 92 (4096 x 2048, 16, 31 rows); against register-staged tiles 141 -> 108 (2048 x 1408, 64,
-//    15 rows), 46 -> 30 (3072 x 1024, 8, 50 rows); against mid 357 -> 320 (4096 x 14336, 50 rows),
-//    378 -> 352 (83 rows), and behind it from there (120 rows: 404 / 410, 150: 428 / 557).
-//  - mid (192-row tiles, half lines): above that, and at K < 4096 from 48 rows if there are tiles for
-//    two rounds of the chip (2048 x 1408, 64 experts: register-staged 220 -> 199 at 120 rows, 178 -> 157
-//    at 48), or from 96 rows (1024 x 2048, 16 experts, 128 rows: 49 -> 30 uniform, 49 -> 45 skewed; but
-//    31 -> 43 at 64 rows, skewed).
+//    64 tiles on 256 CUs (3072 x 1024, 200 rows: 76 -> 36 with the ring).
+//  - ring or mid, chosen on the device, for K >= 2048: against register-staged tiles 141 -> 108 (2048 x
+//    1408, 64 experts, 15 rows), 67 -> 33 (3072 x 1024, 8, 6 to 50 rows), 181 -> 149 (2048 x 1408, 64, 52 rows
+//    under a Zipf exponent of 1.1).
+//  - mid at shorter K from 96 rows with 192 tiles or more (1024 x 2048, 16 experts, 128 rows: 49 -> 30
+//    uniform, 49 -> 45 skewed).  From 48 rows it gains as much when uniform and loses as much when skewed
+//    (1024 x 1024, 64 experts, 70 rows: 70 -> 63 / 70 -> 83; 512 x 2048, 32 experts 41 -> 36 / 42 -> 51).
 //  - register-staged otherwise: contractions of a few dozen steps, where several co-resident
 //    workgroups hide each other's prologue (1024 x 2048, 25 rows: 29 against 31 with the ring).
 hipError_t launch_expert_up_bf16(const bf16_t* x_perm, const int32_t* offsets, const bf16_t* wg,
@@ -316,21 +313,16 @@ hipError_t launch_expert_up_bf16(const bf16_t* x_perm, const int32_t* offsets, c
     typedef TileCfg<64, 256, 1, 4, true> Staged;
     if (!rows_aligned(x_perm, wg, wu, h))
         return launch_one<Staged>(x_perm, offsets, wg, wu, n_rows, E, f, d, h, s, row_src, topk);
-    const long long tiles = (long long)E * ((f + 127) / 128);
-    const bool few = few_wide_tiles(n_rows, E, f, 128);
-    if (large_batch(n_rows, E) && !(few && d >= 2048))
+    if (large_batch(n_rows, E) && !(d >= 2048 && few_wide_tiles(n_rows, E, f, 128)))
         return launch_expert_up_bf16_large16(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s,
                                              row_src, topk);
-    bool mid;
-    if (d >= kLongK) mid = rows_at_least(n_rows, E, 88);
-    else if (rows_at_least(n_rows, E, 96)) mid = tiles > (d >= 2048 ? 128 : 191);
-    else mid = rows_at_least(n_rows, E, g_mid_rows) && tiles >= 512;
-    if (mid && !large_batch(n_rows, E))
+    if (d >= 2048)
+        return launch_expert_up_bf16_ring_or_mid(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s,
+                                                 row_src, topk);
+    const long long tiles = (long long)E * ((f + 127) / 128);
+    if (rows_at_least(n_rows, E, 96) && tiles > 191)
         return launch_expert_up_bf16_mid(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s, row_src,
                                          topk);
-    if (d >= 2048)
-        return launch_expert_up_bf16_ring(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s, row_src,
-                                          topk);
     return launch_one<Staged>(x_perm, offsets, wg, wu, n_rows, E, f, d, h, s, row_src, topk);
 }
 

@@ -379,9 +379,14 @@ def _rows_around(mean, E, seed):
 @pytest.mark.parametrize("d,f,rows", [
     (2048, 64, [128, 129, 1, 0, 61]),                # gate/up ring: one and two m-tiles
     (2048, 192, [300, 129, 128, 250]),               # ... many rows but few tiles
-    (4096, 64, [90, 88, 87, 86]),                    # ... on both sides of its last row count:
-    (4096, 64, [90, 88, 87, 88]),                    # mid from 88 rows per expert
-    (64, 1024, _rows_around(50, 64, 1)),             # mid, short contraction, many tiles
+    (4096, 64, [90, 88, 87, 86]),                    # ... long contraction, on both sides of 88 rows
+    (4096, 64, [90, 88, 87, 88]),
+    # ... or mid: 3 rounds of ring tiles against 1, 2 against 1 with a long contraction, and a second
+    # round of ring tiles (16 x 17) that is hardly begun
+    (2048, 1152, [0, 1, 129, 192, 191, 150, 160, 170, 180, 140, 130, 131, 132, 133, 134, 135]),
+    (4096, 2112, [90, 88, 100, 86, 96, 128, 1, 127]),
+    (2048, 1088, [3, 17, 1, 32, 33, 5, 64, 9, 2, 8, 16, 31, 1, 1, 40, 7]),
+    (64, 1024, _rows_around(50, 64, 1)),             # short contraction, many tiles
     (128, 1024, _rows_around(100, 24, 2)),           # mid from 96 rows
     (64, 1280, _rows_around(13, 9, 3)),              # down: 128-row tiles from 12 rows
     (256, 4096, _rows_around(101, 64, 4)),           # down: 128-row tiles, one round of tiles
