@@ -548,7 +548,7 @@ def test_rmsnorm(dtype, T, d):
     assert row_rel_err(f64(out), orc.rmsnorm(f64(x), f64(gain), 1e-5)) <= TOL[dtype]
 
 
-@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 24), (torch.bfloat16, 2048), (torch.bfloat16, 4096),
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 24), (torch.bfloat16, 264), (torch.bfloat16, 2048), (torch.bfloat16, 4096),
                                      (torch.bfloat16, 5120), (torch.bfloat16, 8192), (torch.float32, 1024),
                                      (torch.float32, 1028), (torch.float32, 4096)])
 def test_rmsnorm_does_not_depend_on_alignment(dtype, d):
