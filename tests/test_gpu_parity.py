@@ -352,14 +352,27 @@ def test_grouped_fp32_tile_forms(mean, d, f, E):
     _grouped_case(torch.float32, d, f, rows, seed=d + f + mean)
 
 
+def _wide_rows(mean):
+    """70 experts with the given mean, among them the edges of the 192- and 320-row tiles.  With 320
+    outputs (down) and 192 hidden columns (gate/up) that is 140 tiles of 256 weight rows, every second one
+    partial: too many for the forms that serve batches with few wide tiles."""
+    rng = np.random.default_rng(mean)
+    rows = rng.integers(0, 2 * mean + 1, size=70)
+    edge = [0, 1, 17, 191, 192, 193, 319, 320, 321] if mean >= 192 else [0, 1, 15, 16, 17, 193]
+    rows[:len(edge)] = edge
+    rows[-1] = max(0, mean * 70 - int(rows[:-1].sum()))
+    return rows.tolist()
+
+
 @pytest.mark.parametrize("d,f,rows", [
-    (256, 384, [300, 0, 37, 1, 513, 256, 330]),      # large-batch tiles: full, ragged, empty
+    (256, 384, [300, 0, 37, 1, 513, 256, 330]),      # gate/up: 320-row tiles, full, ragged, empty
     (512, 1408, [700, 650]),
-    (4096, 256, [100, 0, 60, 129, 1, 170]),          # mid tier (128-row tiles) in the gate/up GEMM
-    (256, 4096, [100, 0, 60, 129, 1, 170]),          # mid tier in the down GEMM
-    (256, 384, [3, 0, 70, 1, 129, 64, 0, 0]),        # few rows per expert: narrow tiles
+    (4096, 256, [100, 0, 60, 129, 1, 170]),          # long contraction in the gate/up GEMM
+    (256, 4096, [100, 0, 60, 129, 1, 170]),          # long contraction in the down GEMM
+    (256, 384, [3, 0, 70, 1, 129, 64, 0, 0]),        # few rows per expert
     (2048, 1408, [0, 40, 1, 0, 310, 7, 0, 22]),      # cfg-3 shape, skewed
     (64, 64, [1]),
+    (320, 192, _wide_rows(200)),                     # 320 x 256 tiles in both GEMMs, the last one partial
 ])
 def test_grouped_bf16(d, f, rows):
     _say(f"grouped bf16 d={d} f={f} rows={rows}")
@@ -895,6 +908,9 @@ def test_pack_weights_layout(E, R, K):
     (2304, 128, [300, 320, 321, 1, 150, 130, 140, 129]),
     (4096, 128, [500, 400, 330, 1, 0, 17, 100, 64]),
     (512, 128, [641] * 13 + [64] * 27),
+    # too many wide tiles for those, in both projections, every second one partial: 192 and 320 rows
+    (320, 192, _wide_rows(20)),
+    (320, 192, _wide_rows(200)),
 ])
 def test_packed_expert_gemms(d, f, rows):
     """moe_expert_up_swiglu_gather_packed + moe_expert_down_packed against the oracle, and - where
