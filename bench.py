@@ -311,28 +311,38 @@ def packed_weights_for(sm, torch, cfg, L, T, row_major=False):
     return packed
 
 
+def few_wide_tiles(rows, E, n_out, wide):
+    """WideTiles of csrc/common.h: (do the tiles of `wide` outputs leave much of the chip idle?, how many)."""
+    m = -(-115 * rows // (32000 * E))
+    tiles = E * m * -(-n_out // wide)
+    return tiles <= (128 if m <= 1 else 64), tiles
+
+
 def kernel_name(cfg, T, packed=True):
-    """Which gate/up kernel runs for this shape (names for the report)."""
+    """Which gate/up kernel runs for this shape (names for the report): the rules of
+    launch_expert_up_bf16 and launch_expert_up_bf16_packed_x."""
     import paper_2604_10152_amd as sm
     if cfg.dtype != "bf16":
         return "grouped_gemm_f32_kernel<true> (gate/up + SwiGLU)"
     rows = T * cfg.k
-    tile = 320 if rows >= 192 * cfg.E else 192
-    if packed and sm.MoEVerifyLayer.packed_plan(rows, cfg.E, cfg.d_model, cfg.d_ff)[0]:
-        return (f"grouped_gemm_bf16_pipe16_kernel<PipeCfg<{tile},256,32,4,2,4,true>,PA,PB> (gate/up + "
-                "SwiGLU on tile-packed operands: the permute step writes the dispatched rows "
-                "tile-packed)")
-    tiles = cfg.E * -(-cfg.d_ff // 128)      # gate/up tiles of 256 weight rows, for the lines below
-    if cfg.d_model >= 4096:
-        mid = rows >= 88 * cfg.E
-    elif rows >= 96 * cfg.E:
-        mid = tiles > (128 if cfg.d_model >= 2048 else 191)
-    else:
-        mid = rows >= 48 * cfg.E and tiles >= 512
-    if rows >= 192 * cfg.E or mid:
-        return f"grouped_gemm_bf16_pipe16_kernel<PipeCfg<{tile},256,32,4,2,4,true>> (gate/up + SwiGLU)"
+    large = rows >= 192 * cfg.E
+    tile = 320 if large else 192
+    few, tiles = few_wide_tiles(rows, cfg.E, cfg.d_ff, 128)
+    if packed:
+        up, down = sm.MoEVerifyLayer.packed_plan(rows, cfg.E, cfg.d_model, cfg.d_ff)
+        if up:
+            narrow = down and few and (tiles <= 64 or 115 * rows <= 12800 * cfg.E)
+            form = "128,128" if narrow else f"{tile},256"
+            return (f"grouped_gemm_bf16_pipe16_kernel<PipeCfg<{form},32,4,2,4,true>,PA,PB> (gate/up + "
+                    "SwiGLU on tile-packed operands: the permute step writes the dispatched rows "
+                    "tile-packed)")
+    if large and not (cfg.d_model >= 2048 and few):
+        return "grouped_gemm_bf16_pipe16_kernel<PipeCfg<320,256,32,4,2,4,true>> (gate/up + SwiGLU)"
     if cfg.d_model >= 2048:
-        return "grouped_gemm_bf16_pipe_kernel<PipeCfg<128,128,64,4,4,2,true>> (gate/up + SwiGLU)"
+        return ("grouped_up_bf16_kernel: PipeCfg<128,128,64,4,4,2,true> or <192,256,32,4,2,4,true>, chosen "
+                "on the device (gate/up + SwiGLU)")
+    if rows >= 96 * cfg.E and cfg.E * -(-cfg.d_ff // 128) > 191:
+        return "grouped_gemm_bf16_pipe16_kernel<PipeCfg<192,256,32,4,2,4,true>> (gate/up + SwiGLU)"
     return "grouped_gemm_bf16_kernel<TileCfg<64,256,1,4,true>> (gate/up + SwiGLU)"
 
 

@@ -159,7 +159,8 @@ int moe_expert_up_swiglu_gather(const void* x, const int32_t* row_src, int T, in
  * Results are identical to the row-major entry points' large-batch kernels (same arithmetic in
  * the same order) where both pick the same tile.  moe_expert_up_swiglu_packed and
  * moe_expert_down_packed choose 320-row tiles from 192 rows per expert on average and 192-row
- * tiles below, and narrower ones for batches with few tiles; moe_expert_up_swiglu_gather_packed without a workspace always uses 320-row tiles.
+ * tiles below, and tiles of fewer weight rows for batches with few tiles (not with h_row_major);
+ * moe_expert_up_swiglu_gather_packed without a workspace always uses 320-row tiles.
  * With long contractions (>= 4096) and fewer than about 48 rows per expert the row-major entry
  * points are the faster ones.  bf16 only. */
 int moe_pack_weights(const void* w, int E, int n_rows, int n_cols, int dtype, void* w_packed,

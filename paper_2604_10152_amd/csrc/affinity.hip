@@ -11,8 +11,8 @@
 // products and sums in fp64.  v_mfma_f64_16x16x4 takes 64 cycles for 16 x 16 pairs x 4 columns; a
 // wave holds up to 64 experts at a time (10 tiles of the upper triangle: 640 cycles per 4 columns
 // of 64 experts, 0.57 ms at the shape above) and reads and converts every weight once.  Measured,
-// bf16, before -> now: 12 experts x 2048 x 2048 249 -> 160 us, 16 x 5120 x 8192 2.29 -> 1.45 ms,
-// 24 x 2048 x 1408 500 -> 253 us, 64 x 2048 x 1408 3.36 -> 0.70 ms, 130 x 1024 x 704 7.39 -> 1.43.
+// bf16, pair by pair / Gram matrix: 12 experts x 2048 x 2048 249 / 160 us, 16 x 5120 x 8192 2.29 / 1.45
+// ms, 24 x 2048 x 1408 500 / 253 us, 64 x 2048 x 1408 3.36 / 0.70 ms, 130 x 1024 x 704 7.39 / 1.43.
 // Cancellation: subtracting W_0 removes what all experts have in common (experts grown from one
 // dense model).  A pair that still lies closer together than 2^-10 of its norms - a copy, or any pair
 // where expert 0 lies far from all others - takes its distance from its differences: the finish
@@ -27,8 +27,8 @@
 // Up to 8 experts (28 pairs): the direct sums are the faster form (the matrix kernel spends the
 // same 64 cycles on 16 rows however few experts there are: 1.03 ms at 8 x 4096 x 14336 with two
 // column slices in the 16 rows): affinity_pairs_kernel, bound by HBM since the next pieces are
-// requested ahead (before -> now: 4 x 4096 x 14336 675 -> 247 us = 5.7 TB/s, 8 x 4096 x 14336
-// 883 -> 525 us = 5.4 TB/s).
+// requested ahead (4 x 4096 x 14336 247 us = 5.7 TB/s, 675 without; 8 x 4096 x 14336 525 us = 5.4
+// TB/s, 883 without).
 //
 // All sums run in a fixed order (deterministic, no floating-point atomics).
 //

@@ -213,9 +213,8 @@ __device__ __forceinline__ void pipe_tile(
         // epilogue.  The matrix instruction is issued as (weights x activations^T), so a lane
         // holds ONE tile row (lane%32) and, for each g = r/4, four consecutive output columns
         // 8g + 4*(lane/32) + r%4, i.e. 8 bytes of bf16.
-        //  - SwiGLU tile (BN/2 = 128 output columns, written once per n-tile of every row
-        //    block: the h matrix is 117 MB at the large-batch shape): the 8-byte pieces go to an
-        //    LDS image of the tile and the workgroup then writes whole 256-byte rows.
+        //  - SwiGLU tile (BN/2 = 64 output columns): the 8-byte pieces go to an LDS image of the tile
+        //    and the workgroup then writes whole 128-byte rows.
         //  - plain tile: 8-byte stores straight to global memory (y is small).
         const int row = lane & 31, chalf = (lane >> 5) * 4;
         if (C::SWIGLU) __builtin_amdgcn_s_barrier();   // every wave's loads have landed: LDS is free

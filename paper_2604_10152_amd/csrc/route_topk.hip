@@ -234,8 +234,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
 // that several share a CU and hide each other's memory and ranking phases.  What bounds it is
 // issue on the fp64 pipe, about half of it the widening conversions (as fast as a multiply-add,
 // but one per weight and 4 RT tokens).
-// A workgroup owns 4 RT tokens (a widened router weight serves RT instructions).  Lane l = i + 4 (b + 4 q) of an operand is row i, contraction element
-// q of block b: the blocks hold the same 4 tokens and 4 experts each (16 experts per instruction,
+// A workgroup owns 4 RT tokens (a widened router weight serves RT instructions).  Lane l = i + 4 (b +
+// 4 q) of an operand is row i, contraction element q of block b: the blocks hold the same 4 tokens and 4 experts each (16 experts per instruction,
 // NG instructions for all), or with KS = 2 or 4 (at most 8 or 4 experts) the same experts at KS
 // different column ranges, which are added at the end.  A lane loads 16 bytes, so a unit of 32 KS
 // columns is 8 steps; the waves take units in turn.  Every expert's logit goes through the same

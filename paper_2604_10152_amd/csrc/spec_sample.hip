@@ -48,7 +48,7 @@ __device__ __forceinline__ double wave_scan_incl(double v, int lane) {
 // sums meet in LDS; a wave scan over them, 64 tiles at a time, gives the total and then the tile
 // where the threshold is crossed, and one wave scans that tile.  Only the order of the fp64
 // additions differs from a sequential running sum.  B = 256, gamma = 7, V = 32000: 32 us with one
-// tile at a time and a serial walk over the tile sums -> 16.2 us; HBM is the bound (2 V 4 bytes per
+// tile at a time and a serial walk over the tile sums, 15.4 like this; HBM is the bound (2 V 4 bytes per
 // sequence, after two dependent round trips for the first rejection).
 __global__ __launch_bounds__(kSampleThreads) void spec_accept_sample_kernel(
     const int32_t* __restrict__ draft, const float* __restrict__ p_draft,

@@ -7,12 +7,14 @@
 // known on the device only.  The ring of grouped_gemm_bf16_pipe.hip shares a stage of 128 weight
 // rows between its waves: two active experts of 4096 x 14336 are then 64 workgroups on 256 CUs
 // (90 us, 2.6 TB/s).  Here every wave owns 32 weight rows and a private LDS ring of BK = 64 stages
-// (one 128-byte line per row), so no barrier sits in the loop, and the KW waves of a tile split the
-// contraction: 64 or 32 weight rows per workgroup, whichever first gives the chip a workgroup
-// per CU.  The partial sums of the KW waves meet in LDS in wave order (deterministic).
-// Measured, down projection of 4096 x 14336, 16 rows per active expert, ring -> this: 1 expert 83 ->
-// 37 us, 2 90 -> 47, 3 99 -> 79, 4 111 -> 91, 6 133 -> 146; 5120 x 8192: 1 expert 46 -> 26, 2 54 -> 48,
-// 4 67 -> 89.  Hence the line at 128 tiles of 32 x 128 (half the CUs): stream_few().
+// (one 128-byte line per row), so no barrier sits in the loop, and the four waves of a workgroup
+// split the contraction of one slab of 32 weight rows.  Two slabs with two waves each where that gives
+// every CU a workgroup, i.e. at the line below: 8192 outputs, 2 active experts 32 us against 41 with
+// one slab (4096 outputs, 4 of them 94 / 90; 4 m-tiles of 2 experts 78 / 84).  The partial sums of
+// the waves meet in LDS in wave order (deterministic).
+// Measured, down projection of 4096 x 14336, 16 rows per active expert, ring / this: 1 expert 83 /
+// 37 us, 2 90 / 47, 3 99 / 79, 4 111 / 91, 6 133 / 146; 5120 x 8192: 1 expert 46 / 26, 2 54 / 48, 4 67 / 89.
+// Hence the line at 128 tiles of 32 x 128 (half the CUs): stream_few().
 #pragma once
 #include "pipe_common.h"
 
@@ -48,9 +50,9 @@ __device__ __forceinline__ void stream_tiles(
     constexpr int OUT = 32;                                 // weight rows = output columns of a wave
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int slabs = (N + OUT - 1) / OUT;                  // 32-weight-row slabs of an expert
-    const int KW = (long long)total_mt * ((slabs + 1) / 2) >= kCus ? 2 : 4;
-    const int NW = kStreamWaves / KW, NT = (slabs + NW - 1) / NW;
+    const int slabs = N / OUT;                              // of an expert: an even number
+    const int KW = (long long)total_mt * (slabs / 2) >= kCus ? 2 : 4;
+    const int NW = kStreamWaves / KW, NT = slabs / NW;
     const int wk = wave % KW, wn = wave / KW;
     const long long G = (long long)total_mt * NT;
     const long long per_xcd = (G + kXcds - 1) / kXcds;
@@ -64,14 +66,13 @@ __device__ __forceinline__ void stream_tiles(
         const long long L = (long long)(blockIdx.x % kXcds) * per_xcd + slot;
         TileLoc t;
         if (L >= G || !locate<Split, From::place>(offsets, E, NT, L, 0, t)) break;
-        const int n0 = (t.nt * NW + wn) * OUT;              // may lie beyond N (last tile)
-        const int n_left = N - n0;
+        const int n0 = (t.nt * NW + wn) * OUT;
 
         // ---- wave-loads: 8 rows of 128 bytes each; lane -> row lane / 8, LDS chunk lane % 8
         const int srow = lane >> 3, pc = lane & 7;
         const unsigned char* a_base = uniform_ptr(
             reinterpret_cast<const unsigned char*>(A + (size_t)t.row0 * K));
-        const size_t wrow = (size_t)t.expert * N + min(n0, N - 1);
+        const size_t wrow = (size_t)t.expert * N + n0;
         const unsigned char* w_base =
             uniform_ptr(reinterpret_cast<const unsigned char*>(W + wrow * K));
         const int a_cnt = (t.tile_rows + 7) / 8;            // wave-loads that hold real rows, 1..4
@@ -80,7 +81,7 @@ __device__ __forceinline__ void stream_tiles(
         for (int j = 0; j < 4; ++j) {
             const int r = 8 * j + srow, c = pc ^ ((r >> 1) & 7);
             a_off[j] = ((unsigned)min(r, t.tile_rows - 1) * (unsigned)K + (unsigned)(c * 8)) * 2u;
-            w_off[j] = ((unsigned)min(r, max(n_left, 1) - 1) * (unsigned)K + (unsigned)(c * 8)) * 2u;
+            w_off[j] = ((unsigned)r * (unsigned)K + (unsigned)(c * 8)) * 2u;
         }
         const bool once = t.mt == 1;                        // no other workgroup reads these weights
         const int a_bytes = a_cnt * 1024, stage = kWBytes + a_bytes;
@@ -160,11 +161,9 @@ __device__ __forceinline__ void stream_tiles(
             bf16_t* crow = Cout + (size_t)(t.row0 + row) * N;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int col = n0 + 8 * g + ch;            // N is a multiple of 64: all four or none
-                if (col < N)
-                    *reinterpret_cast<uint2*>(crow + col) =
-                        make_uint2(pack_bf16x2(acc[4 * g], acc[4 * g + 1]),
-                                   pack_bf16x2(acc[4 * g + 2], acc[4 * g + 3]));
+                *reinterpret_cast<uint2*>(crow + n0 + 8 * g + ch) =
+                    make_uint2(pack_bf16x2(acc[4 * g], acc[4 * g + 1]),
+                               pack_bf16x2(acc[4 * g + 2], acc[4 * g + 3]));
             }
         }
     }

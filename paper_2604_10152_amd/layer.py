@@ -36,11 +36,12 @@ class MoEVerifyLayer:
         self.x_packed = None
 
     # Which projections run on tile-packed operands (measured crossovers, average rows per
-    # expert r = T*k/E): the packed gate/up kernel is ahead from r >= 48, and at any r when the
-    # contraction is short (d_model < 4096, where the row-major alternative is the
-    # register-staged kernel); the packed down kernel from r >= 96, or with d_ff < 4096, or from
-    # r >= 56 where its narrow tiles fill the chip (at most 128 tiles of 256 outputs: 8 experts x
-    # 4096 outputs, 65 rows each 156 us against 173 row-major; 16 x 5120, 75 rows 287 against 264).
+    # expert r = T*k/E).  Gate/up, with the gather of its rows: from r >= 48, and at any r for
+    # d_model < 4096 (64 experts x 2048 x 1408, 6 to 24 rows: 118-122 us against 126-130 row-major, 70
+    # rows 147 against 155; few tiles are level or 3 us behind, 8 x 3072 x 1024 34 against 31).  Down:
+    # from r >= 96, or with d_ff < 4096, or from r >= 56 where its narrow tiles fill the chip (at most
+    # 128 tiles of 256 outputs: 8 experts x 4096 outputs, 65 rows each 156 us against 173 row-major;
+    # 16 x 5120, 75 rows 287 against 264).
     PACKED_UP_MIN_ROWS = 48
     PACKED_DOWN_MIN_ROWS = 96
     PACKED_DOWN_MIN_ROWS_FEW_TILES = 56
