@@ -366,14 +366,29 @@ __global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
     typedef EvenPolicy<UpMid::BM, 16> Mid;
     const int NR = (N + UpRing::BN_OUT - 1) / UpRing::BN_OUT;
     const int NM = (N + UpMid::BN_OUT - 1) / UpMid::BN_OUT;
-    int mt[2];
-    count_mtiles<Ring, Mid>(offsets, E, mt);
-    const int ring = tile_rounds(mt[0], NR), mid = 2 * tile_rounds(mt[1], NM);
+    // every count costs a workgroup two divisions per expert and lane: mid is counted where it may win
+    int mt[2] = {0, 0};
+    bool mid = false;
+    if (mid_if_less) {
+        count_mtiles<Ring, Mid>(offsets, E, mt);
+        const int ring_rounds = tile_rounds(mt[0], NR), mid_rounds = 2 * tile_rounds(mt[1], NM);
+        mid = mid_rounds < ring_rounds || (mid_rounds == ring_rounds && mid_if_equal);
+    } else {
+        int ring[1];
+        count_mtiles<Ring>(offsets, E, ring);
+        mt[0] = ring[0];
+    }
     // contractions below 4096: a second round of ring tiles that is at most half full
-    const bool small = K < 4096 && 2ll * __builtin_amdgcn_readfirstlane(mt[0]) * NR <= 3ll * kCus &&
-                       2ll * __builtin_amdgcn_readfirstlane(mt[1]) * NM >= kCus;
+    const long long tiles = (long long)__builtin_amdgcn_readfirstlane(mt[0]) * NR;
+    if (!mid && K < 4096 && tiles > kCus && 2 * tiles <= 3 * kCus) {
+        int one[1];
+        count_mtiles<Mid>(offsets, E, one);
+        mt[1] = one[0];
+        const long long mid_tiles = (long long)__builtin_amdgcn_readfirstlane(mt[1]) * NM;
+        mid = mid_tiles <= kCus && 2 * mid_tiles >= kCus;
+    }
     TileLoc t;
-    if (mid < ring ? mid_if_less : (mid == ring && (mid_if_equal || small))) {
+    if (mid) {
         if (locate<Mid, From::counted>(offsets, E, NM, blockIdx.x, mt[1], t))
             pipe16_tile<UpMid>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk);
     } else if (locate<Ring, From::counted>(offsets, E, NR, blockIdx.x, mt[0], t)) {

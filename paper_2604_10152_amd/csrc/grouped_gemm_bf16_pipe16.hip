@@ -52,17 +52,20 @@ __global__ __launch_bounds__(Wide::THREADS) void grouped_down_bf16_packed_few_ke
     typedef EvenPolicy<DownNarrowTall::BM, 16> High;
     typedef EvenPolicy<Wide::BM, 16> Full;
     const int NT = (N + 127) / 128;
-    int mt[3];
-    count_mtiles<Low, High, Full>(offsets, E, mt);
+    int low[1], mt[2];
+    count_mtiles<Low>(offsets, E, low);
     TileLoc t;
-    if (tile_rounds(mt[0], NT) == 1) {
-        if (locate<Low, From::counted>(offsets, E, NT, blockIdx.x, mt[0], t))
+    if (tile_rounds(low[0], NT) == 1) {
+        if (locate<Low, From::counted>(offsets, E, NT, blockIdx.x, low[0], t))
             pipe16_tile<DownNarrow, true, true>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
-    } else if (tile_rounds(mt[1], NT) == 1) {
-        if (locate<High, From::counted>(offsets, E, NT, blockIdx.x, mt[1], t))
+        return;
+    }
+    count_mtiles<High, Full>(offsets, E, mt);
+    if (tile_rounds(mt[0], NT) == 1) {
+        if (locate<High, From::counted>(offsets, E, NT, blockIdx.x, mt[0], t))
             pipe16_tile<DownNarrowTall, true, true>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
-    } else if (locate<Full, From::counted>(offsets, E, (N + Wide::BN_OUT - 1) / Wide::BN_OUT, blockIdx.x,
-                                    mt[2], t)) {
+    } else if (locate<Full, From::counted>(offsets, E, (N + Wide::BN_OUT - 1) / Wide::BN_OUT,
+                                           blockIdx.x, mt[1], t)) {
         pipe16_tile<Wide, true, true>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
     }
 }
