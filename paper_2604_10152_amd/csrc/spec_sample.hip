@@ -326,11 +326,13 @@ template <typename T>
 static void launch_greedy_typed(const void* logits, int R, int V, int32_t* tokens, hipStream_t s) {
     const bool vec = V % Row<T>::N == 0 && ((uintptr_t)logits & 15u) == 0 &&
                      ((size_t)V * sizeof(T)) % 16 == 0;
-    // Up to 1024 rows (four workgroups per CU) of at least four chunks per thread, one thread's
-    // chunks are requested together: 512 x 32000 bf16 10.9 -> 7.7 us.  More rows keep enough loads in
-    // flight by themselves (2048 x 32000 bf16: 22.3 us = 5.9 TB/s, 23.0 with the burst), and
-    // shorter rows have nothing to request ahead (2048 x 1000: 4.2 us, 5.3 with it).
-    const bool burst = vec && R <= 1024 && V / Row<T>::N >= 256 * kRowBurst;
+    // Few rows (up to 640) of at least four chunks per thread: one thread's chunks are requested
+    // together, 512 x 32000 bf16 10.5 -> 7.2 us, 640 rows 11.0 -> 8.8.  Up to 1024 rows only where they are
+    // long (1024 x 128256 47.4 -> 43.2; 1024 x 32000 12.8 -> 13.0, fp32 21.3 -> 22.1).  More rows keep
+    // enough loads in flight by themselves (2048 x 32000 bf16: 22.3 us = 5.9 TB/s, 23.0 with the burst),
+    // and shorter rows have nothing to request ahead (2048 x 1000: 4.2 us, 5.3 with it).
+    const int per_thread = V / Row<T>::N / 256;
+    const bool burst = vec && per_thread >= kRowBurst && (R <= 640 || (R <= 1024 && per_thread >= 48));
     if (burst)
         hipLaunchKernelGGL((greedy_tokens_kernel<T, true, kRowBurst>), dim3(R), dim3(256), 0, s,
                            (const T*)logits, V, tokens);

@@ -430,6 +430,8 @@ def test_accept_sample_vocabulary_edges(B, gamma, V):
 
 
 @pytest.mark.parametrize("R,V,dtype", [(1024, 8192, torch.bfloat16), (1025, 8192, torch.bfloat16),
+                                       (640, 8192, torch.bfloat16), (641, 8192, torch.bfloat16),
+                                       (642, 49160, torch.float32),
                                        (3, 8200, torch.bfloat16), (2, 4100, torch.float32)])
 def test_greedy_tokens_burst_edges(R, V, dtype):
     """Rows at the edge of the burst rule, and a burst whose last chunks lie beyond the row."""
