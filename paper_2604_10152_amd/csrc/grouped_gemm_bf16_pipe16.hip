@@ -156,9 +156,12 @@ hipError_t launch_expert_down_bf16_packed(const bf16_t* h_packed, const int32_t*
                                           int E, bf16_t* y, hipStream_t s) {
     // Short contractions with up to 12 rows per expert on average: also the 128 x 128 tiles.  Such a
     // batch may activate a few experts only (the draft model: 16 of 64 experts are 128 wide tiles,
-    // 24.0 -> 20.2 us at 2048 x 1408; 4 of 16, 1024 x 2048: 23.4 -> 19.5), which the host does not know,
-    // and with all of them active nothing is lost (64 of 64: 62.6 -> 62.0).  Gate/up gains with few
-    // active experts (4 of 64: 24.6 -> 20.4) and loses with more (16 of 64: 32.4 -> 35.5).
+    // 24.0 -> 20.2 us at 2048 x 1408; 4 of 16, 1024 x 2048: 23.4 -> 19.5), which the host does not know.
+    // With all of them active nothing is lost on even rows (64 of 64: 62.6 -> 62.0), but 8 % on skewed
+    // ones (8 rows each under a Zipf exponent of 1.1: 69 -> 75).  Choosing on the device instead gave
+    // 64.6, 70.5 and, with 16 of 64 active, 21.0: the even batch pays for it, so the host's rule stayed.
+    // Gate/up gains with few active experts (4 of 64: 24.6 -> 20.4) and loses with more (16 of 64: 32.4
+    // -> 35.5).
     const bool maybe_few = f < 4096 && (long long)n_rows <= 12ll * E;
     const WideTiles w(n_rows, E, d, 256);
     if (maybe_few || (w.few() && w.tiles <= 64))
