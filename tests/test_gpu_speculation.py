@@ -349,6 +349,42 @@ def test_affinity_table_close_pairs_and_non_finite_weights():
     assert _gpu_affinity(wg, w2, wd)[2, 3] == np.inf
 
 
+# fp32 rounds a distance by at most 2^-24; the integer products may move it by 2^-27 (standard deviation)
+EXACT_RTOL = 2.0 ** -24 + 4 * 2.0 ** -27
+
+
+@pytest.mark.parametrize("kind", ["normal", "heavy tails", "spikes", "scales", "sparse", "steps", "huge and tiny"])
+@pytest.mark.parametrize("E,d,f", [(9, 520, 561), (16, 264, 601), (17, 376, 401), (33, 264, 288), (49, 256, 200),
+                                   (64, 512, 128)])
+def test_affinity_table_integer_products(E, d, f, kind):
+    """The integer form (from 2.5 million weights per matrix on), one to four row blocks, whole and ragged
+    last units, and values that change the scale of a row again and again."""
+    assert E * d * f >= 2500000
+    _say(f"affinity, integer products E={E} d={d} f={f} {kind}")
+    g = torch.Generator().manual_seed(E + d)
+    W = []
+    for shape in ((E, f, d), (E, f, d), (E, d, f)):
+        w = torch.randn(shape, generator=g) * 0.02
+        if kind == "heavy tails":
+            w = w * torch.exp(2 * torch.randn(shape, generator=g))
+        elif kind == "spikes":
+            w = torch.where(torch.rand(shape, generator=g) < 0.01, w * 3000, w)
+        elif kind == "scales":                     # experts of different magnitude
+            w = w * (10.0 ** torch.linspace(-3, 3, E)).view(-1, 1, 1)
+        elif kind == "sparse":
+            w = w * (torch.rand(shape, generator=g) < 0.03)
+        elif kind == "steps":                      # magnitude changes along the columns
+            w = w * 2.0 ** (torch.arange(w[0].numel()) // 100 % 7 * 4 - 12).view(1, *shape[1:])
+        elif kind == "huge and tiny":              # beyond 2^+-100: through the fp64 instruction
+            w = w * torch.where(torch.rand(shape, generator=g) < 0.5, 1e-34, 1.0)
+            w[:, 0, :2] *= 1e32
+        W.append(w.to(torch.bfloat16))
+    got = _gpu_affinity(*W)
+    want = orc.affinity_table(*(f64(w) for w in W))
+    assert np.all(np.diag(got) == 0) and np.array_equal(got, got.T)
+    np.testing.assert_allclose(got, want, rtol=EXACT_RTOL, atol=0)
+
+
 def _many_close(kind, wg, wu, wd):
     E = wg.shape[0]
     for w in (wg, wu, wd):
