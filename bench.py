@@ -276,7 +276,8 @@ class LayerRun:
         active = int((counts > 0).sum())
         packed_rows = (self.packed is not None and self.cfg.dtype == "bf16" and
                        self.layer.packed_plan(self.T * self.cfg.k, self.cfg.E, self.cfg.d_model,
-                                              self.cfg.d_ff)[0])
+                                              self.cfg.d_ff)[0] and
+                       not self.layer.gathers_packed(self.T * self.cfg.k, self.cfg.E, self.cfg.d_ff))
         work = algorithmic_work(self.cfg, self.T, active, rows_materialised=packed_rows)
         kernels = {}
         for n in KERNELS:

@@ -103,17 +103,6 @@ hipError_t launch_expert_down_bf16_large16(const bf16_t* h, const int32_t* offse
                                                                 d, f, y, s);
 }
 
-// Tile-packed variants: weights packed by moe_pack_weights, h tile-packed between the two
-// projections.  This one gathers the token rows itself from the row-major token matrix (per-lane
-// row addresses, 64-byte requests on the activation side) and always uses 320-row tiles.
-hipError_t launch_expert_up_bf16_packed(const bf16_t* x, const int32_t* offsets,
-                                        const bf16_t* wg_packed, const bf16_t* wu_packed,
-                                        int n_rows, int d, int f, int E, bf16_t* h_packed,
-                                        hipStream_t s, const int32_t* row_src, int topk) {
-    return launch_pipe16<PipeCfg<320, 256, 32, 4, 2, 4, true>, false, true, true>(
-        x, offsets, wg_packed, wu_packed, n_rows, E, f, d, h_packed, s, row_src, topk);
-}
-
 // Tiles of 128 weight rows instead of 256 where a batch has few tiles: a 256-wide tile takes a
 // whole CU (112 or 144 KB of LDS), so up to 128 of them leave half the chip idle.  At most 64 wide
 // tiles, or up to 128 in gate/up while an expert's rows (the average plus 15 % for the spread) fit in 128: 128 x
@@ -149,6 +138,25 @@ hipError_t launch_expert_up_bf16_packed_x(const bf16_t* x_packed, const int32_t*
                                                           n_rows, E, f, d, h, s)
                  : launch_pipe16<Mid, true, true, true>(x_packed, offsets, wg_packed, wu_packed,
                                                         n_rows, E, f, d, h, s);
+}
+
+// Tile-packed variant that gathers the token rows itself from the row-major token matrix (per-lane
+// row addresses, 64-byte requests on the activation side); weights and h tile-packed.
+hipError_t launch_expert_up_bf16_packed(const bf16_t* x, const int32_t* offsets,
+                                        const bf16_t* wg_packed, const bf16_t* wu_packed,
+                                        int n_rows, int d, int f, int E, bf16_t* h_packed,
+                                        hipStream_t s, const int32_t* row_src, int topk) {
+    typedef PipeCfg<320, 256, 32, 4, 2, 4, true> Large;
+    typedef PipeCfg<192, 256, 32, 4, 2, 4, true> Mid;
+    typedef PipeCfg<128, 128, 32, 4, 2, 4, true> Small;
+    if (narrow_tiles(n_rows, E, f, Large::BN_OUT))
+        return launch_pipe16<Small, false, true, true>(x, offsets, wg_packed, wu_packed, n_rows, E, f, d,
+                                                       h_packed, s, row_src, topk);
+    if ((long long)n_rows < 192ll * E)
+        return launch_pipe16<Mid, false, true, true>(x, offsets, wg_packed, wu_packed, n_rows, E, f, d,
+                                                     h_packed, s, row_src, topk);
+    return launch_pipe16<Large, false, true, true>(x, offsets, wg_packed, wu_packed, n_rows, E, f, d,
+                                                   h_packed, s, row_src, topk);
 }
 
 hipError_t launch_expert_down_bf16_packed(const bf16_t* h_packed, const int32_t* offsets,

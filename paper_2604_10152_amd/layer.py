@@ -56,6 +56,22 @@ class MoEVerifyLayer:
         down = up and (n_pairs >= min_rows * E or d_ff < 4096)
         return up, down
 
+    # Packed gate/up: rows gathered by the GEMM itself (64-byte requests, once per 128 outputs), or written
+    # tile-packed first ((T + n_pairs) rows and a launch).  Gathering is ahead up to 2048 outputs at any batch
+    # size (us, packed first / gathered, 64 experts x 2048 x 1408, top-6: 64 tokens 74.5 / 70.7, 320 118 / 110,
+    # 1285 167 / 158; 32 x 512 x 2048, 1600 tokens 62.3 / 60.5) and up to 4096 with few rows per expert (16 x 2048 x
+    # 4096, 50 rows 89.5 / 87.6; 150 rows 130 / 134); wider ones read the rows too often (8 x 4096 x 14336, 256
+    # rows 473 / 493; 16 x 5120 x 8192, 32 rows 451 / 459).
+    GATHER_MAX_FF = 2048
+    GATHER_MAX_FF_FEW_ROWS = 4096
+    GATHER_FEW_ROWS = 64
+
+    @classmethod
+    def gathers_packed(cls, n_pairs, E, d_ff):
+        """Whether the packed gate/up GEMM reads the token rows in place (row-major)."""
+        return d_ff <= cls.GATHER_MAX_FF or (
+            d_ff <= cls.GATHER_MAX_FF_FEW_ROWS and n_pairs <= cls.GATHER_FEW_ROWS * E)
+
     @staticmethod
     def pack_weights(w_gate, w_up, w_down, stream=None):
         """One-time re-layout of the expert weights for the tile-packed kernels (bf16 only):
@@ -73,7 +89,8 @@ class MoEVerifyLayer:
         """Enqueues the layer.  `marks`, if given, is a sequence of six torch events recorded on
         `stream` before the router and after each of the five steps (route, permute, gate/up,
         down, combine): the benchmark's per-kernel times.  On the tile-packed path the permute
-        step includes the gather of the token rows into tile-packed form.
+        step includes the gather of the token rows into tile-packed form, unless the gate/up
+        kernel gathers them (gathers_packed()).
         `draft_remap` ([E] int32 from moe_nearest_draft_expert) switches to the draft model's
         routing: selected experts that are not resident are replaced by their nearest draft
         expert, so only draft experts compute.
@@ -95,21 +112,28 @@ class MoEVerifyLayer:
             marks[1].record(stream)
         B.moe_permute(x, self.topk_idx, self.E, None if self.fuse_gather else self.x_perm,
                       self.expert_offsets, self.row_src, self.row_of, stream)
+        gathered = (down_packed and self.gathers_packed(self.T * self.k, self.E, self.f)
+                    and x.data_ptr() % 16 == 0)
         if up_packed:
-            if self.x_packed is None:
-                self.x_packed = torch.empty(
+            if self.x_packed is None:              # also where this call gathers: x may be another tensor
+                self.x_packed = torch.empty(       # next time, and a captured call must not allocate
                     (B.moe_packed_h_bytes(self.T * self.k, self.d, self.E),), dtype=torch.uint8,
                     device=self.h.device)
             if down_packed and self.h_packed is None:
                 self.h_packed = torch.empty(
                     (B.moe_packed_h_bytes(self.T * self.k, self.f, self.E),), dtype=torch.uint8,
                     device=self.h.device)
+        if up_packed and not gathered:
             # the data movement of the permute step, written once in the GEMM's own layout
             B.moe_permute_rows_packed(x, self.row_src, self.k, self.expert_offsets,
                                       self.T * self.k, self.x_packed, stream)
         if marks is not None:
             marks[2].record(stream)
-        if up_packed:
+        if gathered:
+            B.moe_expert_up_swiglu_gather_packed(x, self.row_src, self.k, self.expert_offsets,
+                                                 packed["w_gate"], packed["w_up"],
+                                                 self.T * self.k, self.h_packed, None, stream)
+        elif up_packed:
             B.moe_expert_up_swiglu_packed(self.x_packed, self.expert_offsets, packed["w_gate"],
                                           packed["w_up"], self.T * self.k,
                                           self.h_packed if down_packed else self.h,

@@ -1015,3 +1015,23 @@ def test_layer_packed_plans(name, cfg, plan):
     want = orc.moe_layer_brute_force(f64(L["x"]), f64(L["w_router"]), LazyF64(L["w_gate"]),
                                      LazyF64(L["w_up"]), LazyF64(L["w_down"]), cfg.k)
     check_float(f64(out), want, cfg.torch_dtype, name)
+
+
+@pytest.mark.parametrize("d,f,E,k,T", [(256, 384, 8, 2, 40), (320, 2048, 70, 3, 33), (128, 2048, 4, 2, 700),
+                                       (128, 2112, 6, 2, 192), (128, 2112, 6, 2, 193), (1024, 1408, 64, 6, 640)])
+def test_layer_gathers_packed(d, f, E, k, T, monkeypatch):
+    """Packed gate/up with the token rows gathered by the GEMM or written tile-packed first: the same
+    bits, on both sides of the rule and on each of its tiles (narrow, 192 and 320 rows)."""
+    _say(f"layer gathers packed d={d} f={f} E={E} k={k} T={T}")
+    cfg = synth.MoEConfig("g", "bf16", d, f, E, k, T, 0, 1 / 16, 0.05, 1.0)
+    L = synth.make_layer(cfg, "cuda", seed=5)
+    rule = sm.MoEVerifyLayer.gathers_packed(T * k, E, f)
+    assert rule == (f <= 2048 or T * k <= 64 * E)
+    outs = []
+    for gathered in (True, False):
+        monkeypatch.setattr(sm.MoEVerifyLayer, "gathers_packed", classmethod(lambda *a, g=gathered: g))
+        _, out = _run_layer(cfg, L, packed=True)
+        outs.append(out.clone())
+    torch.cuda.synchronize()
+    assert torch.isfinite(outs[0].float()).all()
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
