@@ -41,21 +41,16 @@ __global__ __launch_bounds__(256) void gather_pack_rows_kernel(
         const int e = e0 + lane;
         const int lo = e < E ? offsets[e] : 0, hi = e < E ? offsets[e + 1] : 0;
         const int nblk = (hi - lo + 15) / 16;
-        int incl = nblk;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int v = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += v;
-        }
+        const int incl = wave_scan(nblk);
         const unsigned long long hit = __ballot(nblk > 0 && (int)blockIdx.x < base + incl);
         if (hit) {
             const int src = __ffsll((long long)hit) - 1;
-            const int lb =
-                (int)blockIdx.x - (base + __shfl(incl, src, kWave) - __shfl(nblk, src, kWave));
-            row0 = __shfl(lo, src, kWave) + lb * 16;
-            rows = min(16, __shfl(hi, src, kWave) - row0);
+            auto of = [&](int v) { return __builtin_amdgcn_readlane(v, src); };
+            const int lb = (int)blockIdx.x - (base + of(incl) - of(nblk));
+            row0 = of(lo) + lb * 16;
+            rows = min(16, of(hi) - row0);
         }
-        base += __shfl(incl, kWave - 1, kWave);
+        base += __builtin_amdgcn_readlane(incl, kWave - 1);
     }
     if (row0 < 0) return;                         // beyond the last block in use
     const int kblocks = K / pipe::kPackCols;

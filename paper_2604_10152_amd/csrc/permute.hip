@@ -90,12 +90,7 @@ __global__ __launch_bounds__(kSmallWaves * kWave) void permute_index_small_kerne
         for (int w = 0; w < kSmallWaves; ++w) c[w] = cnt[w][lane];
 #pragma unroll
         for (int w = 0; w < kSmallWaves; ++w) total += c[w];
-        int incl = total;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int v = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += v;
-        }
+        const int incl = wave_scan(total);
         int run = incl - total;
         if (lane < E) offsets[lane] = run;
         if (lane == E - 1) offsets[E] = incl;
@@ -172,15 +167,10 @@ __global__ __launch_bounds__(kPermWaves * kWave) void permute_index_kernel(
         int carry = 0;
         for (int e0 = 0; e0 < E; e0 += kWave) {
             int e = e0 + lane;
-            int v = (e < E) ? excl[e] : 0;
-            int inc = v;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                int n = __shfl_up(inc, off, kWave);
-                if (lane >= off) inc += n;
-            }
+            const int v = (e < E) ? excl[e] : 0;
+            const int inc = wave_scan(v);
             if (e < E) { excl[e] = carry + inc - v; offsets[e] = carry + inc - v; }
-            carry += __shfl(inc, kWave - 1, kWave);
+            carry += __builtin_amdgcn_readlane(inc, kWave - 1);
         }
         if (lane == 0) offsets[E] = carry;
     }

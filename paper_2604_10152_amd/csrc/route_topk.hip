@@ -312,8 +312,9 @@ __global__ __launch_bounds__(kMfmaWaves * kWave) void route_topk_mfma_kernel(
     // lane l holds token l / 16, expert column l % 4 of block (l / 4) % 4
 #pragma unroll
     for (int g = 0; g < RT * NG; ++g) {
-        if (KS >= 2) acc[g] += __shfl_xor(acc[g], 8, kWave);
-        if (KS >= 4) acc[g] += __shfl_xor(acc[g], 4, kWave);
+        auto add = [](double u, double v) { return u + v; };
+        if (KS >= 2) acc[g] = lane_pair<8>(acc[g], add);
+        if (KS >= 4) acc[g] = lane_pair<4>(acc[g], add);
         part[wave][g][lane] = acc[g];
     }
     __syncthreads();

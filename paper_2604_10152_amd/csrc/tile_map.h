@@ -33,9 +33,9 @@ template <int BM_MAX, int GRAN>
 __device__ __forceinline__ EvenSplit even_split(int M) {
     EvenSplit s{0, 0};
     if (M <= 0) return s;
-    const int mt0 = (M + BM_MAX - 1) / BM_MAX;
-    s.rpt = ((M + mt0 - 1) / mt0 + GRAN - 1) / GRAN * GRAN;
-    s.mt = (M + s.rpt - 1) / s.rpt;
+    const unsigned m = M, mt0 = (m + BM_MAX - 1) / BM_MAX;
+    s.rpt = (int)(((m + mt0 - 1) / mt0 + GRAN - 1) / GRAN * GRAN);
+    s.mt = (int)((m + s.rpt - 1) / (unsigned)s.rpt);
     return s;
 }
 
@@ -44,7 +44,7 @@ __device__ __forceinline__ EvenSplit even_split(int M) {
 // count comes from a wave scan, and the owning expert is the first lane whose range reaches the
 // tile index.  Every wave of the workgroup calls this with all 64 lanes active and gets the same
 // answer; a scalar walk over the experts costs several microseconds of integer divisions per
-// workgroup, this one memory round trip and ~100 vector instructions.
+// workgroup, this one memory round trip and ~100 vector instructions, exchanges between lanes included.
 template <int BM_MAX, int GRAN>
 struct EvenPolicy {
     __device__ __forceinline__ static EvenSplit of(int M) { return even_split<BM_MAX, GRAN>(M); }
@@ -89,7 +89,7 @@ template <typename Split, From FROM>
 __device__ __forceinline__ bool locate(const int32_t* __restrict__ offsets, int E, int NT,
                                        long long at, int total_mt, TileLoc& t) {
     const int lane = threadIdx.x % kWave;
-    long long L = at;
+    unsigned L = (unsigned)at;                    // a grid has less than 2^32 threads
     if constexpr (FROM != From::place) {
         if constexpr (FROM == From::workgroup) {
             total_mt = 0;
@@ -100,10 +100,10 @@ __device__ __forceinline__ bool locate(const int32_t* __restrict__ offsets, int 
             }
         }
         const unsigned block_id = (unsigned)at;
-        const long long G = (long long)total_mt * NT;
-        const long long per_xcd = (G + kXcds - 1) / kXcds;
-        const long long slot = block_id / kXcds;
-        L = (long long)(block_id % kXcds) * per_xcd + slot;
+        const unsigned G = (unsigned)total_mt * (unsigned)NT;
+        const unsigned per_xcd = (G + kXcds - 1) / kXcds;
+        const unsigned slot = block_id / kXcds;
+        L = block_id % kXcds * per_xcd + slot;
         if (slot >= per_xcd || L >= G) return false;
     }
     int base_mt = 0;                              // m-tiles of the experts before this sweep
@@ -114,32 +114,24 @@ __device__ __forceinline__ bool locate(const int32_t* __restrict__ offsets, int 
         const int lo = e < E ? offsets[e] : 0, hi = e < E ? offsets[e + 1] : 0;
         const EvenSplit sp = Split::of(hi - lo);
         const int nblk = (hi - lo + 15) / 16;
-        int incl = sp.mt, incl_blk = nblk;        // inclusive scans over the lanes
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int v = __shfl_up(incl, off, kWave);
-            const int vb = __shfl_up(incl_blk, off, kWave);
-            if (lane >= off) { incl += v; incl_blk += vb; }
-        }
-        const long long end = (long long)(base_mt + incl) * NT;      // tiles up to and incl. e
+        const int incl = wave_scan(sp.mt), incl_blk = wave_scan(nblk);   // inclusive
+        const unsigned end = (unsigned)(base_mt + incl) * (unsigned)NT;  // tiles up to and incl. e
         const unsigned long long hit = __ballot(sp.mt > 0 && L < end);
         if (hit) {
             const int src = __ffsll((long long)hit) - 1;              // first such expert
-            const int mt = __shfl(sp.mt, src, kWave), rpt = __shfl(sp.rpt, src, kWave);
-            const int excl = __shfl(incl, src, kWave) - mt;
-            const int lo_s = __shfl(lo, src, kWave), hi_s = __shfl(hi, src, kWave);
-            const long long rem = L - (long long)(base_mt + excl) * NT;
-            nt = (int)(rem / mt);
-            const int mi = (int)(rem - (long long)nt * mt);
+            auto of = [&](int v) { return __builtin_amdgcn_readlane(v, src); };
+            const int mt = of(sp.mt), rpt = of(sp.rpt), excl = of(incl) - mt;
+            const unsigned rem = L - (unsigned)(base_mt + excl) * (unsigned)NT;
+            nt = (int)(rem / (unsigned)mt);
+            const int mi = (int)(rem - (unsigned)nt * (unsigned)mt);
             expert = e0 + src;
             mts = mt;
-            row0 = lo_s + mi * rpt;
-            rows = min(rpt, hi_s - row0);
-            blk0 = base_blk + __shfl(incl_blk, src, kWave) - __shfl(nblk, src, kWave) +
-                   mi * rpt / 16;                 // tile heights are multiples of 16
+            row0 = of(lo) + mi * rpt;
+            rows = min(rpt, of(hi) - row0);
+            blk0 = base_blk + of(incl_blk) - of(nblk) + mi * rpt / 16;   // tile heights are multiples of 16
         }
-        base_mt += __shfl(incl, kWave - 1, kWave);
-        base_blk += __shfl(incl_blk, kWave - 1, kWave);
+        base_mt += __builtin_amdgcn_readlane(incl, kWave - 1);
+        base_blk += __builtin_amdgcn_readlane(incl_blk, kWave - 1);
     }
     // the values are the same in every lane; say so to the compiler (scalar registers)
     t.expert = __builtin_amdgcn_readfirstlane(expert);
