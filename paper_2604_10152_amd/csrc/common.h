@@ -73,16 +73,22 @@ __device__ __forceinline__ T lane_pair(T v, F f) {
     }
     return f(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b));
 }
-// the sum over all lanes, in every lane; pairs at distance 32 first
+// f over all lanes, in every lane; pairs at distance 32 first
+template <typename T, typename F>
+__device__ __forceinline__ T wave_all(T v, F f) {
+    v = lane_pair<32>(v, f);
+    v = lane_pair<16>(v, f);
+    v = lane_pair<8>(v, f);
+    v = lane_pair<4>(v, f);
+    v = lane_pair<2>(v, f);
+    return lane_pair<1>(v, f);
+}
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-    auto add = [](T a, T b) { return a + b; };
-    v = lane_pair<32>(v, add);
-    v = lane_pair<16>(v, add);
-    v = lane_pair<8>(v, add);
-    v = lane_pair<4>(v, add);
-    v = lane_pair<2>(v, add);
-    return lane_pair<1>(v, add);
+    return wave_all(v, [](T a, T b) { return a + b; });
+}
+__device__ __forceinline__ double wave_max(double v) {      // of the values that are not NaN
+    return wave_all(v, [](double a, double b) { return fmax(a, b); });
 }
 // inclusive running sum over the lanes
 __device__ __forceinline__ int wave_scan(int v) {

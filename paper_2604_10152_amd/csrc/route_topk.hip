@@ -16,36 +16,28 @@
 // Every value is summed over the same pairs of lanes in the same order, and fp addition is
 // commutative, so two experts with identical router rows get bit-identical logits and the tie
 // goes to the lower id.  The W wave totals are added in fixed order.  Wave t then ranks token
-// t: the E logits sit in LDS, top-k is k rounds of a wave-wide arg-max on the key (logit
-// descending, expert id ascending).
+// t, the E logits sitting in LDS.  It is a chain of latencies: the columns are requested one step ahead,
+// the bias and the substitution at the start, the lanes exchange in registers: 64 experts x 2048, 64 tokens
+// 11.0 -> 8.9 us, 320 tokens 13.4 -> 11.0 (4 of these the fp64 work of one CU, 2.5 the launch).
 #include "common.h"
 
 namespace specmoe {
 namespace {
 
 constexpr int kRouteThreads = 1024;                   // 16 wavefronts: groups of W, which split the experts
+constexpr int kAheadRows = 9;                         // token and router rows a lane can request twice
 
 template <typename T, bool VEC> struct Chunk;
 template <> struct Chunk<float, true> {
     static constexpr int N = 4;
     typedef U128 Raw;
     __device__ static Raw load(const float* p) { return *reinterpret_cast<const U128*>(p); }
-    __device__ static void widen(Raw v, double (&o)[4]) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = (double)__uint_as_float(v[i]);
-    }
+    __device__ static double get(const Raw& v, int i) { return (double)__uint_as_float(v[i]); }
 };
 template <> struct Chunk<bf16_t, true> {
     static constexpr int N = 8;
     typedef U128 Raw;
     __device__ static Raw load(const bf16_t* p) { return *reinterpret_cast<const U128*>(p); }
-    __device__ static void widen(Raw v, double (&o)[8]) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            o[2 * i] = (double)bf16_bits_to_float(v[i] & 0xffffu);
-            o[2 * i + 1] = (double)bf16_bits_to_float(v[i] >> 16);
-        }
-    }
     __device__ static double get(const Raw& v, int i) {
         const uint32_t w = v[i >> 1];
         return (double)__uint_as_float(i & 1 ? w & 0xffff0000u : w << 16);
@@ -55,38 +47,44 @@ template <typename T> struct Chunk<T, false> {          // any d_model, any alig
     static constexpr int N = 1;
     typedef float Raw;
     __device__ static Raw load(const T* p) { return load_as_float(p); }
-    __device__ static void widen(Raw v, double (&o)[1]) { o[0] = (double)v; }
+    __device__ static double get(const Raw& v, int) { return (double)v; }
 };
 
 __device__ __forceinline__ bool better(double av, int aid, double bv, int bid) {
     return (av > bv) || (av == bv && aid < bid);
 }
 
-// Ranks token t by one wave, E <= 64: one expert per lane.  Every lane counts the experts that beat
-// its own on the key (logit descending, id ascending) - its rank, i.e. the slot it would fill.  The
-// other lanes' logits arrive through v_readlane broadcasts (a few cycles each) instead of the
-// k x 6 dependent cross-lane exchanges of arg-max rounds.
+// Ranks token t by one wave, E <= 64: one expert per lane, on the key (logit descending, id
+// ascending).  A round per slot (the largest logit that is left, exchanged in registers) costs about 200
+// cycles.  Up to 3 k experts every lane counts the experts that beat its own instead - its rank, i.e.
+// the slot it would fill -, the other logits arriving through v_readlane broadcasts.  Kernel time, rounds /
+// counting: 64 experts x 2048, top-6 8.9 / 11.2 us, top-16 11.0 / 11.6, 16 experts top-4 5.1 / 5.3, 8 top-2 4.3 / 4.3.
+// id: what an expert is called in the output (the draft mode's substitution).
 __device__ __forceinline__ void rank_token(const double* logit, int lane, int E, int k, int renorm,
                                            int t, int32_t* __restrict__ idx_out,
-                                           float* __restrict__ w_out,
-                                           const int32_t* __restrict__ remap) {
+                                           float* __restrict__ w_out, int id) {
     const bool valid = lane < E;
     const double v = valid ? logit[lane] : 0.0;
-    const int vlo = (int)(uint32_t)__double_as_longlong(v);
-    const int vhi = (int)(uint32_t)((uint64_t)__double_as_longlong(v) >> 32);
     auto lane_value = [&](double val, int src) __attribute__((always_inline)) -> double {
         const long long bits = __double_as_longlong(val);
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, src);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)bits >> 32), src);
         return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
     };
-    int rank = 0;
+    int rank;
+    if (E <= 3 * k) {
+        rank = 0;
 #pragma unroll 8
-    for (int j = 0; j < E; ++j) {
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(vlo, j);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(vhi, j);
-        const double vj = __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-        rank += better(vj, j, v, lane) ? 1 : 0;
+        for (int j = 0; j < E; ++j) rank += better(lane_value(v, j), j, v, lane) ? 1 : 0;
+    } else {
+        rank = k;
+        for (int sl = 0; sl < k; ++sl) {
+            const bool open = valid && rank == k;
+            const double top = wave_max(open ? v : -__builtin_inf());
+            unsigned long long at = __ballot(open && v == top);       // the lowest id of equal logits
+            if (!at) at = __ballot(open);                             // nothing left but NaN
+            if (lane == __ffsll((long long)at) - 1) rank = sl;
+        }
     }
     const int first = __builtin_amdgcn_readfirstlane(
         __ffsll((long long)__ballot(valid && rank == 0)) - 1);
@@ -101,7 +99,7 @@ __device__ __forceinline__ void rank_token(const double* logit, int lane, int E,
         wsum_sel += lane_value(p, src);
     }
     if (valid && rank < k) {
-        idx_out[(size_t)t * k + rank] = remap ? remap[lane] : lane;
+        idx_out[(size_t)t * k + rank] = id;
         w_out[(size_t)t * k + rank] = (float)(renorm ? p / wsum_sel : p);
     }
 }
@@ -119,6 +117,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     typedef Chunk<T, VEC> CH;
     constexpr int V = CH::N;
     constexpr int G = EC < 8 ? EC : 8;                // router rows loaded together
+    // the next columns are requested before the present ones are used, where the registers allow it
+    constexpr bool AHEAD = VEC && EC <= 8 && TOK + EC <= kAheadRows;
     const int lane = threadIdx.x % kWave;
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int group = wave_all / W, wave = wave_all % W;
@@ -126,6 +126,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     double* part = lds_d + (size_t)TOK * E + (size_t)group * W * NV;
     const int t0 = blockIdx.x * TOK;
     const int nq = d / V;                             // chunks per row (VEC: d % V == 0)
+    // what the ranking needs from memory is requested up front
+    const int id = remap && lane < E ? remap[lane] : lane;      // E <= 64
 
     // every group runs the same number of passes (the barriers inside are workgroup-wide); a
     // group whose chunk lies beyond E skips the arithmetic of that pass
@@ -136,29 +138,62 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
         double acc[NV];                               // index t * EC + c
 #pragma unroll
         for (int i = 0; i < NV; ++i) acc[i] = 0.0;
-        for (int q = gtid; live && q < nq; q += kGroupThreads) {
-            typename CH::Raw xr[TOK];
+        const int e_mine = e0 + gtid % EC;
+        const double shift = bias && gtid < NV && e_mine < E ? (double)bias[e_mine] : 0.0;
+        typedef typename CH::Raw Raw;
+        auto load_x = [&](Raw (&xr)[TOK], int q) __attribute__((always_inline)) {
 #pragma unroll
             for (int t = 0; t < TOK; ++t)
                 xr[t] = CH::load(x + (size_t)min(t0 + t, Tn - 1) * d + (size_t)q * V);
-            double xv[TOK][V];
+        };
+        auto load_w = [&](Raw (&w)[G], int c0, int q) __attribute__((always_inline)) {
 #pragma unroll
-            for (int t = 0; t < TOK; ++t) CH::widen(xr[t], xv[t]);
+            for (int c = 0; c < G; ++c)
+                w[c] = CH::load(wr + (size_t)min(e0 + c0 + c, E - 1) * d + (size_t)q * V);
+        };
+        auto add = [&](const Raw (&xr)[TOK], const Raw (&w)[G], int c0) __attribute__((always_inline)) {
 #pragma unroll
-            for (int c0 = 0; c0 < EC; c0 += G) {
-                typename CH::Raw wraw[G];
+            for (int i = 0; i < V; ++i) {
+                double xv[TOK];
 #pragma unroll
-                for (int c = 0; c < G; ++c)
-                    wraw[c] = CH::load(wr + (size_t)min(e0 + c0 + c, E - 1) * d + (size_t)q * V);
+                for (int t = 0; t < TOK; ++t) xv[t] = CH::get(xr[t], i);
 #pragma unroll
                 for (int c = 0; c < G; ++c) {
-                    double wv[V];
-                    CH::widen(wraw[c], wv);
+                    const double wv = CH::get(w[c], i);
 #pragma unroll
                     for (int t = 0; t < TOK; ++t)
+                        acc[t * EC + c0 + c] = fma(xv[t], wv, acc[t * EC + c0 + c]);
+                }
+            }
+        };
+        if constexpr (AHEAD) {
+            Raw xn[TOK], wn[G];
+            if (live) {
+                load_x(xn, min(gtid, nq - 1));
+                load_w(wn, 0, min(gtid, nq - 1));
+            }
+            for (int q = gtid; live && q < nq; q += kGroupThreads) {
+                Raw xr[TOK], w[G];
 #pragma unroll
-                        for (int i = 0; i < V; ++i)
-                            acc[t * EC + c0 + c] = fma(xv[t][i], wv[i], acc[t * EC + c0 + c]);
+                for (int t = 0; t < TOK; ++t) xr[t] = xn[t];
+#pragma unroll
+                for (int c = 0; c < G; ++c) w[c] = wn[c];
+                const int next = q + kGroupThreads;
+                if (next < nq) {
+                    load_x(xn, next);
+                    load_w(wn, 0, next);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                add(xr, w, 0);
+            }
+        } else {
+            for (int q = gtid; live && q < nq; q += kGroupThreads) {
+                Raw xr[TOK], w[G];
+                load_x(xr, q);
+#pragma unroll
+                for (int c0 = 0; c0 < EC; c0 += G) {
+                    load_w(w, c0, q);
+                    add(xr, w, c0);
                 }
             }
         }
@@ -173,7 +208,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
                 double s = part[gtid];
 #pragma unroll
                 for (int w = 1; w < W; ++w) s += part[w * NV + gtid];
-                logits[(size_t)t * E + e0 + c] = s + (bias ? (double)bias[e0 + c] : 0.0);
+                logits[(size_t)t * E + e0 + c] = s + shift;
             }
         }
         __syncthreads();
@@ -184,7 +219,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     const int t = t0 + wave_all;
     const double* logit = logits + (size_t)wave_all * E;
     if (E <= kWave) {
-        rank_token(logit, lane, E, k, renorm, t, idx_out, w_out, remap);
+        rank_token(logit, lane, E, k, renorm, t, idx_out, w_out, id);
         return;
     }
     // More than 64 experts: lane owns experts lane, lane+64, ...; `taken` marks the ones already
@@ -265,6 +300,11 @@ __global__ __launch_bounds__(kMfmaWaves * kWave) void route_topk_mfma_kernel(
 #pragma unroll
     for (int g = 0; g < NG; ++g) wrow[g] = wr + (size_t)min(16 * g + 4 * (b % BE) + i, E - 1) * d;
     const int units = (d + 32 * KS - 1) / (32 * KS);
+    // what the ranking needs from memory is requested up front
+    static_assert(RT * NG <= kMfmaWaves, "a wave adds up one result register");
+    const int id = remap && lane < E ? remap[lane] : lane;
+    const int e_mine = 16 * (wave % NG) + 4 * (b % BE) + i;
+    const double shift = bias && e_mine < E ? (double)bias[e_mine] : 0.0;
 
     U128 xr[PF][RT], wv[PF][NG];
     bool live[PF];
@@ -318,19 +358,16 @@ __global__ __launch_bounds__(kMfmaWaves * kWave) void route_topk_mfma_kernel(
         part[wave][g][lane] = acc[g];
     }
     __syncthreads();
-    for (int rg = wave; rg < RT * NG; rg += kMfmaWaves) {
-        const int e = 16 * (rg % NG) + 4 * (b % BE) + i;
-        if (b < BE && e < E) {
-            double s = part[0][rg][lane];             // waves in order
+    if (wave < RT * NG && b < BE && e_mine < E) {
+        double s = part[0][wave][lane];               // waves in order
 #pragma unroll
-            for (int w = 1; w < kMfmaWaves; ++w) s += part[w][rg][lane];
-            logits[4 * (rg / NG) + q][e] = s + (bias ? (double)bias[e] : 0.0);
-        }
+        for (int w = 1; w < kMfmaWaves; ++w) s += part[w][wave][lane];
+        logits[4 * (wave / NG) + q][e_mine] = s + shift;
     }
     __syncthreads();
     static_assert(4 * RT <= kMfmaWaves, "a wave ranks one token");
     if (wave < 4 * RT && t0 + wave < Tn)
-        rank_token(logits[wave], lane, E, k, renorm, t0 + wave, idx_out, w_out, remap);
+        rank_token(logits[wave], lane, E, k, renorm, t0 + wave, idx_out, w_out, id);
 }
 
 template <int RT>
@@ -360,7 +397,7 @@ void launch_variant(const T* x, const T* wr, const float* bias, int Tn, int d, i
 // Experts per group and pass: the group's share of E rounded up to a power of two, at most 16 / TOK.
 // Up to 16 experts 4 groups of 4 waves, beyond that 8 groups of 2: twice the columns per lane, but
 // half the sums to exchange over the lanes: 64 x 2048, 64 tokens 12.5 -> 11.3 us, 320 tokens 16.0 ->
-// 13.6; 64 x 512 12.1 -> 9.2; 256 x 1024 38.1 -> 27.9.
+// 13.6; 64 x 512 12.1 -> 9.2; 256 x 1024 38.1 -> 27.9 (with the exchanges through LDS).
 template <typename T, bool VEC, int TOK, int W>
 void launch_by_share(const T* x, const T* wr, const float* bias, int Tn, int d, int E, int k,
                      int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
@@ -402,7 +439,7 @@ void launch_typed(const void* x, const void* wr, const float* bias, int Tn, int 
     // below, 4 tokens per workgroup: from 513 tokens (64 x 2048, 640 tokens 22.8 -> 18.2; up to 32
     // experts only with rows up to 2048: 20 x 5120, 1000 tokens 16.6 against 17.2), or 257 if rows are
     // short (64 x 512, 320 tokens 15.2 -> 10.4).  Its workgroups take longer than the vector form's, so
-    // fewer tokens stay there (64 tokens 11.3 against 17.5).
+    // fewer tokens stay there (64 tokens 8.9 against 15).
     if constexpr (sizeof(T) == 2) {
         if (E <= kWave && Tn > 1024) {
             launch_mfma<2>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);

@@ -136,6 +136,21 @@ def test_route_matrix_forms(T, d, E, k, bias):
     _check_route(x, wr, b, k, True)
 
 
+@pytest.mark.parametrize("E,k", [(9, 3), (10, 3), (64, 22), (64, 21), (63, 1), (2, 1)])
+@pytest.mark.parametrize("T", [5, 1030])
+def test_route_ranking_forms(T, E, k):
+    """Counting (up to 3 k experts) and rounds, on both sides of the line and in both forms of the logits,
+    with ties of duplicated rows and experts that a bias of -inf shuts out."""
+    _say(f"route ranking T={T} E={E} k={k}")
+    g = torch.Generator().manual_seed(T + E + k)
+    x = (torch.randn(T, 72, generator=g) / 72 ** 0.5).to(torch.bfloat16)
+    wr = torch.randn(E, 72, generator=g).to(torch.bfloat16)
+    wr[E - 1] = wr[0]
+    b = torch.zeros(E)
+    b[E // 2:E // 2 + max(0, E - k - 1)] = float("-inf")      # k + 1 left, or k with one of them at -inf
+    _check_route(x, wr, b, k, True)
+
+
 def test_route_ties_go_to_lower_expert_id():
     _say("route ties")
     g = torch.Generator().manual_seed(5)
