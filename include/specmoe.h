@@ -191,6 +191,31 @@ int moe_combine(const void* y_perm, const int32_t* row_of, const float* topk_w,
                 const void* residual, int T, int d_model, int k, int dtype, void* out,
                 void* stream);
 
+/* The whole layer in one call: moe_route_topk (moe_route_topk_draft if remap is given), moe_permute
+ * without x_perm, the experts, moe_combine, enqueued in this order with the same results as the calls one
+ * by one.  `layout` says what the experts' weights and the intermediate rows are:
+ *   SPECMOE_ROW_MAJOR     moe_expert_up_swiglu_gather and moe_expert_down (x_packed unused);
+ *   SPECMOE_PACKED_UP     w_gate, w_up packed: moe_permute_rows_packed into x_packed,
+ *                         moe_expert_up_swiglu_packed with row-major h, moe_expert_down;
+ *   SPECMOE_PACKED        all three packed: moe_permute_rows_packed, moe_expert_up_swiglu_packed,
+ *                         moe_expert_down_packed;
+ *   SPECMOE_PACKED_GATHER all three packed: moe_expert_up_swiglu_gather_packed without the packed rows
+ *                         (x_packed unused, x 16-byte aligned), moe_expert_down_packed.
+ * Buffers as in those calls, h_bytes and x_packed_bytes their sizes; T * d_model elements of x less than
+ * 4 GB.  The packed layouts are bf16 only. */
+typedef enum {
+    SPECMOE_ROW_MAJOR = 0,
+    SPECMOE_PACKED_UP = 1,
+    SPECMOE_PACKED = 2,
+    SPECMOE_PACKED_GATHER = 3
+} specmoe_layout;
+int moe_layer_forward(const void* x, const void* w_router, const float* router_bias,
+                      const int32_t* remap, const void* w_gate, const void* w_up, const void* w_down,
+                      const void* residual, int T, int d_model, int d_ff, int E, int k, int renorm,
+                      int dtype, int layout, int32_t* topk_idx, float* topk_w, int32_t* expert_offsets,
+                      int32_t* row_src, int32_t* row_of, void* x_packed, size_t x_packed_bytes, void* h,
+                      size_t h_bytes, void* y_perm, void* out, void* stream);
+
 /* Greedy verification (Sec. 2.2 Fig. 4; Sec. 4: only drafts that exactly match the target's
  * greedy tokens are accepted).  draft_ids [B,gamma]; target_ids [B,gamma+1], target_ids[b,i]
  * being the target's token for the position draft_ids[b,i] was proposed for and

@@ -8,6 +8,6 @@ from .binding import (  # noqa: F401
     moe_grouped_swiglu_workspace_bytes, moe_hot_experts, moe_permute, moe_rmsnorm, moe_route_topk, spec_accept,
     status_string, EXPORTED_SYMBOLS,
     moe_affinity_table, moe_affinity_table_workspace_bytes, moe_nearest_draft_expert,
-    moe_route_topk_draft, spec_accept_sample, spec_greedy_tokens, moe_active_expert_bytes,
+    moe_layer_forward, moe_route_topk_draft, spec_accept_sample, spec_greedy_tokens, moe_active_expert_bytes,
 )
 from .layer import GraphedStep, MoEVerifyLayer, MoEVerifyStack  # noqa: F401

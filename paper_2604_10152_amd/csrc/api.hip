@@ -308,6 +308,67 @@ int moe_combine(const void* y_perm, const int32_t* row_of, const float* topk_w,
                               (hipStream_t)stream));
 }
 
+int moe_layer_forward(const void* x, const void* w_router, const float* router_bias,
+                      const int32_t* remap, const void* w_gate, const void* w_up, const void* w_down,
+                      const void* residual, int T, int d_model, int d_ff, int E, int k, int renorm,
+                      int dtype, int layout, int32_t* topk_idx, float* topk_w, int32_t* expert_offsets,
+                      int32_t* row_src, int32_t* row_of, void* x_packed, size_t x_packed_bytes, void* h,
+                      size_t h_bytes, void* y_perm, void* out, void* stream) {
+    // everything that one of the steps would refuse is refused before the first is enqueued
+    int st = check_expert_shapes(T, d_model, d_ff, E, dtype);
+    if (st != SPECMOE_OK) return st;
+    if (k < 1 || k > E || k > SPECMOE_MAX_TOPK || pairs_overflow(T, k) || layout < SPECMOE_ROW_MAJOR ||
+        layout > SPECMOE_PACKED_GATHER)
+        return SPECMOE_ERR_SHAPE;
+    if (layout != SPECMOE_ROW_MAJOR && dtype != SPECMOE_BF16) return SPECMOE_ERR_DTYPE;
+    if ((unsigned long long)T * (unsigned long long)d_model * esize(dtype) >= (1ull << 32))
+        return SPECMOE_ERR_SHAPE;
+    if (!expert_offsets) return SPECMOE_ERR_NULL;
+    const int P = T * k;
+    const bool rows_packed = layout == SPECMOE_PACKED_UP || layout == SPECMOE_PACKED;
+    const bool h_packed = layout >= SPECMOE_PACKED;
+    if (T > 0) {
+        if (!x || !w_router || !w_gate || !w_up || !w_down || !topk_idx || !topk_w || !row_src || !row_of ||
+            !h || !y_perm || !out || (rows_packed && !x_packed))
+            return SPECMOE_ERR_NULL;
+        const size_t h_need = h_packed ? moe_packed_h_bytes(P, d_ff, E)
+                                       : (size_t)P * (size_t)d_ff * esize(dtype);
+        if (h_bytes < h_need || (layout != SPECMOE_ROW_MAJOR && (((uintptr_t)h | (uintptr_t)x) & 15u) != 0) ||
+            (rows_packed && (x_packed_bytes < moe_packed_h_bytes(P, d_model, E) ||
+                             ((uintptr_t)x_packed & 15u) != 0)))
+            return SPECMOE_ERR_WORKSPACE;
+    }
+    st = remap ? moe_route_topk_draft(x, w_router, router_bias, T, d_model, E, k, renorm, dtype, remap,
+                                      topk_idx, topk_w, stream)
+               : moe_route_topk(x, w_router, router_bias, T, d_model, E, k, renorm, dtype, topk_idx,
+                                topk_w, stream);
+    if (st == SPECMOE_OK)
+        st = moe_permute(x, topk_idx, T, d_model, E, k, dtype, nullptr, expert_offsets, row_src, row_of,
+                         stream);
+    if (st == SPECMOE_OK && rows_packed)
+        st = moe_permute_rows_packed(x, row_src, T, k, expert_offsets, P, d_model, E, dtype, x_packed,
+                                     x_packed_bytes, stream);
+    if (st == SPECMOE_OK) {
+        if (rows_packed)
+            st = moe_expert_up_swiglu_packed(x_packed, x_packed_bytes, expert_offsets, w_gate, w_up, P,
+                                             d_model, d_ff, E, dtype, h, h_bytes, !h_packed, stream);
+        else if (h_packed)
+            st = moe_expert_up_swiglu_gather_packed(x, row_src, T, k, expert_offsets, w_gate, w_up, P,
+                                                    d_model, d_ff, E, dtype, h, h_bytes, nullptr, 0, stream);
+        else
+            st = moe_expert_up_swiglu_gather(x, row_src, T, k, expert_offsets, w_gate, w_up, P, d_model,
+                                             d_ff, E, dtype, h, stream);
+    }
+    if (st == SPECMOE_OK)
+        st = h_packed ? moe_expert_down_packed(h, expert_offsets, w_down, P, d_model, d_ff, E, dtype, y_perm,
+                                               stream)
+                      : moe_expert_down(h, expert_offsets, w_down, P, d_model, d_ff, E, dtype, y_perm,
+                                        stream);
+    if (st == SPECMOE_OK)
+        st = moe_combine(y_perm, row_of, topk_w, residual, T, d_model, k, dtype, out, stream);
+    return st;
+}
+
 int spec_accept(const int32_t* draft_ids, const int32_t* target_ids, int B, int gamma,
                 int32_t* accept_len, int32_t* out_tokens, void* stream) {
     if (B < 0 || gamma < 0 || (long long)B * (gamma + 1ll) > INT_MAX) return SPECMOE_ERR_SHAPE;

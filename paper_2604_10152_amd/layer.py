@@ -1,4 +1,4 @@
-"""Buffers of one MoE verify layer plus the five library calls in order.  No arithmetic here:
+"""Buffers of one MoE verify layer plus the library call of its five steps.  No arithmetic here:
 the class only owns the output / scratch tensors (allocated once) and marshals arguments."""
 from __future__ import annotations
 
@@ -100,6 +100,30 @@ class MoEVerifyLayer:
         up_packed = down_packed = False
         if packed is not None and self.dtype == torch.bfloat16 and self.fuse_gather:
             up_packed, down_packed = self.packed_plan(self.T * self.k, self.E, self.d, self.f)
+        gathered = (down_packed and self.gathers_packed(self.T * self.k, self.E, self.f)
+                    and x.data_ptr() % 16 == 0)
+        if up_packed:
+            if self.x_packed is None:              # also where this call gathers: x may be another tensor
+                self.x_packed = torch.empty(       # next time, and a captured call must not allocate
+                    (B.moe_packed_h_bytes(self.T * self.k, self.d, self.E),), dtype=torch.uint8,
+                    device=self.h.device)
+            if down_packed and self.h_packed is None:
+                self.h_packed = torch.empty(
+                    (B.moe_packed_h_bytes(self.T * self.k, self.f, self.E),), dtype=torch.uint8,
+                    device=self.h.device)
+        gate = packed["w_gate"] if up_packed else w_gate
+        if (marks is None and self.fuse_gather and x.dtype == self.dtype
+                and x.shape == (self.T, self.d) and gate.shape == (self.E, self.f, self.d)
+                and w_router.shape[0] == self.E):
+            layout = (B.ROW_MAJOR if not up_packed else B.PACKED_GATHER if gathered else
+                      B.PACKED if down_packed else B.PACKED_UP)
+            B.moe_layer_forward(
+                x, w_router, bias, draft_remap, gate, packed["w_up"] if up_packed else w_up,
+                packed["w_down"] if down_packed else w_down,
+                residual, self.k, self.renorm, layout, self.topk_idx, self.topk_w, self.expert_offsets,
+                self.row_src, self.row_of, self.x_packed, self.h_packed if down_packed else self.h,
+                self.y_perm, out, stream)
+            return out
         if marks is not None:
             marks[0].record(stream)
         if draft_remap is None:
@@ -112,17 +136,6 @@ class MoEVerifyLayer:
             marks[1].record(stream)
         B.moe_permute(x, self.topk_idx, self.E, None if self.fuse_gather else self.x_perm,
                       self.expert_offsets, self.row_src, self.row_of, stream)
-        gathered = (down_packed and self.gathers_packed(self.T * self.k, self.E, self.f)
-                    and x.data_ptr() % 16 == 0)
-        if up_packed:
-            if self.x_packed is None:              # also where this call gathers: x may be another tensor
-                self.x_packed = torch.empty(       # next time, and a captured call must not allocate
-                    (B.moe_packed_h_bytes(self.T * self.k, self.d, self.E),), dtype=torch.uint8,
-                    device=self.h.device)
-            if down_packed and self.h_packed is None:
-                self.h_packed = torch.empty(
-                    (B.moe_packed_h_bytes(self.T * self.k, self.f, self.E),), dtype=torch.uint8,
-                    device=self.h.device)
         if up_packed and not gathered:
             # the data movement of the permute step, written once in the GEMM's own layout
             B.moe_permute_rows_packed(x, self.row_src, self.k, self.expert_offsets,

@@ -1050,3 +1050,29 @@ def test_layer_gathers_packed(d, f, E, k, T, monkeypatch):
     torch.cuda.synchronize()
     assert torch.isfinite(outs[0].float()).all()
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+@pytest.mark.parametrize("dtype,d,f,E,k,T,draft", [
+    ("f32", 33, 50, 5, 2, 9, True), ("bf16", 4096, 128, 4, 2, 30, False),          # row-major
+    ("bf16", 256, 4096, 4, 2, 100, True),                                          # packed gate/up
+    ("bf16", 64, 4096, 3, 1, 290, False), ("bf16", 256, 384, 8, 2, 40, True)])     # packed; packed, gathered
+def test_layer_call_equals_its_steps(dtype, d, f, E, k, T, draft):
+    """moe_layer_forward against the calls one by one (the path with marks): identical bits."""
+    _say(f"layer call {dtype} d={d} f={f} E={E} k={k} T={T}")
+    cfg = synth.MoEConfig("c", dtype, d, f, E, k, T, 0, 1 / 16, 0.05, 1.0)
+    L = synth.make_layer(cfg, "cuda", seed=8)
+    layer = sm.MoEVerifyLayer(T, d, f, E, k, cfg.torch_dtype)
+    packed = (sm.MoEVerifyLayer.pack_weights(L["w_gate"], L["w_up"], L["w_down"])
+              if dtype == "bf16" else None)
+    remap = torch.arange(E, dtype=I32, device="cuda").flip(0).contiguous() if draft else None
+    residual = torch.randn(T, d, device="cuda").to(cfg.torch_dtype)
+    seen = []
+    for marks in (None, [torch.cuda.Event() for _ in range(6)]):
+        for t in (layer.topk_idx, layer.topk_w, layer.expert_offsets, layer.row_of, layer.out):
+            t.fill_(-1)
+        out = layer.forward(L["x"], L["w_router"], L["w_gate"], L["w_up"], L["w_down"], L["bias"],
+                            residual=residual, draft_remap=remap, packed=packed, marks=marks)
+        torch.cuda.synchronize()
+        seen.append([t.clone() for t in (out, layer.topk_idx, layer.topk_w, layer.expert_offsets, layer.row_of)])
+    assert all(torch.equal(a, b) for a, b in zip(*seen))
+    assert torch.isfinite(seen[0][0].float()).all()

@@ -211,3 +211,19 @@ def test_binding_refuses_cpu_tensors():
     with pytest.raises(TypeError):
         sm.moe_route_topk(x, torch.zeros(2, 8), None, 1, True, torch.zeros(4, 1, dtype=torch.int32),
                           torch.zeros(4, 1), stream=object())
+
+
+def test_layer_forward_validation(lib):
+    f = lib.moe_layer_forward
+
+    def call(T=8, d=64, ff=64, E=4, k=2, dtype=1, layout=0, x=P, h=P, hb=1 << 20, xp=P, xb=1 << 20, off=P, out=P):
+        return f(x, P, N, N, P, P, P, N, T, d, ff, E, k, 1, dtype, layout, P, P, off, P, P, xp, xb, h, hb, P,
+                 out, N)
+
+    assert call(dtype=7) == 3 and call(dtype=0, layout=2) == 3               # dtype; packed layouts are bf16
+    assert call(d=60) == 2 and call(k=5) == 2 and call(layout=4) == 2 and call(T=-1) == 2
+    assert call(T=1 << 25, d=64, k=1) == 2                                   # x of 4 GB
+    assert call(x=N) == 1 and call(out=N) == 1 and call(off=N) == 1 and call(layout=2, xp=N) == 1
+    assert call(hb=8 * 2 * 64 * 2 - 1) == 4 and call(layout=3, hb=(1 + 4) * 16 * 64 * 2 - 1) == 4
+    assert call(layout=2, xb=(1 + 4) * 16 * 64 * 2 - 1) == 4
+    assert call(layout=3, x=ctypes.c_void_p(0x1008)) == 4                    # the GEMM gathers 16-byte pieces
