@@ -331,7 +331,7 @@ typedef PipeCfg<192, 128, 64, 4, 2, 4, false> DownTall;
 
 __global__ __launch_bounds__(DownTall::THREADS) void grouped_down_bf16_mid_kernel(
     const bf16_t* __restrict__ h, const int32_t* __restrict__ offsets,
-    const bf16_t* __restrict__ wd, int E, int N, int K, bf16_t* __restrict__ y) {
+    const bf16_t* __restrict__ wd, int E, int N, int K, bf16_t* __restrict__ y, int group) {
     static_assert(DownTall::THREADS == DownMid::THREADS && DownTall::BN_OUT == DownMid::BN_OUT,
                   "one launch serves both");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
@@ -342,9 +342,9 @@ __global__ __launch_bounds__(DownTall::THREADS) void grouped_down_bf16_mid_kerne
     count_mtiles<Mid, Tall>(offsets, E, mt);
     TileLoc t;
     if (tile_rounds(mt[1], NT) < tile_rounds(mt[0], NT)) {
-        if (locate<Tall, From::counted>(offsets, E, NT, blockIdx.x, mt[1], t))
+        if (locate<Tall, From::counted>(offsets, E, NT, blockIdx.x, mt[1], t, group))
             pipe_tile<DownTall>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
-    } else if (locate<Mid, From::counted>(offsets, E, NT, blockIdx.x, mt[0], t)) {
+    } else if (locate<Mid, From::counted>(offsets, E, NT, blockIdx.x, mt[0], t, group)) {
         pipe_tile<DownMid>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
     }
 }
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets,
     const bf16_t* __restrict__ wg, const bf16_t* __restrict__ wu, int E, int N, int K,
     bf16_t* __restrict__ h, const int32_t* __restrict__ row_src, int topk, int mid_if_less,
-    int mid_if_equal) {
+    int mid_if_equal, int group) {
     static_assert(UpRing::THREADS == UpMid::THREADS && UpRing::LDS_BYTES >= UpMid::LDS_BYTES,
                   "one launch serves both");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
@@ -389,9 +389,9 @@ __global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
     }
     TileLoc t;
     if (mid) {
-        if (locate<Mid, From::counted>(offsets, E, NM, blockIdx.x, mt[1], t))
+        if (locate<Mid, From::counted>(offsets, E, NM, blockIdx.x, mt[1], t, group))
             pipe16_tile<UpMid>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk);
-    } else if (locate<Ring, From::counted>(offsets, E, NR, blockIdx.x, mt[0], t)) {
+    } else if (locate<Ring, From::counted>(offsets, E, NR, blockIdx.x, mt[0], t, group)) {
         pipe_tile<UpRing>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk);
     }
 }
@@ -411,6 +411,10 @@ __global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
 // At equal rounds mid is ahead only for long contractions from about 88 rows on (5120 x 8192, 16
 // experts: 92 rows 550 / 530, 110 rows 575 / 546; 52 rows 490 / 502), and where a short one leaves the
 // ring's second round at most half full (2048 x 1408, 16 of 64 experts active, 40 rows each: 43 / 33).
+// From 48 rows on the tile order goes by groups of n-tiles (tile_map.h) from 48 ring tiles per expert: expert-major / in groups of 8 (4
+// below 96), us: 16 x 5120 x 8192, 62 rows under a Zipf exponent of 0.5 600 / 555, 128 rows 688 / 650, 88 even rows
+// 575 / 561; 8 x 4096 x 14336, 83 rows 395 / 365; 32 x 2048 x 4096, 100 rows 258 / 243; 20 x 4096 x 3072, 150 rows, 1.1 290 /
+// 271.  With fewer it loses as often: 64 x 2048 x 1408, 94 rows 193 / 198.
 // Below 60 rows per expert a mid tile of a hot expert outlasts the round it saves (4096 x 8192, 8 experts,
 // 52 rows, exponent 1.1: 201 / 254).
 hipError_t launch_expert_up_bf16_ring_or_mid(const bf16_t* x_perm, const int32_t* offsets,
@@ -425,10 +429,11 @@ hipError_t launch_expert_up_bf16_ring_or_mid(const bf16_t* x_perm, const int32_t
     const int mid_if_less = (long long)n_rows >= 60ll * E;
     const int mid_if_equal = d >= 4096 && (long long)n_rows >= 88ll * E;
     const long long NR = (f + UpRing::BN_OUT - 1) / UpRing::BN_OUT;
+    const int group = (long long)n_rows < 48ll * E ? 0 : NR >= 96 ? 8 : NR >= 48 ? 4 : 0;
     const long long grid = grid_upper_bound(n_rows, E, UpRing::BM, NR);
     hipLaunchKernelGGL(grouped_up_bf16_kernel, dim3((unsigned)grid), dim3(UpRing::THREADS),
                        UpRing::LDS_BYTES, s, x_perm, offsets, wg, wu, E, f, d, h, row_src, topk,
-                       mid_if_less, mid_if_equal);
+                       mid_if_less, mid_if_equal, group);
     return hipGetLastError();
 }
 
@@ -458,6 +463,11 @@ hipError_t launch_expert_down_bf16_small(const bf16_t* h, const int32_t* offsets
 // its rows are spread, which only the device knows.  Measured, us, 128 / 192 rows (rounds): 12 experts x
 // 2048 x 3072, 130 rows each 59 (2) / 44 (1); 4096 x 14336, 8 experts, 120 rows 301 (2) / 198 (1), two
 // active with 440 rows each 112 (1) / 128 (1), under a Zipf exponent of 1.1 253 (2) / 296 (2).
+// Tile order by groups of four n-tiles (tile_map.h), us, expert-major / in groups: 64 x 1408 x 2048, 120 rows under an
+// exponent of 1.1 125 / 116, even 108 / 105; 16 x 8192 x 5120, 128 rows 343 / 327, 88 even rows 284 / 269; 20 x 3072 x
+// 4096, 150 rows 172 / 145; 8 x 14336 x 4096, 83 rows 204 / 203.
+constexpr int kDownGroup = 4;
+
 hipError_t launch_expert_down_bf16_mid(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
                                        int n_rows, int d, int f, int E, bf16_t* y,
                                        hipStream_t s) {
@@ -469,7 +479,7 @@ hipError_t launch_expert_down_bf16_mid(const bf16_t* h, const int32_t* offsets, 
     const long long NT = (d + DownMid::BN_OUT - 1) / DownMid::BN_OUT;
     const long long grid = grid_upper_bound(n_rows, E, DownMid::BM, NT);
     hipLaunchKernelGGL(grouped_down_bf16_mid_kernel, dim3((unsigned)grid), dim3(DownTall::THREADS),
-                       DownTall::LDS_BYTES, s, h, offsets, wd, E, d, f, y);
+                       DownTall::LDS_BYTES, s, h, offsets, wd, E, d, f, y, kDownGroup);
     return hipGetLastError();
 }
 

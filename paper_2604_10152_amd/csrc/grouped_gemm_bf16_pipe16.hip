@@ -6,32 +6,75 @@ namespace {
 
 using namespace pipe;
 
-template <typename C, bool PA = false, bool PB = false, bool PO = false>
+// 256-wide tiles on tile-packed weights: the last round may be shared out in halves (tile_map.h)
+template <typename C, bool PB, bool PO>
+constexpr bool kHalves = C::BN == 256 && PB && (PO || !C::SWIGLU);
+
+template <typename C, bool PA, bool PB, bool PO, bool SHARE>
 __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe16_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets,
     const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int E, int N, int K,
-    bf16_t* __restrict__ Cout, const int32_t* __restrict__ row_src, int topk) {
+    bf16_t* __restrict__ Cout, const int32_t* __restrict__ row_src, int topk, int group) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
     TileLoc t;
-    if (locate_tile_even<C::BM, 16>(offsets, E, (N + C::BN_OUT - 1) / C::BN_OUT, blockIdx.x, t))
-        pipe16_tile<C, PA, PB, PO>(lds_raw, t, A, W0, W1, N, K, Cout, row_src, topk);
+    const bool halves = kHalves<C, PB, PO> && K >= kTailMinK;
+    if (!locate_tile_even<C::BM, 16, SHARE>(offsets, E, (N + C::BN_OUT - 1) / C::BN_OUT, blockIdx.x, t,
+                                            group, halves))
+        return;
+    if constexpr (SHARE && kHalves<C, PB, PO>) {
+        if (t.half >= 0) {
+            typedef PipeCfg<C::BM, C::BN / 2, C::BK, C::STAGES, C::WM, C::WN, C::SWIGLU> Half;
+            t.nt = 2 * t.nt + t.half;
+            if (t.nt * Half::BN_OUT < N)
+                pipe16_tile<Half, PA, PB, PO>(lds_raw, t, A, W0, W1, N, K, Cout, row_src, topk);
+            return;
+        }
+    }
+    pipe16_tile<C, PA, PB, PO>(lds_raw, t, A, W0, W1, N, K, Cout, row_src, topk);
 }
 
+// n-tiles per group of the tile order (tile_map.h) for gate/up batches spread unevenly over the experts.  Measured,
+// packed operands, us, expert-major / in groups: 16 x 5120 x 8192, 128 rows per expert on average 578 / 523, 62
+// rows 540 / 480; 8 x 4096 x 14336, 375 rows under a Zipf exponent of 1.1 710 / 617, 86 rows, 0.5 434 / 427.  With
+// fewer rows or n-tiles it loses as often (64 x 2048 x 1408: 30 rows 108 / 113, 192 rows 209 / 197 to 208 / 217,
+// by which die gets which expert), and so it does in the down projection (16 x 8192 x 5120 297 / 288 to 317).
+template <typename C>
+int tile_group(int n_rows, int E, int N) {
+    return C::SWIGLU && N >= 24 * C::BN_OUT && (long long)n_rows >= 60ll * E ? 8 : 0;
+}
+
+template <typename C, bool PA, bool PB, bool PO, bool SHARE>
+hipError_t launch_pipe16_form(const bf16_t* A, const int32_t* offsets, const bf16_t* W0,
+                              const bf16_t* W1, int n_rows, int E, int N, int K, bf16_t* Cout,
+                              hipStream_t s, const int32_t* row_src, int topk, int group) {
+    // one-time, thread-safe (C++11 static initialisation): raise the dynamic LDS limit
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&grouped_gemm_bf16_pipe16_kernel<C, PA, PB, PO, SHARE>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES);
+    if (attr != hipSuccess) return attr;
+    const long long NT = (N + C::BN_OUT - 1) / C::BN_OUT;
+    const long long grid = grid_upper_bound(n_rows, E, C::BM, NT) +
+                           (kHalves<C, PB, PO> && K >= kTailMinK ? kTailBlocks : 0);
+    hipLaunchKernelGGL((grouped_gemm_bf16_pipe16_kernel<C, PA, PB, PO, SHARE>), dim3((unsigned)grid),
+                       dim3(C::THREADS), C::LDS_BYTES, s, A, offsets, W0, W1, E, N, K, Cout,
+                       row_src, topk, group);
+    return hipGetLastError();
+}
+
+// SHARE: the tile order in groups and the halved last round (tile_map.h).  A form of its own, since working out a
+// tile takes 0.3 us longer with them: 64 x 2048 x 1408, 6 rows each, a layer of 83.6 us 84.3.
 template <typename C, bool PA = false, bool PB = false, bool PO = false>
 hipError_t launch_pipe16(const bf16_t* A, const int32_t* offsets, const bf16_t* W0,
                          const bf16_t* W1, int n_rows, int E, int N, int K, bf16_t* Cout,
                          hipStream_t s, const int32_t* row_src = nullptr, int topk = 1) {
-    // one-time, thread-safe (C++11 static initialisation): raise the dynamic LDS limit
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&grouped_gemm_bf16_pipe16_kernel<C, PA, PB, PO>),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS_BYTES);
-    if (attr != hipSuccess) return attr;
-    const long long NT = (N + C::BN_OUT - 1) / C::BN_OUT;
-    const long long grid = grid_upper_bound(n_rows, E, C::BM, NT);
-    hipLaunchKernelGGL((grouped_gemm_bf16_pipe16_kernel<C, PA, PB, PO>), dim3((unsigned)grid),
-                       dim3(C::THREADS), C::LDS_BYTES, s, A, offsets, W0, W1, E, N, K, Cout,
-                       row_src, topk);
-    return hipGetLastError();
+    if constexpr (C::BN == 256) {
+        const int group = tile_group<C>(n_rows, E, N);
+        if (group > 0 || (kHalves<C, PB, PO> && K >= kTailMinK))
+            return launch_pipe16_form<C, PA, PB, PO, true>(A, offsets, W0, W1, n_rows, E, N, K, Cout, s,
+                                                           row_src, topk, group);
+    }
+    return launch_pipe16_form<C, PA, PB, PO, false>(A, offsets, W0, W1, n_rows, E, N, K, Cout, s,
+                                                    row_src, topk, 0);
 }
 
 // Down projection on packed operands where 256-wide tiles would leave part of the chip idle: the

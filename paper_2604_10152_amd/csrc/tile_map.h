@@ -19,6 +19,7 @@ struct TileLoc {
     int nt;          // n-tile index
     int blk0;        // 16-row blocks in front of the tile when every expert's rows are padded to
                      // a whole number of blocks (row numbering of the tile-packed matrices)
+    int half;        // -1, or the half of the tile's outputs that the workgroup takes
     int mt;          // m-tiles of the tile's expert (1: its weight tiles are read by one workgroup)
 };
 
@@ -82,29 +83,73 @@ __device__ __forceinline__ int tile_rounds(int total_mt, int NT) {
 
 enum class From { workgroup, counted, place };
 
+// A die's last round is shared out in half tiles (`halves`) where whole ones would keep at most half of its CUs
+// busy: a batch of 3.5 rounds takes 3.5 rounds' time and not 4.  More halves than that would start a
+// second round of them.  Measured, packed operands, us, whole / half: gate/up 8 x 4096 x 14336 (896 tiles): 83 rows
+// each 372 / 364, 150 rows 397 / 383, 250 rows 457 / 442; down 16 x 8192 x 5120 (320 tiles), 88 rows 276 / 260.
+// Halving every unfinished round: the same where it is under half full, 64 x 2048 x 1408 109 -> 123.  For
+// contractions from kTailMinK on: below (64 x 2048 x 1408, 94 rows 145.7 / 146.5) the surplus workgroups cost as much.
+constexpr int kCusPerXcd = kCus / kXcds;
+constexpr int kTailBlocks = kXcds * (kCusPerXcd / 2);       // more workgroups than tiles, at most
+constexpr int kTailMinK = 4096;
+
+// Groups of n-tiles (`group` > 0): the logical order is n-tile group, expert, n-tile, m-tile.  A die then
+// meets every expert; expert-major, the dies that get cold experts read several times the weights that
+// those of a hot expert do, and the launch waits for them.  From::workgroup drops it where every active
+// expert has equally many m-tiles: the dies are even already (and 83 rows each, 8 x 4096 x 14336, 361 -> 363).
+// The launchers state the sizes and figures.
+//
 // The tile of workgroup `at` (From::counted: of total_mt m-tiles), or at place `at` of the logical
 // order (expert, n-tile, m-tile).  One function: with the second half in one of its own the compiler
 // lays the packed GEMM kernels out differently, 1 to 4 % slower on batches of few tiles.
-template <typename Split, From FROM>
+template <typename Split, From FROM, bool SHARE = false>
 __device__ __forceinline__ bool locate(const int32_t* __restrict__ offsets, int E, int NT,
-                                       long long at, int total_mt, TileLoc& t) {
+                                       long long at, int total_mt, TileLoc& t, int group = 0,
+                                       bool halves = false) {
+    constexpr bool GROUPS = SHARE || FROM == From::counted;
     const int lane = threadIdx.x % kWave;
     unsigned L = (unsigned)at;                    // a grid has less than 2^32 threads
+    int nt0 = 0, ntn = NT, half = -1;             // n-tiles of the tile's group: the first, how many
     if constexpr (FROM != From::place) {
         if constexpr (FROM == From::workgroup) {
             total_mt = 0;
+            int first_mt = 0;                     // m-tiles of the first expert that has any
+            bool even = true;
             for (int e0 = 0; e0 < E; e0 += kWave) {
                 const int e = e0 + lane;
                 const int M = e < E ? offsets[e + 1] - offsets[e] : 0;
-                total_mt += wave_sum(Split::of(M).mt);
+                const int mt = Split::of(M).mt;
+                total_mt += wave_sum(mt);
+                if (SHARE && group > 0) {
+                    const unsigned long long has = __ballot(mt > 0);
+                    if (first_mt == 0 && has)
+                        first_mt = __builtin_amdgcn_readlane(mt, __ffsll((long long)has) - 1);
+                    even = even && __ballot(mt > 0 && mt != first_mt) == 0;
+                }
             }
+            if (even) group = 0;
         }
         const unsigned block_id = (unsigned)at;
         const unsigned G = (unsigned)total_mt * (unsigned)NT;
         const unsigned per_xcd = (G + kXcds - 1) / kXcds;
-        const unsigned slot = block_id / kXcds;
-        L = block_id % kXcds * per_xcd + slot;
-        if (slot >= per_xcd || L >= G) return false;
+        const unsigned first = block_id % kXcds * per_xcd;
+        unsigned slot = block_id / kXcds;
+        const unsigned n = first < G ? min(per_xcd, G - first) : 0u;      // the die's tiles
+        if (SHARE && halves) {
+            const unsigned rem = n % kCusPerXcd, whole = n - rem;
+            if (slot >= whole && rem <= kCusPerXcd / 2) {
+                half = (int)((slot - whole) & 1u);
+                slot = whole + (slot - whole) / 2;
+            }
+        }
+        L = first + slot;
+        if (slot >= n) return false;
+        if (GROUPS && group > 0) {
+            const unsigned per_group = (unsigned)total_mt * (unsigned)group, q = L / per_group;
+            L -= q * per_group;
+            nt0 = (int)q * group;
+            ntn = min(group, NT - nt0);
+        }
     }
     int base_mt = 0;                              // m-tiles of the experts before this sweep
     int base_blk = 0;                             // 16-row blocks of the experts before this sweep
@@ -115,15 +160,16 @@ __device__ __forceinline__ bool locate(const int32_t* __restrict__ offsets, int 
         const EvenSplit sp = Split::of(hi - lo);
         const int nblk = (hi - lo + 15) / 16;
         const int incl = wave_scan(sp.mt), incl_blk = wave_scan(nblk);   // inclusive
-        const unsigned end = (unsigned)(base_mt + incl) * (unsigned)NT;  // tiles up to and incl. e
+        const unsigned end = (unsigned)(base_mt + incl) * (unsigned)ntn; // tiles up to and incl. e
         const unsigned long long hit = __ballot(sp.mt > 0 && L < end);
         if (hit) {
             const int src = __ffsll((long long)hit) - 1;              // first such expert
             auto of = [&](int v) { return __builtin_amdgcn_readlane(v, src); };
             const int mt = of(sp.mt), rpt = of(sp.rpt), excl = of(incl) - mt;
-            const unsigned rem = L - (unsigned)(base_mt + excl) * (unsigned)NT;
-            nt = (int)(rem / (unsigned)mt);
-            const int mi = (int)(rem - (unsigned)nt * (unsigned)mt);
+            const unsigned rem = L - (unsigned)(base_mt + excl) * (unsigned)ntn;
+            const unsigned j = rem / (unsigned)mt;
+            nt = nt0 + (int)j;
+            const int mi = (int)(rem - j * (unsigned)mt);
             expert = e0 + src;
             mts = mt;
             row0 = of(lo) + mi * rpt;
@@ -139,14 +185,17 @@ __device__ __forceinline__ bool locate(const int32_t* __restrict__ offsets, int 
     t.tile_rows = __builtin_amdgcn_readfirstlane(rows);
     t.nt = __builtin_amdgcn_readfirstlane(nt);
     t.blk0 = __builtin_amdgcn_readfirstlane(blk0);
+    t.half = __builtin_amdgcn_readfirstlane(half);
     t.mt = __builtin_amdgcn_readfirstlane(mts);
     return t.expert >= 0;
 }
 
-template <int BM_MAX, int GRAN = 32>
+template <int BM_MAX, int GRAN = 32, bool SHARE = false>
 __device__ __forceinline__ bool locate_tile_even(const int32_t* __restrict__ offsets, int E,
-                                                 int NT, unsigned block_id, TileLoc& t) {
-    return locate<EvenPolicy<BM_MAX, GRAN>, From::workgroup>(offsets, E, NT, block_id, 0, t);
+                                                 int NT, unsigned block_id, TileLoc& t,
+                                                 int group = 0, bool halves = false) {
+    return locate<EvenPolicy<BM_MAX, GRAN>, From::workgroup, SHARE>(offsets, E, NT, block_id, 0, t,
+                                                                    group, halves);
 }
 template <int BM>
 __device__ __forceinline__ bool locate_tile(const int32_t* __restrict__ offsets, int E, int NT,

@@ -991,6 +991,46 @@ def test_packed_expert_gemms(d, f, rows):
         assert torch.equal(y.cpu().view(torch.int16), y2.view(torch.int16))
 
 
+@pytest.mark.parametrize("d,f,rows", [
+    # contractions from 4096 on, a last round of 3 tiles per die in halves (the last n-tile has one half): 320
+    # rows (13 m-tiles x 41 and x 21) and 192 rows (the same)
+    (5184, 5184, [640, 700, 330, 1, 0, 900, 321]),
+    (5184, 5184, [192, 400, 193, 17, 100, 65, 300]),
+    # gate/up order in groups of n-tiles, a last group of one; experts on both sides of the 64-expert sweep
+    (256, 3136, [700, 0, 16] + [40] * 60 + [900, 1, 650]),
+    (128, 3072, [0, 193, 60, 192, 1]),
+    (128, 3072, [64, 64, 190]),                      # one m-tile each: expert-major
+])
+def test_packed_tile_order(d, f, rows):
+    """Every tile of the packed GEMMs is computed once and in its place, against fp32 products."""
+    _say(f"packed tile order d={d} f={f} rows={rows}")
+    E, n = len(rows), sum(rows)
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(d + f + n)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    xp = (rnd(n, d) / d ** 0.5).to(torch.bfloat16)
+    wg, wu = ((rnd(E, f, d) * 0.5).to(torch.bfloat16) for _ in range(2))
+    wd = (rnd(E, d, f) * (0.5 / f ** 0.5)).to(torch.bfloat16)
+    doff = dev(torch.from_numpy(off))
+    pk = sm.MoEVerifyLayer.pack_weights(wg, wu, wd)
+    hp = torch.full((sm.moe_packed_h_bytes(n, f, E),), 0xff, dtype=torch.uint8, device="cuda")
+    y = torch.full((n, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sm.moe_expert_up_swiglu_gather_packed(xp, None, 1, doff, pk["w_gate"], pk["w_up"], n, hp)
+    sm.moe_expert_down_packed(hp, doff, pk["w_down"], y)
+    h_rm = torch.full((n, f), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sm.moe_expert_up_swiglu(xp, doff, wg, wu, h_rm)
+    for e, r in enumerate(rows):
+        if not r:
+            continue
+        s = slice(int(off[e]), int(off[e + 1]))
+        x = xp[s].float()
+        h = torch.nn.functional.silu(x @ wg[e].float().t()) * (x @ wu[e].float().t())
+        want = h.to(torch.bfloat16).float() @ wd[e].float().t()
+        for got, ref in ((h_rm[s], h), (y[s], want)):
+            err = (got.float() - ref).abs().amax(1) / ref.abs().amax(1)
+            assert float(err.max()) <= 1e-2, (e, float(err.max()))      # NaN fails as well
+
+
 def test_layer_cfg4_packed_path():
     """The benchmark workload on the tile-packed path: same routing, output bit-identical to the
     row-major path (same kernels' arithmetic in the same order)."""
