@@ -1072,6 +1072,27 @@ def test_layer_packed_plans(name, cfg, plan):
     check_float(f64(out), want, cfg.torch_dtype, name)
 
 
+@pytest.mark.parametrize("d,f,E,k,B,plan,draft_plan", [
+    (64, 4096, 112, 2, 18, (True, False), (True, False)),       # 108 pairs: less than one row per expert
+    (64, 4096, 112, 2, 19, (True, True), (True, False)),        # 112 wide tiles, one row per expert
+    (64, 4096, 129, 2, 300, (True, True), (True, False)),       # 129 of them, below 24 rows
+    (4096, 192, 128, 4, 11, (True, True), (False, False)),      # 256 gate/up tiles, one row per expert
+])
+def test_layer_plan_by_tiles(d, f, E, k, B, plan, draft_plan):
+    """Packed operands from one row per expert on, by the number of wide tiles, against the full oracle; a draft
+    step keeps the plan of few experts."""
+    cfg = synth.MoEConfig("tiles", "bf16", d, f, E, k, B, 2, 1 / d ** 0.5, 0.05, 1.0)
+    _say(f"layer plan by tiles d={d} f={f} E={E}")
+    assert sm.MoEVerifyLayer.packed_plan(cfg.T * k, E, d, f) == plan
+    assert sm.MoEVerifyLayer.packed_plan(cfg.T * k, E, d, f, few_experts=True) == draft_plan
+    L = synth.make_layer(cfg, "cuda", seed=37)
+    layer, out = _run_layer(cfg, L, packed=True)
+    assert ((layer.x_packed is not None), (layer.h_packed is not None)) == plan
+    want = orc.moe_layer_brute_force(f64(L["x"]), f64(L["w_router"]), LazyF64(L["w_gate"]),
+                                     LazyF64(L["w_up"]), LazyF64(L["w_down"]), k)
+    check_float(f64(out), want, cfg.torch_dtype, "layer plan by tiles")
+
+
 @pytest.mark.parametrize("d,f,E,k,T", [(256, 384, 8, 2, 40), (320, 2048, 70, 3, 33), (128, 2048, 4, 2, 700),
                                        (128, 2112, 6, 2, 192), (128, 2112, 6, 2, 193), (1024, 1408, 64, 6, 640)])
 def test_layer_gathers_packed(d, f, E, k, T, monkeypatch):
