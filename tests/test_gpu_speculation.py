@@ -103,6 +103,23 @@ def test_nearest_draft_expert_matches_oracle():
     assert _gpu_remap(A, [7, 2, -1]).tolist() == [2, 2, 2]
 
 
+@pytest.mark.parametrize("N", [1, 2, 3, 16, 17, 64, 65, 130])
+def test_nearest_draft_expert_in_steps(N):
+    """Ids are taken 64 and distances 2 or 16 at a time: whole and partial steps, with invalid
+    ids and repeats among them."""
+    _say(f"nearest draft expert, {N} ids")
+    rng = np.random.default_rng(N)
+    E = 140
+    A = rng.integers(1, 4, size=(E, E)).astype(np.float32)
+    A = np.triu(A, 1) + np.triu(A, 1).T
+    for _ in range(4):
+        draft = rng.integers(-3, E + 3, size=N).tolist()
+        draft[-1] = int(rng.integers(0, E))
+        valid = [q for q in draft if 0 <= q < E]
+        assert np.array_equal(_gpu_remap(A, draft), orc.nearest_draft_expert(A.astype(np.float64), valid))
+    assert _gpu_remap(A, [-1] * (N - 1) + [E]).tolist() == list(range(E))       # none valid: identity
+
+
 # ------------------------------------------------------------------ n2 draft routing and layer
 def _draft_setup(cfg, seed, n_draft):
     """Verification pass -> hot experts -> remap, all on the GPU; returns the pieces."""
