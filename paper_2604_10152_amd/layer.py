@@ -113,21 +113,18 @@ class MoEVerifyLayer:
         packed_plan() says they are the faster ones (bf16 only)."""
         out = self.out if out is None else out
         up_packed = down_packed = False
-        full = (False, False)
         if packed is not None and self.dtype == torch.bfloat16 and self.fuse_gather:
             size = self.T * self.k, self.E, self.d, self.f
-            full = up_packed, down_packed = self.packed_plan(*size)
-            if draft_remap is not None:
-                up_packed, down_packed = self.packed_plan(*size, few_experts=True)
+            up_packed, down_packed = self.packed_plan(*size, few_experts=draft_remap is not None)
         gathered = (down_packed and self.gathers_packed(self.T * self.k, self.E, self.f)
                     and x.data_ptr() % 16 == 0)
-        # what any call of this layer may need (the next one may have another x, or be no draft step): a captured
-        # call must not allocate
-        if self.x_packed is None and full[0]:
+        # x_packed also where this call gathers: x may be another tensor next time, and a captured call must not
+        # allocate once such a call has run
+        if self.x_packed is None and up_packed:
             self.x_packed = torch.empty(
                 (B.moe_packed_h_bytes(self.T * self.k, self.d, self.E),), dtype=torch.uint8,
                 device=self.h.device)
-        if self.h_packed is None and full[1]:
+        if self.h_packed is None and down_packed:
             self.h_packed = torch.empty(
                 (B.moe_packed_h_bytes(self.T * self.k, self.f, self.E),), dtype=torch.uint8,
                 device=self.h.device)
