@@ -17,8 +17,9 @@ namespace {
 // remap[e] = e for a draft expert, else the draft expert with the smallest D[e, .]; equal
 // distances go to the lower id.  Ids outside [0, E) in draft_ids are ignored; with no valid id
 // at all the map is the identity.
-// Latency only: an id, then the distance that it points at.  A wave reads 64 ids at once and requests up to
-// 16 distances together (64 experts, 16 ids, as a graph node 4.4 -> 3.2 us; 1024, 256 ids 61 -> 48); one or two ids take a shorter step, whose instructions they would wait for.
+// Latency only: an id, then the distance that it points at.  A wave reads 64 ids at once and requests
+// up to 16 distances together (64 experts, 16 ids, as a graph node 4.4 -> 3.2 us; 1024, 256 ids 61 ->
+// 48); one or two ids take a shorter step, whose instructions they would wait for (1.9; 2.3 with 8).
 __global__ __launch_bounds__(256) void nearest_draft_kernel(const float* __restrict__ affinity,
                                                             int E,
                                                             const int32_t* __restrict__ draft_ids,
