@@ -115,7 +115,9 @@ class MoEVerifyLayer:
         up_packed = down_packed = False
         if packed is not None and self.dtype == torch.bfloat16 and self.fuse_gather:
             size = self.T * self.k, self.E, self.d, self.f
-            up_packed, down_packed = self.packed_plan(*size, few_experts=draft_remap is not None)
+            # the packed kernels take 16-byte aligned rows only: any other x keeps the shorter plan as well
+            up_packed, down_packed = self.packed_plan(
+                *size, few_experts=draft_remap is not None or x.data_ptr() % 16 != 0)
         gathered = (down_packed and self.gathers_packed(self.T * self.k, self.E, self.f)
                     and x.data_ptr() % 16 == 0)
         # x_packed also where this call gathers: x may be another tensor next time, and a captured call must not

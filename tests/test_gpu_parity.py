@@ -1093,6 +1093,19 @@ def test_layer_plan_by_tiles(d, f, E, k, B, plan, draft_plan):
     check_float(f64(out), want, cfg.torch_dtype, "layer plan by tiles")
 
 
+def test_layer_plan_by_tiles_takes_rows_of_any_alignment():
+    """Tokens that start at an odd element, at a size where aligned ones run on packed operands."""
+    cfg = synth.MoEConfig("odd", "bf16", 4096, 192, 128, 4, 11, 2, 1 / 64, 0.05, 1.0)
+    _say("layer plan by tiles, unaligned tokens")
+    L = synth.make_layer(cfg, "cuda", seed=41)
+    _, want = _run_layer(cfg, L, packed=True)
+    buf = torch.empty(L["x"].numel() + 1, dtype=torch.bfloat16, device="cuda")
+    L["x"] = buf[1:].view(L["x"].shape).copy_(L["x"])
+    layer, got = _run_layer(cfg, L, packed=True)
+    assert L["x"].data_ptr() % 16 and layer.x_packed is None
+    check_float(f64(got), f64(want), cfg.torch_dtype, "unaligned tokens")
+
+
 @pytest.mark.parametrize("d,f,E,k,T", [(256, 384, 8, 2, 40), (320, 2048, 70, 3, 33), (128, 2048, 4, 2, 700),
                                        (128, 2112, 6, 2, 192), (128, 2112, 6, 2, 193), (1024, 1408, 64, 6, 640)])
 def test_layer_gathers_packed(d, f, E, k, T, monkeypatch):
