@@ -244,8 +244,9 @@ int moe_hot_experts(const int32_t* expert_offsets, int E, int n_hot, int32_t* ho
  * for the expert entry points; d_model*d_ff*sizeof(element) must be a multiple of 16 and the
  * weight pointers 16-byte aligned (else SPECMOE_ERR_SHAPE).  `workspace`: device scratch of at
  * least moe_affinity_table_workspace_bytes(E) bytes, 8-byte aligned, contents irrelevant
- * (SPECMOE_ERR_WORKSPACE if smaller).  Sums are accumulated in fp64 (or exactly, in integers) in a
- * fixed order, so the result is deterministic. */
+ * (SPECMOE_ERR_WORKSPACE if smaller).  Sums are accumulated in fp64 in a fixed order, so the result is
+ * deterministic.  Larger bf16 tables of up to 64 experts are summed in integers first: before its
+ * rounding to float a distance is then within 2^-27 of itself of the direct sum, whatever the weights. */
 size_t moe_affinity_table_workspace_bytes(int E);
 int moe_affinity_table(const void* w_gate, const void* w_up, const void* w_down, int E,
                        int d_model, int d_ff, int dtype, float* affinity, void* workspace,

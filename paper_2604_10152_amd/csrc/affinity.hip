@@ -4,24 +4,27 @@
 //
 // More than 8 experts.  Summing the squared differences pair by pair costs a subtraction and a
 // fused multiply-add per element and PAIR (2016 pairs for 64 experts: bound by the vector units,
-// 3.36 ms at 64 experts x 3 x 2048 x 1408).  Here the table comes out of one Gram matrix: with
-// V_i = W_i - W_0 (distances do not change when one expert is subtracted from all),
-//   D[i,j]^2 = G[i,i] + G[j,j] - 2 G[i,j],   G = V V^T.
-// bf16, up to 64 experts: exact integer products of the digits of V (affinity_gram_exact_kernel).
-// Otherwise (fp32, more experts, few weights) products and sums in fp64: v_mfma_f64_16x16x4 takes 64
-// cycles for 16 x 16 pairs x 4 columns; a wave holds up to 64 experts at a time (10 tiles of the upper
-// triangle: 640 cycles per 4 columns of 64 experts, 0.57 ms at the shape above) and reads and converts
-// every weight once.  Measured, bf16, us, pair by pair / fp64 / integer products: 12 experts x 2048 x 2048
-// 249 / 169 / 109, 16 x 4096 x 4096 966 / 614 / 418, 24 x 2048 x 1408 500 / 253 / 142, 40 x 2048 x 1408
-// - / 452 / 237, 64 x 2048 x 1408 3360 / 703 / 307; 130 x 1024 x 704 7390 / 1430.
-// Cancellation: subtracting W_0 removes what all experts have in common (experts grown from one
-// dense model).  A pair that still lies closer together than 2^-10 of its norms - a copy, or any pair
-// where expert 0 lies far from all others - takes its distance from its differences: the finish
-// kernel lists the 8 x 8 blocks of the table that hold such a pair, and a second pass sums the
-// differences of all pairs of a listed block, so no distance is less exact than a direct sum.  A
-// block costs as much however many of its pairs are close: with every pair close, 64 experts x 2048 x 1408
-// take 1.94 ms in all, 16 x 4096 x 4096 0.99 - where direct sums alone would take 0.97, so up to 16 experts such
+// 3.36 ms at 64 experts x 3 x 2048 x 1408).  Here the table comes out of one Gram matrix,
+//   D[i,j]^2 = G[i,i] + G[j,j] - 2 G[i,j].
+// bf16, up to 64 experts, from 2.5 million weights per matrix on: G = W W^T from integer products of the digits of W
+// (affinity_gram_exact_kernel): a distance may differ by 2^-27 of it from the direct sum, in general not at all.
+// Otherwise G = V V^T with V_i = W_i - W_0 (distances do not change when one expert is subtracted from all),
+// products and sums in fp64: v_mfma_f64_16x16x4 takes 64 cycles for 16 x 16 pairs x 4 columns; a wave holds
+// up to 64 experts at a time (10 tiles of the upper triangle: 640 cycles per 4 columns of 64 experts,
+// 0.57 ms at the shape above) and reads and converts every weight once.  Measured, bf16, normal weights, us, fp64 /
+// integer products: 12 experts x 2048 x 2048 159 / 120 (pair by pair 249), 16 x 4096 x 4096 587 / 389, 24 x 2048 x 1408
+// 253 / 169 (500), 40 x 2048 x 1408 450 / 263, 64 x 2048 x 1408 702 / 365 (3360); 130 x 1024 x 704 in fp64 1430.
+// Cancellation: a pair that lies closer together than 2^-10 of its norms (of W or V: subtracting W_0 removes what
+// all experts have in common) - a copy, or in fp64 any pair where expert 0 lies far from all others - takes its
+// distance from its differences: the finish kernel lists the 8 x 8 blocks of the table that hold such a pair, and a
+// second pass sums the differences of all pairs of a listed block.  The pairs that the integer products may have moved by
+// more than 2^-27 go there too.  A block costs as much however many of its pairs are listed: all of them, 64 experts x 2048 x
+// 1408, take 1.9 ms more, 16 x 4096 x 4096 0.9 - where direct sums alone would take 0.97, so up to 16 experts such
 // a table is the one case where they would be faster.
+// What the integer products take by the kind of weights (64 x 2048 x 1408, a call waited for, us; fp64 760 for any
+// weights): normal, or Student's t of 3 degrees 440; experts of magnitudes from 1e-3 to 1e3 455; 1 % of the weights 3000 times
+// larger 515; half of them 1e-34 times smaller 495; magnitudes that spread over more than about 2^22, so that the whole table is
+// listed (log-normal with a standard deviation of 2 times normal, or steps up to 2^24) 2250 to 2360.
 //
 // Up to 8 experts (28 pairs): the direct sums are the faster form (the matrix kernel spends the
 // same 64 cycles on 16 rows however few experts there are: 1.03 ms at 8 x 4096 x 14336 with two
@@ -72,7 +75,7 @@ struct CloseList {
     __host__ __device__ CloseList(double* partial, int E)
         : n(reinterpret_cast<int*>(partial + (size_t)side_pairs(E) * kCloseSlabs * 64)),
           blocks(n + 2), flags(blocks + side_pairs(E)) {}
-    // behind the list: [groups][2][16 row_blocks(E)] (affinity_gram_exact_kernel)
+    // behind the list: [groups][16 row_blocks(E)] (affinity_gram_exact_kernel)
     double* spread(int E) const {
         return reinterpret_cast<double*>(((uintptr_t)(flags + side_blocks(E) * side_blocks(E)) + 7) & ~(uintptr_t)7);
     }
@@ -313,53 +316,55 @@ __global__ __launch_bounds__(WAVES * kWave) void affinity_gram_kernel(
         }
 }
 
-// bf16, 9 to 64 experts: the same partial Gram matrices from exact integer products.  A difference
-// v = w - w_0 of two bf16 numbers has few significant bits, so it is written as q * 2^ex, with one ex per
-// expert for as long as it fits, q a whole number below 2^22 in three signed 8-bit digits, and
-// v_mfma_i32_16x16x64_i8 multiplies the digits: 64 columns of 16 x 16 pairs in 9 instructions of 16 cycles
-// where the fp64 instruction takes 16 of 64.  int32 sums are exact; they move to fp64 sums in LDS when
-// an ex changes and after kExactUnits units.  So the table holds the exact distances of the rounded
-// vectors q * 2^ex.  A v with bits below 2^ex (which is at most 2^-17 of the largest of a row's 64
-// columns) is off by a residual r of at most half of it.  The kernel adds up r^2 (of a quarter of the
-// columns: 13 % less time than of all), alone (spread[0]) and
-// with the squares of the values next to it (spread[1]), and the finish kernel sends the pairs whose
-// distance this may move by 2^-27 to the second pass; fp32 rounds it at 2^-25.  Normal weights stay at 2^-31 from
-// 200 thousand on (hardly any of them rounds), with the heaviest tails a few millions do.
-// Units of 64 columns with a number that is not finite, or beyond 2^+-100, go through the fp64 instruction.
-// Bound by HBM and, close behind, by the vector instructions that make the digits (6 to 7 per weight).
-// So every weight is converted once: a team of two waves shares a unit, each wave converts half of the
-// row blocks, the digits meet in LDS, and each wave multiplies half of the tiles.  The two waves of a
-// SIMD belong to one team; between two barriers one multiplies unit i and then converts unit i + 1, the
-// other does it in the opposite order, so matrix and vector units run side by side.  64 experts x 2048 x
-// 1408: 0.29 ms (1.1 GB: 3.8 TB/s), 0.69 with the fp64 instruction; converting alone 0.24, multiplying alone 0.12.
-constexpr int kExactUnits = 512;             // 3 products per sum, 64 x 2^14 each: below 2^31
-constexpr float kMagic = 12582912.f + 32896.f;   // 1.5 * 2^23 + 0x8080: the low bits are q + 0x8080
-constexpr int kTopBit = 19;                  // a new ex puts the largest v of a unit at 2^19 .. 2^20
-constexpr float kFits = 4.1e6f;              // below 2^22 - 0x8080
-constexpr int kNoEx = -1000;                 // no v but zero so far
-constexpr int kUnit = 64;                    // columns of a unit: 16 per lane
+// bf16, 9 to 64 experts: the Gram matrix of W itself from exact integer products.  bf16 numbers have few significant
+// bits, so a weight is written as q * 2^ex, with one ex per row block (16 experts) for as long as it fits, q a whole
+// number below 2^30 in four signed 8-bit digits, and v_mfma_i32_16x16x64_i8 multiplies the digits: 64 columns of
+// 16 x 16 pairs in 16 instructions of 16 cycles where the fp64 instruction takes 16 of 64.  int32 sums are exact;
+// they move to fp64 sums in LDS when an ex changes and after kExactColumns columns.  So the table holds the exact
+// distances of the vectors q * 2^ex.  These are the weights themselves where none but zero is below 2^(ex + 7), whose
+// last bit is 2^ex; ex puts the largest of the 16 x 64 weights at 2^(ex + 27) .. 2^(ex + 30) in general.  Where a weight is smaller,
+// the squares of all residuals r = w - q * 2^ex of the unit (below 2^ex each) are added up.  By the triangle
+// inequality a distance moves by at most |r_i| + |r_j|, in whatever columns and with whatever signs they are, and
+// the finish kernel sends the pairs that this may move by more than 2^-27 to the second pass; fp32 rounds at 2^-24.
+// Units of 64 columns with a number that is not finite, and the ragged last ones, go through the fp64 instruction.
+// A team of waves shares a unit: each converts one row block, the digits meet in LDS, each multiplies a share
+// of the tiles.  Between two barriers half of the waves of a SIMD multiply unit i and then convert unit i + 1, the others
+// do it in the opposite order, so matrix and vector units run side by side.  At 64 x 2048 x 1408 either is busy for
+// less than half of the time (10 vector instructions per weight and lane); the rest is the chain of a step: barrier,
+// digits out of LDS, products, conversion.  So 64 experts take 128 columns per step (a call waited for: 64 columns 518 us, 128
+// 440); 12 waves with 64 columns take 449.
+constexpr int kExactColumns = 28672;         // 4 products per sum, at most 2^14 each: below 2^31
+constexpr int kTopBit = 27;                  // a new ex puts the largest weight of a unit at 2^27 .. 2^28
+constexpr int kLowBit = 17;                  // below, a unit whose weights lose bits may take a new ex
+constexpr int kLowUnits = 32;                // ... if it has been the same for so many units
+constexpr int kMinEx = -120;                 // 2^-ex is a float
 
 typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
 
-// whether an expert's ex suits a unit whose largest |v| is top (NaN: no)
-__device__ __forceinline__ bool row_fits(float top, float scale) {
-    return top == 0.f || (top * scale < kFits && top * scale >= (float)(1 << (kTopBit - 2)));
-}
+// twice the bits without the sign (which order bf16 numbers by size) from which ex holds a weight with its
+// last one, and from which it would overflow
+__device__ __forceinline__ int holds_from(int ex) { return (ex + 7 + 127) << 8; }
+__device__ __forceinline__ int overflows_at(int ex) { return min((ex + 30 + 127) << 8, 0xff00); }
 
 template <int NBI> struct Exact {
-    static constexpr int WAVES = NBI <= 2 ? 16 : 8;             // as many as the registers allow
-    static constexpr int TILES = NBI * (NBI + 1) / 2, DIGITS = 3;
-    static constexpr int TEAM = NBI > 1 ? 2 : 1, TEAMS = WAVES / TEAM;
-    static constexpr int CB = (NBI + TEAM - 1) / TEAM;          // row blocks a wave converts
-    static constexpr int HT = (TILES + TEAM - 1) / TEAM;        // tiles a wave multiplies
-    // teams that add at a time, each to sums of its own (as many as the LDS holds)
-    static constexpr int BANKS = NBI == 4 ? 2 : TEAMS;
-    static constexpr int SPREAD = 2 * NBI * kRows;
+    static constexpr int SUB = NBI == 4 ? 2 : 1, UNIT = 64 * SUB;       // columns of a unit: 16 * SUB per lane
+    static constexpr int WAVES = NBI == 4 ? 8 : NBI > 1 ? 12 : 16;     // as many as the registers allow
+    static constexpr int AHEAD = 2;                             // units in flight per team
+    static constexpr int TILES = NBI * (NBI + 1) / 2, DIGITS = 4;
+    static constexpr int TEAM = NBI, TEAMS = WAVES / TEAM;
+    static constexpr int HT = (TILES + TEAM - 1) / TEAM;        // tiles a wave multiplies, at most
+    __host__ __device__ static constexpr int first_tile(int part) {
+        return part * (TILES / TEAM) + (part < TILES % TEAM ? part : TILES % TEAM);
+    }
+    // teams that add at a time, each to sums of its own (as the LDS holds)
+    static constexpr int BANKS = NBI == 4 ? 1 : NBI == 1 ? 8 : TEAMS;
+    static constexpr int SPREAD = NBI * kRows;
     static constexpr size_t SUMS = (size_t)BANKS * TILES * kTile * sizeof(double);
-    static constexpr size_t DIGIT_BYTES = (size_t)2 * TEAMS * NBI * DIGITS * kWave * 16;
-    static constexpr int EX = TEAMS * NBI * kRows;
-    static constexpr size_t LDS = SUMS + DIGIT_BYTES + EX * (2 * sizeof(int) + sizeof(float)) +
-                                  BANKS * SPREAD * sizeof(double) + 2 * WAVES * sizeof(int);
+    static constexpr size_t DIGIT_BYTES = (size_t)2 * WAVES * SUB * DIGITS * kWave * 16;
+    static constexpr int REST = WAVES * kRows;
+    static constexpr size_t LDS = SUMS + DIGIT_BYTES + BANKS * SPREAD * sizeof(double) +
+                                  REST * sizeof(float) + 4 * WAVES * sizeof(int);
     static_assert(LDS <= 160 * 1024, "LDS");
 };
 // tiles of the upper triangle of n x n row blocks, in rows (known at compile time once t is)
@@ -371,20 +376,20 @@ __global__ __launch_bounds__(Exact<NBI>::WAVES * kWave) void affinity_gram_exact
     const bf16_t* __restrict__ wg, const bf16_t* __restrict__ wu, const bf16_t* __restrict__ wd, int E,
     size_t n1 /* elements of one matrix of one expert, a multiple of 8 */,
     double* __restrict__ partial /* [tiles][groups][kTile] */, CloseList close,
-    double* __restrict__ spread_out /* [groups][2][NBI * kRows] */) {
+    double* __restrict__ spread_out /* [groups][NBI * kRows] */) {
     typedef Exact<NBI> X;
-    constexpr int DIGITS = X::DIGITS, CB = X::CB, HT = X::HT, TEAMS = X::TEAMS;
+    constexpr int DIGITS = X::DIGITS, TEAMS = X::TEAMS, SUB = X::SUB, UNIT = X::UNIT;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     double* sums = reinterpret_cast<double*>(lds_raw);          // [BANKS][TILES][4][kWave]
-    intx4* digits = reinterpret_cast<intx4*>(lds_raw + X::SUMS);   // [2][TEAMS][NBI][DIGITS][kWave]
-    double* spread = reinterpret_cast<double*>(lds_raw + X::SUMS + X::DIGIT_BYTES);   // [BANKS][2][NBI * kRows]
-    float* rest = reinterpret_cast<float*>(spread + X::BANKS * X::SPREAD);   // [TEAMS][NBI][kRows]: sum of (r / 2^ex)^2
-    int* ex_now = reinterpret_cast<int*>(rest + X::EX);         // the same: ex of acc
-    int* ex_new = ex_now + X::EX;                               // ex of the newest digits
-    int* flags = ex_new + X::EX;                                // [2][waves]: 1 ex changed, 2 fp64 unit
+    intx4* digits = reinterpret_cast<intx4*>(lds_raw + X::SUMS);   // [2][TEAMS][NBI][SUB][DIGITS][kWave]
+    double* spread = reinterpret_cast<double*>(lds_raw + X::SUMS + X::DIGIT_BYTES);   // [BANKS][NBI * kRows]
+    float* rest = reinterpret_cast<float*>(spread + X::BANKS * X::SPREAD);   // [waves][kRows]: sum of (r / 2^ex)^2
+    int* ex_now = reinterpret_cast<int*>(rest + X::REST);       // [waves]: ex of acc
+    int* ex_new = ex_now + X::WAVES;                            // ex of the newest digits
+    int* flags = ex_new + X::WAVES;                             // [2][waves]: 1 ex changed, 2 fp64 unit
     const int lane = threadIdx.x % kWave, g = lane / kRows;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int half = wave / TEAMS, team = wave % TEAMS;         // waves w and w + 4 share a SIMD
+    const int part = wave / TEAMS, team = wave % TEAMS;         // part: the row block that the wave converts
     const int nb = row_blocks(E);
     if (blockIdx.x == 0) {                                      // nothing listed yet
         const int ns = side_blocks(E);
@@ -392,10 +397,10 @@ __global__ __launch_bounds__(Exact<NBI>::WAVES * kWave) void affinity_gram_exact
         for (int i = threadIdx.x; i < ns * ns; i += X::WAVES * kWave) close.flags[i] = 0;
     }
     for (int i = threadIdx.x; i < X::BANKS * X::TILES * kTile; i += X::WAVES * kWave) sums[i] = 0.0;
-    for (int i = threadIdx.x; i < 2 * X::EX; i += X::WAVES * kWave) ex_now[i] = kNoEx;
     for (int i = threadIdx.x; i < X::BANKS * X::SPREAD; i += X::WAVES * kWave) spread[i] = 0.0;
+    if (threadIdx.x < 2 * X::WAVES) ex_now[threadIdx.x] = kMinEx;
 
-    const int units = (int)((n1 + kUnit - 1) / kUnit), total = 3 * units;
+    const int units = (int)((n1 + UNIT - 1) / UNIT), total = 3 * units;
     const int stride = gridDim.x * TEAMS, iters = (total + stride - 1) / stride;
     const int first = blockIdx.x * TEAMS + team;
     const uint64_t base = (uint64_t)wg, to_up = (uint64_t)wu - base, to_down = (uint64_t)wd - (uint64_t)wu;
@@ -403,251 +408,235 @@ __global__ __launch_bounds__(Exact<NBI>::WAVES * kWave) void affinity_gram_exact
     // unit u: its matrix and first column (the last unit of a matrix may be ragged)
     auto unit_base = [&](int u, size_t& col0) __attribute__((always_inline)) -> uint64_t {
         const int uc = min(u, total - 1), m = uc / units;
-        col0 = (size_t)(uc - m * units) * kUnit;
+        col0 = (size_t)(uc - m * units) * UNIT;
         return base + (m >= 1 ? to_up : 0) + (m == 2 ? to_down : 0);
     };
     auto row_bytes = [&](int b) __attribute__((always_inline)) -> size_t {
         return (size_t)min(b * kRows + lane % kRows, E - 1) * n1 * 2;
     };
 
-    // ---- loads: this wave's row blocks and expert 0; a lane's columns are two pieces of 8.  In place of a
+    // ---- loads, AHEAD units ahead: this wave's row block; a lane's columns are pieces of 8.  In place of a
     // ragged unit the last whole one is read (its digits are not used).
-    uint64_t row_at[CB + 1];
-#pragma unroll
-    for (int c = 0; c <= CB; ++c) row_at[c] = (c < CB ? row_bytes(half * CB + c) : 0) + 16 * g;
-    U128 raw[CB + 1][2];
-    auto load = [&](int u) __attribute__((always_inline)) {
+    const uint64_t row_at = row_bytes(part) + 16 * g;
+    U128 raw[X::AHEAD][2 * SUB];
+    auto load = [&](U128 (&to)[2 * SUB], int u) __attribute__((always_inline)) {
         size_t col0;
         const uint64_t W = unit_base(u, col0);
-        const uint64_t at = W + (col0 + kUnit > n1 ? n1 - kUnit : col0) * 2;
+        const uint64_t at = W + (col0 + UNIT > n1 ? n1 - UNIT : col0) * 2;
 #pragma unroll
-        for (int c = 0; c <= CB; ++c)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) raw[c][h] = *(Global)(at + row_at[c] + 64 * h);
+        for (int h = 0; h < 2 * SUB; ++h) to[h] = *(Global)(at + row_at + 64 * h);
         __builtin_amdgcn_sched_barrier(0);      // the loads stay here, ahead of their use
     };
 
-    // ---- digits of unit i (in raw) into slot i % 2, then the next loads
-    float scale[CB];                            // 2^-ex of row lane % 16; 0 before the first unit
-    float left[CB], left_new[CB];               // sampled sums of (r / 2^ex)^2: units in acc, newest unit
-#pragma unroll
-    for (int c = 0; c < CB; ++c) scale[c] = left[c] = left_new[c] = 0.f;
-    auto convert = [&](int i) __attribute__((always_inline)) {
+    // ---- digits of unit i (in `from`) into slot i % 2, then the loads of unit i + AHEAD
+    int ex = kMinEx, ex_since = -kLowUnits;     // ex and the first unit that had it
+    float left = 0.f, left_new = 0.f;           // sum of (r / 2^ex)^2 of row lane % 16: units in acc, newest unit
+    auto convert = [&](U128 (&from)[2 * SUB], int i) __attribute__((always_inline)) {
         const int u = first + i * stride;
-        auto element = [&](int c, int j) __attribute__((always_inline)) -> float {
-            return Piece<bf16_t>::get(raw[c][j / 8], j % 8);
-        };
-        intx4* slot = digits + (size_t)((i & 1) * TEAMS + team) * NBI * DIGITS * kWave;
-        float top[CB];                          // the largest |v| of this lane, NaN if one is
-        int flag = 0;
+        left += left_new;
+        left_new = 0.f;
+        ushortx2 most2 = {0, 0}, least2 = {0xffff, 0xffff};     // of this lane's columns; least: minus 1 (zero: 0xffff)
 #pragma unroll
-        for (int c = 0; c < CB; ++c) left[c] += left_new[c];
-        for (bool once = true;; once = false) {
-            bool fits = true;
-            float ref[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) ref[j] = element(CB, j);
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                const int b = half * CB + c;
-                top[c] = left_new[c] = 0.f;
-                if (b >= NBI) continue;
-                intx4 d[DIGITS];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    uint32_t q[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const float v = element(c, 4 * j + k) - ref[4 * j + k];
-                        top[c] = __builtin_elementwise_maximum(top[c], __builtin_fabsf(v));
-                        const float whole = fmaf(v, scale[c], kMagic);
-                        if (k == j) {                           // a sample of 4 of 16
-                            const float r = fmaf(v, scale[c], kMagic - whole);
-                            left_new[c] = fmaf(r, r, left_new[c]);
-                        }
-                        q[k] = __float_as_uint(whole);
-                    }
-                    const uint32_t p01 = __builtin_amdgcn_perm(q[1], q[0], 0x05010400u);
-                    const uint32_t p23 = __builtin_amdgcn_perm(q[3], q[2], 0x05010400u);
-                    const uint32_t hi = __builtin_amdgcn_perm(q[1], q[0], 0x0c0c0602u) |
-                                        __builtin_amdgcn_perm(q[3], q[2], 0x06020c0cu);
-                    d[0][j] = (int)(__builtin_amdgcn_perm(p23, p01, 0x05040100u) ^ 0x80808080u);
-                    d[1][j] = (int)(__builtin_amdgcn_perm(p23, p01, 0x07060302u) ^ 0x80808080u);
-                    // the top byte is 64 + digit, in 0 .. 127: minus 64, byte by byte without a borrow
-                    d[2][j] = (int)(((hi ^ 0x80808080u) - 0x40404040u) ^ 0x80808080u);
-                }
-#pragma unroll
-                for (int x = 0; x < DIGITS; ++x) slot[(b * DIGITS + x) * kWave + lane] = d[x];
-                const float in_units = top[c] * scale[c];
-                fits = fits && in_units < kFits &&
-                       (top[c] == 0.f || in_units >= (float)(1 << (kTopBit - 4)));
-                __builtin_amdgcn_sched_barrier(0);              // registers: one block at a time
-            }
-            if (__all(fits) || !once) break;
-            // the largest |v| of each row: its four lanes
-            bool keep = true, plain = true;
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                top[c] = __builtin_elementwise_maximum(top[c], __shfl_xor(top[c], 16, kWave));
-                top[c] = __builtin_elementwise_maximum(top[c], __shfl_xor(top[c], 32, kWave));
-                keep = keep && row_fits(top[c], scale[c]);
-                plain = plain && (top[c] == 0.f || (top[c] > 0x1p-100f && top[c] < 0x1p+100f));
-            }
-            if (!__all(plain)) {
-                flag = 2;
-                break;
-            }
-            if (__all(keep)) break;
-            flag = 1;
-#pragma unroll
-            for (int c = 0; c < CB; ++c)
-                if (!row_fits(top[c], scale[c])) {
-                    const int ex = (int)(__float_as_uint(top[c]) >> 23) - 127 - kTopBit;
-                    scale[c] = __uint_as_float((uint32_t)(127 - ex) << 23);
-                    ex_new[(team * NBI + half * CB + c) * kRows + lane % kRows] = ex;
-                }
+        for (int j = 0; j < 8 * SUB; ++j) {
+            const uint32_t pair = from[j / 4][j % 4];
+            const ushortx2 a = __builtin_bit_cast(ushortx2, pair) << 1;
+            most2 = __builtin_elementwise_max(most2, a);
+            least2 = __builtin_elementwise_min(least2, (ushortx2)(a - (ushortx2){1, 1}));
         }
-        if ((size_t)(u % units + 1) * kUnit > n1) flag = 2;     // ragged
-        if (flag == 2 || u >= total)
+        int most = max((int)most2[0], (int)most2[1]), least = min((int)least2[0], (int)least2[1]) + 1;
+        int flag = 0;
+        bool loses = false;
+        if (!__all(most < overflows_at(ex) && least >= holds_from(ex))) {
+            most = __builtin_amdgcn_readfirstlane(wave_all(most, [](int a, int b) { return max(a, b); }));
+            least = __builtin_amdgcn_readfirstlane(wave_all(least, [](int a, int b) { return min(a, b); }));
+            if (most >= 0xff00) {
+                flag = 2;
+            } else if (most >= overflows_at(ex) || (most < (ex + kLowBit + 127) << 8 && ex > kMinEx &&
+                                                    i - ex_since >= kLowUnits)) {
+                flag = 1;
+                ex = max((most >> 8) - 127 - kTopBit, kMinEx);
+                ex_since = i;
+                if (lane == 0) ex_new[wave] = ex;
+            }
+            loses = least < holds_from(ex);
+        }
+        const float scale = __uint_as_float((uint32_t)(127 - ex) << 23);    // 2^-ex
+        intx4* slot = digits + ((size_t)((i & 1) * TEAMS + team) * NBI + part) * SUB * DIGITS * kWave + lane;
 #pragma unroll
-            for (int c = 0; c < CB; ++c) left_new[c] = 0.f;
+        for (int c = 0; c < SUB; ++c) {
+            intx4 d[DIGITS];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uint32_t q[4];                      // + 0x808080: the three low digits + 128, the top one as it is
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    q[k] = (uint32_t)(int)(Piece<bf16_t>::get(from[2 * c + j / 2], (4 * j + k) % 8) * scale) + 0x808080u;
+                const uint32_t p01 = __builtin_amdgcn_perm(q[1], q[0], 0x05010400u);
+                const uint32_t p23 = __builtin_amdgcn_perm(q[3], q[2], 0x05010400u);
+                const uint32_t h01 = __builtin_amdgcn_perm(q[1], q[0], 0x07030602u);
+                const uint32_t h23 = __builtin_amdgcn_perm(q[3], q[2], 0x07030602u);
+                d[0][j] = (int)(__builtin_amdgcn_perm(p23, p01, 0x05040100u) ^ 0x80808080u);
+                d[1][j] = (int)(__builtin_amdgcn_perm(p23, p01, 0x07060302u) ^ 0x80808080u);
+                d[2][j] = (int)(__builtin_amdgcn_perm(h23, h01, 0x05040100u) ^ 0x80808080u);
+                d[3][j] = (int)__builtin_amdgcn_perm(h23, h01, 0x07060302u);
+            }
+#pragma unroll
+            for (int x = 0; x < DIGITS; ++x) slot[(c * DIGITS + x) * kWave] = d[x];
+        }
+        if ((size_t)(u % units + 1) * UNIT > n1) flag = 2;     // ragged
+        if (flag != 2 && u < total && loses) {
+#pragma unroll
+            for (int j = 0; j < 16 * SUB; ++j) {
+                const float a = Piece<bf16_t>::get(from[j / 8], j % 8) * scale, r = a - truncf(a);
+                left_new += r != 0.f ? fmaxf(r * r, 0x1p-100f) : 0.f;       // (no underflow)
+            }
+        }
         if (lane == 0) flags[(i & 1) * X::WAVES + wave] = u < total ? flag : 0;
-        load(u + stride);
+        load(from, u + X::AHEAD * stride);
     };
 
-    // ---- the main loop, for each half of a team
-    auto run = [&](auto half_tag) __attribute__((always_inline)) {
-    constexpr int H = decltype(half_tag)::value;
+    // ---- the main loop, for each part of a team (PART); FIRST: multiplies before it converts
+    auto run = [&](auto part_tag, auto first_tag) __attribute__((always_inline)) {
+    constexpr int T0 = X::first_tile(decltype(part_tag)::value), T1 = X::first_tile(decltype(part_tag)::value + 1);
+    constexpr bool FIRST = decltype(first_tag)::value;
     // products of a slot; this wave's tiles
-    intx4 acc[HT][2 * DIGITS - 1];              // [x + y]: digit x of the row times digit y of the column
+    intx4 acc[X::HT][2 * DIGITS - 1];           // [x + y]: digit x of the row times digit y of the column
     auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int t = 0; t < HT; ++t)
+        for (int t = 0; t < X::HT; ++t)
 #pragma unroll
             for (int s = 0; s < 2 * DIGITS - 1; ++s) acc[t][s] = intx4{0, 0, 0, 0};
     };
     auto multiply = [&](int i) __attribute__((always_inline)) {
-        const intx4* slot = digits + (size_t)((i & 1) * TEAMS + team) * NBI * DIGITS * kWave + lane;
-        intx4 da[DIGITS], db[DIGITS];
+        const intx4* slot = digits + (size_t)((i & 1) * TEAMS + team) * NBI * SUB * DIGITS * kWave + lane;
 #pragma unroll
-        for (int t = 0; t < HT; ++t) {
-            const int tile = H * HT + t;
-            if (tile >= X::TILES) continue;
-            const int a = kTriRow[NBI][tile], b = kTriCol[NBI][tile];
+        for (int c = 0; c < SUB; ++c) {
+            intx4 da[DIGITS], db[DIGITS];
 #pragma unroll
-            for (int x = 0; x < DIGITS; ++x) {
-                if (t == 0 || a != kTriRow[NBI][tile - 1]) da[x] = slot[(a * DIGITS + x) * kWave];
-                db[x] = a == b ? da[x] : slot[(b * DIGITS + x) * kWave];
-            }
+            for (int t = T0; t < T1; ++t) {
+                const int a = kTriRow[NBI][t], b = kTriCol[NBI][t];
 #pragma unroll
-            for (int z = 0; z < DIGITS; ++z)
-#pragma unroll
-                for (int x = 0; x < DIGITS; ++x) {              // neighbours add to different sums
-                    const int y = (x + z) % DIGITS;
-                    acc[t][x + y] =
-                        __builtin_amdgcn_mfma_i32_16x16x64_i8(da[x], db[y], acc[t][x + y], 0, 0, 0);
+                for (int x = 0; x < DIGITS; ++x) {
+                    if (t == T0 || a != kTriRow[NBI][t - 1]) da[x] = slot[((a * SUB + c) * DIGITS + x) * kWave];
+                    db[x] = a == b ? da[x] : slot[((b * SUB + c) * DIGITS + x) * kWave];
                 }
+#pragma unroll
+                for (int z = 0; z < DIGITS; ++z)
+#pragma unroll
+                    for (int x = 0; x < DIGITS; ++x) {              // neighbours add to different sums
+                        const int y = (x + z) % DIGITS;
+                        acc[t - T0][x + y] =
+                            __builtin_amdgcn_mfma_i32_16x16x64_i8(da[x], db[y], acc[t - T0][x + y], 0, 0, 0);
+                    }
+            }
         }
     };
     // all waves: acc into the sums (in one order of additions); wide: unit i of this team in fp64
     auto settle = [&](int i, int held, bool wide) __attribute__((always_inline)) {
-#pragma unroll
-        for (int c = 0; c < CB; ++c) {
-            left[c] += __shfl_xor(left[c], 16, kWave);
-            left[c] += __shfl_xor(left[c], 32, kWave);
-            if (half * CB + c < NBI) rest[(team * NBI + half * CB + c) * kRows + lane % kRows] = left[c];
-            left[c] = 0.f;
-        }
+        left += __shfl_xor(left, 16, kWave);
+        left += __shfl_xor(left, 32, kWave);
+        rest[wave * kRows + lane % kRows] = left;
+        left = 0.f;
         __syncthreads();
         double* mine = sums + (size_t)(team % X::BANKS) * X::TILES * kTile;
         double* spread_mine = spread + (team % X::BANKS) * X::SPREAD;
         for (int turn = 0; turn < TEAMS / X::BANKS; ++turn) {
             if (turn == team / X::BANKS) {
 #pragma unroll
-                for (int t = 0; t < HT; ++t) {
-                    const int tile = H * HT + t;
-                    if (tile >= X::TILES || held == 0) continue;
-                    const int a = kTriRow[NBI][tile], b = kTriCol[NBI][tile];
-                    const int* ea = ex_now + (team * NBI + a) * kRows + 4 * g;
-                    const int eb = ex_now[(team * NBI + b) * kRows + lane % kRows];
+                for (int t = T0; t < T1; ++t) {
+                    if (held == 0) continue;
+                    const int a = kTriRow[NBI][t], b = kTriCol[NBI][t];
+                    const int wa = a * TEAMS + team, wb = b * TEAMS + team;     // the waves that converted them
+                    const int both = ex_now[wa] + ex_now[wb];
                     // a lane holds rows 4 * (lane / 16) + r, r = 0 .. 3, column lane % 16
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        double v = (double)acc[t][4][r];
+                        double v = (double)acc[t - T0][2 * DIGITS - 2][r];
 #pragma unroll
-                        for (int s = 3; s >= 0; --s) v = fma(v, 256.0, (double)acc[t][s][r]);
-                        v = ldexp(v, ea[r] + eb);
-                        mine[(tile * 4 + r) * kWave + lane] += v;
-                        if (a == b && 4 * g + r == lane % kRows) {      // v: squares of a row
-                            const double r2 = ldexp(4.0 * rest[(team * NBI + a) * kRows + 4 * g + r], 2 * eb);
-                            spread_mine[a * kRows + 4 * g + r] += r2;
-                            spread_mine[(NBI + a) * kRows + 4 * g + r] += r2 * v / (kUnit * held);
-                        }
+                        for (int s = 2 * DIGITS - 3; s >= 0; --s) v = fma(v, 256.0, (double)acc[t - T0][s][r]);
+                        mine[(t * 4 + r) * kWave + lane] += ldexp(v, both);
+                        if (a == b && 4 * g + r == lane % kRows)
+                            spread_mine[a * kRows + lane % kRows] +=
+                                ldexp((double)rest[wa * kRows + lane % kRows], both);
                     }
                 }
                 if (wide) {
                     size_t col0;
                     const uint64_t W = unit_base(first + i * stride, col0);
-                    for (int t = 0; t < HT && H * HT + t < X::TILES; ++t) {
-                        const int tile = H * HT + t;
-                        const size_t oa = row_bytes(kTriRow[NBI][tile]), ob = row_bytes(kTriCol[NBI][tile]);
+                    for (int t = T0; t < T1; ++t) {
+                        const size_t oa = row_bytes(kTriRow[NBI][t]), ob = row_bytes(kTriCol[NBI][t]);
                         doublex4 d = doublex4{0.0, 0.0, 0.0, 0.0};
-                        for (int h = 0; h < 2; ++h) {
+                        for (int h = 0; h < 2 * SUB; ++h) {
                             const size_t col = col0 + 32 * h + 8 * g;
-                            U128 ra = {0, 0, 0, 0}, rb = ra, r0 = ra;
+                            U128 ra = {0, 0, 0, 0}, rb = ra;
                             if (col < n1) {
                                 ra = *(Global)(W + col * 2 + oa);
                                 rb = *(Global)(W + col * 2 + ob);
-                                r0 = *(Global)(W + col * 2);
                             }
 #pragma unroll
-                            for (int j = 0; j < 8; ++j) {
-                                // a reference that is not finite is left out, for all experts alike
-                                const float f0 = Piece<bf16_t>::get(r0, j);
-                                const double rd = (double)(__builtin_isfinite(f0) ? f0 : 0.f);
-                                d = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                                    (double)Piece<bf16_t>::get(ra, j) - rd,
-                                    (double)Piece<bf16_t>::get(rb, j) - rd, d, 0, 0, 0);
-                            }
+                            for (int j = 0; j < 8; ++j)
+                                d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Piece<bf16_t>::get(ra, j),
+                                                                         (double)Piece<bf16_t>::get(rb, j), d, 0, 0, 0);
                         }
                         // element q of a lane is row 4 * q + lane / 16, column lane % 16 of its tile
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
-                            mine[(tile * 4 + g) * kWave + 16 * q + lane % kRows] += d[q];
+                            mine[(t * 4 + g) * kWave + 16 * q + lane % kRows] += d[q];
                     }
                 }
             }
             __syncthreads();
         }
-        for (int j = threadIdx.x; j < X::EX; j += X::WAVES * kWave) ex_now[j] = ex_new[j];
+        if (threadIdx.x < X::WAVES) ex_now[threadIdx.x] = ex_new[threadIdx.x];
         __syncthreads();
         clear();
     };
 
     clear();
     int held = 0;                               // units in acc
-    for (int i = 0;; ++i) {
+    // unit i; `next` has the weights of unit i + 1; true after the last one
+    auto step = [&](int i, U128 (&next)[2 * SUB]) __attribute__((always_inline)) -> bool {
         __syncthreads();                        // digits and flags of unit i are there
         const int flag = i < iters ? flags[(i & 1) * X::WAVES + lane % X::WAVES] : 1;
-        bool plain = first + i * stride < total;                // the same in both waves of a team
-        if (held == kExactUnits || __any(flag != 0)) {
-            const bool wide = __any(flag == 2 && lane % TEAMS == team);
+        bool plain = first + i * stride < total;                // the same in all waves of a team
+        if (held == kExactColumns / UNIT || __any(flag != 0)) {
+            const bool wide = __any(flag == 2 && lane % X::WAVES % TEAMS == team);
             settle(i, held, wide);
             plain = plain && !wide;
             held = 0;
         }
-        if (i == iters) break;
+        if (i == iters) return true;
         ++held;
-        if (H == 0 && plain) multiply(i);
-        convert(i + 1);
-        if (H == 1 && plain) multiply(i);
+        if (FIRST && plain) multiply(i);
+        convert(next, i + 1);
+        if (!FIRST && plain) multiply(i);
+        return false;
+    };
+    bool done = false;
+    for (int i = 0; !done; i += X::AHEAD) {
+#pragma unroll
+        for (int p = 0; p < X::AHEAD; ++p)
+            if (!done) done = step(i + p, raw[(p + 1) % X::AHEAD]);
     }
     };
-    load(first);
+#pragma unroll
+    for (int p = 0; p < X::AHEAD; ++p) load(raw[p], first + p * stride);
     __syncthreads();                            // ex_new is cleared
-    convert(0);
-    if (half == 0) run(std::integral_constant<int, 0>{});
-    else run(std::integral_constant<int, X::TEAM - 1>{});
+    convert(raw[0], 0);
+    // The waves of a team meet in barriers of several copies of this code: a barrier counts the waves that have
+    // arrived, wherever they are.
+    auto of = [&](auto part_tag) __attribute__((always_inline)) {
+        if constexpr (X::TEAM == 1) {
+            if (2 * wave < X::WAVES) run(part_tag, std::true_type{});
+            else run(part_tag, std::false_type{});
+        } else {
+            run(part_tag, std::integral_constant<bool, 2 * decltype(part_tag)::value < X::TEAM>{});
+        }
+    };
+    if (part == 0) of(std::integral_constant<int, 0>{});
+    if constexpr (NBI > 1) if (part == 1) of(std::integral_constant<int, 1>{});
+    if constexpr (NBI > 2) if (part == 2) of(std::integral_constant<int, 2>{});
+    if constexpr (NBI > 3) if (part == 3) of(std::integral_constant<int, 3>{});
     for (int j = threadIdx.x; j < X::TILES * kTile; j += X::WAVES * kWave) {
         const int tile = j / kTile, row = j % kTile / kRows, c = j % kRows;
         const int a = kTriRow[NBI][tile], b = kTriCol[NBI][tile];
@@ -666,12 +655,12 @@ __global__ __launch_bounds__(Exact<NBI>::WAVES * kWave) void affinity_gram_exact
 
 // One workgroup per row segment: entries (i, 16 J .. 16 J + 15) of the table.  Thread (s, c) adds
 // the partials s, s + 16, ... of G[i,j], G[j,j] and G[i,i]; the 16 slices are added in order.
-// spread (EXACT, [groups][2][16 nb]): what affinity_gram_exact_kernel rounded away of each expert.
+// spread (EXACT, [groups][16 nb]): squares of what affinity_gram_exact_kernel rounded away of each expert.
 template <bool EXACT>
 __global__ __launch_bounds__(256) void affinity_finish_kernel(
     const double* __restrict__ partial, int E, int groups, float* __restrict__ table,
-    CloseList close, const double* __restrict__ spread, double columns) {
-    constexpr int SUMS = EXACT ? 7 : 3;
+    CloseList close, const double* __restrict__ spread) {
+    constexpr int SUMS = EXACT ? 5 : 3;
     __shared__ double red[SUMS][16][kRows];
     const int nb = row_blocks(E);
     const int i = blockIdx.x, J = blockIdx.y, I = i / kRows;
@@ -690,11 +679,9 @@ __global__ __launch_bounds__(256) void affinity_finish_kernel(
             sum[1] += pii[(size_t)g * kTile];
             sum[2] += pjj[(size_t)g * kTile];
             if constexpr (EXACT) {
-                const double* at = spread + (size_t)g * 2 * nb * kRows;
+                const double* at = spread + (size_t)g * nb * kRows;
                 sum[3] += at[i];
                 sum[4] += at[j];
-                sum[5] += at[nb * kRows + i];
-                sum[6] += at[nb * kRows + j];
             }
         }
     }
@@ -721,11 +708,9 @@ __global__ __launch_bounds__(256) void affinity_finish_kernel(
     table[(size_t)j * E + i] = dist;
     bool drifts = false;
     if constexpr (EXACT) {
-        // D^2 = sum of (v_i - v_j)^2 moves by the sum of r^2, and by 2 (v_i - v_j) (r_i - r_j) at random: with
-        // independent signs a variance of 4 (v_i^2 + v_j^2) (r_i^2 + r_j^2), taken twice; of D a quarter of it / D^2
-        const double r2 = sum[3] + sum[4];
-        const double var = 2.0 * (sum[5] + sum[6] + (sum[3] * gjj + sum[4] * gii) / columns);
-        drifts = var > kDrift * kDrift * sq * sq || r2 > kDrift * sq;
+        // the squares were summed in fp32: 1 % covers that
+        const double moves = sqrt(sum[3]) + sqrt(sum[4]);
+        drifts = 1.01 * moves * moves > kDrift * kDrift * sq;
     }
     // (order of the list does not matter; two experts with infinite weights go there as well)
     if (sq < kClose * norms || drifts || (__builtin_isinf(gii) && __builtin_isinf(gjj))) {
@@ -845,7 +830,7 @@ hipError_t launch_gram_exact(const bf16_t* wg, const bf16_t* wu, const bf16_t* w
         hipFuncSetAttribute(reinterpret_cast<const void*>(&affinity_gram_exact_kernel<NBI>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)X::LDS);
     if (attr != hipSuccess) return attr;
-    const size_t units = 3 * ((n1 + kUnit - 1) / kUnit), teams = X::TEAMS;
+    const size_t units = 3 * ((n1 + X::UNIT - 1) / X::UNIT), teams = X::TEAMS;
     groups = (int)(units < kMaxGroups * teams ? (units + teams - 1) / teams : kMaxGroups);
     hipLaunchKernelGGL((affinity_gram_exact_kernel<NBI>), dim3(groups), dim3(X::WAVES * kWave), X::LDS,
                        s, wg, wu, wd, E, n1, partial, close, spread);
@@ -875,9 +860,9 @@ hipError_t launch_affinity_typed(const T* wg, const T* wu, const T* wd, int E, s
     int groups;                                  // workgroups of the Gram kernel, each with partial sums
     bool exact = false;
     if constexpr (std::is_same<T, bf16_t>::value) {
-        // integer products from 2.5 million weights per matrix on (9 experts x 512 x 704: 34.1 -> 31.0 us, 40 x
-        // 256 x 256: 31.4 -> 29.0); below, the passes that move int32 sums to fp64 cost more than the
-        // products gain (32 x 256 x 256: 23.9 -> 27.7, 64 x 264 x 65: 30.0 -> 36.6)
+        // integer products from 2.5 million weights per matrix on (fp64 / integer, us: 9 experts x 512 x 704 33.2 /
+        // 29.9, 40 x 256 x 256 31.1 / 27.2); below, the passes that move int32 sums to fp64 cost what the products
+        // gain (9 x 256 x 512 21.4 / 24.2, 16 x 256 x 512 21.6 / 24.6, 32 x 256 x 256 23.8 / 23.8)
         exact = nb <= kSuper && (size_t)E * n1 >= 2500000;
         if (exact) {
             double* out = close.spread(E);
@@ -888,7 +873,7 @@ hipError_t launch_affinity_typed(const T* wg, const T* wu, const T* wd, int E, s
             else err = launch_gram_exact<4>(wg, wu, wd, E, n1, partial, close, out, s, groups);
             if (err != hipSuccess) return err;
             hipLaunchKernelGGL(affinity_finish_kernel<true>, dim3(E, nb), dim3(256), 0, s, partial, E, groups,
-                               table, close, out, 3.0 * (double)n1);
+                               table, close, out);
         }
     }
     if (!exact) {
@@ -904,7 +889,7 @@ hipError_t launch_affinity_typed(const T* wg, const T* wu, const T* wd, int E, s
         if (ns > 1) SPECMOE_GRAM(4, true, 8, 1, ns * (ns - 1) / 2);
 #undef SPECMOE_GRAM
         hipLaunchKernelGGL(affinity_finish_kernel<false>, dim3(E, nb), dim3(256), 0, s, partial, E, groups,
-                           table, close, nullptr, 0.0);
+                           table, close, nullptr);
     }
     hipLaunchKernelGGL((affinity_close_kernel<T>), dim3(kCloseGroups), dim3(kCloseThreads), 0, s, wg,
                        wu, wd, E, n1, slabs, close, partial);
@@ -920,7 +905,7 @@ hipError_t launch_affinity_typed(const T* wg, const T* wu, const T* wd, int E, s
 // kMaxGroups x 256 doubles per pair of 16-expert blocks: with n = row_blocks(E), n (n + 1) / 2 x 128
 // partials of 512 doubles, and 8-expert blocks come in at least n (2 n - 1) >= n (n + 1) pairs from
 // n = 2 on, in 3 for n = 1, of 64 partials of 512 doubles), then of the listed blocks - and CloseList
-// follows them, with at most 256 x 128 doubles behind it.
+// follows them, with at most 256 x 64 doubles behind it.
 size_t affinity_workspace_bytes(int E) {
     const size_t nb8 = (size_t)(E + 7) / 8;
     return nb8 * (nb8 + 1) / 2 * 1024 * 64 * sizeof(double);

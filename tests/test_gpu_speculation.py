@@ -366,7 +366,7 @@ def test_affinity_table_close_pairs_and_non_finite_weights():
     assert _gpu_affinity(wg, w2, wd)[2, 3] == np.inf
 
 
-# fp32 rounds a distance by at most 2^-24; the integer products may move it by 2^-27 (standard deviation)
+# fp32 rounds a distance by at most 2^-24; the integer products may move it by 2^-27
 EXACT_RTOL = 2.0 ** -24 + 4 * 2.0 ** -27
 
 
@@ -392,7 +392,7 @@ def test_affinity_table_integer_products(E, d, f, kind):
             w = w * (torch.rand(shape, generator=g) < 0.03)
         elif kind == "steps":                      # magnitude changes along the columns
             w = w * 2.0 ** (torch.arange(w[0].numel()) // 100 % 7 * 4 - 12).view(1, *shape[1:])
-        elif kind == "huge and tiny":              # beyond 2^+-100: through the fp64 instruction
+        elif kind == "huge and tiny":              # more than 2^100 apart, in one unit
             w = w * torch.where(torch.rand(shape, generator=g) < 0.5, 1e-34, 1.0)
             w[:, 0, :2] *= 1e32
         W.append(w.to(torch.bfloat16))
@@ -400,6 +400,45 @@ def test_affinity_table_integer_products(E, d, f, kind):
     want = orc.affinity_table(*(f64(w) for w in W))
     assert np.all(np.diag(got) == 0) and np.array_equal(got, got.T)
     np.testing.assert_allclose(got, want, rtol=EXACT_RTOL, atol=0)
+
+
+def _structured(kind, E, d, f):
+    """Weights whose low bits are alike from column to column or row to row (d, f: multiples of 64)."""
+    g = torch.Generator().manual_seed(E)
+    W = []
+    for shape in ((E, f, d), (E, f, d), (E, d, f)):
+        col = torch.arange(shape[2])
+        odd = torch.isin(col % 8, torch.tensor([1, 3, 4, 6]))
+        if kind == "half the columns":             # and a large value in one of 64
+            sign = torch.randint(0, 2, shape, generator=g) * 2.0 - 1
+            w = torch.where(col % 64 == 1, torch.ones(shape), torch.where(odd, sign * 255 * 2.0 ** -20, 0.0))
+            w[0] = 0
+        elif kind == "outlier channels":           # of expert 0, larger still in its first rows
+            w = torch.randn(shape, generator=g) * 0.02 * odd
+            w[0, :, torch.isin(col % 64, torch.tensor([1, 9, 17, 25]))] = 20
+            if not W:
+                w[0, :shape[1] // 11, torch.isin(col % 64, torch.tensor([1, 9, 17, 25]))] = 280
+        else:                                      # expert 0 small and constant, the others zero or positive
+            w = (torch.rand(shape, generator=g) + 1) * (torch.rand(shape, generator=g) < 0.5)
+            w[0] = 0.4 * 2.0 ** -19
+            if kind == "one sign, larger at first" and not W:
+                w[1:, :shape[1] // 4] *= 4
+        W.append(w.to(torch.bfloat16))
+    return W
+
+
+@pytest.mark.parametrize("kind", ["half the columns", "outlier channels", "one sign", "one sign, larger at first"])
+@pytest.mark.parametrize("E,d,f", [(9, 512, 576), (64, 256, 192)])
+def test_affinity_table_structured_residuals(E, d, f, kind):
+    """Whatever the integer form cannot hold of a weight, in whichever columns and with whatever signs: D moves
+    by at most 2^-27 of it, then by the rounding to fp32."""
+    assert E * d * f >= 2500000
+    _say(f"affinity, structured residuals E={E} d={d} f={f} {kind}")
+    W = _structured(kind, E, d, f)
+    got = _gpu_affinity(*W)
+    want = orc.affinity_table(*(f64(w) for w in W))
+    assert np.all(np.diag(got) == 0) and np.array_equal(got, got.T)
+    np.testing.assert_allclose(got, want, rtol=2.0 ** -24 + 2.0 ** -27, atol=0)
 
 
 def _many_close(kind, wg, wu, wd):
