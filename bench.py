@@ -276,7 +276,7 @@ class LayerRun:
         active = int((counts > 0).sum())
         packed_rows = (self.packed is not None and self.cfg.dtype == "bf16" and
                        self.layer.packed_plan(self.T * self.cfg.k, self.cfg.E, self.cfg.d_model,
-                                              self.cfg.d_ff)[0] and
+                                              self.cfg.d_ff, k=self.cfg.k)[0] and
                        not self.layer.gathers_packed(self.T * self.cfg.k, self.cfg.E, self.cfg.d_ff))
         work = algorithmic_work(self.cfg, self.T, active, rows_materialised=packed_rows)
         kernels = {}
@@ -305,7 +305,7 @@ def packed_weights_for(sm, torch, cfg, L, T, row_major=False):
     parameters); None otherwise."""
     if cfg.dtype != "bf16" or row_major:
         return None
-    if not sm.MoEVerifyLayer.packed_plan(T * cfg.k, cfg.E, cfg.d_model, cfg.d_ff)[0]:
+    if not sm.MoEVerifyLayer.packed_plan(T * cfg.k, cfg.E, cfg.d_model, cfg.d_ff, k=cfg.k)[0]:
         return None
     packed = sm.MoEVerifyLayer.pack_weights(L["w_gate"], L["w_up"], L["w_down"])
     torch.cuda.synchronize()
@@ -330,7 +330,7 @@ def kernel_name(cfg, T, packed=True):
     tile = 320 if large else 192
     few, tiles = few_wide_tiles(rows, cfg.E, cfg.d_ff, 128)
     if packed:
-        up, down = sm.MoEVerifyLayer.packed_plan(rows, cfg.E, cfg.d_model, cfg.d_ff)
+        up, down = sm.MoEVerifyLayer.packed_plan(rows, cfg.E, cfg.d_model, cfg.d_ff, k=cfg.k)
         if up:
             narrow = down and few and (tiles <= 64 or 115 * rows <= 12800 * cfg.E)
             form = "128,128" if narrow else f"{tile},256"

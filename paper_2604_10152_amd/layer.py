@@ -38,38 +38,38 @@ class MoEVerifyLayer:
     # Which projections run on tile-packed operands (measured crossovers, average rows per
     # expert r = T*k/E).  Gate/up, with the gather of its rows: from r >= 48, and at any r for
     # d_model < 4096 (64 experts x 2048 x 1408, 6 to 24 rows: 118-122 us against 126-130 row-major, 70
-    # rows 147 against 155; few tiles are level or 3 us behind, 8 x 3072 x 1024 34 against 31), or where
-    # its 128-output tiles fill the chip (16 x 5120 x 8192, whole layer: 4 rows 666 against 638, 20 rows
-    # 698 / 660, 44 rows 841 / 782; 16 x 5120 with one row in all: 80 / 94).  Down: from r >= 96, or with
-    # d_ff < 4096, or from r >= 56 where its narrow tiles fill the chip (at most 128 tiles of 256 outputs: 8
-    # experts x 4096 outputs, 65 rows each 156 us against 173 row-major; 16 x 5120, 75 rows 287 against
-    # 264).  With 112 to 128 such tiles already from one row, with up to 256 below 24 rows: they take one round
-    # of the chip (layer, us, row-major down / packed: 8 x 4096 x 14336, 20 rows 471 / 466, 45 rows 524 / 490; 16 x
-    # 2048 x 8192, 30 rows 320 / 281; 16 x 4096 x 4096, 10 rows 297 / 274; 48 x 1024 x 4096, 10 rows 224 / 207, 30
-    # rows 239 / 246; 96 tiles, 12 x 2048 x 5120, 10 rows 136 / 144).
-    # A draft model's batch meets a few experts only, for which the row-major kernels have forms of their
-    # own (8 x 4096 x 14336, 2 active, 16 tokens: 141 against 206): it keeps the first lines of the rule.
+    # rows 147 against 155; few tiles are level or 3 us behind, 8 x 3072 x 1024 34 against 31).  Down:
+    # from r >= 96, or with d_ff < 4096, or from r >= 56 where its narrow tiles fill the chip (at most
+    # 128 tiles of 256 outputs: 8 experts x 4096 outputs, 65 rows each 156 us against 173 row-major;
+    # 16 x 5120, 75 rows 287 against 264).
+    # Only the device knows how many experts a batch meets: at least k, however many rows there are.  Below 48 rows gate/up
+    # goes packed where it is ahead for few of them as well: at least 8192 outputs and 256 tiles of 128, and from 20 rows or
+    # where k experts have 192 of them (layer, us, row-major / packed gate/up, by active experts: 8 x 4096 x 14336, 8 rows all 457 / 454, 4
+    # 295 / 251, 2 164 / 143, 24 rows 483 / 469, 341 / 293, 223 / 202; 16 x 5120 x 8192, 20 rows all 673 / 662, 2 186 / 181, 1 160 / 155,
+    # but 14 rows, 2 153 / 171, 1 112 / 137; 16 x 4096 x 4096, 24 rows all 290 / 302, 2 79 / 109).  The packed down
+    # projection has no form for few experts (row-major / packed, gate/up packed: 8 x 4096 x 14336, 8 rows all 454 / 449, 4 251 / 287, 2
+    # 143 / 206; 16 x 2048 x 8192, 8 rows all 292 / 271, 8 156 / 182, 2 69 / 112), so its lines stay above.
     PACKED_UP_MIN_ROWS = 48
+    PACKED_UP_MIN_ROWS_WIDE = 20
+    PACKED_UP_WIDE = 8192
     PACKED_UP_MIN_TILES = 256
+    PACKED_UP_MIN_TILES_ACTIVE = 192
     PACKED_DOWN_MIN_ROWS = 96
     PACKED_DOWN_MIN_ROWS_FEW_TILES = 56
-    PACKED_DOWN_ROUND_TILES = (112, 128, 256)
-    PACKED_DOWN_ROUND_MAX_ROWS = 24
 
     @classmethod
-    def packed_plan(cls, n_pairs, E, d_model, d_ff, few_experts=False):
-        """(gate/up on packed operands?, down on packed operands?) for a batch of n_pairs
-        (token, expert) pairs; few_experts: a draft model's, spread over a fraction of them."""
+    def packed_plan(cls, n_pairs, E, d_model, d_ff, few_experts=False, k=1):
+        """(gate/up on packed operands?, down on packed operands?) for a batch of n_pairs (token, expert)
+        pairs that meets at least k experts; few_experts: a draft model's, which may meet a single one."""
         up = n_pairs >= cls.PACKED_UP_MIN_ROWS * E or d_model < 4096
-        tiles = E * -(-d_model // 256)
-        min_rows = cls.PACKED_DOWN_MIN_ROWS_FEW_TILES if tiles <= 128 else cls.PACKED_DOWN_MIN_ROWS
-        down = n_pairs >= min_rows * E or d_ff < 4096
-        if not few_experts and n_pairs >= E:
-            up = up or E * -(-d_ff // 128) >= cls.PACKED_UP_MIN_TILES
-            least, narrow, most = cls.PACKED_DOWN_ROUND_TILES
-            down = down or least <= tiles <= narrow or (
-                narrow < tiles <= most and n_pairs < cls.PACKED_DOWN_ROUND_MAX_ROWS * E)
-        return up, up and down
+        min_rows = (cls.PACKED_DOWN_MIN_ROWS_FEW_TILES if E * -(-d_model // 256) <= 128 else
+                    cls.PACKED_DOWN_MIN_ROWS)
+        down = up and (n_pairs >= min_rows * E or d_ff < 4096)
+        tiles = -(-d_ff // 128)                  # of 128 gate/up outputs, per expert
+        if not few_experts and d_ff >= cls.PACKED_UP_WIDE and E * tiles >= cls.PACKED_UP_MIN_TILES:
+            up = up or n_pairs >= cls.PACKED_UP_MIN_ROWS_WIDE * E or (
+                n_pairs >= E and k * tiles >= cls.PACKED_UP_MIN_TILES_ACTIVE)
+        return up, down
 
     # Packed gate/up: rows gathered by the GEMM itself (64-byte requests, once per 128 outputs), or written
     # tile-packed first ((T + n_pairs) rows and a launch).  Gathering is ahead up to 2048 outputs at any batch
@@ -114,10 +114,10 @@ class MoEVerifyLayer:
         out = self.out if out is None else out
         up_packed = down_packed = False
         if packed is not None and self.dtype == torch.bfloat16 and self.fuse_gather:
-            size = self.T * self.k, self.E, self.d, self.f
             # the packed kernels take 16-byte aligned rows only: any other x keeps the shorter plan as well
             up_packed, down_packed = self.packed_plan(
-                *size, few_experts=draft_remap is not None or x.data_ptr() % 16 != 0)
+                self.T * self.k, self.E, self.d, self.f,
+                few_experts=draft_remap is not None or x.data_ptr() % 16 != 0, k=self.k)
         gathered = (down_packed and self.gathers_packed(self.T * self.k, self.E, self.f)
                     and x.data_ptr() % 16 == 0)
         # x_packed also where this call gathers: x may be another tensor next time, and a captured call must not

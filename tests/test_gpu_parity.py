@@ -1073,18 +1073,18 @@ def test_layer_packed_plans(name, cfg, plan):
 
 
 @pytest.mark.parametrize("d,f,E,k,B,plan,draft_plan", [
-    (64, 4096, 112, 2, 18, (True, False), (True, False)),       # 108 pairs: less than one row per expert
-    (64, 4096, 112, 2, 19, (True, True), (True, False)),        # 112 wide tiles, one row per expert
-    (64, 4096, 129, 2, 300, (True, True), (True, False)),       # 129 of them, below 24 rows
-    (4096, 192, 128, 4, 11, (True, True), (False, False)),      # 256 gate/up tiles, one row per expert
+    (64, 4096, 112, 2, 19, (True, False), (True, False)),       # the down projection goes by rows alone
+    (4096, 8192, 4, 3, 1, (True, False), (False, False)),       # 192 gate/up tiles for three experts
+    (4096, 8192, 4, 2, 13, (False, False), (False, False)),     # 128 for two, 78 pairs
+    (4096, 8192, 4, 2, 14, (True, False), (False, False)),      # 84 pairs
 ])
 def test_layer_plan_by_tiles(d, f, E, k, B, plan, draft_plan):
-    """Packed operands from one row per expert on, by the number of wide tiles, against the full oracle; a draft
+    """Packed gate/up below 48 rows per expert, by the number of its tiles, against the full oracle; a draft
     step keeps the plan of few experts."""
     cfg = synth.MoEConfig("tiles", "bf16", d, f, E, k, B, 2, 1 / d ** 0.5, 0.05, 1.0)
-    _say(f"layer plan by tiles d={d} f={f} E={E}")
-    assert sm.MoEVerifyLayer.packed_plan(cfg.T * k, E, d, f) == plan
-    assert sm.MoEVerifyLayer.packed_plan(cfg.T * k, E, d, f, few_experts=True) == draft_plan
+    _say(f"layer plan by tiles d={d} f={f} E={E} k={k}")
+    assert sm.MoEVerifyLayer.packed_plan(cfg.T * k, E, d, f, k=k) == plan
+    assert sm.MoEVerifyLayer.packed_plan(cfg.T * k, E, d, f, few_experts=True, k=k) == draft_plan
     L = synth.make_layer(cfg, "cuda", seed=37)
     layer, out = _run_layer(cfg, L, packed=True)
     assert ((layer.x_packed is not None), (layer.h_packed is not None)) == plan
@@ -1095,7 +1095,7 @@ def test_layer_plan_by_tiles(d, f, E, k, B, plan, draft_plan):
 
 def test_layer_plan_by_tiles_takes_rows_of_any_alignment():
     """Tokens that start at an odd element, at a size where aligned ones run on packed operands."""
-    cfg = synth.MoEConfig("odd", "bf16", 4096, 192, 128, 4, 11, 2, 1 / 64, 0.05, 1.0)
+    cfg = synth.MoEConfig("odd", "bf16", 4096, 8192, 4, 3, 2, 2, 1 / 64, 0.05, 1.0)
     _say("layer plan by tiles, unaligned tokens")
     L = synth.make_layer(cfg, "cuda", seed=41)
     _, want = _run_layer(cfg, L, packed=True)

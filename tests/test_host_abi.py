@@ -227,3 +227,20 @@ def test_layer_forward_validation(lib):
     assert call(hb=8 * 2 * 64 * 2 - 1) == 4 and call(layout=3, hb=(1 + 4) * 16 * 64 * 2 - 1) == 4
     assert call(layout=2, xb=(1 + 4) * 16 * 64 * 2 - 1) == 4
     assert call(layout=3, x=ctypes.c_void_p(0x1008)) == 4                    # the GEMM gathers 16-byte pieces
+
+
+def test_packed_plan_holds_for_few_active_experts():
+    """Below 48 rows per expert a batch may meet k experts only: the down projection, whose row-major
+    kernels have a form for that, stays row-major, and gate/up where k experts are few tiles."""
+    def plan(rows, E, d, f, k):
+        return sm.MoEVerifyLayer.packed_plan(rows * E, E, d, f, k=k)
+
+    for rows in (1, 4, 10, 19, 20, 30, 47):
+        assert plan(rows, 8, 4096, 14336, 2) == (True, False)
+        assert plan(rows, 16, 2048, 8192, 2) == (True, False)
+        assert plan(rows, 14, 2048, 8192, 2) == (True, False)
+        assert plan(rows, 48, 1024, 4096, 4) == (True, False)
+        assert plan(rows, 16, 4096, 4096, 2) == (False, False)
+        assert plan(rows, 16, 5120, 8192, 1) == (rows >= 20, False)
+    assert plan(48, 16, 5120, 8192, 1) == (True, False) and plan(96, 16, 5120, 8192, 1) == (True, True)
+    assert plan(56, 8, 4096, 14336, 2) == (True, True) and plan(1, 64, 2048, 1408, 6) == (True, True)
