@@ -52,7 +52,7 @@ typedef enum { SPECMOE_F32 = 0, SPECMOE_BF16 = 1 } specmoe_dtype;
 /* Gate of one MoE block (Sec. 2.1: "the gate selects the top-K experts per token").
  *   logits l[t,e] = router_bias[e] + sum_j x[t,j] * w_router[e,j], accumulated in fp64;
  *   topk_idx[t,0..k-1] = the k experts with the largest LOGITS, slot order = descending
- *   logit, equal logits -> lower expert id first;
+ *   logit, equal logits -> lower expert id first, NaN after every number;
  *   topk_w[t,s] = softmax(l[t,:])[topk_idx[t,s]], divided by sum_s topk_w[t,s] if renorm != 0.
  * x [T,d_model], w_router [E,d_model] in `dtype`; router_bias [E] float or NULL;
  * topk_idx [T,k] int32; topk_w [T,k] float. */

@@ -21,6 +21,8 @@
 // 11.0 -> 8.9 us, 320 tokens 13.4 -> 11.0 (4 of these the fp64 work of one CU, 2.5 the launch).
 #include "common.h"
 
+#include <type_traits>
+
 namespace specmoe {
 namespace {
 
@@ -50,12 +52,13 @@ template <typename T> struct Chunk<T, false> {          // any d_model, any alig
     __device__ static double get(const Raw& v, int) { return (double)v; }
 };
 
+// among numbers
 __device__ __forceinline__ bool better(double av, int aid, double bv, int bid) {
     return (av > bv) || (av == bv && aid < bid);
 }
 
 // Ranks token t by one wave, E <= 64: one expert per lane, on the key (logit descending, id
-// ascending).  A round per slot (the largest logit that is left, exchanged in registers) costs about 200
+// ascending; NaN last).  A round per slot (the largest logit that is left, exchanged in registers) costs about 200
 // cycles.  Up to 3 k experts every lane counts the experts that beat its own instead - its rank, i.e.
 // the slot it would fill -, the other logits arriving through v_readlane broadcasts.  Kernel time, rounds /
 // counting: 64 experts x 2048, top-6 8.9 / 11.2 us, top-16 11.0 / 11.6, 16 experts top-4 5.1 / 5.3, 8 top-2 4.3 / 4.3.
@@ -76,6 +79,8 @@ __device__ __forceinline__ void rank_token(const double* logit, int lane, int E,
         rank = 0;
 #pragma unroll 8
         for (int j = 0; j < E; ++j) rank += better(lane_value(v, j), j, v, lane) ? 1 : 0;
+        const unsigned long long nan = __ballot(valid && v != v);   // (none of them beats a number)
+        if (v != v) rank = E - __popcll(nan) + __popcll(nan & ((1ull << lane) - 1));
     } else {
         rank = k;
         for (int sl = 0; sl < k; ++sl) {
@@ -225,37 +230,49 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     // More than 64 experts: lane owns experts lane, lane+64, ...; `taken` marks the ones already
     // selected.  Lane s keeps the result of round s (k <= 64), so the final stores are coalesced.
     constexpr int kOwn = 1024 / kWave;                // SPECMOE_MAX_EXPERTS / 64
-    uint32_t taken = 0;
-    double vmax = 0.0, denom = 1.0, wsum_sel = 0.0, my_p = 0.0;
+    double wsum_sel, my_p = 0.0;
     int my_id = 0;
-    for (int s = 0; s < k; ++s) {
-        double bv = 0.0; int bid = -1;
+    // NANS: ranks NaN last; without, false if there is one (256 tokens, 1024 columns, 256 experts, top-8: 25.9 us; with
+    // the comparison for all tokens, exchanges through LDS as before, 29.2 against 27.3)
+    auto rank = [&](auto nans) __attribute__((always_inline)) -> bool {
+        constexpr bool NANS = decltype(nans)::value;
+        auto wins = [](double av, int aid, double bv, int bid) {
+            return better(av, aid, bv, bid) || (NANS && bv != bv && (av == av || aid < bid));
+        };
+        uint32_t taken = 0;
+        double vmax = 0.0, denom = 1.0;
+        wsum_sel = 0.0;
+        for (int s = 0; s < k; ++s) {
+            struct Best { double v; int64_t id; } best = {0.0, -1};      // (no padding: exchanged by words)
 #pragma unroll 1
-        for (int o = 0; o < kOwn; ++o) {
-            int e = lane + o * kWave;
-            if (e >= E) break;
-            if (taken & (1u << o)) continue;
-            double v = logit[e];
-            if (bid < 0 || better(v, e, bv, bid)) { bv = v; bid = e; }
+            for (int o = 0; o < kOwn; ++o) {
+                int e = lane + o * kWave;
+                if (e >= E) break;
+                if (taken & (1u << o)) continue;
+                double v = logit[e];
+                if (best.id < 0 || wins(v, e, best.v, (int)best.id)) best = {v, e};
+            }
+            best = specmoe::wave_all(best, [&](Best a, Best b) {
+                return b.id >= 0 && (a.id < 0 || wins(b.v, (int)b.id, a.v, (int)a.id)) ? b : a;
+            });
+            const double bv = best.v;
+            const int bid = (int)best.id;
+            if ((bid % kWave) == lane) taken |= 1u << (bid / kWave);
+            if (s == 0) {
+                // softmax denominator over all E experts, relative to the largest logit
+                vmax = bv;
+                double p = 0.0;
+                for (int e = lane; e < E; e += kWave) p += exp(logit[e] - vmax);
+                denom = wave_sum(p);
+                if (!NANS && __any(denom != denom)) return false;
+            }
+            double p = exp(bv - vmax) / denom;
+            wsum_sel += p;                            // slot order, identical on every lane
+            if (lane == s) { my_p = p; my_id = bid; }
         }
-#pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) {
-            double ov = __shfl_xor(bv, off, kWave);
-            int oid = __shfl_xor(bid, off, kWave);
-            if (oid >= 0 && (bid < 0 || better(ov, oid, bv, bid))) { bv = ov; bid = oid; }
-        }
-        if ((bid % kWave) == lane) taken |= 1u << (bid / kWave);
-        if (s == 0) {
-            // softmax denominator over all E experts, relative to the largest logit
-            vmax = bv;
-            double p = 0.0;
-            for (int e = lane; e < E; e += kWave) p += exp(logit[e] - vmax);
-            denom = wave_sum(p);
-        }
-        double p = exp(bv - vmax) / denom;
-        wsum_sel += p;                                // slot order, identical on every lane
-        if (lane == s) { my_p = p; my_id = bid; }
-    }
+        return true;
+    };
+    if (!rank(std::false_type{})) rank(std::true_type{});
     if (lane < k) {
         idx_out[(size_t)t * k + lane] = remap ? remap[my_id] : my_id;
         w_out[(size_t)t * k + lane] = (float)(renorm ? my_p / wsum_sel : my_p);

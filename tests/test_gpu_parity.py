@@ -151,6 +151,27 @@ def test_route_ranking_forms(T, E, k):
     _check_route(x, wr, b, k, True)
 
 
+@pytest.mark.parametrize("E,k", [(9, 3), (10, 3), (64, 22), (64, 21), (3, 2), (130, 7)])
+@pytest.mark.parametrize("T", [5, 1030])
+@pytest.mark.parametrize("numbers", ["enough", "too few"])
+def test_route_nan_logits_come_last(T, E, k, numbers):
+    """Counting, rounds and more than 64 experts: a NaN logit ranks after every number (-inf as well), NaN by id;
+    every slot is filled with an expert of its own, and the weights of such a token are NaN."""
+    _say(f"route NaN T={T} E={E} k={k} {numbers}")
+    g = torch.Generator().manual_seed(T + E + k)
+    x = (torch.randn(T, 72, generator=g) / 72 ** 0.5).to(torch.bfloat16)
+    wr = torch.randn(E, 72, generator=g).to(torch.bfloat16)
+    b = torch.zeros(E)
+    b[torch.arange(E) < (E - k + 1 if numbers == "too few" else 1)] = float("nan")
+    b[E - 1] = float("-inf")
+    idx, w = _gpu_route(x, wr, b, k, True)
+    logits = orc.router_logits(f64(x), f64(wr), f64(b))
+    for t in range(T):
+        want = sorted(range(E), key=lambda e: (np.isnan(logits[t, e]), 0 if np.isnan(logits[t, e]) else -logits[t, e], e))
+        assert idx[t].tolist() == want[:k], t
+    assert np.isnan(w).all()
+
+
 def test_route_ties_go_to_lower_expert_id():
     _say("route ties")
     g = torch.Generator().manual_seed(5)
