@@ -274,11 +274,10 @@ class LayerRun:
             whole.append(m[0].elapsed_time(m[6]))
         counts = (self.layer.expert_offsets[1:] - self.layer.expert_offsets[:-1]).cpu()
         active = int((counts > 0).sum())
-        packed_rows = (self.packed is not None and self.cfg.dtype == "bf16" and
-                       self.layer.packed_plan(self.T * self.cfg.k, self.cfg.E, self.cfg.d_model,
-                                              self.cfg.d_ff, k=self.cfg.k)[0] and
-                       not self.layer.gathers_packed(self.T * self.cfg.k, self.cfg.E, self.cfg.d_ff))
-        work = algorithmic_work(self.cfg, self.T, active, rows_materialised=packed_rows)
+        packed_up = gathered = False
+        if self.packed is not None:
+            packed_up, _, gathered = gate_up_plan(self.cfg, self.T, self.draft_remap is not None)
+        work = algorithmic_work(self.cfg, self.T, active, rows_materialised=packed_up and not gathered)
         kernels = {}
         for n in KERNELS:
             ms = statistics.median(per[n])
@@ -295,17 +294,25 @@ class LayerRun:
             kernels[n] = e
         return {"ms_per_step": wall_ms, "ms_per_step_median": statistics.median(whole),
                 "ms_per_step_back_to_back": b2b_ms, "ms_per_step_back_to_back_median": b2b_median,
-                "kernels": kernels, "active_experts": active, "packed_up": bool(packed_rows),
+                "kernels": kernels, "active_experts": active, "packed_up": packed_up,
                 "max_rows_per_expert": int(counts.max()), "min_rows_per_expert": int(counts.min())}
+
+
+def gate_up_plan(cfg, T, draft=False):
+    """MoEVerifyLayer's plan, with packed weights: (gate/up packed, down packed, rows gathered by gate/up)."""
+    import paper_2604_10152_amd as sm
+    rows = T * cfg.k
+    if cfg.dtype != "bf16":
+        return False, False, False
+    up, down = sm.MoEVerifyLayer.packed_plan(rows, cfg.E, cfg.d_model, cfg.d_ff, few_experts=draft, k=cfg.k)
+    return up, down, down and sm.MoEVerifyLayer.gathers_packed(rows, cfg.E, cfg.d_ff)
 
 
 def packed_weights_for(sm, torch, cfg, L, T, row_major=False):
     """Tile-packed copies of the expert weights if the layer runs any projection of a T-token
     batch on them (one-time re-layout, outside every timed region: the weights are resident model
     parameters); None otherwise."""
-    if cfg.dtype != "bf16" or row_major:
-        return None
-    if not sm.MoEVerifyLayer.packed_plan(T * cfg.k, cfg.E, cfg.d_model, cfg.d_ff, k=cfg.k)[0]:
+    if row_major or not gate_up_plan(cfg, T)[0]:
         return None
     packed = sm.MoEVerifyLayer.pack_weights(L["w_gate"], L["w_up"], L["w_down"])
     torch.cuda.synchronize()
@@ -321,8 +328,7 @@ def few_wide_tiles(rows, E, n_out, wide):
 
 def kernel_name(cfg, T, packed=True):
     """Which gate/up kernel runs for this shape (names for the report): the rules of
-    launch_expert_up_bf16 and launch_expert_up_bf16_packed_x."""
-    import paper_2604_10152_amd as sm
+    launch_expert_up_bf16, launch_expert_up_bf16_packed_x and launch_expert_up_bf16_packed."""
     if cfg.dtype != "bf16":
         return "grouped_gemm_f32_kernel<true> (gate/up + SwiGLU)"
     rows = T * cfg.k
@@ -330,10 +336,13 @@ def kernel_name(cfg, T, packed=True):
     tile = 320 if large else 192
     few, tiles = few_wide_tiles(rows, cfg.E, cfg.d_ff, 128)
     if packed:
-        up, down = sm.MoEVerifyLayer.packed_plan(rows, cfg.E, cfg.d_model, cfg.d_ff, k=cfg.k)
+        up, down, gathered = gate_up_plan(cfg, T)
         if up:
             narrow = down and few and (tiles <= 64 or 115 * rows <= 12800 * cfg.E)
             form = "128,128" if narrow else f"{tile},256"
+            if gathered:
+                return (f"grouped_gemm_bf16_pipe16_kernel<PipeCfg<{form},32,4,2,4,true>,PB> (gate/up + SwiGLU "
+                        "on tile-packed weights, the token rows gathered by the kernel)")
             return (f"grouped_gemm_bf16_pipe16_kernel<PipeCfg<{form},32,4,2,4,true>,PA,PB> (gate/up + "
                     "SwiGLU on tile-packed operands: the permute step writes the dispatched rows "
                     "tile-packed)")

@@ -244,3 +244,16 @@ def test_packed_plan_holds_for_few_active_experts():
         assert plan(rows, 16, 5120, 8192, 1) == (rows >= 20, False)
     assert plan(48, 16, 5120, 8192, 1) == (True, False) and plan(96, 16, 5120, 8192, 1) == (True, True)
     assert plan(56, 8, 4096, 14336, 2) == (True, True) and plan(1, 64, 2048, 1408, 6) == (True, True)
+
+
+def test_bench_names_the_gate_up_kernel_that_runs():
+    """A layer that gathers its rows runs the packed kernel as well, without rows written first."""
+    import bench
+    from workloads import synth
+    cfg = synth.MoEConfig("fine", "bf16", 2048, 1408, 64, 6, 64, 4, 1.0, 0.02, 1.0)
+    assert bench.gate_up_plan(cfg, 320) == (True, True, True)
+    assert "gathered by the kernel" in bench.kernel_name(cfg, 320)
+    big = synth.MoEConfig("big", "bf16", 4096, 14336, 8, 2, 256, 7, 1.0, 0.02, 1.0)
+    assert bench.gate_up_plan(big, 2048) == (True, True, False) and ",PA,PB>" in bench.kernel_name(big, 2048)
+    assert bench.gate_up_plan(big, 80) == (True, False, False)
+    assert bench.kernel_name(cfg, 320, packed=False).startswith("grouped_up_bf16_kernel")
