@@ -411,10 +411,13 @@ __global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
 // At equal rounds mid is ahead only for long contractions from about 88 rows on (5120 x 8192, 16
 // experts: 92 rows 550 / 530, 110 rows 575 / 546; 52 rows 490 / 502), and where a short one leaves the
 // ring's second round at most half full (2048 x 1408, 16 of 64 experts active, 40 rows each: 43 / 33).
-// From 48 rows on the tile order goes by groups of n-tiles (tile_map.h) from 48 ring tiles per expert: expert-major / in groups of 8 (4
-// below 96), us: 16 x 5120 x 8192, 62 rows under a Zipf exponent of 0.5 600 / 555, 128 rows 688 / 650, 88 even rows
-// 575 / 561; 8 x 4096 x 14336, 83 rows 395 / 365; 32 x 2048 x 4096, 100 rows 258 / 243; 20 x 4096 x 3072, 150 rows, 1.1 290 /
-// 271.  With fewer it loses as often: 64 x 2048 x 1408, 94 rows 193 / 198.
+// The tile order goes by groups of n-tiles (tile_map.h) from 48 ring tiles per expert: with 1536 in all (six rounds of the
+// chip) from 48 rows on, with fewer from 96.  Expert-major / in groups of 8 (4 below 96), us, means over three
+// seeds, under an exponent of 1.1, of 0.5 and even: 16 x 5120 x 8192, 50 rows 530 / 515, 516 / 484, 482 / 479, 100 rows 664 / 614, 636 / 604, 544 /
+// 539; 8 x 4096 x 14336, 64 rows 364 / 344, 361 / 324, 343 / 317; 16 x 4096 x 4096, 100 rows 278 / 253, 226 / 225, 212 / 207.  With fewer
+// tiles and rows an even batch reads the token rows on more dies for nothing (16 x 2048 x 3072, 50 rows 82 / 79, 70 / 72, 73 / 80, 100
+// rows 104 / 100, 100 / 97, 89 / 90; 12 x 2048 x 6144, 50 rows 106 / 110, 107 / 110, 113 / 120, 180 rows 189 / 182, 171 / 159, 165 / 161).
+// With fewer tiles per expert it loses as often: 64 x 2048 x 1408, 94 rows 193 / 198.
 // Below 60 rows per expert a mid tile of a hot expert outlasts the round it saves (4096 x 8192, 8 experts,
 // 52 rows, exponent 1.1: 201 / 254).
 hipError_t launch_expert_up_bf16_ring_or_mid(const bf16_t* x_perm, const int32_t* offsets,
@@ -429,7 +432,8 @@ hipError_t launch_expert_up_bf16_ring_or_mid(const bf16_t* x_perm, const int32_t
     const int mid_if_less = (long long)n_rows >= 60ll * E;
     const int mid_if_equal = d >= 4096 && (long long)n_rows >= 88ll * E;
     const long long NR = (f + UpRing::BN_OUT - 1) / UpRing::BN_OUT;
-    const int group = (long long)n_rows < 48ll * E ? 0 : NR >= 96 ? 8 : NR >= 48 ? 4 : 0;
+    const int min_rows = E * NR >= 1536 ? 48 : 96;
+    const int group = (long long)n_rows < (long long)min_rows * E ? 0 : NR >= 96 ? 8 : NR >= 48 ? 4 : 0;
     const long long grid = grid_upper_bound(n_rows, E, UpRing::BM, NR);
     hipLaunchKernelGGL(grouped_up_bf16_kernel, dim3((unsigned)grid), dim3(UpRing::THREADS),
                        UpRing::LDS_BYTES, s, x_perm, offsets, wg, wu, E, f, d, h, row_src, topk,
@@ -463,9 +467,12 @@ hipError_t launch_expert_down_bf16_small(const bf16_t* h, const int32_t* offsets
 // its rows are spread, which only the device knows.  Measured, us, 128 / 192 rows (rounds): 12 experts x
 // 2048 x 3072, 130 rows each 59 (2) / 44 (1); 4096 x 14336, 8 experts, 120 rows 301 (2) / 198 (1), two
 // active with 440 rows each 112 (1) / 128 (1), under a Zipf exponent of 1.1 253 (2) / 296 (2).
-// Tile order by groups of four n-tiles (tile_map.h), us, expert-major / in groups: 64 x 1408 x 2048, 120 rows under an
-// exponent of 1.1 125 / 116, even 108 / 105; 16 x 8192 x 5120, 128 rows 343 / 327, 88 even rows 284 / 269; 20 x 3072 x
-// 4096, 150 rows 172 / 145; 8 x 14336 x 4096, 83 rows 204 / 203.
+// Tile order by groups of four n-tiles (tile_map.h) where the weight tiles take more than one round of the chip.  us,
+// contraction x outputs, expert-major / in groups (means over three seeds), under an exponent of 1.1, of 0.5 and even: 64 experts x 1408 x
+// 2048, 180 rows 138 / 131, 125 / 124, 120 / 117; 16 x 8192 x 5120, 100 rows 272 / 277, 270 / 267, 272 / 266, 180 rows 392 / 356, 373 / 356,
+// 328 / 328; 20 x 3072 x 4096, 180 rows 151 / 145, 154 / 140, 150 / 142.  With 256 weight tiles or fewer an even batch reads
+// the rows of h on more dies for nothing (16 x 4096 x 2048, 62 rows 76 / 70, 66 / 71, 61 / 73; 8 x 14336 x 4096, 100 rows 257 / 233, 195 / 199,
+// 177 / 179).
 constexpr int kDownGroup = 4;
 
 hipError_t launch_expert_down_bf16_mid(const bf16_t* h, const int32_t* offsets, const bf16_t* wd,
@@ -479,7 +486,7 @@ hipError_t launch_expert_down_bf16_mid(const bf16_t* h, const int32_t* offsets, 
     const long long NT = (d + DownMid::BN_OUT - 1) / DownMid::BN_OUT;
     const long long grid = grid_upper_bound(n_rows, E, DownMid::BM, NT);
     hipLaunchKernelGGL(grouped_down_bf16_mid_kernel, dim3((unsigned)grid), dim3(DownTall::THREADS),
-                       DownTall::LDS_BYTES, s, h, offsets, wd, E, d, f, y, kDownGroup);
+                       DownTall::LDS_BYTES, s, h, offsets, wd, E, d, f, y, E * NT > kCus ? kDownGroup : 0);
     return hipGetLastError();
 }
 

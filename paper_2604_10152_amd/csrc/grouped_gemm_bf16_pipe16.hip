@@ -35,9 +35,11 @@ __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe16_kernel(
 
 // n-tiles per group of the tile order (tile_map.h) for gate/up batches spread unevenly over the experts.  Measured,
 // packed operands, us, expert-major / in groups: 16 x 5120 x 8192, 128 rows per expert on average 578 / 523, 62
-// rows 540 / 480; 8 x 4096 x 14336, 375 rows under a Zipf exponent of 1.1 710 / 617, 86 rows, 0.5 434 / 427.  With
-// fewer rows or n-tiles it loses as often (64 x 2048 x 1408: 30 rows 108 / 113, 192 rows 209 / 197 to 208 / 217,
-// by which die gets which expert), and so it does in the down projection (16 x 8192 x 5120 297 / 288 to 317).
+// rows 540 / 480; 8 x 4096 x 14336, 375 rows under a Zipf exponent of 1.1 710 / 617, 86 rows, 0.5 434 / 427.  The line at 24 n-tiles
+// (means over three seeds, exponents of 1.1 and 0.5; 16 x 2048): 28 n-tiles, 100 rows 110 / 103, 87 / 90, 200 rows 145 / 132, 113 / 109; 24,
+// 62 rows 75 / 75, 71 / 71, 200 rows 105 / 103, 103 / 99; 20, 100 rows 75 / 73, 74 / 76, 200 rows 99 / 94, 96 / 91; 12, 200 rows 54 / 56,
+// 51 / 52.  With fewer rows it loses as often (64 x 2048 x 1408, 30 rows 108 / 113), and so it does in the down projection (16 x
+// 8192 x 5120 297 / 288 to 317).
 template <typename C>
 int tile_group(int n_rows, int E, int N) {
     return C::SWIGLU && N >= 24 * C::BN_OUT && (long long)n_rows >= 60ll * E ? 8 : 0;

@@ -1052,6 +1052,36 @@ def test_packed_tile_order(d, f, rows):
             assert float(err.max()) <= 1e-2, (e, float(err.max()))      # NaN fails as well
 
 
+@pytest.mark.parametrize("rows", [
+    [0, 193, 600, 1, 192, 385] + [90] * 26,          # both projections in groups of four n-tiles, a last one of one
+    [130, 64, 0, 300, 1, 100],                       # fewer tiles: expert-major
+])
+def test_row_major_tile_order(rows):
+    """Every tile of the row-major GEMMs is computed once and in its place, against fp32 products."""
+    d, f, E, n = 2176, 3136, len(rows), sum(rows)
+    _say(f"row-major tile order E={E} rows={n}")
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(E)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    xp = (rnd(n, d) / d ** 0.5).to(torch.bfloat16)
+    wg, wu = ((rnd(E, f, d) * 0.5).to(torch.bfloat16) for _ in range(2))
+    wd = (rnd(E, d, f) * (0.5 / f ** 0.5)).to(torch.bfloat16)
+    doff = dev(torch.from_numpy(off))
+    h = torch.full((n, f), float("nan"), dtype=torch.bfloat16, device="cuda")
+    y = torch.full((n, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sm.moe_expert_up_swiglu(xp, doff, wg, wu, h)
+    sm.moe_expert_down(h, doff, wd, y)
+    for e, r in enumerate(rows):
+        s = slice(int(off[e]), int(off[e + 1]))
+        if not r:
+            continue
+        x = xp[s].float()
+        want = torch.nn.functional.silu(x @ wg[e].float().t()) * (x @ wu[e].float().t())
+        for got, ref in ((h[s], want), (y[s], h[s].float() @ wd[e].float().t())):
+            err = (got.float() - ref).abs().amax(1) / ref.abs().amax(1)
+            assert float(err.max()) <= 1e-2, (e, float(err.max()))      # NaN fails as well
+
+
 def test_layer_cfg4_packed_path():
     """The benchmark workload on the tile-packed path: same routing, output bit-identical to the
     row-major path (same kernels' arithmetic in the same order)."""
