@@ -441,6 +441,49 @@ def test_affinity_table_structured_residuals(E, d, f, kind):
     np.testing.assert_allclose(got, want, rtol=2.0 ** -24 + 2.0 ** -27, atol=0)
 
 
+@pytest.mark.parametrize("E,d,f", [(9, 520, 561), (17, 376, 401), (33, 264, 288), (64, 512, 128)])
+def test_affinity_table_integer_products_non_finite(E, d, f):
+    """The integer form with infinite and NaN weights, in expert 0, in the middle and in the last row block, in the
+    first columns and in the last (ragged) unit: exactly the pairs of their experts are reached."""
+    assert E * d * f >= 2500000
+    _say(f"affinity, integer products, non-finite E={E} d={d} f={f}")
+    wg, wu, wd = _weights(E, d, f, torch.bfloat16, seed=E, planted=False)
+    want = orc.affinity_table(f64(wg), f64(wu), f64(wd))
+    for bad in (float("inf"), -float("inf"), float("nan")):
+        for e, at in ((0, (0, 0)), (E // 2, (f - 1, d - 1)), (E - 1, (f // 2, d // 2))):
+            w2 = wu.clone()
+            w2[(e,) + at] = bad
+            got = _gpu_affinity(wg, w2, wd)
+            hit = np.zeros((E, E), dtype=bool)
+            hit[e, :] = hit[:, e] = True
+            hit[e, e] = False
+            assert np.array_equal(~np.isfinite(got), hit), (bad, e)
+            assert np.all(got[hit] == np.inf) if np.isinf(bad) else np.all(np.isnan(got[hit]))
+            np.testing.assert_allclose(got[~hit], want[~hit], rtol=EXACT_RTOL, atol=0)
+    w2 = wu.clone()
+    w2[1, 3, 5] = w2[E - 1, 4, 6] = float("inf")       # two experts, at different places: infinite
+    w2[2, 7, 9] = w2[3, 7, 9] = float("inf")           # at the same place: no difference
+    got = _gpu_affinity(wg, w2, wd)
+    assert got[1, E - 1] == np.inf and got[1, 2] == np.inf and np.isnan(got[2, 3])
+    ok = [e for e in range(E) if e not in (1, 2, 3, E - 1)]
+    np.testing.assert_allclose(got[np.ix_(ok, ok)], want[np.ix_(ok, ok)], rtol=EXACT_RTOL, atol=0)
+
+
+def test_affinity_table_integer_products_long_sums():
+    """More columns per team than the int32 sums hold (28672), all products of one sign."""
+    E, d, f = 9, 4096, 14336
+    assert 3 * d * f > 256 * 16 * 28672
+    _say(f"affinity, integer products, long sums E={E} d={d} f={f}")
+    g = torch.Generator(device="cuda").manual_seed(1)
+    W = [torch.rand(s, generator=g, device="cuda", dtype=torch.bfloat16) + 1 for s in ((E, f, d), (E, f, d), (E, d, f))]
+    table = torch.empty((E, E), dtype=torch.float32, device="cuda")
+    ws = torch.empty((sm.moe_affinity_table_workspace_bytes(E),), dtype=torch.uint8, device="cuda")
+    sm.moe_affinity_table(*W, table, ws)
+    for i, j in ((0, 1), (0, 8), (3, 8), (5, 6)):
+        sq = sum(float((w[i].double() - w[j].double()).square_().sum()) for w in W)
+        assert abs(float(table[i, j]) - sq ** 0.5) <= EXACT_RTOL * sq ** 0.5, (i, j)
+
+
 def _many_close(kind, wg, wu, wd):
     E = wg.shape[0]
     for w in (wg, wu, wd):
