@@ -43,14 +43,16 @@ class MoEVerifyLayer:
     # 128 tiles of 256 outputs: 8 experts x 4096 outputs, 65 rows each 156 us against 173 row-major;
     # 16 x 5120, 75 rows 287 against 264).
     # Only the device knows how many experts a batch meets: at least k, however many rows there are.  Below 48 rows gate/up
-    # goes packed where it is ahead for few of them as well: at least 8192 outputs and 256 tiles of 128, and from 20 rows or
-    # where k experts have 192 of them (layer, us, row-major / packed gate/up, by active experts: 8 x 4096 x 14336, 8 rows all 457 / 454, 4
-    # 295 / 251, 2 164 / 143, 24 rows 483 / 469, 341 / 293, 223 / 202; 16 x 5120 x 8192, 20 rows all 673 / 662, 2 186 / 181, 1 160 / 155,
-    # but 14 rows, 2 153 / 171, 1 112 / 137; 16 x 4096 x 4096, 24 rows all 290 / 302, 2 79 / 109).  The packed down
-    # projection has no form for few experts (row-major / packed, gate/up packed: 8 x 4096 x 14336, 8 rows all 454 / 449, 4 251 / 287, 2
-    # 143 / 206; 16 x 2048 x 8192, 8 rows all 292 / 271, 8 156 / 182, 2 69 / 112), so its lines stay above.
+    # goes packed where it is ahead for few of them as well: at least 8192 outputs and 256 tiles of 128, and from 20 rows, or from
+    # 4 where k experts have 192 tiles (layer, us, row-major / packed gate/up, by active experts: 8 x 4096 x 14336, 4 rows all 453 /
+    # 450, 7 437 / 444, 6 377 / 356, 5 318 / 325, 4 254 / 242, 3 205 / 215, 2 137 / 136, 20 rows all 470 / 458, 40 rows 488 / 476, but one row, 5
+    # active 296 / 313; 16 x 5120 x 8192, 20 rows all 673 / 662, 2 186 / 181, 1 160 / 155, but 14 rows, 2 153 / 171, 1 112 / 137;
+    # 16 x 4096 x 4096, 24 rows all 290 / 302, 2 79 / 109).  The packed down projection has no form for few experts (row-major /
+    # packed, gate/up packed: 8 x 4096 x 14336, 8 rows all 454 / 449, 4 251 / 287, 2 143 / 206; 16 x 2048 x 8192, 8 rows all 292 / 271, 8
+    # 156 / 182, 2 69 / 112), so its lines stay above.
     PACKED_UP_MIN_ROWS = 48
     PACKED_UP_MIN_ROWS_WIDE = 20
+    PACKED_UP_MIN_ROWS_ACTIVE = 4
     PACKED_UP_WIDE = 8192
     PACKED_UP_MIN_TILES = 256
     PACKED_UP_MIN_TILES_ACTIVE = 192
@@ -68,7 +70,7 @@ class MoEVerifyLayer:
         tiles = -(-d_ff // 128)                  # of 128 gate/up outputs, per expert
         if not few_experts and d_ff >= cls.PACKED_UP_WIDE and E * tiles >= cls.PACKED_UP_MIN_TILES:
             up = up or n_pairs >= cls.PACKED_UP_MIN_ROWS_WIDE * E or (
-                n_pairs >= E and k * tiles >= cls.PACKED_UP_MIN_TILES_ACTIVE)
+                n_pairs >= cls.PACKED_UP_MIN_ROWS_ACTIVE * E and k * tiles >= cls.PACKED_UP_MIN_TILES_ACTIVE)
         return up, down
 
     # Packed gate/up: rows gathered by the GEMM itself (64-byte requests, once per 128 outputs), or written
@@ -143,6 +145,7 @@ class MoEVerifyLayer:
                 self.row_src, self.row_of, self.x_packed, self.h_packed if down_packed else self.h,
                 self.y_perm, out, stream)
             return out
+        # with marks, or x_perm written first: the same steps and layouts as calls of their own
         if marks is not None:
             marks[0].record(stream)
         if draft_remap is None:

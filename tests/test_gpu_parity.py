@@ -1125,7 +1125,8 @@ def test_layer_packed_plans(name, cfg, plan):
 
 @pytest.mark.parametrize("d,f,E,k,B,plan,draft_plan", [
     (64, 4096, 112, 2, 19, (True, False), (True, False)),       # the down projection goes by rows alone
-    (4096, 8192, 4, 3, 1, (True, False), (False, False)),       # 192 gate/up tiles for three experts
+    (4096, 8192, 4, 3, 2, (True, False), (False, False)),       # 192 gate/up tiles for three experts, 18 pairs
+    (4096, 8192, 4, 3, 1, (False, False), (False, False)),      # 9 pairs
     (4096, 8192, 4, 2, 13, (False, False), (False, False)),     # 128 for two, 78 pairs
     (4096, 8192, 4, 2, 14, (True, False), (False, False)),      # 84 pairs
 ])
