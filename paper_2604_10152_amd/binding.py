@@ -127,9 +127,9 @@ def _ptr(t, dtype=None, name="tensor"):
 
 
 def _stream(stream):
-    """Raw handle of `stream`, or of the current device's current stream.  A layer is five calls of
-    a few microseconds of device work each, so the handle is taken without building the stream
-    object and its device first (about 2 us per call)."""
+    """Raw handle of `stream`, or of the current device's current stream.  A call is a few microseconds of
+    device work in small layers, so the handle is taken without building the stream object and its device
+    first (about 2 us per call)."""
     if stream is None:
         return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream

@@ -17,7 +17,7 @@
 // commutative, so two experts with identical router rows get bit-identical logits and the tie
 // goes to the lower id.  The W wave totals are added in fixed order.  Wave t then ranks token
 // t, the E logits sitting in LDS.  It is a chain of latencies: the columns are requested one step ahead,
-// the bias and the substitution at the start, the lanes exchange in registers: 64 experts x 2048, 64 tokens
+// the bias and (up to 64 experts) the substitution at the start, the lanes exchange in registers: 64 experts x 2048, 64 tokens
 // 11.0 -> 8.9 us, 320 tokens 13.4 -> 11.0 (4 of these the fp64 work of one CU, 2.5 the launch).
 #include "common.h"
 
