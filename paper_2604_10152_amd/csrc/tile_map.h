@@ -87,8 +87,8 @@ enum class From { workgroup, counted, place };
 // busy: a batch of 3.5 rounds takes 3.5 rounds' time and not 4.  More halves than that would start a
 // second round of them.  Measured, packed operands, us, whole / half: gate/up 8 x 4096 x 14336 (896 tiles): 83 rows
 // each 372 / 364, 150 rows 397 / 383, 250 rows 457 / 442; down 16 x 8192 x 5120 (320 tiles), 88 rows 276 / 260; 200 rows
-329 / 299 under a Zipf exponent of 0.5.  A hot expert's tile in halves at the end may cost more than it saves: the same, 30
-rows under an exponent of 1.1 233 / 253 (a size that the layer runs row-major); gate/up 16 x 4096 x 4096, 200 rows 260 / 268.
+// 329 / 299 under a Zipf exponent of 0.5.  A hot expert's tile in halves at the end may cost more than it saves: the same, 30
+// rows under an exponent of 1.1 233 / 253 (a size that the layer runs row-major); gate/up 16 x 4096 x 4096, 200 rows 260 / 268.
 // Halving every unfinished round: the same where it is under half full, 64 x 2048 x 1408 109 -> 123.  For
 // contractions from kTailMinK on: below (64 x 2048 x 1408, 94 rows 145.7 / 146.5) the surplus workgroups cost as much.
 constexpr int kCusPerXcd = kCus / kXcds;
