@@ -151,6 +151,13 @@ inline bool few_wide_tiles(int n_rows, int E, int N, int wide) {
     return WideTiles(n_rows, E, N, wide).few();
 }
 
+// Whether the expert GEMMs store with the non-temporal hint.  What they write is read by the next kernel, from any die,
+// and until then every line of it takes the place of operands in the L2.  Measured, packed operands, us, without / with the hint
+// (bytes written): gate/up 8 x 4096 x 14336, 175 rows each (40 MB) 377 / 359, 83 rows (19 MB) 339 / 334, 64 x 2048 x 1408, 120
+// rows (22 MB) 171 / 165; down, the same, 60 rows (16 MB) 71 / 66.  A small output stays in the L2: gate/up, 6 rows (1 MB) 30.7 / 31.1, 30
+// rows (5 MB) 109.5 / 110.4; down, 6 rows (1.6 MB) 42.0 / 42.7, but 30 rows (8 MB) 62.2 / 61.0.
+inline bool streams_output(int n_rows, int N) { return (long long)n_rows * N * 2 >= (6ll << 20); }
+
 // ---- launchers (host side, defined in the .hip files) -------------------------------
 hipError_t launch_route_topk(const void* x, const void* wr, const float* bias, int T, int d,
                              int E, int k, int renorm, int dtype, int32_t* idx, float* w,

@@ -38,7 +38,8 @@ __device__ __forceinline__ void pipe_tile(
     const bf16_t* __restrict__ W0,       // [E, N, K]   (gate, or down)
     const bf16_t* __restrict__ W1,       // [E, N, K]   (up; SWIGLU only)
     int N, int K, bf16_t* __restrict__ Cout /* [n_rows, N] */,
-    const int32_t* __restrict__ row_src /* nullable: A row r is A[row_src[r] / topk] */, int topk) {
+    const int32_t* __restrict__ row_src /* nullable: A row r is A[row_src[r] / topk] */, int topk,
+    bool stream_out /* streams_output() */) {
     static_assert(!C::SWIGLU || ((C::BN / 2 / C::ROWS_PER_DMA) % C::NWAVES == 0 && C::TN % 2 == 0),
                   "gate/up halves must split on a wave-load round and pair up inside a wave");
     const int row0 = t.row0, tile_rows = t.tile_rows;
@@ -215,20 +216,19 @@ __device__ __forceinline__ void pipe_tile(
         // 8g + 4*(lane/32) + r%4, i.e. 8 bytes of bf16.
         //  - SwiGLU tile (BN/2 = 64 output columns): the 8-byte pieces go to an LDS image of the tile
         //    and the workgroup then writes whole 128-byte rows.
-        //  - plain tile: 8-byte stores straight to global memory (y is small).
+        //  - plain tile: lanes l and l ^ 32 exchange halves of two g, so a lane stores 8 columns (without the
+        //    hint: the row-major down projection is level or 2 % behind with it).
         const int row = lane & 31, chalf = (lane >> 5) * 4;
         if (C::SWIGLU) __builtin_amdgcn_s_barrier();   // every wave's loads have landed: LDS is free
 #pragma unroll
         for (int i = 0; i < TA; ++i) {
-            const int trow = 32 * (wm + C::WM * i) + row;
+            const int sub = 32 * (wm + C::WM * i), trow = sub + row;
             if (!C::SWIGLU && trow >= tile_rows) continue;
-            bf16_t* crow = Cout + (size_t)(row0 + trow) * N;
             constexpr int JN = C::SWIGLU ? C::TN / 2 : C::TN;
 #pragma unroll
             for (int j = 0; j < JN; ++j) {
-                const int ctile = 32 * (wn * JN + j) + chalf;     // column inside the tile
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
+                const int c0 = 32 * (wn * JN + j);                // first column inside the tile
+                auto value = [&](int g) __attribute__((always_inline)) -> uint2 {
                     float v[4];
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
@@ -239,19 +239,20 @@ __device__ __forceinline__ void pipe_tile(
                             v[q] = acc[i][j][4 * g + q];
                         }
                     }
-                    const uint2 pk = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-                    if (C::SWIGLU) {
-                        *reinterpret_cast<uint2*>(lds_raw + trow * kStageRowBytes +
-                                                  (ctile + 8 * g) * 2) = pk;
-                    } else {
-                        const int col = n0 + ctile + 8 * g;
-                        if (col + 3 < N) {
-                            *reinterpret_cast<uint2*>(crow + col) = pk;
-                        } else {
+                    return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+                };
+                if (C::SWIGLU) {
 #pragma unroll
-                            for (int q = 0; q < 4; ++q)
-                                if (col + q < N) crow[col + q] = (bf16_t)v[q];
-                        }
+                    for (int g = 0; g < 4; ++g)
+                        *reinterpret_cast<uint2*>(lds_raw + trow * kStageRowBytes + (c0 + chalf + 8 * g) * 2) = value(g);
+                } else if (n0 + c0 < N) {                         // N is a multiple of 64
+#pragma unroll
+                    for (int g = 0; g < 4; g += 2) {
+                        uint2 a = value(g), b = value(g + 1);
+                        lane_swap<32>(a.x, b.x);
+                        lane_swap<32>(a.y, b.y);
+                        store16(false, Cout + (size_t)(row0 + sub) * N + n0 + c0,
+                                (uint32_t)(row * N + 8 * g + 2 * chalf) * 2u, U128{a.x, a.y, b.x, b.y});
                     }
                 }
             }
@@ -290,13 +291,8 @@ __device__ __forceinline__ void pipe_tile(
         const int col = n0 + cc * 8;
         for (int r = cr; r < tile_rows; r += RPP) {
             const U128 v = *reinterpret_cast<const U128*>(lds_raw + r * kStageRowBytes + cc * 16);
-            bf16_t* dst = Cout + (size_t)(row0 + r) * N + col;
-            if (col + 7 < N) {
-                *reinterpret_cast<U128*>(dst) = v;
-            } else {
-                for (int q = 0; q < 8; ++q)
-                    if (col + q < N) dst[q] = reinterpret_cast<const bf16_t*>(&v)[q];
-            }
+            if (col < N)                                    // N is a multiple of 64
+                store16(stream_out, Cout + (size_t)row0 * N, (uint32_t)(r * N + col) * 2u, v);
         }
     }
 }
@@ -321,7 +317,7 @@ __global__ __launch_bounds__(DownSmall::THREADS) void grouped_down_bf16_small_ke
     if (stream::stream_few(streams, N))
         stream::stream_tiles(lds_raw, h, offsets, wd, E, N, K, y, streams);
     else if (locate<Ring, From::counted>(offsets, E, NT, blockIdx.x, mt[1], t))
-        pipe_tile<DownSmall>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
+        pipe_tile<DownSmall>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1, false);
 }
 
 // Down projection from tens of rows per expert on: 128-row tiles, or 192-row ones if the chip then
@@ -343,9 +339,9 @@ __global__ __launch_bounds__(DownTall::THREADS) void grouped_down_bf16_mid_kerne
     TileLoc t;
     if (tile_rounds(mt[1], NT) < tile_rounds(mt[0], NT)) {
         if (locate<Tall, From::counted>(offsets, E, NT, blockIdx.x, mt[1], t, group))
-            pipe_tile<DownTall>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
+            pipe_tile<DownTall>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1, false);
     } else if (locate<Mid, From::counted>(offsets, E, NT, blockIdx.x, mt[0], t, group)) {
-        pipe_tile<DownMid>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
+        pipe_tile<DownMid>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1, false);
     }
 }
 
@@ -358,7 +354,7 @@ __global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets,
     const bf16_t* __restrict__ wg, const bf16_t* __restrict__ wu, int E, int N, int K,
     bf16_t* __restrict__ h, const int32_t* __restrict__ row_src, int topk, int mid_if_less,
-    int mid_if_equal, int group) {
+    int mid_if_equal, int group, int stream_out) {
     static_assert(UpRing::THREADS == UpMid::THREADS && UpRing::LDS_BYTES >= UpMid::LDS_BYTES,
                   "one launch serves both");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
@@ -390,9 +386,9 @@ __global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
     TileLoc t;
     if (mid) {
         if (locate<Mid, From::counted>(offsets, E, NM, blockIdx.x, mt[1], t, group))
-            pipe16_tile<UpMid>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk);
+            pipe16_tile<UpMid>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk, stream_out);
     } else if (locate<Ring, From::counted>(offsets, E, NR, blockIdx.x, mt[0], t, group)) {
-        pipe_tile<UpRing>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk);
+        pipe_tile<UpRing>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk, stream_out);
     }
 }
 
@@ -437,7 +433,7 @@ hipError_t launch_expert_up_bf16_ring_or_mid(const bf16_t* x_perm, const int32_t
     const long long grid = grid_upper_bound(n_rows, E, UpRing::BM, NR);
     hipLaunchKernelGGL(grouped_up_bf16_kernel, dim3((unsigned)grid), dim3(UpRing::THREADS),
                        UpRing::LDS_BYTES, s, x_perm, offsets, wg, wu, E, f, d, h, row_src, topk,
-                       mid_if_less, mid_if_equal, group);
+                       mid_if_less, mid_if_equal, group, (int)streams_output(n_rows, f));
     return hipGetLastError();
 }
 

@@ -14,7 +14,8 @@ template <typename C, bool PA, bool PB, bool PO, bool SHARE>
 __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe16_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets,
     const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int E, int N, int K,
-    bf16_t* __restrict__ Cout, const int32_t* __restrict__ row_src, int topk, int group) {
+    bf16_t* __restrict__ Cout, const int32_t* __restrict__ row_src, int topk, int group,
+    int stream_out) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
     TileLoc t;
     const bool halves = kHalves<C, PB, PO> && K >= kTailMinK;
@@ -26,11 +27,11 @@ __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_pipe16_kernel(
             typedef PipeCfg<C::BM, C::BN / 2, C::BK, C::STAGES, C::WM, C::WN, C::SWIGLU> Half;
             t.nt = 2 * t.nt + t.half;
             if (t.nt * Half::BN_OUT < N)
-                pipe16_tile<Half, PA, PB, PO>(lds_raw, t, A, W0, W1, N, K, Cout, row_src, topk);
+                pipe16_tile<Half, PA, PB, PO>(lds_raw, t, A, W0, W1, N, K, Cout, row_src, topk, stream_out);
             return;
         }
     }
-    pipe16_tile<C, PA, PB, PO>(lds_raw, t, A, W0, W1, N, K, Cout, row_src, topk);
+    pipe16_tile<C, PA, PB, PO>(lds_raw, t, A, W0, W1, N, K, Cout, row_src, topk, stream_out);
 }
 
 // n-tiles per group of the tile order (tile_map.h) for gate/up batches spread unevenly over the experts.  Measured,
@@ -59,7 +60,7 @@ hipError_t launch_pipe16_form(const bf16_t* A, const int32_t* offsets, const bf1
                            (kHalves<C, PB, PO> && K >= kTailMinK ? kTailBlocks : 0);
     hipLaunchKernelGGL((grouped_gemm_bf16_pipe16_kernel<C, PA, PB, PO, SHARE>), dim3((unsigned)grid),
                        dim3(C::THREADS), C::LDS_BYTES, s, A, offsets, W0, W1, E, N, K, Cout,
-                       row_src, topk, group);
+                       row_src, topk, group, (int)streams_output(n_rows, N));
     return hipGetLastError();
 }
 
@@ -87,7 +88,7 @@ typedef PipeCfg<320, 128, 32, 4, 2, 4, false> DownNarrowTall;
 template <typename Wide>
 __global__ __launch_bounds__(Wide::THREADS) void grouped_down_bf16_packed_few_kernel(
     const bf16_t* __restrict__ h, const int32_t* __restrict__ offsets,
-    const bf16_t* __restrict__ wd, int E, int N, int K, bf16_t* __restrict__ y) {
+    const bf16_t* __restrict__ wd, int E, int N, int K, bf16_t* __restrict__ y, int stream_out) {
     static_assert(Wide::THREADS == DownNarrow::THREADS && Wide::THREADS == DownNarrowTall::THREADS,
                   "one launch serves all");
     static_assert(Wide::LDS_BYTES >= DownNarrow::LDS_BYTES &&
@@ -102,16 +103,16 @@ __global__ __launch_bounds__(Wide::THREADS) void grouped_down_bf16_packed_few_ke
     TileLoc t;
     if (tile_rounds(low[0], NT) == 1) {
         if (locate<Low, From::counted>(offsets, E, NT, blockIdx.x, low[0], t))
-            pipe16_tile<DownNarrow, true, true>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
+            pipe16_tile<DownNarrow, true, true>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1, stream_out);
         return;
     }
     count_mtiles<High, Full>(offsets, E, mt);
     if (tile_rounds(mt[0], NT) == 1) {
         if (locate<High, From::counted>(offsets, E, NT, blockIdx.x, mt[0], t))
-            pipe16_tile<DownNarrowTall, true, true>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
+            pipe16_tile<DownNarrowTall, true, true>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1, stream_out);
     } else if (locate<Full, From::counted>(offsets, E, (N + Wide::BN_OUT - 1) / Wide::BN_OUT,
                                            blockIdx.x, mt[1], t)) {
-        pipe16_tile<Wide, true, true>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1);
+        pipe16_tile<Wide, true, true>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1, stream_out);
     }
 }
 
@@ -127,7 +128,8 @@ hipError_t launch_down_packed_few(const bf16_t* h, const int32_t* offsets, const
     const long long wide = grid_upper_bound(n_rows, E, Wide::BM, (N + Wide::BN_OUT - 1) / Wide::BN_OUT);
     const long long grid = wide > kCus ? wide : kCus;
     hipLaunchKernelGGL(grouped_down_bf16_packed_few_kernel<Wide>, dim3((unsigned)grid),
-                       dim3(Wide::THREADS), Wide::LDS_BYTES, s, h, offsets, wd, E, N, K, y);
+                       dim3(Wide::THREADS), Wide::LDS_BYTES, s, h, offsets, wd, E, N, K, y,
+                       (int)streams_output(n_rows, N));
     return hipGetLastError();
 }
 

@@ -43,7 +43,8 @@ __device__ __forceinline__ void pipe16_tile(
     const bf16_t* __restrict__ W0,       // [E, N, K]   (gate, or down)
     const bf16_t* __restrict__ W1,       // [E, N, K]   (up; SWIGLU only)
     int N, int K, bf16_t* __restrict__ Cout /* [n_rows, N] */,
-    const int32_t* __restrict__ row_src /* nullable: A row r is A[row_src[r] / topk] */, int topk) {
+    const int32_t* __restrict__ row_src /* nullable: A row r is A[row_src[r] / topk] */, int topk,
+    bool stream_out /* streams_output() */) {
     static_assert(C::BK == 32, "a stage is exactly one 16x16x32 k-step");
     constexpr int TM16 = C::BM / (16 * C::WM);       // 16-row A sub-tiles per wave
     constexpr int TN16 = C::BN / (16 * C::WN);       // 16-col B sub-tiles per wave
@@ -153,61 +154,88 @@ __device__ __forceinline__ void pipe16_tile(
 
     const int ta = min(TM16, max(0, (nsub - wm + C::WM - 1) / C::WM));   // active A sub-tiles
 
-    // epilogue: SwiGLU tiles are staged in LDS and written as whole rows by the workgroup,
-    // plain tiles go straight to global memory, 8 bytes (4 columns) per lane.  acc[i] is the
-    // wave's i-th A sub-tile (tile rows 16 * (wm + WM * i) ..).
+    // epilogue: row-major SwiGLU tiles are staged in LDS and written as whole rows by the workgroup; tile-packed ones
+    // and plain tiles go straight to global memory.  acc[i] is the wave's i-th A sub-tile (tile rows
+    // 16 * (wm + WM * i) ..), a lane holds one row and 4 consecutive columns of every sub-tile.  Lanes l and l ^ 16
+    // exchange halves of two sub-tiles (neighbours in columns, or in rows where a wave has one column of them), so a
+    // lane stores 16 bytes: a packed block of 1 KB, or 64 bytes of 16 rows, by one instruction.
     auto epilogue = [&](auto& acc, auto ta_tag) __attribute__((always_inline)) {
-        constexpr int TA = decltype(ta_tag)::value;
+        constexpr int TA = decltype(ta_tag)::value, JN = C::SWIGLU ? TN16 / 2 : TN16;
         wait_vmcnt<0>();                           // no load may outlive the workgroup's LDS
 
         const int mrow = lane & 15, cq = (lane >> 4) * 4;
-        if (C::SWIGLU && !PO) __builtin_amdgcn_s_barrier();   // every wave's loads have landed
+        // the lane's 4 values of sub-tile (i, j)
+        auto value = [&](int i, int j) __attribute__((always_inline)) -> uint2 {
+            float v[4];
 #pragma unroll
-        for (int i = 0; i < TA; ++i) {
-            const int trow = 16 * (wm + C::WM * i) + mrow;
-            if (!C::SWIGLU && trow >= tile_rows) continue;
-            bf16_t* crow = Cout + (size_t)(row0 + trow) * N;
-            constexpr int JN = C::SWIGLU ? TN16 / 2 : TN16;
-#pragma unroll
-            for (int j = 0; j < JN; ++j) {
-                const int ctile = 16 * (wn * JN + j) + cq;            // column inside the tile
-                float v[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (C::SWIGLU) {
-                        const float gt = acc[i][j][q], up = acc[i][j + JN][q];
-                        v[q] = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
-                    } else {
-                        v[q] = acc[i][j][q];
-                    }
-                }
-                const uint2 pk = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-                if (C::SWIGLU && PO) {
-                    // tile-packed h straight from the registers: 16 of the 32 columns of a block of
-                    // row block (wm + WM*i); this lane holds half a 16-byte chunk.  Rows beyond the
-                    // tile's last row (padding of the expert's last block) are written as zeros.
-                    const int col0 = n0 + 16 * (wn * JN + j);
-                    if (col0 < N) {
-                        const int chunk = ((col0 & 31) >> 3) + (cq >> 3);
-                        const int piece = 4 * mrow + (chunk ^ ((mrow >> 1) & 3));
-                        unsigned char* blk = reinterpret_cast<unsigned char*>(
-                            Cout + ((size_t)(t.blk0 + wm + C::WM * i) * 16 * N +
-                                    (size_t)(col0 / 32) * 512));
-                        *reinterpret_cast<uint2*>(blk + piece * 16 + ((cq >> 2) & 1) * 8) =
-                            trow < tile_rows ? pk : make_uint2(0u, 0u);
-                    }
-                } else if (C::SWIGLU) {
-                    *reinterpret_cast<uint2*>(lds_raw + trow * kStageRowBytes + ctile * 2) = pk;
+            for (int q = 0; q < 4; ++q) {
+                if (C::SWIGLU) {
+                    const float gt = acc[i][j][q], up = acc[i][j + JN][q];
+                    v[q] = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
                 } else {
-                    const int col = n0 + ctile;
-                    if (col + 3 < N) {
-                        *reinterpret_cast<uint2*>(crow + col) = pk;
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            if (col + q < N) crow[col + q] = (bf16_t)v[q];
-                    }
+                    v[q] = acc[i][j][q];
                 }
+            }
+            return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+        };
+        if (C::SWIGLU && !PO) {
+            __builtin_amdgcn_s_barrier();          // every wave's loads have landed
+#pragma unroll
+            for (int i = 0; i < TA; ++i)
+#pragma unroll
+                for (int j = 0; j < JN; ++j)
+                    *reinterpret_cast<uint2*>(lds_raw + (16 * (wm + C::WM * i) + mrow) * kStageRowBytes +
+                                              (16 * (wn * JN + j) + cq) * 2) = value(i, j);
+            return;
+        }
+        // Row mrow of sub-tile i, `at` columns behind its first: the address is a uniform base and a lane's
+        // offset that is the same for all sub-tiles.  Columns go on for N, a multiple of 64.
+        auto lane_offset = [&](int at) __attribute__((always_inline)) -> uint32_t {
+            return PO ? (uint32_t)((4 * mrow + ((at >> 3) ^ ((mrow >> 1) & 3))) * 16 + (at & 4) * 2)
+                      : (uint32_t)(mrow * N + at) * 2u;
+        };
+        auto store = [&](auto v, int i, int col, uint32_t offset, int trow) __attribute__((always_inline)) {
+            if (n0 + col >= N) return;
+            const int sub = wm + C::WM * i;
+            unsigned char* base = reinterpret_cast<unsigned char*>(
+                Cout + (PO ? (size_t)(t.blk0 + sub) * 16 * N + (size_t)((n0 + col) / 32) * 512
+                           : (size_t)(row0 + 16 * sub) * N + n0 + col));
+            if (PO) {
+                // rows beyond the tile's last one (padding of the expert's last block) are zeros
+                if (trow >= tile_rows) v = decltype(v){};
+            } else if (trow >= tile_rows) {
+                return;
+            }
+            if constexpr (sizeof(v) == 16) store16(stream_out, base, offset, v);
+            else *reinterpret_cast<decltype(v)*>(base + offset) = v;
+        };
+        const int odd = (lane >> 4) & 1, c8 = (lane >> 5) * 8;
+        auto exchange = [&](uint2 a, uint2 b) __attribute__((always_inline)) -> U128 {
+            lane_swap<16>(a.x, b.x);
+            lane_swap<16>(a.y, b.y);
+            return U128{a.x, a.y, b.x, b.y};       // 8 columns of a (even lanes) or of b (odd ones)
+        };
+        if constexpr (JN % 2 == 0) {
+            const uint32_t offset = lane_offset(16 * odd + c8);
+#pragma unroll
+            for (int i = 0; i < TA; ++i)
+#pragma unroll
+                for (int j = 0; j < JN; j += 2)
+                    store(exchange(value(i, j), value(i, j + 1)), i, 16 * (wn * JN + j), offset,
+                          16 * (wm + C::WM * i) + mrow);
+        } else {
+            static_assert(JN % 2 == 0 || (JN == 1 && PO), "sub-tiles pair up in columns or in rows");
+            const int half = 16 * (wn & 1);        // of the block's 32 columns; odd lanes: the next sub-tile's rows
+            const uint32_t offset = lane_offset(half + c8) + (uint32_t)odd * (32u * C::WM) * (uint32_t)N;
+#pragma unroll
+            for (int i = 0; i + 1 < TA; i += 2)
+                store(exchange(value(i, 0), value(i + 1, 0)), i, 32 * (wn / 2), offset,
+                      16 * (wm + C::WM * (i + odd)) + mrow);
+            if constexpr (TA % 2 == 1) {
+                typedef uint32_t U64 __attribute__((ext_vector_type(2)));
+                const uint2 v = value(TA - 1, 0);
+                store(U64{v.x, v.y}, TA - 1, 32 * (wn / 2), lane_offset(half + cq),
+                      16 * (wm + C::WM * (TA - 1)) + mrow);
             }
         }
     };
@@ -311,13 +339,8 @@ __device__ __forceinline__ void pipe16_tile(
         const int col = n0 + cc * 8;
         for (int r = cr; r < tile_rows; r += RPP) {
             const U128 v = *reinterpret_cast<const U128*>(lds_raw + r * kStageRowBytes + cc * 16);
-            bf16_t* dst = Cout + (size_t)(row0 + r) * N + col;
-            if (col + 7 < N) {
-                *reinterpret_cast<U128*>(dst) = v;
-            } else {
-                for (int q = 0; q < 8; ++q)
-                    if (col + q < N) dst[q] = reinterpret_cast<const bf16_t*>(&v)[q];
-            }
+            if (col < N)                                    // N is a multiple of 64
+                store16(stream_out, Cout + (size_t)row0 * N, (uint32_t)(r * N + col) * 2u, v);
         }
     }
 }

@@ -72,6 +72,17 @@ __device__ __forceinline__ void dma16_nt(const void* gbase, uint32_t voff, uint3
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                  :: "v"(voff), "s"(gbase), "s"(lds_addr) : "memory", "m0");
 }
+// 16 bytes per lane to global memory; `stream`: with the non-temporal hint (streams_output()).  The hinted store is
+// inline assembly because the compiler merges the two sides of the choice into one store without the hint; the
+// s_nop keeps a following write to the data registers one wait state away, as stores of 16 bytes need.
+__device__ __forceinline__ void store16(bool stream, void* base, uint32_t offset, U128 v) {
+    typedef U128 Any __attribute__((aligned(2)));
+    unsigned char* p = static_cast<unsigned char*>(base) + offset;
+    if (stream)
+        asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 0" :: "v"(p), "v"(v) : "memory");
+    else
+        *reinterpret_cast<Any*>(p) = v;
+}
 // tells the compiler that a pointer is the same in every lane (it then lives in scalar registers,
 // which the "s" operand of dma16 requires)
 template <typename T>

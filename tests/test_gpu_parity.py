@@ -1013,6 +1013,16 @@ def test_packed_expert_gemms(d, f, rows):
 
 
 @pytest.mark.parametrize("d,f,rows", [
+    (64, 3136, [350, 333, 321, 17]),        # h of 6.4 MB, last n-tile half empty
+    (4096, 3136, [350, 0, 333, 321, 17]),   # the same, last round in half tiles; y of 8.4 MB
+    (3136, 64, [350, 333, 321, 1]),         # y of 6.3 MB, h small
+])
+def test_packed_expert_gemms_with_streamed_outputs(d, f, rows):
+    """Outputs from 6 MB on are stored with the non-temporal hint."""
+    test_packed_expert_gemms(d, f, rows)
+
+
+@pytest.mark.parametrize("d,f,rows", [
     # contractions from 4096 on, a last round of 3 tiles per die in halves (the last n-tile has one half): 320
     # rows (13 m-tiles x 41 and x 21) and 192 rows (the same)
     (5184, 5184, [640, 700, 330, 1, 0, 900, 321]),
