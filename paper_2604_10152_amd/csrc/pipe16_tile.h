@@ -35,6 +35,79 @@ __device__ __forceinline__ void dispatch_count(int n, F& f, std::integer_sequenc
     ((n == Is ? (f(std::integral_constant<int, Is>{}), 0) : 0), ...);
 }
 
+// What a lane holds of a 16 x 16 sub-tile: one row and 4 consecutive columns, as bf16.  acc: the
+// wave's sub-tiles of these rows; SwiGLU: the second half of them are the `up` columns.
+template <bool SWIGLU, int TN>
+__device__ __forceinline__ uint2 sub_tile(const floatx4 (&acc)[TN], int j) {
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        v[q] = acc[j][q];
+        if constexpr (SWIGLU) v[q] = v[q] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[q])) * acc[j + TN / 2][q];
+    }
+    return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+}
+
+// A wave's sub-tiles straight to global memory (acc[i]: tile rows 16 * (wm + WM * i) ..; PO: tile-packed).  Lanes l and
+// l ^ 16 exchange halves of two sub-tiles (neighbours in columns, or in rows where a wave has one column of them),
+// so a lane stores 16 bytes: a packed block of 1 KB, or 64 bytes of 16 rows, by one instruction.
+template <int TA, int WM, bool SWIGLU, bool PO, int TAX, int TN>
+__device__ __forceinline__ void write_sub_tiles(const floatx4 (&acc)[TAX][TN], const TileLoc& t, int n0, int N,
+                                                bf16_t* __restrict__ Cout, int wm, int wn, bool stream_out) {
+    constexpr int JN = SWIGLU ? TN / 2 : TN;
+    const int lane = threadIdx.x % kWave, mrow = lane & 15, cq = (lane >> 4) * 4;
+    const int odd = (lane >> 4) & 1, c8 = (lane >> 5) * 8;
+    // Row mrow of sub-tile i, `at` columns behind column `col` of the tile: the address is a uniform base and a
+    // lane's offset that is the same for all sub-tiles.  Columns go on for N, a multiple of 64.
+    auto lane_offset = [&](int at) __attribute__((always_inline)) -> uint32_t {
+        return PO ? (uint32_t)((4 * mrow + ((at >> 3) ^ ((mrow >> 1) & 3))) * 16 + (at & 4) * 2)
+                  : (uint32_t)(mrow * N + at) * 2u;
+    };
+    auto store = [&](auto v, int i, int col, uint32_t offset, int trow) __attribute__((always_inline)) {
+        if (n0 + col >= N) return;
+        const int sub = wm + WM * i;
+        unsigned char* base = reinterpret_cast<unsigned char*>(
+            Cout + (PO ? (size_t)(t.blk0 + sub) * 16 * N + (size_t)((n0 + col) / 32) * 512
+                       : (size_t)(t.row0 + 16 * sub) * N + n0 + col));
+        if (PO) {
+            // rows beyond the tile's last one (padding of the expert's last block) are zeros
+            if (trow >= t.tile_rows) v = decltype(v){};
+        } else if (trow >= t.tile_rows) {
+            return;
+        }
+        if constexpr (sizeof(v) == 16) store16(stream_out, base, offset, v);
+        else *reinterpret_cast<decltype(v)*>(base + offset) = v;
+    };
+    auto exchange = [&](uint2 a, uint2 b) __attribute__((always_inline)) -> U128 {
+        lane_swap<16>(a.x, b.x);
+        lane_swap<16>(a.y, b.y);
+        return U128{a.x, a.y, b.x, b.y};           // 8 columns of a (even lanes) or of b (odd ones)
+    };
+    if constexpr (JN % 2 == 0) {
+        const uint32_t offset = lane_offset(16 * odd + c8);
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int j = 0; j < JN; j += 2)
+                store(exchange(sub_tile<SWIGLU>(acc[i], j), sub_tile<SWIGLU>(acc[i], j + 1)), i,
+                      16 * (wn * JN + j), offset, 16 * (wm + WM * i) + mrow);
+    } else {
+        static_assert(JN == 1, "sub-tiles pair up in columns or in rows");
+        // odd lanes: the next sub-tile's rows.  A packed block has 32 columns, the wave 16 of them.
+        const int col = PO ? 32 * (wn / 2) : 16 * wn, in_block = PO ? 16 * (wn & 1) : 0;
+        const uint32_t offset = lane_offset(in_block + c8) + (uint32_t)odd * (32u * WM) * (uint32_t)N;
+#pragma unroll
+        for (int i = 0; i + 1 < TA; i += 2)
+            store(exchange(sub_tile<SWIGLU>(acc[i], 0), sub_tile<SWIGLU>(acc[i + 1], 0)), i, col, offset,
+                  16 * (wm + WM * (i + odd)) + mrow);
+        if constexpr (TA % 2 == 1) {
+            typedef uint32_t U64 __attribute__((ext_vector_type(2)));
+            const uint2 v = sub_tile<SWIGLU>(acc[TA - 1], 0);
+            store(U64{v.x, v.y}, TA - 1, col, lane_offset(in_block + cq), 16 * (wm + WM * (TA - 1)) + mrow);
+        }
+    }
+}
+
 // the work of one workgroup: tile t (lds_raw: C::LDS_BYTES)
 template <typename C, bool PA = false, bool PB = false, bool PO = false>
 __device__ __forceinline__ void pipe16_tile(
@@ -156,87 +229,22 @@ __device__ __forceinline__ void pipe16_tile(
 
     // epilogue: row-major SwiGLU tiles are staged in LDS and written as whole rows by the workgroup; tile-packed ones
     // and plain tiles go straight to global memory.  acc[i] is the wave's i-th A sub-tile (tile rows
-    // 16 * (wm + WM * i) ..), a lane holds one row and 4 consecutive columns of every sub-tile.  Lanes l and l ^ 16
-    // exchange halves of two sub-tiles (neighbours in columns, or in rows where a wave has one column of them), so a
-    // lane stores 16 bytes: a packed block of 1 KB, or 64 bytes of 16 rows, by one instruction.
+    // 16 * (wm + WM * i) ..).
     auto epilogue = [&](auto& acc, auto ta_tag) __attribute__((always_inline)) {
-        constexpr int TA = decltype(ta_tag)::value, JN = C::SWIGLU ? TN16 / 2 : TN16;
+        constexpr int TA = decltype(ta_tag)::value;
         wait_vmcnt<0>();                           // no load may outlive the workgroup's LDS
-
-        const int mrow = lane & 15, cq = (lane >> 4) * 4;
-        // the lane's 4 values of sub-tile (i, j)
-        auto value = [&](int i, int j) __attribute__((always_inline)) -> uint2 {
-            float v[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (C::SWIGLU) {
-                    const float gt = acc[i][j][q], up = acc[i][j + JN][q];
-                    v[q] = gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * up;
-                } else {
-                    v[q] = acc[i][j][q];
-                }
-            }
-            return make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-        };
-        if (C::SWIGLU && !PO) {
+        if constexpr (C::SWIGLU && !PO) {
+            constexpr int JN = TN16 / 2;
             __builtin_amdgcn_s_barrier();          // every wave's loads have landed
 #pragma unroll
             for (int i = 0; i < TA; ++i)
 #pragma unroll
                 for (int j = 0; j < JN; ++j)
-                    *reinterpret_cast<uint2*>(lds_raw + (16 * (wm + C::WM * i) + mrow) * kStageRowBytes +
-                                              (16 * (wn * JN + j) + cq) * 2) = value(i, j);
-            return;
-        }
-        // Row mrow of sub-tile i, `at` columns behind its first: the address is a uniform base and a lane's
-        // offset that is the same for all sub-tiles.  Columns go on for N, a multiple of 64.
-        auto lane_offset = [&](int at) __attribute__((always_inline)) -> uint32_t {
-            return PO ? (uint32_t)((4 * mrow + ((at >> 3) ^ ((mrow >> 1) & 3))) * 16 + (at & 4) * 2)
-                      : (uint32_t)(mrow * N + at) * 2u;
-        };
-        auto store = [&](auto v, int i, int col, uint32_t offset, int trow) __attribute__((always_inline)) {
-            if (n0 + col >= N) return;
-            const int sub = wm + C::WM * i;
-            unsigned char* base = reinterpret_cast<unsigned char*>(
-                Cout + (PO ? (size_t)(t.blk0 + sub) * 16 * N + (size_t)((n0 + col) / 32) * 512
-                           : (size_t)(row0 + 16 * sub) * N + n0 + col));
-            if (PO) {
-                // rows beyond the tile's last one (padding of the expert's last block) are zeros
-                if (trow >= tile_rows) v = decltype(v){};
-            } else if (trow >= tile_rows) {
-                return;
-            }
-            if constexpr (sizeof(v) == 16) store16(stream_out, base, offset, v);
-            else *reinterpret_cast<decltype(v)*>(base + offset) = v;
-        };
-        const int odd = (lane >> 4) & 1, c8 = (lane >> 5) * 8;
-        auto exchange = [&](uint2 a, uint2 b) __attribute__((always_inline)) -> U128 {
-            lane_swap<16>(a.x, b.x);
-            lane_swap<16>(a.y, b.y);
-            return U128{a.x, a.y, b.x, b.y};       // 8 columns of a (even lanes) or of b (odd ones)
-        };
-        if constexpr (JN % 2 == 0) {
-            const uint32_t offset = lane_offset(16 * odd + c8);
-#pragma unroll
-            for (int i = 0; i < TA; ++i)
-#pragma unroll
-                for (int j = 0; j < JN; j += 2)
-                    store(exchange(value(i, j), value(i, j + 1)), i, 16 * (wn * JN + j), offset,
-                          16 * (wm + C::WM * i) + mrow);
+                    *reinterpret_cast<uint2*>(lds_raw + (16 * (wm + C::WM * i) + (lane & 15)) * kStageRowBytes +
+                                              (16 * (wn * JN + j) + (lane >> 4) * 4) * 2) =
+                        sub_tile<C::SWIGLU>(acc[i], j);
         } else {
-            static_assert(JN % 2 == 0 || (JN == 1 && PO), "sub-tiles pair up in columns or in rows");
-            const int half = 16 * (wn & 1);        // of the block's 32 columns; odd lanes: the next sub-tile's rows
-            const uint32_t offset = lane_offset(half + c8) + (uint32_t)odd * (32u * C::WM) * (uint32_t)N;
-#pragma unroll
-            for (int i = 0; i + 1 < TA; i += 2)
-                store(exchange(value(i, 0), value(i + 1, 0)), i, 32 * (wn / 2), offset,
-                      16 * (wm + C::WM * (i + odd)) + mrow);
-            if constexpr (TA % 2 == 1) {
-                typedef uint32_t U64 __attribute__((ext_vector_type(2)));
-                const uint2 v = value(TA - 1, 0);
-                store(U64{v.x, v.y}, TA - 1, 32 * (wn / 2), lane_offset(half + cq),
-                      16 * (wm + C::WM * (TA - 1)) + mrow);
-            }
+            write_sub_tiles<TA, C::WM, C::SWIGLU, PO>(acc, t, n0, N, Cout, wm, wn, stream_out);
         }
     };
 

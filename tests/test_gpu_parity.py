@@ -1092,6 +1092,47 @@ def test_row_major_tile_order(rows):
             assert float(err.max()) <= 1e-2, (e, float(err.max()))      # NaN fails as well
 
 
+@pytest.mark.parametrize("d,f,rows", [
+    # both projections: one and two m-tiles, tiles of every height, ragged columns, two rounds of tiles per workgroup
+    (2112, 1344, [160, 161, 0, 1, 16, 17, 320, 33] + [(37 * e) % 161 for e in range(56)]),
+    (2048, 1984, [0] * 20 + [3] + [0] * 43),         # one workgroup per die with tiles, most without
+    (2048, 1280, [160, 159, 1, 64] * 6),             # one tile per workgroup
+    # long contraction: groups of n-tiles, a die's last round in halves whose second half lies beyond the columns
+    (4096, 3136, [161, 0, 160, 1, 100, 17, 330, 20, 64, 65] + [48] * 11),
+    (4096, 4160, [16, 1, 160, 159] * 4),             # the same with one m-tile each: expert-major
+])
+@pytest.mark.parametrize("gather", [False, True])
+def test_persistent_tiles(d, f, rows, gather):
+    """Every tile of the persistent GEMMs is computed once and in its place, against fp32 products."""
+    _say(f"persistent tiles d={d} f={f} E={len(rows)} gather={gather}")
+    E, n, k = len(rows), sum(rows), 3
+    off = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(d + f)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x = (rnd(n, d) / d ** 0.5).to(torch.bfloat16)
+    src = torch.randperm(n * k, generator=g, device="cuda")[:n].to(torch.int32)
+    wg, wu = ((rnd(E, f, d) * 0.5).to(torch.bfloat16) for _ in range(2))
+    wd = (rnd(E, d, f) * (0.5 / f ** 0.5)).to(torch.bfloat16)
+    doff = dev(torch.from_numpy(off))
+    h = torch.full((n, f), float("nan"), dtype=torch.bfloat16, device="cuda")
+    y = torch.full((n, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    if gather:
+        sm.moe_expert_up_swiglu_gather(x, src, k, doff, wg, wu, h)
+        x = x[(src // k).long()]
+    else:
+        sm.moe_expert_up_swiglu(x, doff, wg, wu, h)
+    sm.moe_expert_down(h, doff, wd, y)
+    for e, r in enumerate(rows):
+        if not r:
+            continue
+        s = slice(int(off[e]), int(off[e + 1]))
+        xe = x[s].float()
+        want = torch.nn.functional.silu(xe @ wg[e].float().t()) * (xe @ wu[e].float().t())
+        for got, ref in ((h[s], want), (y[s], h[s].float() @ wd[e].float().t())):
+            err = (got.float() - ref).abs().amax(1) / ref.abs().amax(1)
+            assert float(err.max()) <= 1e-2, (e, float(err.max()))      # NaN fails as well
+
+
 def test_layer_cfg4_packed_path():
     """The benchmark workload on the tile-packed path: same routing, output bit-identical to the
     row-major path (same kernels' arithmetic in the same order)."""
