@@ -289,6 +289,19 @@ def test_greedy_tokens_match_oracle(R, V, dtype):
     assert np.all(t == (lf == mx[:, None]).argmax(axis=1))
 
 
+@pytest.mark.parametrize("R,V,dtype", [(1100, 48008, torch.bfloat16), (1030, 24308, torch.float32)])
+def test_greedy_tokens_of_many_long_rows(R, V, dtype):
+    """From 100 MB on the logits are read with the non-temporal hint."""
+    _say(f"spec_greedy_tokens R={R} V={V} {dtype}")
+    g = torch.Generator(device="cuda").manual_seed(R + V)
+    logits = (torch.randn(R, V, generator=g, device="cuda") * 6).round().to(dtype) / 2       # ties at the top
+    tok = torch.full((R,), -5, dtype=I32, device="cuda")
+    sm.spec_greedy_tokens(logits, tok)
+    ids = torch.arange(V, device="cuda")
+    want = torch.where(logits == logits.amax(dim=1, keepdim=True), ids, V).amin(dim=1)
+    assert torch.equal(tok.long(), want)
+
+
 def test_active_expert_bytes_and_greedy_accept_chain():
     _say("active expert bytes + greedy head feeding spec_accept")
     for counts in ([3, 0, 5, 0, 0, 1, 2, 9], [0] * 64, list(range(130))):
