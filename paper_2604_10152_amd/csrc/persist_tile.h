@@ -142,6 +142,7 @@ __device__ __forceinline__ void persist_tiles(
     uint32_t a_off[C::A_PW], b_off[C::B_PW];
     int a_cnt, b_cnt;                            // wave-loads of a stage
     bool once;                                   // no other workgroup reads the tile's weights
+    const bool single = !C::SWIGLU || __ballot(table.mt > 1) == 0;
     auto request_from = [&](const TileLoc& t, auto from_lds) __attribute__((always_inline)) {
         a_base = uniform_ptr(reinterpret_cast<const unsigned char*>(
             A + (C::PA ? (size_t)t.blk0 * 16 * K : (GATHER ? (size_t)0 : (size_t)t.row0 * K))));
@@ -152,7 +153,7 @@ __device__ __forceinline__ void persist_tiles(
         w0 = uniform_ptr(reinterpret_cast<const unsigned char*>(W0 + wrow * K));
         if (C::SWIGLU) w1 = uniform_ptr(reinterpret_cast<const unsigned char*>(W1 + wrow * K));
         a_cnt = 0;
-        once = t.mt == 1 && (!C::SWIGLU || t.tile_rows <= 64);
+        once = t.mt == 1 && (!C::SWIGLU || t.tile_rows <= 64 || single);
         const uint32_t chunk = (uint32_t)(((lane & 7) ^ ((lane >> 3) & 6)) * 16);
 #pragma unroll
         for (int jj = 0; jj < C::A_PW; ++jj) {
