@@ -216,6 +216,18 @@ int moe_layer_forward(const void* x, const void* w_router, const float* router_b
                       int32_t* row_src, int32_t* row_of, void* x_packed, size_t x_packed_bytes, void* h,
                       size_t h_bytes, void* y_perm, void* out, void* stream);
 
+/* The same; small batches (up to 64 tokens and 64 experts) take a launch less: the last workgroup of the router does
+ * moe_permute's index phase.  `counter` (nullable: as moe_layer_forward) is a word of device memory that the caller
+ * has set to 0 once and that a call leaves at 0; calls that may overlap in time need a word each, as they need
+ * buffers each. */
+int moe_layer_forward_counted(const void* x, const void* w_router, const float* router_bias,
+                              const int32_t* remap, const void* w_gate, const void* w_up, const void* w_down,
+                              const void* residual, int T, int d_model, int d_ff, int E, int k, int renorm,
+                              int dtype, int layout, int32_t* topk_idx, float* topk_w,
+                              int32_t* expert_offsets, int32_t* row_src, int32_t* row_of, void* x_packed,
+                              size_t x_packed_bytes, void* h, size_t h_bytes, void* y_perm, void* out,
+                              uint32_t* counter, void* stream);
+
 /* Greedy verification (Sec. 2.2 Fig. 4; Sec. 4: only drafts that exactly match the target's
  * greedy tokens are accepted).  draft_ids [B,gamma]; target_ids [B,gamma+1], target_ids[b,i]
  * being the target's token for the position draft_ids[b,i] was proposed for and

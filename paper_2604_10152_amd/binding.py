@@ -20,7 +20,8 @@ EXPORTED_SYMBOLS = (
     "moe_grouped_swiglu_static", "moe_pack_weights", "moe_packed_h_bytes",
     "moe_expert_up_swiglu_gather_packed", "moe_expert_down_packed",
     "moe_permute_rows_packed", "moe_expert_up_swiglu_packed",
-    "moe_expert_up_swiglu", "moe_expert_up_swiglu_gather", "moe_expert_down", "moe_combine", "moe_layer_forward", "spec_accept", "moe_hot_experts", "moe_rmsnorm", "specmoe_status_string", "specmoe_abi_version",
+    "moe_expert_up_swiglu", "moe_expert_up_swiglu_gather", "moe_expert_down", "moe_combine", "moe_layer_forward",
+    "moe_layer_forward_counted", "spec_accept", "moe_hot_experts", "moe_rmsnorm", "specmoe_status_string", "specmoe_abi_version",
     "moe_affinity_table_workspace_bytes", "moe_affinity_table", "moe_nearest_draft_expert",
     "moe_route_topk_draft", "spec_accept_sample", "spec_greedy_tokens", "moe_active_expert_bytes",
 )
@@ -73,6 +74,7 @@ def load_library(build_if_missing: bool = True):
     lib.moe_combine.argtypes = [vp, ip, fp, vp, i, i, i, i, vp, vp]
     lib.moe_layer_forward.argtypes = [vp, vp, fp, ip, vp, vp, vp, vp, i, i, i, i, i, i, i, i, ip, fp, ip, ip,
                                       ip, vp, sz, vp, sz, vp, vp, vp]
+    lib.moe_layer_forward_counted.argtypes = lib.moe_layer_forward.argtypes[:-1] + [ip, vp]
     lib.spec_accept.argtypes = [ip, ip, i, i, ip, ip, vp]
     lib.moe_hot_experts.argtypes = [ip, i, i, ip, ip, vp]
     lib.moe_rmsnorm.argtypes = [vp, vp, i, i, ctypes.c_float, i, vp, vp]
@@ -94,7 +96,7 @@ def load_library(build_if_missing: bool = True):
                  "moe_expert_up_swiglu", "moe_expert_up_swiglu_gather", "moe_expert_down",
                  "moe_hot_experts", "moe_affinity_table", "moe_nearest_draft_expert",
                  "moe_route_topk_draft", "spec_accept_sample", "spec_greedy_tokens",
-                 "moe_active_expert_bytes", "moe_layer_forward",
+                 "moe_active_expert_bytes", "moe_layer_forward", "moe_layer_forward_counted",
                  "spec_accept", "moe_rmsnorm"):
         getattr(lib, name).restype = i
     _LIB = lib
@@ -286,13 +288,14 @@ def moe_combine(y_perm, row_of, topk_w, residual, out, stream=None):
 
 def moe_layer_forward(x, w_router, router_bias, remap, w_gate, w_up, w_down, residual, k, renorm, layout,
                       topk_idx, topk_w, expert_offsets, row_src, row_of, x_packed, h, y_perm, out,
-                      stream=None):
+                      stream=None, counter=None):
     """The steps of a layer in one library call: five calls keep the host busy for 28 to 31 us, longer than
-    the kernels of a small layer take (16 tokens, fp32, 256 x 512: 22 us, now the bound)."""
+    the kernels of a small layer take (16 tokens, fp32, 256 x 512: 20 us, now the bound).  counter: an int32 on the
+    GPU that is 0 and this caller's own (moe_layer_forward_counted)."""
     T, d = x.shape
     E, f, _ = w_gate.shape
     dt = x.dtype
-    _check(load_library().moe_layer_forward(
+    _check(load_library().moe_layer_forward_counted(
         _ptr(x, name="x"), _ptr(w_router, dt, "w_router"), _ptr(router_bias, torch.float32, "router_bias"),
         _ptr(remap, torch.int32, "remap"), _ptr(w_gate, dt, "w_gate"), _ptr(w_up, dt, "w_up"),
         _ptr(w_down, dt, "w_down"), _ptr(residual, dt, "residual"), T, d, f, E, int(k), int(bool(renorm)),
@@ -300,7 +303,8 @@ def moe_layer_forward(x, w_router, router_bias, remap, w_gate, w_up, w_down, res
         _ptr(topk_w, torch.float32, "topk_w"), _ptr(expert_offsets, torch.int32, "expert_offsets"),
         _ptr(row_src, torch.int32, "row_src"), _ptr(row_of, torch.int32, "row_of"),
         _ptr(x_packed, name="x_packed"), 0 if x_packed is None else x_packed.nbytes, _ptr(h, name="h"),
-        h.nbytes, _ptr(y_perm, dt, "y_perm"), _ptr(out, dt, "out"), _stream(stream)), "moe_layer_forward")
+        h.nbytes, _ptr(y_perm, dt, "y_perm"), _ptr(out, dt, "out"), _ptr(counter, torch.int32, "counter"),
+        _stream(stream)), "moe_layer_forward")
 
 
 def spec_accept(draft_ids, target_ids, accept_len, out_tokens, stream=None):

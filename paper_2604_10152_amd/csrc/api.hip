@@ -314,6 +314,18 @@ int moe_layer_forward(const void* x, const void* w_router, const float* router_b
                       int dtype, int layout, int32_t* topk_idx, float* topk_w, int32_t* expert_offsets,
                       int32_t* row_src, int32_t* row_of, void* x_packed, size_t x_packed_bytes, void* h,
                       size_t h_bytes, void* y_perm, void* out, void* stream) {
+    return moe_layer_forward_counted(x, w_router, router_bias, remap, w_gate, w_up, w_down, residual, T, d_model,
+                                     d_ff, E, k, renorm, dtype, layout, topk_idx, topk_w, expert_offsets, row_src,
+                                     row_of, x_packed, x_packed_bytes, h, h_bytes, y_perm, out, nullptr, stream);
+}
+
+int moe_layer_forward_counted(const void* x, const void* w_router, const float* router_bias,
+                              const int32_t* remap, const void* w_gate, const void* w_up, const void* w_down,
+                              const void* residual, int T, int d_model, int d_ff, int E, int k, int renorm,
+                              int dtype, int layout, int32_t* topk_idx, float* topk_w,
+                              int32_t* expert_offsets, int32_t* row_src, int32_t* row_of, void* x_packed,
+                              size_t x_packed_bytes, void* h, size_t h_bytes, void* y_perm, void* out,
+                              uint32_t* counter, void* stream) {
     // everything that one of the steps would refuse is refused before the first is enqueued
     int st = check_expert_shapes(T, d_model, d_ff, E, dtype);
     if (st != SPECMOE_OK) return st;
@@ -338,13 +350,18 @@ int moe_layer_forward(const void* x, const void* w_router, const float* router_b
                              ((uintptr_t)x_packed & 15u) != 0)))
             return SPECMOE_ERR_WORKSPACE;
     }
-    st = remap ? moe_route_topk_draft(x, w_router, router_bias, T, d_model, E, k, renorm, dtype, remap,
-                                      topk_idx, topk_w, stream)
-               : moe_route_topk(x, w_router, router_bias, T, d_model, E, k, renorm, dtype, topk_idx,
-                                topk_w, stream);
-    if (st == SPECMOE_OK)
-        st = moe_permute(x, topk_idx, T, d_model, E, k, dtype, nullptr, expert_offsets, row_src, row_of,
-                         stream);
+    if (counter && T > 0 && T <= kRoutePermuteTokens && E <= kWave) {
+        st = dev(launch_route_permute(x, w_router, router_bias, T, d_model, E, k, renorm, dtype, remap, topk_idx,
+                                      topk_w, expert_offsets, row_src, row_of, counter, (hipStream_t)stream));
+    } else {
+        st = remap ? moe_route_topk_draft(x, w_router, router_bias, T, d_model, E, k, renorm, dtype, remap,
+                                          topk_idx, topk_w, stream)
+                   : moe_route_topk(x, w_router, router_bias, T, d_model, E, k, renorm, dtype, topk_idx,
+                                    topk_w, stream);
+        if (st == SPECMOE_OK)
+            st = moe_permute(x, topk_idx, T, d_model, E, k, dtype, nullptr, expert_offsets, row_src, row_of,
+                             stream);
+    }
     if (st == SPECMOE_OK && rows_packed)
         st = moe_permute_rows_packed(x, row_src, T, k, expert_offsets, P, d_model, E, dtype, x_packed,
                                      x_packed_bytes, stream);

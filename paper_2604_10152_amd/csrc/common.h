@@ -162,6 +162,16 @@ inline bool streams_output(int n_rows, int N) { return (long long)n_rows * N * 2
 hipError_t launch_route_topk(const void* x, const void* wr, const float* bias, int T, int d,
                              int E, int k, int renorm, int dtype, int32_t* idx, float* w,
                              hipStream_t s, const int32_t* remap = nullptr);
+// Router and index phase of the permutation in one launch, done: specmoe.h.  While the router's workgroups are few: they
+// count one after the other, and the last one permutes while the others' CUs are idle.  Kernels, us, two / one: 80
+// tokens, 2 of 8 5.2 + 5.0 / 7.1; 64 tokens, 6 of 64 8.5 + 4.5 / 11.8; 16 tokens in fp32 4.1 + 2.5 / 6.6; 320 tokens, 6 of 64 11.5 + 4.9 /
+// 16.8.  Layers on the same buffers: 16 tokens, 256 x 512 in fp32 22.2 / 20.0, 1 token 24.9 / 24.6, 16 tokens 4096 x 14336 138.7 /
+// 137.8; from 80 tokens on level (80 tokens 468.8 / 469.1, 128 tokens 64 x 2048 x 1408 162.8 / 162.9).
+constexpr int kRoutePermuteTokens = 64;
+hipError_t launch_route_permute(const void* x, const void* wr, const float* bias, int T, int d, int E, int k,
+                                int renorm, int dtype, const int32_t* remap, int32_t* idx, float* w,
+                                int32_t* offsets, int32_t* row_src, int32_t* row_of, uint32_t* done,
+                                hipStream_t s);
 // speculation phase (affinity.hip, draft_route.hip)
 size_t affinity_workspace_bytes(int E);
 hipError_t launch_affinity_table(const void* wg, const void* wu, const void* wd, int E, int d,

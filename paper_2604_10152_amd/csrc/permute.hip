@@ -17,109 +17,21 @@
 // 320 x 6 of 64: 8.7 -> 4.6, 2048 x 2 of 8: 8.4 -> 5.9, 80 x 2 of 8: 4.4 -> 3.2 (a launch is 2.5).  Of
 // 30000 pairs 36 us (152; 38 where the slice was ranked twice; all tokens on the same experts 33, 33, 38).
 // Gather phase: a coalesced 16-byte copy of whole rows over the full grid.
-#include "common.h"
+#include "permute_index.h"
 
 namespace specmoe {
 namespace {
 
 constexpr int kSmallWaves = 16;    // E <= 64: short slices per wave
-constexpr int kSmallRows = 16;     // rows of 64 pairs a wave keeps in registers
 constexpr int kPermWaves = 8;      // otherwise: (waves + 1) * E counters have to fit the LDS default
 constexpr int kBatch = 8;          // index rows fetched ahead per wavefront
 
-__device__ __forceinline__ unsigned long long lanes_below(int lane) {
-    return lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-}
-
-// E <= 64.  BITS: bits of an expert id.
 template <int BITS>
 __global__ __launch_bounds__(kSmallWaves * kWave) void permute_index_small_kernel(
     const int32_t* __restrict__ idx, int P, int E, int32_t* __restrict__ offsets,
     int32_t* __restrict__ row_src, int32_t* __restrict__ row_of) {
     __shared__ int cnt[kSmallWaves][kWave];
-    const int tid = threadIdx.x, lane = tid % kWave;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    volatile int* mine = cnt[wave];
-    const int per_wave = ((P + kSmallWaves - 1) / kSmallWaves + kWave - 1) / kWave * kWave;
-    const int lo = min(P, wave * per_wave), hi = min(P, lo + per_wave);
-    const bool once = per_wave <= kSmallRows * kWave;
-    int ev[kSmallRows], place[kSmallRows];
-    // kSmallRows rows from `base`: the expert of every pair and its place behind mine[expert]
-    auto walk = [&](int base) __attribute__((always_inline)) {
-        const int rows = (hi - base + kWave - 1) / kWave;         // wave-uniform
-#pragma unroll
-        for (int b = 0; b < kSmallRows; ++b) {
-            const int p = base + b * kWave + lane;
-            ev[b] = p < hi ? idx[p] : 0;
-        }
-#pragma unroll
-        for (int b = 0; b < kSmallRows; ++b) {
-            if (b >= rows) break;
-            const bool valid = base + b * kWave + lane < hi;
-            const int e = min(max(ev[b], 0), E - 1);
-            unsigned long long same = __ballot(valid);
-#pragma unroll
-            for (int t = 0; t < BITS; ++t) {
-                const unsigned long long m = __ballot((e >> t) & 1);
-                same &= ((e >> t) & 1) ? m : ~m;
-            }
-            const int before = mine[e];
-            __builtin_amdgcn_wave_barrier();
-            const int rank = __popcll(same & lanes_below(lane));
-            ev[b] = e;
-            place[b] = before + rank;
-            // the last lane of a group moves the count on (LDS accesses of a wave stay in order)
-            if (valid && (same >> lane) == 1ull) mine[e] = before + rank + 1;
-            __builtin_amdgcn_wave_barrier();
-        }
-    };
-    mine[lane] = 0;                                                // private to the wave
-    for (int base = lo; base < hi; base += kSmallRows * kWave) {
-        walk(base);
-        if (once) break;
-#pragma unroll
-        for (int b = 0; b < kSmallRows; ++b) {
-            const int p = base + b * kWave + lane;
-            if (p < hi) row_of[p] = place[b];
-        }
-    }
-    __syncthreads();
-    if (wave == 0) {                                               // lane e: expert e
-        int c[kSmallWaves], total = 0;
-#pragma unroll
-        for (int w = 0; w < kSmallWaves; ++w) c[w] = cnt[w][lane];
-#pragma unroll
-        for (int w = 0; w < kSmallWaves; ++w) total += c[w];
-        const int incl = wave_scan(total);
-        int run = incl - total;
-        if (lane < E) offsets[lane] = run;
-        if (lane == E - 1) offsets[E] = incl;
-#pragma unroll
-        for (int w = 0; w < kSmallWaves; ++w) {
-            cnt[w][lane] = run;
-            run += c[w];
-        }
-    }
-    __syncthreads();
-    for (int base = lo; base < hi; base += kSmallRows * kWave) {
-        if (!once) {
-#pragma unroll
-            for (int b = 0; b < kSmallRows; ++b) {
-                const int p = base + b * kWave + lane;
-                ev[b] = p < hi ? min(max(idx[p], 0), E - 1) : 0;
-                place[b] = p < hi ? row_of[p] : 0;
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < kSmallRows; ++b) {
-            const int p = base + b * kWave + lane;
-            if (p < hi) {
-                const int dest = mine[ev[b]] + place[b];
-                row_src[dest] = p;
-                row_of[p] = dest;
-            }
-        }
-    }
+    permute_index_small<kSmallWaves, BITS, false>(idx, P, E, offsets, row_src, row_of, cnt);
 }
 
 __global__ __launch_bounds__(kPermWaves * kWave) void permute_index_kernel(

@@ -19,7 +19,7 @@
 // t, the E logits sitting in LDS.  It is a chain of latencies: the columns are requested one step ahead,
 // the bias and (up to 64 experts) the substitution at the start, the lanes exchange in registers: 64 experts x 2048, 64 tokens
 // 11.0 -> 8.9 us, 320 tokens 13.4 -> 11.0 (4 of these the fp64 work of one CU, 2.5 the launch).
-#include "common.h"
+#include "permute_index.h"
 
 #include <type_traits>
 
@@ -51,6 +51,11 @@ template <typename T> struct Chunk<T, false> {          // any d_model, any alig
     __device__ static Raw load(const T* p) { return load_as_float(p); }
     __device__ static double get(const Raw& v, int) { return (double)v; }
 };
+
+// An id goes past the L2, which every die has of its own: the workgroup that permutes may run on another one.
+__device__ __forceinline__ void store_id(int32_t* p, int id) {
+    __hip_atomic_store(p, id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // among numbers
 __device__ __forceinline__ bool better(double av, int aid, double bv, int bid) {
@@ -104,16 +109,37 @@ __device__ __forceinline__ void rank_token(const double* logit, int lane, int E,
         wsum_sel += lane_value(p, src);
     }
     if (valid && rank < k) {
-        idx_out[(size_t)t * k + rank] = id;
+        store_id(idx_out + (size_t)t * k + rank, id);
         w_out[(size_t)t * k + rank] = (float)(renorm ? p / wsum_sel : p);
     }
+}
+
+// What follows the ranking where the caller has a counter for it: the index phase of the permutation, by the workgroup
+// that is done last, so that a layer has a launch less (2.4 us of a kernel that does nothing, and the way to it).
+// done: workgroups that are, back at 0 behind the last one.  A workgroup counts only when its ids have arrived in memory
+// (store_id() and the wait), and the last one reads them there.  Fences of agent scope instead write back and drop the
+// whole L2, once per workgroup (320 tokens x 64 experts 11.5 + 4.9 us as two kernels, 20.2 with fences, 16.8 so).
+struct Then {
+    uint32_t* done;
+    int32_t *offsets, *row_src, *row_of;
+};
+template <int WAVES>
+__device__ __forceinline__ void permute_if_last(const Then& then, const int32_t* idx, int P, int E) {
+    if (!then.done) return;
+    __shared__ int cnt[WAVES][kWave];
+    __shared__ bool last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicInc(then.done, gridDim.x - 1) == gridDim.x - 1;
+    __syncthreads();
+    if (last) permute_index_small<WAVES, 6, true>(idx, P, E, then.offsets, then.row_src, then.row_of, cnt);
 }
 
 template <typename T, bool VEC, int TOK, int EC, int W>
 __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     const T* __restrict__ x, const T* __restrict__ wr, const float* __restrict__ bias, int Tn,
-    int d, int E, int k, int renorm, int32_t* __restrict__ idx_out, float* __restrict__ w_out,
-    const int32_t* __restrict__ remap /* nullable: draft-mode expert substitution, [E] */) {
+    int d, int E, int k, int renorm, int32_t* idx_out, float* __restrict__ w_out,
+    const int32_t* __restrict__ remap /* nullable: draft-mode expert substitution, [E] */, Then then) {
     static_assert(TOK * EC <= 16 && (TOK * EC & (TOK * EC - 1)) == 0, "values per wave");
     constexpr int NV = TOK * EC;                      // partial sums per lane and pass
     constexpr int kGroupThreads = W * kWave, kRouteGroups = kRouteThreads / kGroupThreads;
@@ -220,13 +246,14 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     }
 
     // wave t of the workgroup ranks token t0 + t (TOK <= 4)
-    if (wave_all >= TOK || t0 + wave_all >= Tn) return;
     const int t = t0 + wave_all;
     const double* logit = logits + (size_t)wave_all * E;
     if (E <= kWave) {
-        rank_token(logit, lane, E, k, renorm, t, idx_out, w_out, id);
+        if (wave_all < TOK && t < Tn) rank_token(logit, lane, E, k, renorm, t, idx_out, w_out, id);
+        permute_if_last<kRouteThreads / kWave>(then, idx_out, Tn * k, E);
         return;
     }
+    if (wave_all >= TOK || t >= Tn) return;
     // More than 64 experts: lane owns experts lane, lane+64, ...; `taken` marks the ones already
     // selected.  Lane s keeps the result of round s (k <= 64), so the final stores are coalesced.
     constexpr int kOwn = 1024 / kWave;                // SPECMOE_MAX_EXPERTS / 64
@@ -404,11 +431,11 @@ void launch_mfma(const bf16_t* x, const bf16_t* wr, const float* bias, int Tn, i
 
 template <typename T, bool VEC, int TOK, int EC, int W>
 void launch_variant(const T* x, const T* wr, const float* bias, int Tn, int d, int E, int k,
-                    int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
+                    int renorm, int32_t* idx, float* w, const int32_t* remap, Then then, hipStream_t s) {
     dim3 grid((Tn + TOK - 1) / TOK), block(kRouteThreads);
     size_t lds = ((size_t)TOK * E + (size_t)(kRouteThreads / kWave) * TOK * EC) * sizeof(double);
     hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC, W>), grid, block, lds, s, x, wr, bias, Tn,
-                       d, E, k, renorm, idx, w, remap);
+                       d, E, k, renorm, idx, w, remap, then);
 }
 
 // Experts per group and pass: the group's share of E rounded up to a power of two, at most 16 / TOK.
@@ -417,37 +444,37 @@ void launch_variant(const T* x, const T* wr, const float* bias, int Tn, int d, i
 // 13.6; 64 x 512 12.1 -> 9.2; 256 x 1024 38.1 -> 27.9 (with the exchanges through LDS).
 template <typename T, bool VEC, int TOK, int W>
 void launch_by_share(const T* x, const T* wr, const float* bias, int Tn, int d, int E, int k,
-                     int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
+                     int renorm, int32_t* idx, float* w, const int32_t* remap, Then then, hipStream_t s) {
     constexpr int EC_MAX = 16 / TOK, G = 16 / W;
     const int share = (E + G - 1) / G;
     if (share <= 1)
-        launch_variant<T, VEC, TOK, 1, W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+        launch_variant<T, VEC, TOK, 1, W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
     else if (share <= 2 || EC_MAX == 2)
-        launch_variant<T, VEC, TOK, (EC_MAX < 2 ? EC_MAX : 2), W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+        launch_variant<T, VEC, TOK, (EC_MAX < 2 ? EC_MAX : 2), W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
     else if (share <= 4 || EC_MAX == 4)
-        launch_variant<T, VEC, TOK, (EC_MAX < 4 ? EC_MAX : 4), W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+        launch_variant<T, VEC, TOK, (EC_MAX < 4 ? EC_MAX : 4), W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
     else if (share <= 8 || EC_MAX == 8)
-        launch_variant<T, VEC, TOK, (EC_MAX < 8 ? EC_MAX : 8), W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+        launch_variant<T, VEC, TOK, (EC_MAX < 8 ? EC_MAX : 8), W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
     else
-        launch_variant<T, VEC, TOK, EC_MAX, W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+        launch_variant<T, VEC, TOK, EC_MAX, W>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
 }
 template <typename T, bool VEC, int TOK>
 void launch_by_experts(const T* x, const T* wr, const float* bias, int Tn, int d, int E, int k,
-                       int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
+                       int renorm, int32_t* idx, float* w, const int32_t* remap, Then then, hipStream_t s) {
     if (E <= 16)
-        launch_by_share<T, VEC, TOK, 4>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+        launch_by_share<T, VEC, TOK, 4>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
     else
-        launch_by_share<T, VEC, TOK, 2>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+        launch_by_share<T, VEC, TOK, 2>(x, wr, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
 }
 
 template <typename T, int V>
 void launch_typed(const void* x, const void* wr, const float* bias, int Tn, int d, int E, int k,
-                  int renorm, int32_t* idx, float* w, const int32_t* remap, hipStream_t s) {
+                  int renorm, int32_t* idx, float* w, const int32_t* remap, Then then, hipStream_t s) {
     const bool vec = (d % V == 0) && ((((uintptr_t)x | (uintptr_t)wr) & 15u) == 0);
     const T* xt = (const T*)x;
     const T* wt = (const T*)wr;
     if (!vec) {
-        launch_by_experts<T, false, 1>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+        launch_by_experts<T, false, 1>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
         return;
     }
     // Matrix form: from 1025 tokens on with 8 tokens per workgroup (the vector form then needs a
@@ -487,9 +514,9 @@ void launch_typed(const void* x, const void* wr, const float* bias, int Tn, int 
         const long long load = per_cu * passes * (tok + ec);
         if (best < 0 || load < best) { best = load; best_tok = tok; }
     }
-    if (best_tok == 4) launch_by_experts<T, true, 4>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);
-    else if (best_tok == 2) launch_by_experts<T, true, 2>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);
-    else launch_by_experts<T, true, 1>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, s);
+    if (best_tok == 4) launch_by_experts<T, true, 4>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
+    else if (best_tok == 2) launch_by_experts<T, true, 2>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
+    else launch_by_experts<T, true, 1>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
 }
 
 }  // namespace
@@ -498,8 +525,20 @@ hipError_t launch_route_topk(const void* x, const void* wr, const float* bias, i
                              int E, int k, int renorm, int dtype, int32_t* idx, float* w,
                              hipStream_t s, const int32_t* remap) {
     if (T == 0) return hipSuccess;
-    if (dtype == 0) launch_typed<float, 4>(x, wr, bias, T, d, E, k, renorm, idx, w, remap, s);
-    else launch_typed<bf16_t, 8>(x, wr, bias, T, d, E, k, renorm, idx, w, remap, s);
+    const Then then{nullptr, nullptr, nullptr, nullptr};
+    if (dtype == 0) launch_typed<float, 4>(x, wr, bias, T, d, E, k, renorm, idx, w, remap, then, s);
+    else launch_typed<bf16_t, 8>(x, wr, bias, T, d, E, k, renorm, idx, w, remap, then, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_route_permute(const void* x, const void* wr, const float* bias, int T, int d, int E, int k,
+                                int renorm, int dtype, const int32_t* remap, int32_t* idx, float* w,
+                                int32_t* offsets, int32_t* row_src, int32_t* row_of, uint32_t* done,
+                                hipStream_t s) {
+    if (T < 1 || T > kRoutePermuteTokens || E > kWave) return hipErrorInvalidValue;
+    const Then then{done, offsets, row_src, row_of};
+    if (dtype == 0) launch_typed<float, 4>(x, wr, bias, T, d, E, k, renorm, idx, w, remap, then, s);
+    else launch_typed<bf16_t, 8>(x, wr, bias, T, d, E, k, renorm, idx, w, remap, then, s);
     return hipGetLastError();
 }
 

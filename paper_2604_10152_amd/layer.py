@@ -32,6 +32,9 @@ class MoEVerifyLayer:
         self.y_perm = torch.empty((P, d_model), dtype=dtype, device=dev)
         self.out = torch.empty((T, d_model), dtype=dtype, device=dev)
         self.h = torch.empty((P, d_ff), dtype=dtype, device=dev)
+        self.counter = torch.zeros((1,), **i32)  # of the router's workgroups; 0 between calls
+        if dev.type == "cuda" and not torch.cuda.is_current_stream_capturing():
+            torch.cuda.current_stream(dev).synchronize()     # the first call may come on another stream
         self.h_packed = None                     # allocated on first use of packed weights
         self.x_packed = None
 
@@ -143,7 +146,7 @@ class MoEVerifyLayer:
                 packed["w_down"] if down_packed else w_down,
                 residual, self.k, self.renorm, layout, self.topk_idx, self.topk_w, self.expert_offsets,
                 self.row_src, self.row_of, self.x_packed, self.h_packed if down_packed else self.h,
-                self.y_perm, out, stream)
+                self.y_perm, out, stream, self.counter)
             return out
         # with marks, or x_perm written first: the same steps and layouts as calls of their own
         if marks is not None:

@@ -1229,6 +1229,36 @@ def test_layer_gathers_packed(d, f, E, k, T, monkeypatch):
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
 
 
+@pytest.mark.parametrize("T", [1, 3, 63, 64, 65])        # up to 64 tokens: one launch for the router and the permutation
+@pytest.mark.parametrize("dtype,d,E,k", [(torch.float32, 100, 5, 3), (torch.float32, 256, 64, 64), (torch.bfloat16, 128, 64, 6),
+                                         (torch.bfloat16, 64, 1, 1), (torch.bfloat16, 192, 65, 2), (torch.bfloat16, 2048, 13, 4)])
+def test_router_permutes_like_the_two_calls(dtype, d, E, k, T):
+    """The layer's ids, offsets and row maps are those of moe_route_topk and moe_permute, call after call; the counter of the
+    router's workgroups is left at 0."""
+    _say(f"router and permutation in one launch {dtype} d={d} E={E} k={k} T={T}")
+    g = torch.Generator(device="cuda").manual_seed(T * E + d)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(dtype)
+    f = 64
+    wr, wg, wu, wd = rnd(E, d), rnd(E, f, d), rnd(E, f, d), rnd(E, d, f)
+    layer = sm.MoEVerifyLayer(T, d, f, E, k, dtype)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    for turn in range(4):
+        x = rnd(T, d)
+        remap = torch.randint(0, E, (E,), generator=g, **i32) if turn % 2 else None
+        layer.forward(x, wr, wg, wu, wd, draft_remap=remap)
+        idx, w = torch.full((T, k), -1, **i32), torch.empty((T, k), device="cuda")
+        if remap is None:
+            sm.moe_route_topk(x, wr, None, k, True, idx, w)
+        else:
+            sm.moe_route_topk_draft(x, wr, None, k, True, remap, idx, w)
+        off, src, of = torch.empty((E + 1,), **i32), torch.empty((T * k,), **i32), torch.empty((T * k,), **i32)
+        sm.moe_permute(x, idx, E, None, off, src, of)
+        for got, want in ((layer.topk_idx, idx), (layer.topk_w, w), (layer.expert_offsets, off), (layer.row_src, src),
+                          (layer.row_of, of)):
+            assert torch.equal(got, want)
+        assert int(layer.counter.item()) == 0
+
+
 @pytest.mark.parametrize("dtype,d,f,E,k,T,draft", [
     ("f32", 33, 50, 5, 2, 9, True), ("bf16", 4096, 128, 4, 2, 30, False),          # row-major
     ("bf16", 256, 4096, 4, 2, 100, True),                                          # packed gate/up
