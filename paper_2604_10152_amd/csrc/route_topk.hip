@@ -68,6 +68,7 @@ __device__ __forceinline__ bool better(double av, int aid, double bv, int bid) {
 // the slot it would fill -, the other logits arriving through v_readlane broadcasts.  Kernel time, rounds /
 // counting: 64 experts x 2048, top-6 8.9 / 11.2 us, top-16 11.0 / 11.6, 16 experts top-4 5.1 / 5.3, 8 top-2 4.3 / 4.3.
 // id: what an expert is called in the output (the draft mode's substitution).
+template <bool THEN>
 __device__ __forceinline__ void rank_token(const double* logit, int lane, int E, int k, int renorm,
                                            int t, int32_t* __restrict__ idx_out,
                                            float* __restrict__ w_out, int id) {
@@ -109,7 +110,8 @@ __device__ __forceinline__ void rank_token(const double* logit, int lane, int E,
         wsum_sel += lane_value(p, src);
     }
     if (valid && rank < k) {
-        store_id(idx_out + (size_t)t * k + rank, id);
+        if (THEN) store_id(idx_out + (size_t)t * k + rank, id);
+        else idx_out[(size_t)t * k + rank] = id;
         w_out[(size_t)t * k + rank] = (float)(renorm ? p / wsum_sel : p);
     }
 }
@@ -125,7 +127,6 @@ struct Then {
 };
 template <int WAVES>
 __device__ __forceinline__ void permute_if_last(const Then& then, const int32_t* idx, int P, int E) {
-    if (!then.done) return;
     __shared__ int cnt[WAVES][kWave];
     __shared__ bool last;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -135,7 +136,9 @@ __device__ __forceinline__ void permute_if_last(const Then& then, const int32_t*
     if (last) permute_index_small<WAVES, 6, true>(idx, P, E, then.offsets, then.row_src, then.row_of, cnt);
 }
 
-template <typename T, bool VEC, int TOK, int EC, int W>
+// THEN: as Then says.  A form of its own: the registers of the index phase leave room for fewer workgroups (277 tokens of 43
+// columns, fp32 layer 34.9 -> 35.9).
+template <typename T, bool VEC, int TOK, int EC, int W, bool THEN>
 __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     const T* __restrict__ x, const T* __restrict__ wr, const float* __restrict__ bias, int Tn,
     int d, int E, int k, int renorm, int32_t* idx_out, float* __restrict__ w_out,
@@ -249,8 +252,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
     const int t = t0 + wave_all;
     const double* logit = logits + (size_t)wave_all * E;
     if (E <= kWave) {
-        if (wave_all < TOK && t < Tn) rank_token(logit, lane, E, k, renorm, t, idx_out, w_out, id);
-        permute_if_last<kRouteThreads / kWave>(then, idx_out, Tn * k, E);
+        if (wave_all < TOK && t < Tn) rank_token<THEN>(logit, lane, E, k, renorm, t, idx_out, w_out, id);
+        if constexpr (THEN) permute_if_last<kRouteThreads / kWave>(then, idx_out, Tn * k, E);
         return;
     }
     if (wave_all >= TOK || t >= Tn) return;
@@ -411,7 +414,7 @@ __global__ __launch_bounds__(kMfmaWaves * kWave) void route_topk_mfma_kernel(
     __syncthreads();
     static_assert(4 * RT <= kMfmaWaves, "a wave ranks one token");
     if (wave < 4 * RT && t0 + wave < Tn)
-        rank_token(logits[wave], lane, E, k, renorm, t0 + wave, idx_out, w_out, id);
+        rank_token<false>(logits[wave], lane, E, k, renorm, t0 + wave, idx_out, w_out, id);
 }
 
 template <int RT>
@@ -434,8 +437,12 @@ void launch_variant(const T* x, const T* wr, const float* bias, int Tn, int d, i
                     int renorm, int32_t* idx, float* w, const int32_t* remap, Then then, hipStream_t s) {
     dim3 grid((Tn + TOK - 1) / TOK), block(kRouteThreads);
     size_t lds = ((size_t)TOK * E + (size_t)(kRouteThreads / kWave) * TOK * EC) * sizeof(double);
-    hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC, W>), grid, block, lds, s, x, wr, bias, Tn,
-                       d, E, k, renorm, idx, w, remap, then);
+    if (then.done)
+        hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC, W, true>), grid, block, lds, s, x, wr, bias, Tn,
+                           d, E, k, renorm, idx, w, remap, then);
+    else
+        hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC, W, false>), grid, block, lds, s, x, wr, bias, Tn,
+                           d, E, k, renorm, idx, w, remap, then);
 }
 
 // Experts per group and pass: the group's share of E rounded up to a power of two, at most 16 / TOK.

@@ -32,9 +32,12 @@ class MoEVerifyLayer:
         self.y_perm = torch.empty((P, d_model), dtype=dtype, device=dev)
         self.out = torch.empty((T, d_model), dtype=dtype, device=dev)
         self.h = torch.empty((P, d_ff), dtype=dtype, device=dev)
-        self.counter = torch.zeros((1,), **i32)  # of the router's workgroups; 0 between calls
-        if dev.type == "cuda" and not torch.cuda.is_current_stream_capturing():
-            torch.cuda.current_stream(dev).synchronize()     # the first call may come on another stream
+        # Of a small batch's router workgroups (moe_layer_forward_counted), 0 between calls.  Cleared on the stream of this
+        # moment, which the first call waits for if it comes on another one.
+        self.counter = self._cleared_on = None
+        if T <= 64 and E <= 64 and dev.type == "cuda":
+            self.counter = torch.zeros((1,), **i32)
+            self._cleared_on = torch.cuda.current_stream(dev)
         self.h_packed = None                     # allocated on first use of packed weights
         self.x_packed = None
 
@@ -104,6 +107,17 @@ class MoEVerifyLayer:
             out[name] = wp
         return out
 
+    def _own_counter(self, stream):
+        if self._cleared_on is not None:                     # the first call
+            now = torch.cuda.current_stream(self.out.device) if stream is None else stream
+            if now != self._cleared_on:
+                with torch.cuda.stream(now):
+                    if torch.cuda.is_current_stream_capturing():
+                        return None                          # a capture cannot wait for what it does not hold
+                now.wait_stream(self._cleared_on)
+            self._cleared_on = None
+        return self.counter
+
     def forward(self, x, w_router, w_gate, w_up, w_down, bias=None, residual=None, out=None,
                 stream=None, marks=None, draft_remap=None, packed=None):
         """Enqueues the layer.  `marks`, if given, is a sequence of six torch events recorded on
@@ -146,7 +160,7 @@ class MoEVerifyLayer:
                 packed["w_down"] if down_packed else w_down,
                 residual, self.k, self.renorm, layout, self.topk_idx, self.topk_w, self.expert_offsets,
                 self.row_src, self.row_of, self.x_packed, self.h_packed if down_packed else self.h,
-                self.y_perm, out, stream, self.counter)
+                self.y_perm, out, stream, self._own_counter(stream))
             return out
         # with marks, or x_perm written first: the same steps and layouts as calls of their own
         if marks is not None:

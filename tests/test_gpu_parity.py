@@ -1256,7 +1256,7 @@ def test_router_permutes_like_the_two_calls(dtype, d, E, k, T):
         for got, want in ((layer.topk_idx, idx), (layer.topk_w, w), (layer.expert_offsets, off), (layer.row_src, src),
                           (layer.row_of, of)):
             assert torch.equal(got, want)
-        assert int(layer.counter.item()) == 0
+        assert (layer.counter is None) == (T > 64 or E > 64) and not (layer.counter is not None and int(layer.counter.item()))
 
 
 @pytest.mark.parametrize("dtype,d,f,E,k,T,draft", [
