@@ -6,8 +6,8 @@ namespace {
 
 using namespace pipe;
 
-typedef PersistCfg<160, 256, 3, true, false, false> Up;
-typedef PersistCfg<160, 256, 3, false, false, false> Down;
+typedef PersistCfg<160, 256, 3, true> Up;
+typedef PersistCfg<160, 256, 3, false> Down;
 
 template <typename C, bool GATHER, bool HALVES>
 __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_persist_kernel(
@@ -17,7 +17,7 @@ __global__ __launch_bounds__(C::THREADS) void grouped_gemm_bf16_persist_kernel(
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
     TileTable<C::BM> table;
     table.load(offsets, E);
-    persist_tiles<C, false, GATHER, HALVES>(lds_raw, table, A, W0, W1, N, K, Cout, row_src, topk, stream_out,
+    persist_tiles<C, GATHER, HALVES>(lds_raw, table, A, W0, W1, N, K, Cout, row_src, topk, stream_out,
                                             group > 0 && !table.even() ? group : 0);
 }
 

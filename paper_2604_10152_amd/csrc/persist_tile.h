@@ -6,8 +6,8 @@
 // What a tile costs besides its k loop in the other kernels - finding it 1.1 us, the first stage's way out of HBM
 // 1.3, the epilogue 1.2, and the time until the next workgroup starts - passes while requests are in flight here.
 //
-// A stage is 64 columns: whole 128-byte lines of row-major operands, or two 1 KB blocks of tile-packed ones
-// (pipe_common.h), three stages in the LDS, of which one or two are in flight.  Two k-steps per stage, in the ping-pong
+// Row-major operands.  A stage is 64 columns, whole 128-byte lines; three stages in the LDS, of which one or two are
+// in flight.  Two k-steps per stage, in the ping-pong
 // schedule of pipe16_tile.h (s = k-step, q = s / 2 its stage):
 //   phase 2s  : group 0 reads step s        | group 1 multiplies step s-1
 //   phase 2s+1: group 0 multiplies step s   | group 1 reads step s
@@ -19,21 +19,21 @@
 namespace specmoe {
 namespace pipe {
 
-template <int BM_, int BN_, int STAGES_, bool SWIGLU_, bool PA_, bool PB_>
+template <int BM_, int BN_, int STAGES_, bool SWIGLU_>
 struct PersistCfg {
     static constexpr int BM = BM_, BN = BN_, STAGES = STAGES_, WM = 2, WN = 4;
-    static constexpr bool SWIGLU = SWIGLU_, PA = PA_, PB = PB_;
+    static constexpr bool SWIGLU = SWIGLU_;
     static constexpr int BK = 64, KSUB = BK / 32, ROW_BYTES = BK * 2;
     static constexpr int NWAVES = WM * WN, THREADS = NWAVES * kWave;
     static constexpr int TM = BM / (16 * WM), TN = BN / (16 * WN);   // 16 x 16 sub-tiles per wave
     static constexpr int BN_OUT = SWIGLU ? BN / 2 : BN;
-    // wave-loads of 1 KB per stage and wave: 8 rows of whole lines, or one packed block of 16 rows and 32 columns
-    static constexpr int A_PW = PA ? KSUB * ((BM / 16 + NWAVES - 1) / NWAVES) : (BM / 8 + NWAVES - 1) / NWAVES;
+    // wave-loads of 1 KB per stage and wave: 8 rows of whole lines
+    static constexpr int A_PW = (BM / 8 + NWAVES - 1) / NWAVES;
     static constexpr int B_PW = BN / 8 / NWAVES;
     static constexpr int A_BYTES = BM * ROW_BYTES, STAGE_BYTES = (BM + BN) * ROW_BYTES;
     static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE_BYTES + (BM + kWave - 1) / kWave * 256;   // row numbers of the next tile
     static_assert(BM % (16 * WM) == 0 && BN % (32 * WN) == 0, "tile");
-    static_assert(!SWIGLU || BN / 2 / (PB ? 16 : 8) % NWAVES == 0, "a round of wave-loads is all gate or all up");
+    static_assert(!SWIGLU || BN / 2 / 8 % NWAVES == 0, "a round of wave-loads is all gate or all up");
     static_assert(STAGES >= 3 && (STAGES - 2) * (A_PW + B_PW) <= 63, "ring depth (vmcnt is 6 bits)");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
@@ -41,14 +41,12 @@ struct PersistCfg {
 // Tiles of up to 64 experts out of registers: a lane holds one expert.
 template <int BM>
 struct TileTable {
-    int lo, rows, mt, rpt, incl, blk;        // of the lane's expert; incl: m-tiles up to it, blk: 16-row blocks before it
+    int lo, rows, mt, rpt, incl;             // of the lane's expert; incl: m-tiles up to it
     int total;                               // m-tiles of all
     __device__ __forceinline__ void load(const int32_t* __restrict__ offsets, int E) {
         const int e = threadIdx.x % kWave;
         lo = e < E ? offsets[e] : 0;
         rows = e < E ? offsets[e + 1] - lo : 0;
-        const int nb = (rows + 15) / 16;
-        blk = wave_scan(nb) - nb;
         const EvenSplit s = even_split<BM, 16>(rows);
         mt = s.mt;
         rpt = s.rpt;
@@ -81,7 +79,7 @@ struct TileTable {
         t.nt = nt0 + j;
         t.row0 = of(lo) + first;
         t.tile_rows = min(of(rpt), of(rows) - first);
-        t.blk0 = of(blk) + first / 16;
+        t.blk0 = 0;                          // (of tile-packed rows)
         t.half = -1;
         return t;
     }
@@ -104,13 +102,12 @@ __device__ __forceinline__ void wait_stages(int n) {
 }
 
 // The tiles of workgroup blockIdx.x < kCus.  lds_raw: C::LDS_BYTES.  K >= 256, K % 64 == 0.
-// PO: h leaves tile-packed.  GATHER: row r of the activations is A[row_src[r] / topk].
-template <typename C, bool PO, bool GATHER, bool HALVES>
+// GATHER: row r of the activations is A[row_src[r] / topk].
+template <typename C, bool GATHER, bool HALVES>
 __device__ __forceinline__ void persist_tiles(
     unsigned char* lds_raw, const TileTable<C::BM>& table, const bf16_t* __restrict__ A,
     const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N, int K,
     bf16_t* __restrict__ Cout, const int32_t* __restrict__ row_src, int topk, bool stream_out, int group) {
-    static_assert(!(C::PA && GATHER), "packed rows are gathered already");
     constexpr int S = C::STAGES, KSUB = C::KSUB;
     constexpr int B_MIN = HALVES ? C::B_PW / 2 : C::B_PW, MORE = C::A_PW + C::B_PW - B_MIN;     // wave-loads of a stage
     const int lane = threadIdx.x % kWave;
@@ -136,7 +133,7 @@ __device__ __forceinline__ void persist_tiles(
     auto column = [](const TileLoc& t) { return t.nt * C::BN_OUT + (HALVES && t.half > 0 ? C::BN_OUT / 2 : 0); };
     TileLoc t = tile_at(slot);
 
-    // ---- requests.  Row-major: lane l of a wave-load brings chunk (l % 8) ^ swizzle of row l / 8; the swizzle
+    // ---- requests.  Lane l of a wave-load brings chunk (l % 8) ^ swizzle of row l / 8; the swizzle
     // 2 * ((row / 2) % 4) keeps 16-row reads of 128-byte rows free of bank conflicts.
     const unsigned char *a_base, *w0, *w1 = nullptr;
     uint32_t a_off[C::A_PW], b_off[C::B_PW];
@@ -145,7 +142,7 @@ __device__ __forceinline__ void persist_tiles(
     const bool single = !C::SWIGLU || __ballot(table.mt > 1) == 0;
     auto request_from = [&](const TileLoc& t, auto from_lds) __attribute__((always_inline)) {
         a_base = uniform_ptr(reinterpret_cast<const unsigned char*>(
-            A + (C::PA ? (size_t)t.blk0 * 16 * K : (GATHER ? (size_t)0 : (size_t)t.row0 * K))));
+            A + (GATHER ? (size_t)0 : (size_t)t.row0 * K)));
         const int n0 = HALVES ? min(column(t), N - 16) : column(t), n_left = N - n0;   // a second half may lie beyond N
         const int bn = HALVES && t.half >= 0 ? C::BN / 2 : C::BN;    // weight rows of the tile
         b_cnt = HALVES && t.half >= 0 ? C::B_PW / 2 : C::B_PW;
@@ -157,61 +154,40 @@ __device__ __forceinline__ void persist_tiles(
         const uint32_t chunk = (uint32_t)(((lane & 7) ^ ((lane >> 3) & 6)) * 16);
 #pragma unroll
         for (int jj = 0; jj < C::A_PW; ++jj) {
-            if (C::PA) {
-                const int jb = wave + jj / KSUB * C::NWAVES;
-                a_off[jj] = (unsigned)min(jb, (t.tile_rows + 15) / 16 - 1) * 32u * (unsigned)K +
-                            (unsigned)(jj % KSUB) * 1024u + (unsigned)lane * 16u;
-                if (jb * 16 < t.tile_rows) a_cnt = jj + 1;
-            } else {
-                const int j = wave + jj * C::NWAVES, rr = min(j * 8 + (lane >> 3), t.tile_rows - 1);
-                unsigned row = (unsigned)rr;
-                if (GATHER)
-                    row = (unsigned)((decltype(from_lds)::value ? lds_rows[rr] : row_src[t.row0 + rr]) / topk);
-                a_off[jj] = row * (unsigned)K * 2u + chunk;
-                if (j * 8 < t.tile_rows) a_cnt = jj + 1;
-            }
+            const int j = wave + jj * C::NWAVES, rr = min(j * 8 + (lane >> 3), t.tile_rows - 1);
+            unsigned row = (unsigned)rr;
+            if (GATHER)
+                row = (unsigned)((decltype(from_lds)::value ? lds_rows[rr] : row_src[t.row0 + rr]) / topk);
+            a_off[jj] = row * (unsigned)K * 2u + chunk;
+            if (j * 8 < t.tile_rows) a_cnt = jj + 1;
         }
 #pragma unroll
         for (int jj = 0; jj < C::B_PW; ++jj) {
-            if (C::PB) {
-                const int r = (wave + jj / KSUB * C::NWAVES) * 16, rn = C::SWIGLU && r >= bn / 2 ? r - bn / 2 : r;
-                b_off[jj] = (uint32_t)min(rn / 16, n_left / 16 - 1) * 32u * (uint32_t)K +
-                            (uint32_t)(jj % KSUB) * 1024u + (uint32_t)lane * 16u;
-            } else {
-                const int r = (wave + jj * C::NWAVES) * 8 + (lane >> 3);
-                const int rn = C::SWIGLU && r >= bn / 2 ? r - bn / 2 : r;
-                b_off[jj] = (uint32_t)min(rn, n_left - 1) * (uint32_t)K * 2u + chunk;
-            }
+            const int r = (wave + jj * C::NWAVES) * 8 + (lane >> 3);
+            const int rn = C::SWIGLU && r >= bn / 2 ? r - bn / 2 : r;
+            b_off[jj] = (uint32_t)min(rn, n_left - 1) * (uint32_t)K * 2u + chunk;
         }
     };
     // Part `part` of KSUB of this wave's share of stage kq, into ring slot buf.
     auto request = [&](int part, int kq, int buf) __attribute__((always_inline)) {
-        const uint32_t ka = (uint32_t)kq * (C::PA ? KSUB * 1024u : (uint32_t)C::ROW_BYTES);
-        const uint32_t kb = (uint32_t)kq * (C::PB ? KSUB * 1024u : (uint32_t)C::ROW_BYTES);
+        const uint32_t kb = (uint32_t)kq * (uint32_t)C::ROW_BYTES;
         const uint32_t to = lds_base + (uint32_t)buf * C::STAGE_BYTES + wave * 1024u;
-        // packed: the blocks of the stage's first 32 columns, then those of the others
-        auto place = [](bool packed, int rows, int jj) {
-            return packed ? (jj % KSUB) * rows * 64 + jj / KSUB * C::NWAVES * 1024 : jj * C::NWAVES * 1024;
-        };
 #pragma unroll
         for (int jj = 0; jj < C::A_PW; ++jj)
-            if (jj % KSUB == part && jj < a_cnt) dma16(a_base, a_off[jj] + ka, to + place(C::PA, C::BM, jj));
+            if (jj % KSUB == part && jj < a_cnt) dma16(a_base, a_off[jj] + kb, to + jj * C::NWAVES * 1024u);
 #pragma unroll
         for (int jj = 0; jj < C::B_PW; ++jj)
             if (jj % KSUB == part && jj < b_cnt) {
-                const bool up = C::SWIGLU && (HALVES && C::PB && b_cnt < C::B_PW ? wave >= C::NWAVES / 2 : jj >= b_cnt / 2);
-                const uint32_t at = to + C::A_BYTES + place(C::PB, C::BN, jj);
+                const bool up = C::SWIGLU && jj >= b_cnt / 2;
+                const uint32_t at = to + C::A_BYTES + jj * C::NWAVES * 1024u;
                 if (once) dma16_nt(up ? w1 : w0, b_off[jj] + kb, at);
                 else dma16(up ? w1 : w0, b_off[jj] + kb, at);
             }
     };
-    // ---- fragment reads: lane l reads row l % 16 of a sub-tile, 16-byte chunk l / 16 of the k-step
-    auto read_at = [&](bool packed) {
-        const int r = lane & 15, c = lane >> 4;
-        return packed ? r * 64 + ((c ^ ((r >> 1) & 3)) << 4) : r * C::ROW_BYTES + ((c ^ (r & 6)) << 4);
-    };
-    const int a_rd = read_at(C::PA) + 16 * wm * (C::PA ? 64 : C::ROW_BYTES), b_rd = read_at(C::PB);
-    constexpr int A_ROW = C::PA ? 64 : C::ROW_BYTES, B_ROW = C::PB ? 64 : C::ROW_BYTES;
+    // ---- fragment reads: lane l reads row l % 16 of a sub-tile, 16-byte chunk l / 16 of the k-step (the second k-step
+    // of a stage: + 4, which the swizzle makes address ^ 64)
+    const int b_rd = (lane & 15) * C::ROW_BYTES + (((lane >> 4) ^ (lane & 6)) << 4);
+    const int a_rd = b_rd + 16 * wm * C::ROW_BYTES;
 
     request_from(t, std::false_type{});
 #pragma unroll
@@ -260,14 +236,14 @@ __device__ __forceinline__ void persist_tiles(
                         request(h, kq, buf == 0 ? S - 1 : buf - 1);
                         if (TA > 0) {
                             const unsigned char* st = lds_raw + buf * C::STAGE_BYTES;
-                            const unsigned char* sa = st + (C::PA ? a_rd + h * C::BM * 64 : a_rd ^ (h * 64));
-                            const unsigned char* sb = st + C::A_BYTES + (C::PB ? b_rd + h * C::BN * 64 : b_rd ^ (h * 64));
+                            const unsigned char* sa = st + (a_rd ^ (h * 64));
+                            const unsigned char* sb = st + C::A_BYTES + (b_rd ^ (h * 64));
 #pragma unroll
                             for (int j = 0; j < TN; ++j)
-                                bfr[j] = *reinterpret_cast<const bf16x8*>(sb + nb(j) * B_ROW);
+                                bfr[j] = *reinterpret_cast<const bf16x8*>(sb + nb(j) * C::ROW_BYTES);
 #pragma unroll
                             for (int m = 0; m < TA; ++m)
-                                af[m] = *reinterpret_cast<const bf16x8*>(sa + m * 16 * C::WM * A_ROW);
+                                af[m] = *reinterpret_cast<const bf16x8*>(sa + m * 16 * C::WM * C::ROW_BYTES);
                         }
                         if (h == KSUB - 1 && wm == 1) wait_stages<S - 2, B_MIN, MORE>(allow);
                         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -302,7 +278,7 @@ __device__ __forceinline__ void persist_tiles(
             }
             allow = b_cnt + a_cnt;
             // (stores count as loads in flight: the waits that follow are stricter, never weaker)
-            write_sub_tiles<TA, C::WM, C::SWIGLU, PO>(acc, t, column(t), N, Cout, wm, wn, stream_out);
+            write_sub_tiles<TA, C::WM, C::SWIGLU, false>(acc, t, column(t), N, Cout, wm, wn, stream_out);
         };
         auto run = [&](auto ta_tag) __attribute__((always_inline)) {
             if constexpr (HALVES) {
