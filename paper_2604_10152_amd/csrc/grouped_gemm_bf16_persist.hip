@@ -35,10 +35,10 @@ hipError_t launch(const bf16_t* A, const int32_t* offsets, const bf16_t* W0, con
     return hipGetLastError();
 }
 
-// Tiles of an even batch, with 15 % for the spread of its rows.
+// Tiles of an even batch, with 15 % for the spread of its rows; a batch meets no more experts than it has rows.
 long long tiles_of(int n_rows, int E, int N, int rows, int outputs) {
     const long long m = (115ll * n_rows + 100ll * rows * E - 1) / (100ll * rows * E);
-    return E * m * ((N + outputs - 1) / outputs);
+    return (n_rows < E ? n_rows : E) * m * ((N + outputs - 1) / outputs);
 }
 // Whether the persistent tiles are the better ones for an even batch: at least three quarters of the CUs get one, and
 // they take at most half as many rounds of the chip as the half as wide tiles of the other kernels do (`slack`: more).
@@ -58,11 +58,12 @@ bool persist_wins(int n_rows, int E, int N, int outputs, int slack) {
 //  - from 4096 on two rounds of one m-tile per expert, with the tile order in groups and the last round in halves:
 //    16 x 5120 x 8192, 16 rows 437 / 408, 64 rows 557 / 502, skewed 588 / 504, 128 rows 567 / 520; 8 x 4096 x 14336, 20 rows 309 / 304, 125
 //    rows 396 / 349, 83 rows skewed 393 / 335, two of them with 16 rows 79 / 76; but 175 rows (two m-tiles) 447 / 496, and four of 16 x
-//    4096 x 2048 40 / 56.
+//    4096 x 2048 40 / 56.  At least one round of the experts that can be met (one row, 16 x 5120 x 8192, layer 76 / 84).
 bool launches_expert_up_bf16_persist(int n_rows, int d, int f, int E) {
     if (d < kTailMinK) return d >= 2048 && persist_wins(n_rows, E, f, Up::BN_OUT, 0);
-    const long long tiles = tiles_of(n_rows, E, f, Up::BM, Up::BN_OUT);
-    return E <= kWave && 115ll * n_rows <= 100ll * Up::BM * E && tiles >= 2 * kCus;
+    const long long per_expert = (f + Up::BN_OUT - 1) / Up::BN_OUT;
+    return E <= kWave && 115ll * n_rows <= 100ll * Up::BM * E && E * per_expert >= 2 * kCus &&
+           n_rows * per_expert >= kCus;
 }
 hipError_t launch_expert_up_bf16_persist(const bf16_t* x_perm, const int32_t* offsets, const bf16_t* wg,
                                          const bf16_t* wu, int n_rows, int d, int f, int E, bf16_t* h,
