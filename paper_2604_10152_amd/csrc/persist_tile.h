@@ -85,10 +85,11 @@ struct TileTable {
     }
 };
 
-// 64 lanes x 4 bytes: global -> LDS [lds_addr, + 256)
+// 64 lanes x 4 bytes: global -> LDS [lds_addr, + 256); the base as in dma16
 __device__ __forceinline__ void dma4(const void* gbase, uint32_t voff, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
-                 :: "v"(voff), "s"(gbase), "s"(lds_addr) : "memory", "m0");
+    uint64_t base;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dword %1, %0"
+                 : "=&s"(base) : "v"(voff), "s"(gbase), "s"(lds_addr) : "memory", "m0");
 }
 // waits until at most STEP * n loads are in flight, BASE <= n <= BASE + MORE
 template <int STEP, int BASE, int MORE>

@@ -61,16 +61,22 @@ constexpr int kPackRows = 16, kPackCols = 32;
 constexpr int kStageRowBytes = 128 * 2 + 16;
 
 // 64 lanes x 16 bytes: global (uniform base + per-lane byte offset) -> LDS [lds_addr, +1024).
-// The LDS destination travels in m0, which the statement overwrites (declared as a clobber).
+// The LDS destination travels in m0, which the statement overwrites (declared as a clobber).  A load must not read
+// a scalar register that a vector instruction (v_readlane of a spilled base, v_readfirstlane) wrote less than five wait
+// states before, and the compiler does not see the load in here: the base goes through a scalar move, which
+// waits for such a write by itself and is also the wait state that m0 needs before the load.  (Three more wait
+// states instead: 16 x 5120 x 8192, 2048 tokens, gate/up 498 -> 513 us, down 306 -> 319.)
 __device__ __forceinline__ void dma16(const void* gbase, uint32_t voff, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(voff), "s"(gbase), "s"(lds_addr) : "memory", "m0");
+    uint64_t base;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+                 : "=&s"(base) : "v"(voff), "s"(gbase), "s"(lds_addr) : "memory", "m0");
 }
 // The same with the non-temporal hint: for data that is read once (expert weights streamed out
 // of HBM).  Measured on a 4 GiB LDS-DMA stream: 5.7 TB/s without the hint, 6.3 TB/s with it.
 __device__ __forceinline__ void dma16_nt(const void* gbase, uint32_t voff, uint32_t lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
-                 :: "v"(voff), "s"(gbase), "s"(lds_addr) : "memory", "m0");
+    uint64_t base;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0 nt"
+                 : "=&s"(base) : "v"(voff), "s"(gbase), "s"(lds_addr) : "memory", "m0");
 }
 // 16 bytes per lane to global memory; `stream`: with the non-temporal hint (streams_output()).  The hinted store is
 // inline assembly because the compiler merges the two sides of the choice into one store without the hint; the

@@ -1,0 +1,54 @@
+"""Wait states that statements of inline assembly have to bring along, in the built gfx950 code: the compiler inserts
+them for its own instructions only.  Needs no GPU."""
+import re
+import shutil
+import struct
+import subprocess
+
+import pytest
+
+import paper_2604_10152_amd as sm
+from paper_2604_10152_amd import binding
+
+OBJDUMP = shutil.which("llvm-objdump", path="/opt/rocm/llvm/bin") or shutil.which("llvm-objdump")
+
+
+def _code_objects():
+    sm.load_library()                                       # builds it if it is not there
+    blob, magic, at = open(binding.lib_path(), "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", 0
+    while (at := blob.find(magic, at)) >= 0:
+        p = at + len(magic)
+        (entries,) = struct.unpack_from("<Q", blob, p)
+        p += 8
+        for _ in range(entries):
+            offset, size, n = struct.unpack_from("<QQQ", blob, p)
+            if b"gfx950" in blob[p + 24:p + 24 + n] and size:
+                yield blob[at + offset:at + offset + size]
+            p += 24 + n
+        at += len(magic)
+
+
+@pytest.fixture(scope="module")
+def listing(tmp_path_factory):
+    """All instructions in order, one string each."""
+    if OBJDUMP is None:
+        pytest.skip("no llvm-objdump")
+    out = []
+    for i, code in enumerate(_code_objects()):
+        path = tmp_path_factory.mktemp("code") / f"{i}.co"
+        path.write_bytes(code)
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", str(path)],
+                              capture_output=True, text=True, check=True).stdout
+        out += [" ".join(line.split("//")[0].split()) for line in text.splitlines() if line.startswith("\t")]
+    return out
+
+
+def test_lds_loads_take_their_base_from_a_scalar_move(listing):
+    """A load that reads a scalar register needs five wait states behind a vector instruction that wrote it
+    (v_readlane of a spilled pointer); a scalar move right before it waits by itself."""
+    at = [i for i, x in enumerate(listing) if x.startswith("global_load_lds_")]
+    assert len(at) > 500
+    for i in at:
+        base = re.search(r"(s\[\d+:\d+\])", listing[i]).group(1)
+        assert listing[i - 1].startswith(f"s_mov_b64 {base},"), listing[i - 6:i + 1]
+        assert listing[i - 2].startswith("s_mov_b32 m0,"), listing[i - 6:i + 1]
