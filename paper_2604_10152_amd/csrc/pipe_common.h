@@ -80,12 +80,13 @@ __device__ __forceinline__ void dma16_nt(const void* gbase, uint32_t voff, uint3
 }
 // 16 bytes per lane to global memory; `stream`: with the non-temporal hint (streams_output()).  The hinted store is
 // inline assembly because the compiler merges the two sides of the choice into one store without the hint; the
-// s_nop keeps a following write to the data registers one wait state away, as stores of 16 bytes need.
+// s_nop keeps a following vector write to the data registers two wait states away, as stores of more than 8 bytes
+// need on gfx950 (one on gfx90a).
 __device__ __forceinline__ void store16(bool stream, void* base, uint32_t offset, U128 v) {
     typedef U128 Any __attribute__((aligned(2)));
     unsigned char* p = static_cast<unsigned char*>(base) + offset;
     if (stream)
-        asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 0" :: "v"(p), "v"(v) : "memory");
+        asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" :: "v"(p), "v"(v) : "memory");
     else
         *reinterpret_cast<Any*>(p) = v;
 }

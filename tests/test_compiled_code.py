@@ -52,3 +52,12 @@ def test_lds_loads_take_their_base_from_a_scalar_move(listing):
         base = re.search(r"(s\[\d+:\d+\])", listing[i]).group(1)
         assert listing[i - 1].startswith(f"s_mov_b64 {base},"), listing[i - 6:i + 1]
         assert listing[i - 2].startswith("s_mov_b32 m0,"), listing[i - 6:i + 1]
+
+
+def test_hinted_stores_keep_their_data_for_two_wait_states(listing):
+    """A vector instruction must not write the data registers of a 16-byte store within two wait states behind it."""
+    at = [i for i, x in enumerate(listing) if x.startswith("global_store_dwordx4") and x.endswith(" nt")]
+    assert len(at) > 500
+    for i in at:
+        m = re.fullmatch(r"s_nop (\d+)", listing[i + 1])
+        assert m and int(m.group(1)) >= 1, listing[i:i + 4]
