@@ -32,12 +32,10 @@ class MoEVerifyLayer:
         self.y_perm = torch.empty((P, d_model), dtype=dtype, device=dev)
         self.out = torch.empty((T, d_model), dtype=dtype, device=dev)
         self.h = torch.empty((P, d_ff), dtype=dtype, device=dev)
-        # Of a small batch's router workgroups (moe_layer_forward_counted), 0 between calls.  Cleared on the stream of this
-        # moment, which the first call waits for if it comes on another one.
-        self.counter = self._cleared_on = None
-        if T <= 64 and E <= 64 and dev.type == "cuda":
-            self.counter = torch.zeros((1,), **i32)
-            self._cleared_on = torch.cuda.current_stream(dev)
+        # Of a small batch's router workgroups (moe_layer_forward_counted), 0 between calls once _own_counter() has
+        # cleared it.
+        self.counter = torch.empty((1,), **i32) if T <= 64 and E <= 64 and dev.type == "cuda" else None
+        self._counter_is_clear = False
         self.h_packed = None                     # allocated on first use of packed weights
         self.x_packed = None
 
@@ -108,14 +106,14 @@ class MoEVerifyLayer:
         return out
 
     def _own_counter(self, stream):
-        if self._cleared_on is not None:                     # the first call
-            now = torch.cuda.current_stream(self.out.device) if stream is None else stream
-            if now != self._cleared_on:
-                with torch.cuda.stream(now):
-                    if torch.cuda.is_current_stream_capturing():
-                        return None                          # a capture cannot wait for what it does not hold
-                now.wait_stream(self._cleared_on)
-            self._cleared_on = None
+        """The counter, cleared on the stream of the first call that runs at once: whatever stream the layer was made
+        on owes it nothing.  None while a capture comes before that call: its clearing would only be recorded."""
+        if self.counter is not None and not self._counter_is_clear:
+            with torch.cuda.stream(stream if stream is not None else torch.cuda.current_stream(self.out.device)):
+                if torch.cuda.is_current_stream_capturing():
+                    return None
+                self.counter.zero_()
+            self._counter_is_clear = True
         return self.counter
 
     def forward(self, x, w_router, w_gate, w_up, w_down, bias=None, residual=None, out=None,

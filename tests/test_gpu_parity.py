@@ -1259,6 +1259,78 @@ def test_router_permutes_like_the_two_calls(dtype, d, E, k, T):
         assert (layer.counter is None) == (T > 64 or E > 64) and not (layer.counter is not None and int(layer.counter.item()))
 
 
+class _SmallLayer:
+    """A layer of 40 tokens with its inputs, and its steps as calls of their own."""
+
+    def __init__(self):
+        T, d, f, E, k = self.shape = 40, 128, 64, 16, 3
+        g = torch.Generator(device="cuda").manual_seed(40)
+        self.rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+        self.x, self.w = self.rnd(T, d), (self.rnd(E, d), self.rnd(E, f, d), self.rnd(E, f, d), self.rnd(E, d, f))
+        self.ref = sm.MoEVerifyLayer(T, d, f, E, k, torch.bfloat16)
+
+    def make(self):
+        return sm.MoEVerifyLayer(*self.shape, torch.bfloat16)
+
+    def check(self, layer):
+        marks = [torch.cuda.Event() for _ in range(6)]        # with marks, the steps are separate calls
+        torch.cuda.synchronize()
+        self.ref.forward(self.x, *self.w, marks=marks)
+        torch.cuda.synchronize()
+        for name in ("topk_idx", "expert_offsets", "row_src", "row_of", "out"):
+            assert torch.equal(getattr(layer, name), getattr(self.ref, name)), name
+        assert not layer._counter_is_clear or int(layer.counter.item()) == 0
+
+
+def test_small_layer_made_and_first_called_under_capture():
+    """What a capture records has not run: neither a call before the first replay nor one after a capture that was given
+    up may rely on it."""
+    c = _SmallLayer()
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    c.make().forward(c.x, *c.w)                              # one-time set-up of the kernels
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        layer = c.make()
+        layer.forward(c.x, *c.w, stream=stream)
+    layer.counter.fill_(11)                                  # what uncleared memory may hold
+    for turn in range(4):
+        c.x.copy_(c.rnd(*c.x.shape))
+        layer.forward(c.x, *c.w)
+        c.check(layer)
+        c.x.copy_(c.rnd(*c.x.shape))
+        graph.replay()
+        c.check(layer)
+
+
+def test_small_layer_first_called_beside_its_own_stream():
+    """The first call on another stream owes the stream that the layer was made on nothing, not even while that one
+    captures; a later capture of the counted call replays like the eager one."""
+    c = _SmallLayer()
+    made, other, graph = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    c.make().forward(c.x, *c.w)
+    with torch.cuda.stream(made):
+        layer = c.make()
+    y = torch.zeros(8, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=made, capture_error_mode="thread_local"):
+        y.add_(1)
+        layer.forward(c.x, *c.w, stream=other)
+    c.check(layer)
+    graph.replay()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert y.tolist() == [2.0] * 8
+    step = sm.GraphedStep(lambda s: layer.forward(c.x, *c.w, stream=s))
+    for turn in range(4):
+        c.x.copy_(c.rnd(*c.x.shape))
+        torch.cuda.synchronize()
+        step.replay()
+        c.check(layer)
+        layer.forward(c.x, *c.w)
+        c.check(layer)
+
+
+
 @pytest.mark.parametrize("dtype,d,f,E,k,T,draft", [
     ("f32", 33, 50, 5, 2, 9, True), ("bf16", 4096, 128, 4, 2, 30, False),          # row-major
     ("bf16", 256, 4096, 4, 2, 100, True),                                          # packed gate/up
