@@ -334,11 +334,19 @@ static void launch_greedy_typed(const void* logits, int R, int V, int32_t* token
     // and shorter rows have nothing to request ahead (2048 x 1000: 4.2 us, 5.3 with it).
     const int per_thread = V / Row<T>::N / 256;
     const bool burst = vec && per_thread >= kRowBurst && (R <= 640 || (R <= 1024 && per_thread >= 48));
-    // From 100 MB on (two fifths of the memory-side cache, which whatever made the logits shares) the loads carry the
-    // non-temporal hint: a stream out of HBM runs at 7.0 TB/s with it and 6.1 without.  us, with spec_accept, without / with it,
-    // logits out of HBM and out of that cache: 2048 x 32000 bf16 30.5 / 27.7 and 26.0 / 26.9, fp32 53.5 / 47.1; 66 MB 20.6 / 19.8 and
-    // 16.2 / 19.1, 33 MB 11.6 / 12.6.
-    const bool stream = vec && !burst && (long long)R * V * (long long)sizeof(T) >= 100000000ll;
+    // Non-temporal loads for what the memory-side cache (256 MiB) cannot hold, and from 100 MB on for bf16, which
+    // reaches this kernel straight from the head's product; fp32 mostly comes from a cast, which leaves it in that cache.
+    // This kernel alone, us, without / with the hint, by what wrote the logits:
+    //             MB   product      cast or copy  scaling      nothing since a copy of 1 GB
+    //   bf16     102   24.3 / 23.1  21.8 / 26.2   20.1 / 21.6  33.4 / 22.2
+    //            131   29.0 / 27.0  25.2 / 28.5   24.0 / 25.4  41.0 / 26.1
+    //            205   41.2 / 38.8  43.9 / 39.5   44.1 / 41.2  59.4 / 38.4
+    //   fp32     166   35.2 / 28.8  39.3 / 44.4   36.0 / 39.5  50.2 / 31.4
+    //            262   58.4 / 42.5  47.6 / 50.0   53.0 / 54.6  75.9 / 43.6
+    //            269   70.6 / 49.9  62.4 / 58.8   68.0 / 63.1
+    //            352   84.7 / 62.2  102 / 71      98 / 72
+    const long long bytes = (long long)R * V * (long long)sizeof(T);
+    const bool stream = vec && !burst && (bytes > (256ll << 20) || (sizeof(T) == 2 && bytes >= 100000000ll));
     if (stream)
         hipLaunchKernelGGL((greedy_tokens_kernel<T, true, 1, true>), dim3(R), dim3(256), 0, s,
                            (const T*)logits, V, tokens);

@@ -289,9 +289,10 @@ def test_greedy_tokens_match_oracle(R, V, dtype):
     assert np.all(t == (lf == mx[:, None]).argmax(axis=1))
 
 
-@pytest.mark.parametrize("R,V,dtype", [(1100, 48008, torch.bfloat16), (1030, 24308, torch.float32)])
+@pytest.mark.parametrize("R,V,dtype", [(1100, 48008, torch.bfloat16), (1030, 24308, torch.float32),
+                                       (1400, 48008, torch.float32)])
 def test_greedy_tokens_of_many_long_rows(R, V, dtype):
-    """From 100 MB on the logits are read with the non-temporal hint."""
+    """From 100 MB (bf16) or 256 MiB (fp32) on the logits are read with the non-temporal hint."""
     _say(f"spec_greedy_tokens R={R} V={V} {dtype}")
     g = torch.Generator(device="cuda").manual_seed(R + V)
     logits = (torch.randn(R, V, generator=g, device="cuda") * 6).round().to(dtype) / 2       # ties at the top
