@@ -257,6 +257,8 @@ __device__ __forceinline__ void pipe_tile(
                 }
             }
         }
+        // the barrier behind does not wait for the writes to the LDS
+        if (C::SWIGLU) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
 
     static_assert(C::TM <= 5, "extend the dispatch below");
@@ -284,7 +286,7 @@ __device__ __forceinline__ void pipe_tile(
         // cooperative write-out of the staged tile: 16 bytes per lane, whole rows
         static_assert(!C::SWIGLU || (size_t)C::BM * kStageRowBytes <= C::LDS_BYTES, "stage tile");
         __builtin_amdgcn_s_barrier();
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        asm volatile("" ::: "memory");                      // no read moves up across it
         constexpr int CPR = C::BN_OUT / 8;                  // 16-byte chunks per tile row
         constexpr int RPP = C::THREADS / CPR;               // rows per pass
         const int cr = tid / CPR, cc = tid % CPR;

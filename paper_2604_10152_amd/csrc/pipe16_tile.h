@@ -243,6 +243,7 @@ __device__ __forceinline__ void pipe16_tile(
                     *reinterpret_cast<uint2*>(lds_raw + (16 * (wm + C::WM * i) + (lane & 15)) * kStageRowBytes +
                                               (16 * (wn * JN + j) + (lane >> 4) * 4) * 2) =
                         sub_tile<C::SWIGLU>(acc[i], j);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the barrier behind does not wait for the writes
         } else {
             write_sub_tiles<TA, C::WM, C::SWIGLU, PO>(acc, t, n0, N, Cout, wm, wn, stream_out);
         }
@@ -342,7 +343,7 @@ __device__ __forceinline__ void pipe16_tile(
         static_assert(!C::SWIGLU || PO || (size_t)C::BM * kStageRowBytes <= C::LDS_BYTES, "stage tile");
         static_assert(!C::SWIGLU || PO || C::BN_OUT == 128, "stage row pitch assumes 128 columns");
         __builtin_amdgcn_s_barrier();
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        asm volatile("" ::: "memory");                      // no read moves up across it
         constexpr int CPR = C::BN_OUT / 8;                  // 16-byte chunks per tile row
         constexpr int RPP = C::THREADS / CPR;               // rows per pass
         const int cr = tid / CPR, cc = tid % CPR;

@@ -1,5 +1,5 @@
-"""Wait states that statements of inline assembly have to bring along, in the built gfx950 code: the compiler inserts
-them for its own instructions only.  Needs no GPU."""
+"""Waits in the built gfx950 code that the compiler does not insert: the wait states that statements of inline assembly
+have to bring along, and what has to have arrived before a bare barrier.  Needs no GPU."""
 import re
 import shutil
 import struct
@@ -29,8 +29,8 @@ def _code_objects():
 
 
 @pytest.fixture(scope="module")
-def listing(tmp_path_factory):
-    """All instructions in order, one string each."""
+def kernels(tmp_path_factory):
+    """Every function as its instructions in order, each (address, text)."""
     if OBJDUMP is None:
         pytest.skip("no llvm-objdump")
     out = []
@@ -39,8 +39,18 @@ def listing(tmp_path_factory):
         path.write_bytes(code)
         text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--no-leading-addr", str(path)],
                               capture_output=True, text=True, check=True).stdout
-        out += [" ".join(line.split("//")[0].split()) for line in text.splitlines() if line.startswith("\t")]
+        for line in text.splitlines():
+            if line.endswith(">:"):
+                out.append([])
+            elif line.startswith("\t") and "//" in line:
+                instruction, _, comment = line.partition("//")
+                out[-1].append((int(comment.split(":")[0], 16), " ".join(instruction.split())))
     return out
+
+
+@pytest.fixture(scope="module")
+def listing(kernels):
+    return [x for kernel in kernels for _, x in kernel]
 
 
 def test_lds_loads_take_their_base_from_a_scalar_move(listing):
@@ -61,3 +71,32 @@ def test_hinted_stores_keep_their_data_for_two_wait_states(listing):
     for i in at:
         m = re.fullmatch(r"s_nop (\d+)", listing[i + 1])
         assert m and int(m.group(1)) >= 1, listing[i:i + 4]
+
+
+def test_no_barrier_leaves_lds_writes_in_flight(kernels):
+    """A barrier does not wait for the LDS writes of the wave that arrives there; what other waves read behind it has to
+    be written before.  Followed along every branch."""
+    barriers = 0
+    for kernel in kernels:
+        index = {address: i for i, (address, _) in enumerate(kernel)}
+        pending = [False] * len(kernel)                     # LDS writes in flight in front of the instruction
+        todo = [i for i, (_, x) in enumerate(kernel) if x.startswith("ds_write")]
+        while todo:
+            i = todo.pop()
+            address, x = kernel[i]
+            waits = x.startswith("s_waitcnt") and "lgkmcnt(0)" in x
+            if not (pending[i] or x.startswith("ds_write")) or waits:
+                continue
+            after = [] if x.startswith(("s_branch", "s_endpgm")) else [i + 1]
+            if x.startswith(("s_branch", "s_cbranch")):
+                step = int(x.split()[1])
+                after.append(index[address + 4 + 4 * (step - 65536 if step >= 32768 else step)])
+            for j in after:
+                if not pending[j]:
+                    pending[j] = True
+                    todo.append(j)
+        for i, (_, x) in enumerate(kernel):
+            if x.startswith("s_barrier"):
+                barriers += 1
+                assert not pending[i], kernel[max(0, i - 12):i + 1]
+    assert barriers > 200
