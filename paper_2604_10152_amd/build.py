@@ -12,8 +12,7 @@ LIB = os.path.join(HERE, "libspecmoe.so")
 PEAKS_LIB = os.path.join(HERE, "libspecmoe_peaks.so")     # measurement helpers (bench.py --mode peaks)
 PEAKS_SOURCES = ["peaks.hip"]
 SOURCES = ["api.hip", "route_topk.hip", "permute.hip", "grouped_swiglu_f32.hip",
-           "grouped_swiglu_bf16.hip", "grouped_gemm_bf16_pipe.hip", "grouped_gemm_bf16_pipe16.hip", "grouped_gemm_bf16_persist.hip",
-           "combine.hip", "spec_accept.hip", "hot_experts.hip",
+           "grouped_swiglu_bf16.hip", "grouped_gemm_bf16_pipe.hip", "grouped_gemm_bf16_pipe16.hip", "combine.hip", "spec_accept.hip", "hot_experts.hip",
            "draft_route.hip", "spec_sample.hip", "pack.hip", "affinity.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -19,6 +19,7 @@
 // front of every LDS read that follows an LDS-DMA load, which collapses the ring to depth 1.
 // Hand-placed s_waitcnt vmcnt(n) is safe next to compiler-generated waits: extra outstanding
 // loads can only make a compiler-chosen wait stricter, never weaker.
+#include "persist_tile.h"
 #include "pipe16_tile.h"
 #include "pipe_common.h"
 #include "stream_tiles.h"
@@ -347,51 +348,155 @@ __global__ __launch_bounds__(DownTall::THREADS) void grouped_down_bf16_mid_kerne
     }
 }
 
-// Gate/up on row-major operands: the ring above with 128-row tiles or the 192-row tiles of
-// pipe16_tile.h (launch_expert_up_bf16_ring_or_mid).
+// Down projection of contractions of a few dozen stages: persistent tiles, wide ones or low and narrow ones, or the two
+// forms above, one tile after the other (launch_expert_down_bf16_short).  kCus workgroups; E <= 64.
+typedef PersistCfg<160, 256, 3, false> DownWide;
+typedef PersistCfg<64, 128, 6, false> DownLow;
+constexpr size_t kDownShortLds = DownTall::LDS_BYTES > DownWide::LDS_BYTES ? DownTall::LDS_BYTES : DownWide::LDS_BYTES;
+
+__global__ __launch_bounds__(DownTall::THREADS) void grouped_down_bf16_short_kernel(
+    const bf16_t* __restrict__ h, const int32_t* __restrict__ offsets,
+    const bf16_t* __restrict__ wd, int E, int N, int K, bf16_t* __restrict__ y, int group, int stream_out) {
+    static_assert(DownTall::THREADS == DownWide::THREADS && DownTall::THREADS == DownLow::THREADS &&
+                      kDownShortLds >= DownLow::LDS_BYTES && kDownShortLds >= DownMid::LDS_BYTES,
+                  "one launch serves all");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+    typedef EvenPolicy<DownMid::BM, 32> Mid;
+    typedef EvenPolicy<DownTall::BM, 32> Tall;
+    typedef EvenPolicy<DownLow::BM, 16> Low;
+    typedef EvenPolicy<DownWide::BM, 16> Wide;
+    const int NT = (N + DownMid::BN_OUT - 1) / DownMid::BN_OUT, NW = (N + DownWide::BN_OUT - 1) / DownWide::BN_OUT;
+    const ExpertRows experts(offsets, E);
+    const int mid = experts.mtiles<Mid>(), tall = experts.mtiles<Tall>(), low = experts.mtiles<Low>();
+    const bool taller = tile_rounds(tall, NT) < tile_rounds(mid, NT);
+    const int mt = taller ? tall : mid;
+    // what a form takes, in parts of a tile's time: seven tenths by its rounds and three by its tiles
+    auto cost = [](int tile, int mt, int nt) -> long long {
+        return tile * (7ll * kCus * tile_rounds(mt, nt) + 3ll * mt * nt);
+    };
+    const long long wide_cost = cost(40, experts.mtiles<Wide>(), NW), mid_cost = cost(27, mt, NT);
+    const long long low_cost = tile_rounds(low, NT) > 1 && 4 * low <= 5 * mt ? cost(20, low, NT) : mid_cost;
+    if (wide_cost <= min(mid_cost, low_cost)) {
+        persist_tiles<DownWide, false, false>(lds_raw, experts, h, wd, nullptr, N, K, y, nullptr, 1, stream_out, 0);
+    } else if (low_cost < mid_cost) {
+        persist_tiles<DownLow, false, false>(lds_raw, experts, h, wd, nullptr, N, K, y, nullptr, 1, stream_out, 0);
+    } else {
+        TileLoc t;
+        for (unsigned at = blockIdx.x;; at += kCus) {
+            if (!(taller ? locate<Tall, From::counted>(offsets, E, NT, at, mt, t, group)
+                         : locate<Mid, From::counted>(offsets, E, NT, at, mt, t, group)))
+                break;
+            if (taller) pipe_tile<DownTall>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1, false);
+            else pipe_tile<DownMid>(lds_raw, t, h, wd, nullptr, N, K, y, nullptr, 1, false);
+            __syncthreads();                       // the next tile's loads overwrite the LDS
+        }
+    }
+}
+
+// Gate/up on row-major operands: the ring above with 128-row tiles, the 192-row tiles of pipe16_tile.h, or persistent
+// tiles (launch_expert_up_bf16_ring_or_mid).  PERSIST: kCus workgroups, E <= 64; otherwise a workgroup for each tile.
 typedef PipeCfg<128, 128, 64, 4, 4, 2, true> UpRing;
 typedef PipeCfg<192, 256, 32, 4, 2, 4, true> UpMid;
+typedef PersistCfg<160, 256, 3, true> UpWide;
+typedef PersistCfg<64, 128, 6, true> UpLow;
+enum class Persist { no, whole, halves };
+template <Persist PERSIST>
+constexpr size_t kUpLds = PERSIST == Persist::no || UpRing::LDS_BYTES > UpWide::LDS_BYTES ? UpRing::LDS_BYTES
+                                                                                         : UpWide::LDS_BYTES;
 
+template <Persist PERSIST, bool GATHER>
 __global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets,
     const bf16_t* __restrict__ wg, const bf16_t* __restrict__ wu, int E, int N, int K,
     bf16_t* __restrict__ h, const int32_t* __restrict__ row_src, int topk, int mid_if_less,
-    int mid_if_equal, int group, int stream_out) {
-    static_assert(UpRing::THREADS == UpMid::THREADS && UpRing::LDS_BYTES >= UpMid::LDS_BYTES,
-                  "one launch serves both");
+    int mid_if_equal, int group, int wide_group, int stream_out) {
+    static_assert(UpRing::THREADS == UpMid::THREADS && UpRing::LDS_BYTES >= UpMid::LDS_BYTES &&
+                      UpRing::THREADS == UpWide::THREADS && UpWide::BN_OUT == UpMid::BN_OUT &&
+                      UpRing::THREADS == UpLow::THREADS && UpLow::BN_OUT == UpRing::BN_OUT &&
+                      UpWide::LDS_BYTES >= UpLow::LDS_BYTES,
+                  "one launch serves all");
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
     typedef EvenPolicy<UpRing::BM, 32> Ring;
     typedef EvenPolicy<UpMid::BM, 16> Mid;
     const int NR = (N + UpRing::BN_OUT - 1) / UpRing::BN_OUT;
     const int NM = (N + UpMid::BN_OUT - 1) / UpMid::BN_OUT;
-    // every count costs a workgroup two divisions per expert and lane: mid is counted where it may win
+    // every count costs a workgroup two divisions per expert and lane: a form is counted where it may win
     int mt[2] = {0, 0};
-    bool mid = false;
-    if (mid_if_less) {
+    const ExpertRows experts(offsets, PERSIST != Persist::no ? E : 0);
+    if constexpr (PERSIST != Persist::no) {
+        mt[0] = experts.mtiles<Ring>();
+        if (mid_if_less) mt[1] = experts.mtiles<Mid>();
+    } else if (mid_if_less) {
         count_mtiles<Ring, Mid>(offsets, E, mt);
-        const int ring_rounds = tile_rounds(mt[0], NR), mid_rounds = 2 * tile_rounds(mt[1], NM);
-        mid = mid_rounds < ring_rounds || (mid_rounds == ring_rounds && mid_if_equal);
     } else {
         int ring[1];
         count_mtiles<Ring>(offsets, E, ring);
         mt[0] = ring[0];
     }
+    bool mid = false;
+    if (mid_if_less) {
+        const int ring_rounds = tile_rounds(mt[0], NR), mid_rounds = 2 * tile_rounds(mt[1], NM);
+        mid = mid_rounds < ring_rounds || (mid_rounds == ring_rounds && mid_if_equal);
+    }
     // contractions below 4096: a second round of ring tiles that is at most half full
     const long long tiles = (long long)__builtin_amdgcn_readfirstlane(mt[0]) * NR;
     if (!mid && K < 4096 && tiles > kCus && 2 * tiles <= 3 * kCus) {
-        int one[1];
-        count_mtiles<Mid>(offsets, E, one);
-        mt[1] = one[0];
+        if constexpr (PERSIST != Persist::no) {
+            mt[1] = experts.mtiles<Mid>();
+        } else {
+            int one[1];
+            count_mtiles<Mid>(offsets, E, one);
+            mt[1] = one[0];
+        }
         const long long mid_tiles = (long long)__builtin_amdgcn_readfirstlane(mt[1]) * NM;
         mid = mid_tiles <= kCus && 2 * mid_tiles >= kCus;
     }
-    TileLoc t;
-    if (mid) {
-        if (locate<Mid, From::counted>(offsets, E, NM, blockIdx.x, mt[1], t, group))
-            pipe16_tile<UpMid>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk, stream_out);
-    } else if (locate<Ring, From::counted>(offsets, E, NR, blockIdx.x, mt[0], t, group)) {
-        pipe_tile<UpRing>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk, stream_out);
+    if constexpr (PERSIST != Persist::no) {
+        if (tiles > kCus) {
+            typedef EvenPolicy<UpWide::BM, 16> Wide;
+            typedef EvenPolicy<UpLow::BM, 16> Low;
+            // a round's time: wide 20, mid 26, low 9, ring 12 in short contractions and 10 in long ones
+            constexpr int kRing = PERSIST == Persist::whole ? 12 : 10;
+            const int wide = experts.mtiles<Wide>(), low = PERSIST == Persist::whole && !mid ? experts.mtiles<Low>() : 0;
+            const int other = mid ? 26 * tile_rounds(mt[1], NM) : kRing * tile_rounds(mt[0], NR);
+            const int low_cost = low > 0 && 4 * low <= 5 * mt[0] ? 9 * tile_rounds(low, NR) : other;
+            const bool fills = PERSIST == Persist::whole || (long long)wide * NM >= kCus;
+            if (fills && 20 * tile_rounds(wide, NM) <= min(low_cost, other)) {
+                persist_tiles<UpWide, GATHER, PERSIST == Persist::halves>(lds_raw, experts, A, wg, wu, N, K, h, row_src,
+                                                                          topk, stream_out, wide_group);
+                return;
+            }
+            if (PERSIST == Persist::whole && low_cost < other) {
+                persist_tiles<UpLow, GATHER, false>(lds_raw, experts, A, wg, wu, N, K, h, row_src, topk, stream_out, 0);
+                return;
+            }
+        }
     }
+    TileLoc t;
+    for (unsigned at = blockIdx.x;; at += kCus) {
+        if (!(mid ? locate<Mid, From::counted>(offsets, E, NM, at, mt[1], t, group)
+                  : locate<Ring, From::counted>(offsets, E, NR, at, mt[0], t, group)))
+            break;
+        if (mid) pipe16_tile<UpMid>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk, stream_out);
+        else pipe_tile<UpRing>(lds_raw, t, A, wg, wu, N, K, h, row_src, topk, stream_out);
+        if (PERSIST == Persist::no) break;         // a workgroup for each tile
+        __syncthreads();                           // the next tile's loads overwrite the LDS
+    }
+}
+
+template <Persist PERSIST, bool GATHER>
+hipError_t launch_up(unsigned grid, const bf16_t* A, const int32_t* offsets, const bf16_t* wg, const bf16_t* wu, int E,
+                     int N, int K, bf16_t* h, const int32_t* row_src, int topk, int mid_if_less, int mid_if_equal,
+                     int group, int wide_group, int stream_out, hipStream_t s) {
+    // one-time, thread-safe (C++11 static initialisation): raise the dynamic LDS limit
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&grouped_up_bf16_kernel<PERSIST, GATHER>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kUpLds<PERSIST>);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((grouped_up_bf16_kernel<PERSIST, GATHER>), dim3(PERSIST == Persist::no ? grid : kCus),
+                       dim3(UpRing::THREADS), kUpLds<PERSIST>, s, A, offsets, wg, wu, E, N, K, h, row_src, topk,
+                       mid_if_less, mid_if_equal, group, wide_group, stream_out);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -401,7 +506,21 @@ __global__ __launch_bounds__(UpRing::THREADS) void grouped_up_bf16_kernel(
 //    ~10 % of HBM throughput), 4-stage ring of 128 KB, 8 wavefronts, one workgroup per CU.
 //  - mid: 192-row tiles of 128 gate and 128 up rows, twice the weights per workgroup, so about twice the
 //    time, in half lines.
-// The ring is ahead unless its smaller tiles take more rounds of the chip than twice the mid tiles.
+//  - persistent tiles of 160 rows and 128 outputs (persist_tile.h), for up to 64 experts and contractions below 4096, or
+//    longer ones with two rounds of them when every expert has one (those with the tile order in groups and the last round in
+//    halves).  Where their rounds, 20 each, cost no more than those of the ring (12, or 10 in long contractions) or of mid (26), and
+//    in long contractions they fill the chip once (8 x 4096 x 14336, one token, 224 tiles 90 / 94; 7 tokens at 12 a ring round 275 / 285).  us, the ring or
+//    mid / persistent (rounds: persistent, ring, mid): 64 x 2048 x 1408, 6 rows 140 / 126 (2.8, 5.5, 2.8), the same on 37 experts 90 / 84
+//    (1.6, 3.2, 1.6), 30 rows on 16 experts 64 / 46 (0.9, 2.1, 0.9), 120 rows 182 / 153 (2.8, 6.8, 2.8), under an exponent of 1.1 202 / 188
+//    (4.2, 9.4, 3.9), but 90 rows on 24 experts 102 / 116 (2.1, 5.1, 1.9); 24 x 3840 x 1920, 107 rows on 16 of them 116 / 159 (1.4, 3.8, 0.9);
+//    16 x 2048 x 3072, 150 rows 115 / 95 (1.9, 6.0, 1.5); 16 x 5120 x 8192, 6 rows 455 / 439 (4, 8, 4), 75 rows on four experts 260 / 285 (2.3, 6, 2); 8 x
+//    4096 x 14336, 83 rows under an exponent of 1.1 392 / 334 (3.9, 8.8, 3.9), on two experts 184 / 217 (2.6, 5.3, 1.8).
+//  - low: persistent tiles of 64 rows and 64 outputs (9 a round), for contractions below 4096 with more than one round of
+//    ring tiles, where they are at most 5/4 as many: 64 x 2048 x 1408, 12 rows on 24 experts 62 / 58 (2.1 and 2.4 rounds),
+//    16 x 2048 x 3072, 12 rows under an exponent of 1.1 69 / 63 (2.6, 2.8).
+// Where persistent tiles may be chosen, the launch has one workgroup per CU, which takes the other kinds' tiles one after the
+// other: surplus workgroups would each cost the CU 1 to 2 us behind the last tile.
+// The ring is ahead of mid unless its smaller tiles take more rounds of the chip than twice the mid tiles.
 // How many a batch takes depends on how its rows are spread: the draft model routes everything to a
 // few experts.  Measured, us, ring / mid (rounds): 4096 x 14336, 8 experts, 70 rows each 335 (7) / 381 (4),
 // the same rows on two experts 219 (6) / 174 (2); 5120 x 8192, 16 experts, 70 rows under a Zipf exponent of 0.5
@@ -422,21 +541,27 @@ hipError_t launch_expert_up_bf16_ring_or_mid(const bf16_t* x_perm, const int32_t
                                              const bf16_t* wg, const bf16_t* wu, int n_rows, int d,
                                              int f, int E, bf16_t* h, hipStream_t s,
                                              const int32_t* row_src, int topk) {
-    // one-time, thread-safe (C++11 static initialisation): raise the dynamic LDS limit
-    static const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&grouped_up_bf16_kernel),
-        hipFuncAttributeMaxDynamicSharedMemorySize, (int)UpRing::LDS_BYTES);
-    if (attr != hipSuccess) return attr;
     const int mid_if_less = (long long)n_rows >= 60ll * E;
     const int mid_if_equal = d >= 4096 && (long long)n_rows >= 88ll * E;
-    const long long NR = (f + UpRing::BN_OUT - 1) / UpRing::BN_OUT;
+    const long long NR = (f + UpRing::BN_OUT - 1) / UpRing::BN_OUT, NW = (f + UpWide::BN_OUT - 1) / UpWide::BN_OUT;
     const int min_rows = E * NR >= 1536 ? 48 : 96;
     const int group = (long long)n_rows < (long long)min_rows * E ? 0 : NR >= 96 ? 8 : NR >= 48 ? 4 : 0;
-    const long long grid = grid_upper_bound(n_rows, E, UpRing::BM, NR);
-    hipLaunchKernelGGL(grouped_up_bf16_kernel, dim3((unsigned)grid), dim3(UpRing::THREADS),
-                       UpRing::LDS_BYTES, s, x_perm, offsets, wg, wu, E, f, d, h, row_src, topk,
-                       mid_if_less, mid_if_equal, group, (int)streams_output(n_rows, f));
-    return hipGetLastError();
+    const unsigned grid = (unsigned)grid_upper_bound(n_rows, E, UpRing::BM, NR);
+    auto up = [&](auto persist, auto gather) {
+        constexpr Persist P = decltype(persist)::value;
+        return launch_up<P, decltype(gather)::value>(grid, x_perm, offsets, wg, wu, E, f, d, h, row_src, topk,
+                                                     mid_if_less, mid_if_equal, group,
+                                                     P == Persist::halves && NW >= 24 ? 8 : 0,   // as tile_group()
+                                                     (int)streams_output(n_rows, f), s);
+    };
+    const std::integral_constant<Persist, Persist::whole> whole;
+    const std::integral_constant<Persist, Persist::halves> halves;
+    // wide tiles need two rounds of ring tiles or more to be chosen; an expert that is met has a row
+    const long long most = (n_rows < E ? n_rows : E) + n_rows / UpRing::BM;
+    if (most * NR <= kCus) return up(std::integral_constant<Persist, Persist::no>{}, std::false_type{});
+    if (E <= kWave && d < kTailMinK) return row_src ? up(whole, std::true_type{}) : up(whole, std::false_type{});
+    if (E <= kWave && E * NW >= 2 * kCus) return row_src ? up(halves, std::true_type{}) : up(halves, std::false_type{});
+    return up(std::integral_constant<Persist, Persist::no>{}, std::false_type{});
 }
 
 // Down projection with few rows per expert and a long contraction: the weights stream from HBM
@@ -485,6 +610,42 @@ hipError_t launch_expert_down_bf16_mid(const bf16_t* h, const int32_t* offsets, 
     const long long grid = grid_upper_bound(n_rows, E, DownMid::BM, NT);
     hipLaunchKernelGGL(grouped_down_bf16_mid_kernel, dim3((unsigned)grid), dim3(DownTall::THREADS),
                        DownTall::LDS_BYTES, s, h, offsets, wd, E, d, f, y, E * NT > kCus ? kDownGroup : 0);
+    return hipGetLastError();
+}
+
+// Contractions of 1280 to 4095, up to 64 experts: the time is mostly that of the rounds of the chip, and how many the batch
+// takes is known on the device only.  Wide persistent tiles, low ones (their six stages keep more in flight, and the next
+// tile's first stages are under way in the unfinished round) where these are at most 5/4 as many as the 128- or 192-row
+// ones, or the mid kernel's, by the least cost: 40, 20 and 27 for a tile's time, seven tenths of it by the rounds and three by
+// the tiles, as the CUs that have a tile less leave the others their share of the memory.
+// Measured, us, weights out of HBM, register-staged (grouped_swiglu_bf16.hip; *: the mid kernel, which the size took
+// before) / wide / mid or tall / low (rounds; the one chosen first):
+//   64 x 1408 x 2048      6 rows, 64 experts active   77 / 60 (2.0) / 67 (4.0) / 59 (4.0)    wide
+//                         6 rows, 37 active           45 / 51 (1.2) / 48 (2.3) / 45 (2.3)    low
+//                         12 rows, 38 active          44 / 54 (1.2) / 48 (2.4) / 43 (2.6)    low
+//                         30 rows, 55 active          75 / 62 (1.8) / 67 (3.6) / 68 (4.5)    wide
+//                         30 rows, 32 active          58 / 56 (1.1) / 48 (2.2) / 54 (3.1)    tall
+//                         45 rows, 12 active          52 / 33 (0.7) / 36 (1.2) / 57 (3.2)    wide
+//                         120 rows, even              100* / 74 (2.0) / 100 (4.0) / 124      wide
+//                         120 rows, exponent of 1.1   108* / 107 (3.1) / 105 (5.7) / 144     wide
+//   16 x 2048 x 4096      42 rows, exponent of 1.1    75 / 91 (1.1) / 68 (2.1) / 65 (2.6)    low
+//                         80 rows                     83 / 61 (1.0) / 64 (2.0) / 75 (4.0)    wide
+//                         150 rows                    77* / 91 (1.2) / 75 (2.0) / 112        tall
+//   16 x 3072 x 2048      6 rows                      53 / 43 (0.5) / 36 (1.0) / 35 (1.0)    mid
+//                         150 rows                    50* / 66 (0.6) / 51 (1.0) / 87         tall
+// (mid and tall as launches of their own; one tile after the other they are up to 7 % slower.)  The choice against the kernel that
+// the size took before, 352 batches of 6 shapes, 1 to 1800 tokens, even, skewed and on 2 to 48 experts: 0.83 times the time
+// on average; twelve of them more than 3 % behind, up to 9 % (64 x 1408 x 2048, 6 rows on 37 experts 44 / 45, 8 tokens 39 / 43).
+hipError_t launch_expert_down_bf16_short(const bf16_t* h, const int32_t* offsets, const bf16_t* wd, int n_rows, int d,
+                                         int f, int E, bf16_t* y, hipStream_t s) {
+    // one-time, thread-safe (C++11 static initialisation): raise the dynamic LDS limit
+    static const hipError_t attr = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&grouped_down_bf16_short_kernel),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDownShortLds);
+    if (attr != hipSuccess) return attr;
+    const long long NT = (d + DownMid::BN_OUT - 1) / DownMid::BN_OUT;
+    hipLaunchKernelGGL(grouped_down_bf16_short_kernel, dim3(kCus), dim3(DownTall::THREADS), kDownShortLds, s, h, offsets,
+                       wd, E, d, f, y, E * NT > kCus ? kDownGroup : 0, (int)streams_output(n_rows, d));
     return hipGetLastError();
 }
 

@@ -298,8 +298,7 @@ static inline bool rows_aligned(const void* a, const void* b, const void* c, con
 // Gate/up (K = d_model, 128 outputs per 256-wide tile).
 //  - r >= 192, large: up to 320-row tiles, MFMA-bound.  Unless they are few: 8 x 1024 outputs are
 //    64 tiles on 256 CUs (3072 x 1024, 200 rows: 76 -> 36 with the ring).
-//  - persistent tiles for K >= 2048, as grouped_gemm_bf16_persist.hip says.
-//  - ring or mid, chosen on the device, for K >= 2048: against register-staged tiles 141 -> 108 (2048 x
+//  - ring, mid or persistent tiles, chosen on the device, for K >= 2048: against register-staged tiles 141 -> 108 (2048 x
 //    1408, 64 experts, 15 rows), 67 -> 33 (3072 x 1024, 8, 6 to 50 rows), 181 -> 149 (2048 x 1408, 64, 52 rows
 //    under a Zipf exponent of 1.1).
 //  - mid at shorter K from 96 rows with 192 tiles or more (1024 x 2048, 16 experts, 128 rows: 49 -> 30
@@ -317,8 +316,6 @@ hipError_t launch_expert_up_bf16(const bf16_t* x_perm, const int32_t* offsets, c
     if (large_batch(n_rows, E) && !(d >= 2048 && few_wide_tiles(n_rows, E, f, 128)))
         return launch_expert_up_bf16_large16(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s,
                                              row_src, topk);
-    if (launches_expert_up_bf16_persist(n_rows, d, f, E))
-        return launch_expert_up_bf16_persist(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s, row_src, topk);
     if (d >= 2048)
         return launch_expert_up_bf16_ring_or_mid(x_perm, offsets, wg, wu, n_rows, d, f, E, h, s,
                                                  row_src, topk);
@@ -332,9 +329,10 @@ hipError_t launch_expert_up_bf16(const bf16_t* x_perm, const int32_t* offsets, c
 // Down (K = d_ff).
 //  - r >= 192, large, unless its tiles are few: mid then has twice as many (4096 x 14336, 8 experts,
 //    225 rows: 363 -> 308; 1024 x 4096, 8, 250 rows: 88 -> 34).
-//  - persistent tiles at 1280 <= K < 4096, as grouped_gemm_bf16_persist.hip says.
-//  - mid (128 outputs per tile, 128 or 192 rows, chosen on the device): K >= 4096 from 48 rows.  At
-//    1280 <= K < 4096 from 12 rows while the experts' weight tiles make one round of the chip (12 experts x
+//  - short: persistent or mid tiles, chosen on the device, at 1280 <= K < 4096 with up to 64 experts
+//    (launch_expert_down_bf16_short).
+//  - mid (128 outputs per tile, 128 or 192 rows, chosen on the device): K >= 4096 from 48 rows.  With more than 64
+//    experts at 1280 <= K < 4096 from 12 rows while the experts' weight tiles make one round of the chip (12 experts x
 //    2048 outputs, K = 3072: register-staged 51 -> 33 at 14 rows, 56 -> 42 at 110), and from 88 rows with more
 //    (64 x 2048, K = 1408: 113 -> 103 at 110 rows, 128 -> 108 at 130); below that a second round costs more than
 //    the ring gains (16 x 4096, K = 2048, 14 to 52 rows: 45 -> 63; 64 x 2048, K = 1408, 40 rows: 87 -> 80 when
@@ -348,8 +346,8 @@ hipError_t launch_expert_down_bf16(const bf16_t* h, const int32_t* offsets, cons
         return launch_one<Staged>(h, offsets, wd, nullptr, n_rows, E, d, f, y, s);
     if (large_batch(n_rows, E) && !few_wide_tiles(n_rows, E, d, 256))
         return launch_expert_down_bf16_large16(h, offsets, wd, n_rows, d, f, E, y, s);
-    if (!large_batch(n_rows, E) && launches_expert_down_bf16_persist(n_rows, d, f, E))
-        return launch_expert_down_bf16_persist(h, offsets, wd, n_rows, d, f, E, y, s);
+    if (!large_batch(n_rows, E) && f >= 1280 && f < kLongK && E <= kWave)
+        return launch_expert_down_bf16_short(h, offsets, wd, n_rows, d, f, E, y, s);
     const long long tiles = (long long)E * ((d + 127) / 128);
     bool mid = large_batch(n_rows, E);
     if (f >= kLongK) {

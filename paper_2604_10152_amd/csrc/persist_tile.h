@@ -6,12 +6,12 @@
 // What a tile costs besides its k loop in the other kernels - finding it 1.1 us, the first stage's way out of HBM
 // 1.3, the epilogue 1.2, and the time until the next workgroup starts - passes while requests are in flight here.
 //
-// Row-major operands.  A stage is 64 columns, whole 128-byte lines; three stages in the LDS, of which one or two are
+// Row-major operands.  A stage is 64 columns, whole 128-byte lines; S stages in the LDS, of which S - 2 or S - 1 are
 // in flight.  Two k-steps per stage, in the ping-pong
 // schedule of pipe16_tile.h (s = k-step, q = s / 2 its stage):
 //   phase 2s  : group 0 reads step s        | group 1 multiplies step s-1
 //   phase 2s+1: group 0 multiplies step s   | group 1 reads step s
-// Stage q+2 is requested in the read phases of stage q (its slot held stage q-1, which group 1 finished reading one
+// Stage q+S-1 is requested in the read phases of stage q (its slot held stage q-1, which group 1 finished reading one
 // phase before), and every wave waits for its share of stage q+1 before the barrier that ends stage q.
 #pragma once
 #include "pipe16_tile.h"
@@ -38,15 +38,26 @@ struct PersistCfg {
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
-// Tiles of up to 64 experts out of registers: a lane holds one expert.
+// Up to 64 experts in registers, one per lane: where an expert's rows start and how many it has.
+struct ExpertRows {
+    int lo, rows;
+    __device__ __forceinline__ ExpertRows(const int32_t* __restrict__ offsets, int E) {
+        const int e = threadIdx.x % kWave;
+        lo = e < E ? offsets[e] : 0;
+        rows = e < E ? offsets[e + 1] - lo : 0;
+    }
+    // m-tiles of all
+    template <typename Split>
+    __device__ __forceinline__ int mtiles() const {
+        return __builtin_amdgcn_readfirstlane(wave_sum(Split::of(rows).mt));
+    }
+};
+// Their tiles.
 template <int BM>
 struct TileTable {
     int lo, rows, mt, rpt, incl;             // of the lane's expert; incl: m-tiles up to it
     int total;                               // m-tiles of all
-    __device__ __forceinline__ void load(const int32_t* __restrict__ offsets, int E) {
-        const int e = threadIdx.x % kWave;
-        lo = e < E ? offsets[e] : 0;
-        rows = e < E ? offsets[e + 1] - lo : 0;
+    __device__ __forceinline__ TileTable(ExpertRows r) : lo(r.lo), rows(r.rows) {
         const EvenSplit s = even_split<BM, 16>(rows);
         mt = s.mt;
         rpt = s.rpt;
@@ -81,6 +92,7 @@ struct TileTable {
         t.tile_rows = min(of(rpt), of(rows) - first);
         t.blk0 = 0;                          // (of tile-packed rows)
         t.half = -1;
+        t.single = __ballot(mt > 1) == 0;
         return t;
     }
 };
@@ -102,11 +114,11 @@ __device__ __forceinline__ void wait_stages(int n) {
     }
 }
 
-// The tiles of workgroup blockIdx.x < kCus.  lds_raw: C::LDS_BYTES.  K >= 256, K % 64 == 0.
-// GATHER: row r of the activations is A[row_src[r] / topk].
+// The tiles of workgroup blockIdx.x < kCus.  lds_raw: C::LDS_BYTES.  K >= 64 * S, K % 64 == 0.
+// GATHER: row r of the activations is A[row_src[r] / topk].  group: of n-tiles (tile_map.h), unless the batch is even.
 template <typename C, bool GATHER, bool HALVES>
 __device__ __forceinline__ void persist_tiles(
-    unsigned char* lds_raw, const TileTable<C::BM>& table, const bf16_t* __restrict__ A,
+    unsigned char* lds_raw, const ExpertRows& experts, const bf16_t* __restrict__ A,
     const bf16_t* __restrict__ W0, const bf16_t* __restrict__ W1, int N, int K,
     bf16_t* __restrict__ Cout, const int32_t* __restrict__ row_src, int topk, bool stream_out, int group) {
     constexpr int S = C::STAGES, KSUB = C::KSUB;
@@ -117,6 +129,8 @@ __device__ __forceinline__ void persist_tiles(
     const int KT = K / C::BK, NT = (N + C::BN_OUT - 1) / C::BN_OUT;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_raw;
     const int* lds_rows = reinterpret_cast<const int*>(lds_raw + S * C::STAGE_BYTES);
+    const TileTable<C::BM> table(experts);
+    if (group > 0 && table.even()) group = 0;
 
     const unsigned G = (unsigned)table.total * (unsigned)NT, per_xcd = (G + kXcds - 1) / kXcds;
     const unsigned first = blockIdx.x % kXcds * per_xcd, n = first < G ? min(per_xcd, G - first) : 0u;
@@ -140,7 +154,6 @@ __device__ __forceinline__ void persist_tiles(
     uint32_t a_off[C::A_PW], b_off[C::B_PW];
     int a_cnt, b_cnt;                            // wave-loads of a stage
     bool once;                                   // no other workgroup reads the tile's weights
-    const bool single = !C::SWIGLU || __ballot(table.mt > 1) == 0;
     auto request_from = [&](const TileLoc& t, auto from_lds) __attribute__((always_inline)) {
         a_base = uniform_ptr(reinterpret_cast<const unsigned char*>(
             A + (GATHER ? (size_t)0 : (size_t)t.row0 * K)));
@@ -151,7 +164,7 @@ __device__ __forceinline__ void persist_tiles(
         w0 = uniform_ptr(reinterpret_cast<const unsigned char*>(W0 + wrow * K));
         if (C::SWIGLU) w1 = uniform_ptr(reinterpret_cast<const unsigned char*>(W1 + wrow * K));
         a_cnt = 0;
-        once = t.mt == 1 && (!C::SWIGLU || t.tile_rows <= 64 || single);
+        once = t.mt == 1 && (!C::SWIGLU || t.tile_rows <= 64 || t.single);
         const uint32_t chunk = (uint32_t)(((lane & 7) ^ ((lane >> 3) & 6)) * 16);
 #pragma unroll
         for (int jj = 0; jj < C::A_PW; ++jj) {

@@ -21,7 +21,8 @@ struct TileLoc {
                      // a whole number of blocks (row numbering of the tile-packed matrices)
     int half;        // -1, or the half of the tile's outputs that the workgroup takes
     int mt;          // m-tiles of the tile's expert (1: its weight tiles are read by one workgroup)
-    bool single;     // no expert of the 64 at a time up to the tile's has several
+    int single;      // no expert of the 64 at a time up to the tile's has several (a whole word: padding bytes that a copy
+                     // takes along go through scratch memory, and with them every load in flight)
 };
 
 // Even split: an expert with M rows gets ceil(M / BM_MAX) m-tiles of equal height (rounded up
@@ -157,7 +158,7 @@ __device__ __forceinline__ bool locate(const int32_t* __restrict__ offsets, int 
     int base_mt = 0;                              // m-tiles of the experts before this sweep
     int base_blk = 0;                             // 16-row blocks of the experts before this sweep
     int expert = -1, row0 = 0, rows = 0, nt = 0, blk0 = 0, mts = 0;
-    t.single = true;
+    t.single = 1;
     for (int e0 = 0; e0 < E && expert < 0; e0 += kWave) {
         const int e = e0 + lane;
         const int lo = e < E ? offsets[e] : 0, hi = e < E ? offsets[e + 1] : 0;
@@ -166,7 +167,7 @@ __device__ __forceinline__ bool locate(const int32_t* __restrict__ offsets, int 
         const int incl = wave_scan(sp.mt), incl_blk = wave_scan(nblk);   // inclusive
         const unsigned end = (unsigned)(base_mt + incl) * (unsigned)ntn; // tiles up to and incl. e
         const unsigned long long hit = __ballot(sp.mt > 0 && L < end);
-        t.single = t.single && __ballot(sp.mt > 1) == 0;
+        t.single &= __ballot(sp.mt > 1) == 0;
         if (hit) {
             const int src = __ffsll((long long)hit) - 1;              // first such expert
             auto of = [&](int v) { return __builtin_amdgcn_readlane(v, src); };

@@ -1133,6 +1133,21 @@ def test_persistent_tiles(d, f, rows, gather):
             assert float(err.max()) <= 1e-2, (e, float(err.max()))      # NaN fails as well
 
 
+@pytest.mark.parametrize("d,f,rows", [
+    # the kinds of tiles that the device chooses from, by the rounds of the chip that each takes; gate/up and down
+    (2112, 1344, [160, 159, 1, 16, 17, 33, 0, 130] * 8),              # wide, ragged columns, 2.4 rounds; wide, 2.0
+    (2112, 1344, [64, 63, 1, 16, 17, 0, 33, 48] * 5),                 # low, 2.9 rounds; low, 2.3
+    (2112, 1984, [160, 145, 0, 1, 16, 17, 128, 33, 100, 64, 48, 150] * 2 + [40] * 8),     # wide; tall, one after the other
+    (3136, 1344, [65, 64, 1] * 10),                                   # ring, one after the other; wide
+    (2048, 2624, [180, 191, 192, 170, 1] * 5),                        # mid, one after the other; tall
+    (2048, 1280, [1] * 64),                                           # low; wide: one row each
+    (4096, 4160, [100, 100, 1, 330, 16, 64, 161, 1, 160, 64, 16, 16, 160, 64, 64, 16]),   # wide in groups, last rounds in halves
+])
+@pytest.mark.parametrize("gather", [False, True])
+def test_row_major_tiles_chosen_on_the_device(d, f, rows, gather):
+    test_persistent_tiles(d, f, rows, gather)
+
+
 def test_layer_cfg4_packed_path():
     """The benchmark workload on the tile-packed path: same routing, output bit-identical to the
     row-major path (same kernels' arithmetic in the same order)."""
