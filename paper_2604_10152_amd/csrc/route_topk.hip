@@ -437,12 +437,16 @@ void launch_variant(const T* x, const T* wr, const float* bias, int Tn, int d, i
                     int renorm, int32_t* idx, float* w, const int32_t* remap, Then then, hipStream_t s) {
     dim3 grid((Tn + TOK - 1) / TOK), block(kRouteThreads);
     size_t lds = ((size_t)TOK * E + (size_t)(kRouteThreads / kWave) * TOK * EC) * sizeof(double);
-    if (then.done)
-        hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC, W, true>), grid, block, lds, s, x, wr, bias, Tn,
-                           d, E, k, renorm, idx, w, remap, then);
-    else
-        hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC, W, false>), grid, block, lds, s, x, wr, bias, Tn,
-                           d, E, k, renorm, idx, w, remap, then);
+    // up to 64 tokens and 64 experts come to one token per workgroup and at most 8 columns per pass (launch_typed)
+    if constexpr (TOK == 1 && EC <= 8) {
+        if (then.done) {
+            hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC, W, true>), grid, block, lds, s, x, wr, bias, Tn,
+                               d, E, k, renorm, idx, w, remap, then);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((route_topk_kernel<T, VEC, TOK, EC, W, false>), grid, block, lds, s, x, wr, bias, Tn,
+                       d, E, k, renorm, idx, w, remap, then);
 }
 
 // Experts per group and pass: the group's share of E rounded up to a power of two, at most 16 / TOK.
@@ -482,6 +486,10 @@ void launch_typed(const void* x, const void* wr, const float* bias, int Tn, int 
     const T* wt = (const T*)wr;
     if (!vec) {
         launch_by_experts<T, false, 1>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
+        return;
+    }
+    if (then.done) {                              // kRoutePermuteTokens: the minimum below is one token per workgroup
+        launch_by_experts<T, true, 1>(xt, wt, bias, Tn, d, E, k, renorm, idx, w, remap, then, s);
         return;
     }
     // Matrix form: from 1025 tokens on with 8 tokens per workgroup (the vector form then needs a
