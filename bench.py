@@ -349,8 +349,10 @@ def kernel_name(cfg, T, packed=True):
     if large and not (cfg.d_model >= 2048 and few):
         return "grouped_gemm_bf16_pipe16_kernel<PipeCfg<320,256,32,4,2,4,true>> (gate/up + SwiGLU)"
     if cfg.d_model >= 2048:
-        return ("grouped_up_bf16_kernel: PipeCfg<128,128,64,4,4,2,true> or <192,256,32,4,2,4,true>, chosen "
-                "on the device (gate/up + SwiGLU)")
+        forms = "PipeCfg<128,128,64,4,4,2,true> or <192,256,32,4,2,4,true>"
+        if cfg.E <= 64 and (cfg.d_model < 4096 or cfg.E * -(-cfg.d_ff // 128) >= 512):
+            forms = "PersistCfg<160,256,3,true>, " + ("<64,128,6,true>, " if cfg.d_model < 4096 else "") + forms
+        return f"grouped_up_bf16_kernel: {forms}, chosen on the device (gate/up + SwiGLU)"
     if rows >= 96 * cfg.E and cfg.E * -(-cfg.d_ff // 128) > 191:
         return "grouped_gemm_bf16_pipe16_kernel<PipeCfg<192,256,32,4,2,4,true>> (gate/up + SwiGLU)"
     return "grouped_gemm_bf16_kernel<TileCfg<64,256,1,4,true>> (gate/up + SwiGLU)"

@@ -155,7 +155,10 @@ inline bool few_wide_tiles(int n_rows, int E, int N, int wide) {
 // and until then every line of it takes the place of operands in the L2.  Measured, packed operands, us, without / with the hint
 // (bytes written): gate/up 8 x 4096 x 14336, 175 rows each (40 MB) 377 / 359, 83 rows (19 MB) 339 / 334, 64 x 2048 x 1408, 120
 // rows (22 MB) 171 / 165; down, the same, 60 rows (16 MB) 71 / 66.  A small output stays in the L2: gate/up, 6 rows (1 MB) 30.7 / 31.1, 30
-// rows (5 MB) 109.5 / 110.4; down, 6 rows (1.6 MB) 42.0 / 42.7, but 30 rows (8 MB) 62.2 / 61.0.
+// rows (5 MB) 109.5 / 110.4; down, 6 rows (1.6 MB) 42.0 / 42.7, but 30 rows (8 MB) 62.2 / 61.0.  Its price in row-major outputs: an
+// instruction stores half a line of each of 16 rows, and the halves leave the L2 by themselves (8 x 14336 x 4096, 512 rows each, y
+// of 33.6 MB written as 48; 64 x 1408 x 2048, 190 rows 125 us against 119 without the hint, but gate/up 2048 x 1408, 60 rows 150
+// against 158, 120 rows 153 / 164).
 inline bool streams_output(int n_rows, int N) { return (long long)n_rows * N * 2 >= (6ll << 20); }
 
 // ---- launchers (host side, defined in the .hip files) -------------------------------

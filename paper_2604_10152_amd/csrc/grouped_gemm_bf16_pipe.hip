@@ -264,8 +264,8 @@ __device__ __forceinline__ void pipe_tile(
 
     static_assert(C::TM <= 5, "extend the dispatch below");
     // An expert with a single m-tile: every weight tile of it is read by exactly one workgroup,
-    // once - a pure stream out of HBM, which the non-temporal hint speeds up (7.0 against 6.2 TB/s as an
-    // LDS-DMA stream by itself; which tiles of gate/up have it: pipe16_tile.h).  With several m-tiles the workgroups that share a weight tile meet
+    // once - a pure stream out of HBM, which the non-temporal hint speeds up (dma16_nt;
+    // which tiles of gate/up have it: pipe16_tile.h).  With several m-tiles the workgroups that share a weight tile meet
     // in the L2, and the hint would cost those hits.
     // (whole 128-byte lines per row and stage only: half-line loads rely on the L2 keeping the
     // other half for the next stage)

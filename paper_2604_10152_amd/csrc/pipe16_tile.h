@@ -323,8 +323,8 @@ __device__ __forceinline__ void pipe16_tile(
     };
 
     // An expert with a single m-tile: every weight tile of it is read by exactly one workgroup,
-    // once - a pure stream out of HBM, which the non-temporal hint speeds up (7.0 against 6.2 TB/s as an LDS-DMA stream
-    // by itself).  With several m-tiles the workgroups that share a weight tile meet
+    // once - a pure stream out of HBM, which the non-temporal hint speeds up (dma16_nt).
+    // With several m-tiles the workgroups that share a weight tile meet
     // in the L2, and the hint would cost those hits.  In gate/up a batch in which some expert has several m-tiles keeps it to
     // tiles of up to 64 rows: us, up to 64 rows / all, 8 x 4096 x 14336, 83 rows each 334 / 314, 125 rows 359 / 336, 16 x 5120 x 8192, 75
     // rows 461 / 421, but 64 x 2048 x 1408, 30 rows under a Zipf exponent of 1.1 115 / 120.

@@ -41,8 +41,9 @@ class MoEVerifyLayer:
 
     # Which projections run on tile-packed operands (measured crossovers, average rows per
     # expert r = T*k/E).  Gate/up, with the gather of its rows: from r >= 48, and at any r for
-    # d_model < 4096 (64 experts x 2048 x 1408, 6 to 24 rows: 118-122 us against 126-130 row-major, 70
-    # rows 147 against 155; few tiles are level or 3 us behind, 8 x 3072 x 1024 34 against 31).  Down:
+    # d_model < 4096 (layers of 64 experts x 2048 x 1408, packed / row-major, us: 64 tokens 140 / 151, even 192 / 205, 320 210 / 215,
+    # even 205 / 214, 640 273 / 271, even 224 / 244, 1285 324 / 339, even 255 / 254, 2040 379 / 387; 16 x 2048 x 3072, 200 115 / 122, 640
+    # 136 / 148; 8 x 3072 x 1024, 100 52 / 54).  Down:
     # from r >= 96, or with d_ff < 4096, or from r >= 56 where its narrow tiles fill the chip (at most
     # 128 tiles of 256 outputs: 8 experts x 4096 outputs, 65 rows each 156 us against 173 row-major;
     # 16 x 5120, 75 rows 287 against 264).
@@ -122,7 +123,7 @@ class MoEVerifyLayer:
         `stream` before the router and after each of the five steps (route, permute, gate/up,
         down, combine): the benchmark's per-kernel times.  On the tile-packed path the permute
         step includes the gather of the token rows into tile-packed form, unless the gate/up
-        kernel gathers them (gathers_packed()).
+        kernel gathers them (gathers_packed()).  Without marks a small batch routes and permutes in one launch.
         `draft_remap` ([E] int32 from moe_nearest_draft_expert) switches to the draft model's
         routing: selected experts that are not resident are replaced by their nearest draft
         expert, so only draft experts compute.
